@@ -188,12 +188,15 @@ void gemm_large_f32(float* C, int ldc, int N, bool accumulate, const h16_t* Wt, 
                     hipStream_t st, float* part = nullptr, size_t part_floats = 0);
 void gemm_large_swiglu(h16_t* act, const h16_t* Wt, int n_tiles, int k_tiles, const h16_t* Xt,
                        int M, int m_tiles, int lds_min_blocks, int* err_flag, const int* d_rows, hipStream_t st);
-// LDS-staged 256 x 256 kernel behind the two launchers above (epi: 0 store, 1 accumulate, 2 SwiGLU).
+// LDS-staged kernel behind the two launchers above (epi: 0 store, 1 accumulate, 2 SwiGLU); it chooses its block by the
+// sizes of the output and of K (even, at least 4 k-steps).
 void gemm_lds(const LargeArgs& a, int epi, hipStream_t st);
-// Split-K form of the store / accumulate GEMM for outputs of at most 128 blocks: false when it does not apply
+// Split-K form of the store / accumulate GEMM for outputs of at most 128 blocks of 256 x 256: false when it does not apply
 // (no range count from 2 to 8 divides K into even ranges of at least 8 k-steps that fit `part`), and nothing was launched.
 bool gemm_lds_split(const LargeArgs& a, bool accumulate, float* part, size_t part_floats, hipStream_t st);
-int score_head_blocks(int n_tiles, int* groups_per_block);
+// Partial results per row that lmhead_score leaves for M rows, and the room to plan for up to rows_max rows.
+int score_head_parts(int n_tiles, int k_tiles, int M, int lds_min_blocks);
+size_t score_head_part_floats(int n_tiles, int rows_max);
 void lmhead_score(float* part, const h16_t* Wt, int n_tiles, int k_tiles, const h16_t* Xt, int M,
                   int m_tiles, const int* targets, bool want_top, int lds_min_blocks, const int* d_rows,
                   hipStream_t st);
@@ -204,8 +207,9 @@ struct ScorePartial {
   float v2, zt;     // second largest logit, logit of the target token (-inf if not in the slice)
   float pad[2];
 };
-// LDS-staged version (256 rows x 256 vocabulary entries per step, `slices` vocabulary slices of 128 row tiles).
-void lmhead_score_lds(const ScoreHeadArgs& a, int slices, hipStream_t st);
+// LDS-staged version and the partial results it leaves per row.
+void lmhead_score_lds(const ScoreHeadArgs& a, hipStream_t st);
+int lmhead_lds_parts(int n_tiles, int M);
 void score_targets(int* targets, const int* seqs, int R, int S, int first, int n_scored, int seq0,
                    int row0, int vocab, int* err_flag, hipStream_t st);
 void score_reduce(const float* part, int n_parts, int R, int S, int first, int n_scored, int seq0,

@@ -354,9 +354,7 @@ static bool split_k_may_apply(int T, int d) { return (size_t)((T + 255) / 256) *
 
 void bf16_plan_score_extra(const mtmc_weights* w, ScorePlan& p, Carver& cv) {
   const Dims D = dims_of(w);
-  int gpb = 0;
-  const int blocks = bf16::score_head_blocks(D.nt_V, &gpb);
-  p.lm_part = cv.take<float>((size_t)blocks * 2 * p.rows_max * 8);
+  p.lm_part = cv.take<float>(bf16::score_head_part_floats(D.nt_V, p.rows_max));
   p.qb = cv.take<h16_t>((size_t)p.T * D.nq);
   p.targets = cv.take<int>(p.rows_max);
   p.gemm_part = split_k_may_apply(p.T, D.d) ? cv.take<float>(kGemmPartFloats) : nullptr;
@@ -364,9 +362,7 @@ void bf16_plan_score_extra(const mtmc_weights* w, ScorePlan& p, Carver& cv) {
 
 void bf16_plan_actions_extra(const mtmc_weights* w, ActionPlan& p, Carver& cv) {
   const Dims D = dims_of(w);
-  int gpb = 0;
-  const int blocks = bf16::score_head_blocks(D.nt_V, &gpb);
-  p.lm_part = cv.take<float>((size_t)blocks * 2 * p.rows_max * 8);
+  p.lm_part = cv.take<float>(bf16::score_head_part_floats(D.nt_V, p.rows_max));
   p.qb = cv.take<h16_t>((size_t)p.Tmax * D.nq);
   p.targets = cv.take<int>(p.rows_max);
   p.seq_start = cv.take<int>((size_t)p.chunk_rows + 1);
@@ -938,8 +934,6 @@ int bf16_score(const mtmc_weights* w, const ScorePlan& p, const ScoreArgs& a, hi
   launch_build_page_table(p.page_table, p.chunk_seqs, p.pages_per_seq, 1, 0, 0, st);
   launch_fill_u32((uint32_t*)p.kv, 0u, (size_t)2 * p.n_pages * c.n_kv_heads * kPageTokens * c.head_dim / 2, st);
   TokMap map{S, 1, 0, nullptr};
-  int gpb = 0;
-  const int n_parts = bf16::score_head_blocks(D.nt_V, &gpb) * 2;
   for (int s0 = 0; s0 < a.n_seqs; s0 += p.chunk_seqs) {
     const int ns = std::min(p.chunk_seqs, a.n_seqs - s0);
     const int T = ns * S, mt = tiles16(T);
@@ -955,6 +949,7 @@ int bf16_score(const mtmc_weights* w, const ScorePlan& p, const ScoreArgs& a, hi
     bf16::score_targets(p.targets, a.seqs, R, S, a.first, n_scored, s0, 0, D.V, w->err_flag, st);
     bf16::lmhead_score(p.lm_part, (const h16_t*)w->lm_head, D.nt_V, D.kt_d, (const h16_t*)p.xs, R, rt, p.targets,
                        a.out_top1 != nullptr || a.out_margin != nullptr, w->opt_lds_min_blocks, nullptr, st);
+    const int n_parts = bf16::score_head_parts(D.nt_V, D.kt_d, R, w->opt_lds_min_blocks);
     bf16::score_reduce(p.lm_part, n_parts, R, S, a.first, n_scored, s0, 0, a.out_logprobs, a.out_top1, a.out_margin, st);
   }
   return MTMC_OK;
@@ -991,8 +986,6 @@ int bf16_score_actions(const mtmc_weights* w, const ActionPlan& p, const ActionA
   // a_1 .. a_len).  The number of packed tokens is known on the device only: the launches are sized for nr * A
   // rows and the kernels skip the blocks of rows beyond *d_rows.
   TokMap map{p.A, 1, p.Pp, nullptr};
-  int gpb = 0;
-  const int n_parts = bf16::score_head_blocks(D.nt_V, &gpb) * 2;
   for (int r0 = 0; r0 < p.B; r0 += p.chunk_rows) {
     const int nr = std::min(p.chunk_rows, p.B - r0);
     const int T = nr * p.A, mt = tiles16(T);
@@ -1011,6 +1004,7 @@ int bf16_score_actions(const mtmc_weights* w, const ActionPlan& p, const ActionA
     bf16::add_norm(p.h, nullptr, 0, 0, 0, w->final_norm, c.rms_eps, (h16_t*)p.xs, T, mt, D.d, w->err_flag, st, p.d_rows);
     bf16::lmhead_score(p.lm_part, (const h16_t*)w->lm_head, D.nt_V, D.kt_d, (const h16_t*)p.xs, T, mt, p.targets,
                        false, w->opt_lds_min_blocks, p.d_rows, st);
+    const int n_parts = bf16::score_head_parts(D.nt_V, D.kt_d, T, w->opt_lds_min_blocks);
     bf16::score_reduce_scatter(p.lm_part, n_parts, T, p.d_rows, p.out_index, a.out_token, st);
   }
   launch_action_reduce(a.out_token, a.action_len, p.n_states, p.K, p.A, a.normalize, a.out_action, a.out_policy,

@@ -256,11 +256,21 @@ __global__ __launch_bounds__(256) void k_lmhead_score(ScoreHeadArgs a) {
   }
 }
 
-int score_head_blocks(int n_tiles, int* groups_per_block) {
-  const int n_groups = (n_tiles + 7) / 8;           // 128 vocabulary entries per group
-  const int gpb = std::max(1, std::min(n_groups, 16));
-  *groups_per_block = gpb;
-  return (n_groups + gpb - 1) / gpb;
+// Direct kernel: 2048 vocabulary entries per workgroup.
+constexpr int kHeadGroups = 16;  // of 128 entries
+static int head_blocks(int n_tiles) { return ((n_tiles + 7) / 8 + kHeadGroups - 1) / kHeadGroups; }
+
+int score_head_parts(int n_tiles, int k_tiles, int M, int lds_min_blocks) {
+  return use_lds_kernel(n_tiles, k_tiles, (M + 15) / 16, lds_min_blocks) ? lmhead_lds_parts(n_tiles, M) : 2 * head_blocks(n_tiles);
+}
+size_t score_head_part_floats(int n_tiles, int rows_max) {
+  // the number of parts falls as the rows grow: the largest product at either end of each step, either kernel
+  size_t most = (size_t)2 * head_blocks(n_tiles) * rows_max;
+  for (int r : {1024, 4096, 16384, rows_max}) {
+    const int rows = std::min(r, rows_max);
+    most = std::max(most, (size_t)lmhead_lds_parts(n_tiles, rows) * rows);
+  }
+  return most * (sizeof(ScorePartial) / sizeof(float));
 }
 
 void lmhead_score(float* part, const h16_t* Wt, int n_tiles, int k_tiles, const h16_t* Xt, int M,
@@ -272,10 +282,9 @@ void lmhead_score(float* part, const h16_t* Wt, int n_tiles, int k_tiles, const 
   a.Wt = Wt; a.Xt = Xt; a.n_tiles = n_tiles; a.k_tiles = k_tiles; a.m_tiles = m_tiles; a.M = M;
   a.targets = targets; a.part = part;
   a.n_groups = (n_tiles + 7) / 8;
-  const int blocks = score_head_blocks(n_tiles, &a.groups_per_block);
-  // same vocabulary slices (and partial results) in both kernels: 128 row tiles per slice
-  if (use_lds_kernel(n_tiles, k_tiles, m_tiles, lds_min_blocks)) lmhead_score_lds(a, blocks, st);
-  else k_lmhead_score<<<dim3(blocks, (m_tiles + 7) / 8), 256, 0, st>>>(a);
+  a.groups_per_block = kHeadGroups;
+  if (use_lds_kernel(n_tiles, k_tiles, m_tiles, lds_min_blocks)) lmhead_score_lds(a, st);
+  else k_lmhead_score<<<dim3(head_blocks(n_tiles), (m_tiles + 7) / 8), 256, 0, st>>>(a);
 }
 
 // Row r of the chunk is position i = first + (row0 + r) % n_scored of sequence
@@ -298,69 +307,74 @@ void score_targets(int* targets, const int* seqs, int R, int S, int first, int n
                                                   vocab, err_flag);
 }
 
-__global__ __launch_bounds__(64) void k_score_reduce(const ScorePartial* part, int n_parts, int R, int S,
-                                                     int first, int n_scored, int seq0, int row0,
-                                                     float* out_logprobs, int* out_top1,
-                                                     float* out_margin) {
-  const int r = blockIdx.x;
-  const int lane = threadIdx.x;
-  Lse lse = lse_empty();
-  Top2 top = top2_empty();
-  float zt = -INFINITY;
-  for (int g = lane; g < n_parts; g += 64) {
-    const ScorePartial p = part[(size_t)g * R + r];
-    lse = lse_merge(lse, Lse{p.m, p.s});
-    top = top2_merge(top, Top2{p.v1, p.i1, p.v2});
-    zt = fmaxf(zt, p.zt);
+// The parts of kReduceRows rows, taken together so that a part's rows are read as one run of memory: thread t owns row
+// t % kReduceRows and the parts t / kReduceRows, + kReduceGroups, ...; its sums are then merged in a fixed tree.
+constexpr int kReduceRows = 8, kReduceGroups = 32;
+struct ScoreSum { Lse lse; Top2 top; float zt; };
+__device__ __forceinline__ ScoreSum sum_parts(const ScorePartial* part, int n_parts, int R, int r) {
+  __shared__ ScoreSum red[kReduceGroups][kReduceRows];
+  const int row = threadIdx.x % kReduceRows, grp = threadIdx.x / kReduceRows;
+  ScoreSum s{lse_empty(), top2_empty(), -INFINITY};
+  if (r < R) {
+#pragma unroll 4
+    for (int g = grp; g < n_parts; g += kReduceGroups) {
+      const ScorePartial p = part[(size_t)g * R + r];
+      s.lse = lse_merge(s.lse, Lse{p.m, p.s});
+      s.top = top2_merge(s.top, Top2{p.v1, p.i1, p.v2});
+      s.zt = fmaxf(s.zt, p.zt);
+    }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const Lse ol = {__shfl_xor(lse.m, o, 64), __shfl_xor(lse.s, o, 64)};
-    const Top2 ot = {__shfl_xor(top.v1, o, 64), __shfl_xor(top.i1, o, 64), __shfl_xor(top.v2, o, 64)};
-    lse = lse_merge(lse, ol);
-    top = top2_merge(top, ot);
-    zt = fmaxf(zt, __shfl_xor(zt, o, 64));
+  red[grp][row] = s;
+  __syncthreads();
+  for (int w = kReduceGroups / 2; w > 0; w >>= 1) {
+    if (grp < w) {
+      const ScoreSum o = red[grp + w][row];
+      s.lse = lse_merge(s.lse, o.lse);
+      s.top = top2_merge(s.top, o.top);
+      s.zt = fmaxf(s.zt, o.zt);
+      red[grp][row] = s;
+    }
+    __syncthreads();
   }
-  if (lane == 0) {
+  return s;  // complete in the threads of group 0
+}
+
+__global__ __launch_bounds__(kReduceRows * kReduceGroups) void k_score_reduce(const ScorePartial* part, int n_parts, int R,
+                                                                              int S, int first, int n_scored, int seq0,
+                                                                              int row0, float* out_logprobs, int* out_top1,
+                                                                              float* out_margin) {
+  const int r = blockIdx.x * kReduceRows + threadIdx.x % kReduceRows;
+  const ScoreSum s = sum_parts(part, n_parts, R, r);
+  if (threadIdx.x < kReduceRows && r < R) {
     const int n = seq0 + (row0 + r) / n_scored, i = first + (row0 + r) % n_scored;
     const size_t slot = (size_t)n * (S - 1) + i;
-    out_logprobs[slot] = zt - (lse.m + logf(lse.s));
-    if (out_top1) out_top1[slot] = top.i1;
-    if (out_margin) out_margin[slot] = top.v1 - top.v2;
+    out_logprobs[slot] = s.zt - (s.lse.m + logf(s.lse.s));
+    if (out_top1) out_top1[slot] = s.top.i1;
+    if (out_margin) out_margin[slot] = s.top.v1 - s.top.v2;
   }
 }
 void score_reduce(const float* part, int n_parts, int R, int S, int first, int n_scored, int seq0,
                   int row0, float* out_logprobs, int* out_top1, float* out_margin, hipStream_t st) {
-  k_score_reduce<<<R, 64, 0, st>>>(reinterpret_cast<const ScorePartial*>(part), n_parts, R, S, first,
-                                   n_scored, seq0, row0, out_logprobs, out_top1, out_margin);
+  k_score_reduce<<<(R + kReduceRows - 1) / kReduceRows, kReduceRows * kReduceGroups, 0, st>>>(
+      reinterpret_cast<const ScorePartial*>(part), n_parts, R, S, first, n_scored, seq0, row0, out_logprobs, out_top1,
+      out_margin);
 }
 
-__global__ __launch_bounds__(64) void k_score_reduce_scatter(const ScorePartial* part, int n_parts, int R,
-                                                             const int* d_rows, const int* out_index,
-                                                             float* out_logprobs) {
-  const int r = blockIdx.x;
-  if (r >= *d_rows) return;
-  const int lane = threadIdx.x;
-  Lse lse = lse_empty();
-  float zt = -INFINITY;
-  for (int g = lane; g < n_parts; g += 64) {
-    const ScorePartial p = part[(size_t)g * R + r];
-    lse = lse_merge(lse, Lse{p.m, p.s});
-    zt = fmaxf(zt, p.zt);
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const Lse ol = {__shfl_xor(lse.m, o, 64), __shfl_xor(lse.s, o, 64)};
-    lse = lse_merge(lse, ol);
-    zt = fmaxf(zt, __shfl_xor(zt, o, 64));
-  }
-  if (lane == 0) out_logprobs[out_index[r]] = zt - (lse.m + logf(lse.s));
+__global__ __launch_bounds__(kReduceRows * kReduceGroups) void k_score_reduce_scatter(const ScorePartial* part, int n_parts,
+                                                                                      int R, const int* d_rows,
+                                                                                      const int* out_index,
+                                                                                      float* out_logprobs) {
+  const int rows = *d_rows;
+  if ((int)blockIdx.x * kReduceRows >= rows) return;  // whole workgroup
+  const int r = blockIdx.x * kReduceRows + threadIdx.x % kReduceRows;
+  const ScoreSum s = sum_parts(part, n_parts, R, r);
+  if (threadIdx.x < kReduceRows && r < rows) out_logprobs[out_index[r]] = s.zt - (s.lse.m + logf(s.lse.s));
 }
 void score_reduce_scatter(const float* part, int n_parts, int R, const int* d_rows, const int* out_index,
                           float* out_logprobs, hipStream_t st) {
   if (R == 0) return;
-  k_score_reduce_scatter<<<R, 64, 0, st>>>(reinterpret_cast<const ScorePartial*>(part), n_parts, R, d_rows, out_index,
-                                           out_logprobs);
+  k_score_reduce_scatter<<<(R + kReduceRows - 1) / kReduceRows, kReduceRows * kReduceGroups, 0, st>>>(
+      reinterpret_cast<const ScorePartial*>(part), n_parts, R, d_rows, out_index, out_logprobs);
 }
 
 // One workgroup of 1024 threads: thread t owns the candidates t, t + 1024, ... in blocks of consecutive

@@ -1,18 +1,22 @@
 // Large-batch GEMM of the prefill / scoring pass, staged through LDS.
 //
-// Workgroup tile: 256 output features x 256 tokens, full K.  Four wavefronts (one per SIMD) in a
-// 2 x 2 arrangement own 128 x 128 each: 4 x 4 accumulator blocks of v_mfma_f32_32x32x16_f16 per
-// wavefront (a single wavefront per SIMD keeps the matrix pipe above 90 % busy with this shape, but
-// only near 55 % with the 16x16x32 shape), which puts the LDS read rate at 16 KiB per k-step per
-// wavefront (about half of what the LDS can deliver) and the global rate at 32 KiB per k-step per
-// workgroup.
+// Workgroup tile: 32 NB output features x 32 MB tokens, full K.  Four wavefronts (one per SIMD and workgroup) in a
+// 2 x 2 arrangement own NB x MB accumulator blocks of v_mfma_f32_16x16x32_f16 each.  The 16x16x32 shape and not
+// 32x32x16: both are limited by power here, not by issue slots (a register-only loop on random operands reaches
+// 1.91 PFLOP/s with 16x16x32 and 1.67 with 32x32x16; the clock of the GEMM itself rose from 1.39 to 1.76 GHz), because
+// the smaller shape moves half as many accumulator bytes per product.  The sums are the same bit for bit.
 //
-// Both operands already sit in memory as 1 KiB MFMA operand blocks (frag.h), so staging is a plain
-// copy: every k-step (32 columns of K) needs 16 weight blocks and 16 activation blocks, which the
-// wavefronts fetch with LDS-direct 16-byte loads (no registers involved) into a ring of kStages
-// buffers, kStages - 1 steps ahead of the one being multiplied.  One workgroup barrier per step:
-// it makes the step's blocks visible to every wavefront and at the same time guarantees that
-// the buffer refilled next (read in the previous step) is no longer in use.
+// Both operands already sit in memory as 1 KiB MFMA operand blocks (frag.h), so staging is a plain copy: every k-step
+// (32 columns of K) needs 2 NB weight blocks and 2 MB activation blocks, which the wavefronts fetch with LDS-direct
+// 16-byte buffer loads (no registers involved; the block's address is scalar arithmetic alone) into a ring of ST
+// buffers, ST - 1 steps ahead of the one being multiplied.  One workgroup barrier per step: it makes the step's
+// blocks visible to every wavefront and at the same time guarantees that the buffer refilled next (read in the previous
+// step) is no longer in use.
+//
+// What bounds it (256 x 256 tiles, 98 304 tokens, same card): without the copies the loop runs at 1.57 PFLOP/s, with
+// them at 1.38, and with the epilogue's HBM traffic at 1.25 (down projection, 2.41 -> 2.17 ms; gate/up 4.70 -> 4.32 ms;
+// QKV 0.63 -> 0.59; before: 32x32x16, flat addresses).  The fragment reads of a step are issued in its first half: spread over
+// the whole step, their latency stood before the next step's first product (1.19 -> 1.28 PFLOP/s at 4096^2 x 8192).
 #include <algorithm>
 
 #include "bf16_kernels.h"
@@ -24,20 +28,28 @@ namespace bf16 {
 
 namespace {
 
-constexpr int kStages = 4;
-constexpr int kPersistentGrid = 256;                 // CUs of the device; a multiple of the 8 XCDs
-constexpr int kBlkTiles = 16;                       // 16-row tiles per workgroup tile side
-constexpr int kStageBytes = 2 * kBlkTiles * 1024;   // weight blocks, then activation blocks
-constexpr int kTrRow = 36;                          // floats per row of the epilogue's 32 x 32 transposition tile
-constexpr int kTrBytes = 4 * 32 * kTrRow * 4;       // one tile per wavefront, behind the ring
-constexpr int kLoadsPerStage = 2 * kBlkTiles / 4;   // LDS-direct loads each wavefront issues per step
+constexpr int kCus = 256;   // CUs of the device; a multiple of the 8 XCDs
+constexpr int kXcds = 8;
 
-typedef __attribute__((ext_vector_type(16))) float v16f;
+// A workgroup tile: 2 x 2 wavefronts of NB x MB blocks of 16 x 16, a ring of ST stages, PC workgroups per CU.
+template <int NB_, int MB_, int ST_, int PC_>
+struct Tile {
+  static constexpr int NB = NB_, MB = MB_, ST = ST_, PC = PC_;
+  static constexpr int TN = 2 * NB, TM = 2 * MB;               // 16-row tiles per workgroup tile side
+  static constexpr int kStage = (TN + TM) * 1024;              // weight blocks, then activation blocks
+  static constexpr int kLds = ST * kStage;
+  static constexpr int LW = NB / 2, LX = MB / 2, NL = LW + LX; // blocks a wavefront copies per step
+};
+
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
-typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
-__device__ __forceinline__ void copy_block_to_lds(const uint8_t* src_lane, uint8_t* dst_block) {
-  __builtin_amdgcn_global_load_lds((glb_ptr_t)src_lane, (lds_ptr_t)dst_block, 16, 0, 0);
+// One 1 KiB operand block global -> LDS: lane l moves the 16 bytes at base + soff + voff (voff = 16 l) to dst + 16 l.
+// The descriptor spans the address space: every offset is clamped to the operand by its caller.
+__device__ __forceinline__ void copy_block_to_lds(const uint8_t* base, uint32_t voff, uint32_t soff, uint8_t* dst) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, -1, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)dst, 16, voff, soff, 0, 0);
+#endif
 }
 
 // s_waitcnt on the vector-memory counter alone (the other counters left at their maxima).
@@ -47,178 +59,136 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// acc += A B with the accumulator pinned to the AGPR half of the register file (the 256 accumulator
-// registers of a wavefront fill it exactly; left to itself the register allocator spreads them over both
-// halves and spills).  Consecutive uses of one accumulator are 16 MFMAs apart, far beyond the
-// dependent-issue distance of the instruction.
-__device__ __forceinline__ void mfma32_acc(v16f& acc, v8h a, v8h b) {
-  asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b) : "memory");
+// acc += A B with the accumulator pinned to the AGPR half of the register file (left to itself the register allocator
+// spreads the accumulators over both halves and spills).  An accumulator is used again NB MB products later, far
+// beyond the dependent-issue distance of the instruction.
+__device__ __forceinline__ void mfma16_acc(v4f& acc, v8h a, v8h b) {
+  asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b) : "memory");
 }
 
 // silu with the hardware exp2 / reciprocal (about 1e-6 relative error; the result is rounded to fp16 anyway):
-// the 128 evaluations per lane and output block would otherwise take a tenth of the block's time
+// the evaluations would otherwise take a tenth of a block's time
 __device__ __forceinline__ float silu_l(float g) {
   return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
 }
 
-// Launch index -> output block: XCD (L % 8) owns token blocks xcd + 8 i and walks them in bands of
-// kBand token blocks x all feature blocks, so workgroups resident together on an XCD share panels
-// in its L2.  With fewer token blocks than XCDs (a prompt or two) the XCDs share out the feature blocks
-// instead, or most of them would have nothing to do.
+// Output blocks in bands of kBand token blocks x all feature blocks, features slow: workgroups that run together on
+// an XCD share panels in its L2.  Every XCD owns one contiguous run of that order, equal to one block (with whole token
+// blocks per XCD, 21 token blocks gave five XCDs three and three two), and its workgroups walk the run in turn.
 constexpr int kBand = 4;
-struct Block { int nb, mb; bool valid; };
-__device__ __forceinline__ Block block_of(int L, int nb_n, int nb_m) {
-  const bool by_feature = nb_m < 8 && nb_n > nb_m;
-  const int n_walk = by_feature ? nb_m : nb_n, n_own = by_feature ? nb_n : nb_m;
-  const int xcd = L & 7, j = L >> 3;
-  const int band = j / (kBand * n_walk), r = j - band * (kBand * n_walk);
-  const int wb = r / kBand, oi = band * kBand + (r - wb * kBand);
-  const int ob = xcd + 8 * oi;
-  return by_feature ? Block{ob, wb, ob < n_own} : Block{wb, ob, ob < n_own};
+struct Block { int nb, mb; };
+__device__ __forceinline__ Block block_at(int t, int nb_n, int nb_m) {
+  const int band = t / (kBand * nb_n), r = t - band * (kBand * nb_n);
+  const int height = min(kBand, nb_m - band * kBand);
+  const int nb = r / height;
+  return Block{nb, band * kBand + (r - nb * height)};
 }
-// The same order without the gaps: the t-th block of those an XCD owns (t < blocks_of_xcd), band by band; the
-// last band of an XCD is as high as the blocks it has left.  What a persistent workgroup walks: striding over
-// launch indices instead would give the indices that name no block to always the same workgroups.
-__host__ __device__ __forceinline__ int blocks_of_xcd(int xcd, int nb_n, int nb_m) {
-  const bool by_feature = nb_m < 8 && nb_n > nb_m;
-  const int n_walk = by_feature ? nb_m : nb_n, n_own = by_feature ? nb_n : nb_m;
-  return xcd < n_own ? (n_own - xcd + 7) / 8 * n_walk : 0;
-}
-__device__ __forceinline__ Block block_of_xcd(int xcd, int t, int nb_n, int nb_m) {
-  const bool by_feature = nb_m < 8 && nb_n > nb_m;
-  const int n_walk = by_feature ? nb_m : nb_n, n_own = by_feature ? nb_n : nb_m;
-  const int count = (n_own - xcd + 7) / 8;
-  const int band = t / (kBand * n_walk), r = t - band * (kBand * n_walk);
-  const int height = min(kBand, count - band * kBand);
-  const int wb = r / height, ob = xcd + 8 * (band * kBand + (r - wb * height));
-  return by_feature ? Block{ob, wb, true} : Block{wb, ob, true};
-}
-int grid_of(int nb_n, int nb_m) {
-  const bool by_feature = nb_m < 8 && nb_n > nb_m;
-  const int n_walk = by_feature ? nb_m : nb_n, n_own = by_feature ? nb_n : nb_m;
-  const int per_xcd = (n_own + 7) / 8, bands = (per_xcd + kBand - 1) / kBand;
-  return 8 * bands * kBand * n_walk;
-}
+// first block of an XCD's run of `total`
+__device__ __forceinline__ int run_of_xcd(int xcd, int total) { return (int)((long long)total * xcd / kXcds); }
 
 enum { LEPI_STORE = 0, LEPI_ADD = 1, LEPI_SWIGLU = 2 };
 
-// This wavefront's share of the copies of one 256 x 256 output block: weight blocks 4 wave .. + 3 and
-// activation blocks 4 wave .. + 3 of every k-step (tile indices past the end are clamped: such blocks are
-// multiplied but never stored).  Wavefront-uniform addresses of k-step 0; the lane adds its 16-byte slot.
+// Where this wavefront's share of a block's copies comes from: one base per operand (k-step 0), advanced by k-steps,
+// and a 32-bit offset per piece (tile indices past the end are clamped: such blocks are multiplied but never stored).
+template <class T>
 struct TileSrc {
-  const uint8_t* w[4];
-  const uint8_t* x[4];
+  const uint8_t* w;
+  const uint8_t* x;
+  uint32_t wo[T::LW], xo[T::LX];
 };
-__device__ __forceinline__ TileSrc tile_src(const uint8_t* Wt, const uint8_t* Xt, int n_tiles, int m_tiles, int K,
-                                            int nt_base, int mt_base, int uwave, int k0 = 0) {
-  TileSrc t;
+template <class T>
+__device__ __forceinline__ TileSrc<T> tile_src(const uint8_t* Wt, const uint8_t* Xt, int n_tiles, int m_tiles, int K,
+                                               int nt_base, int mt_base, int uwave, int k0) {
+  TileSrc<T> s;
+  s.w = Wt + ((size_t)nt_base * K + k0) * 1024;
+  s.x = Xt + ((size_t)k0 * m_tiles + mt_base) * 1024;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    t.w[j] = Wt + ((size_t)min(nt_base + 4 * uwave + j, n_tiles - 1) * K + k0) * 1024;
-    t.x[j] = Xt + ((size_t)k0 * m_tiles + min(mt_base + 4 * uwave + j, m_tiles - 1)) * 1024;
-  }
-  return t;
+  for (int j = 0; j < T::LW; ++j)
+    s.wo[j] = (uint32_t)(min(nt_base + T::LW * uwave + j, n_tiles - 1) - nt_base) * (uint32_t)K * 1024u;
+#pragma unroll
+  for (int j = 0; j < T::LX; ++j) s.xo[j] = (uint32_t)(min(mt_base + T::LX * uwave + j, m_tiles - 1) - mt_base) * 1024u;
+  return s;
 }
 
-// The matrix pipeline of a workgroup over a SEQUENCE of output blocks.  `tile_at(i, nt_base, mt_base)`
-// names the i-th block (false: no more), `epilogue(acc, nt_base, mt_base)` consumes a finished one:
-// acc = 4 x 4 accumulator blocks of 32 x 32 (v_mfma_f32_32x32x16_f16, 16 registers each) = the 128 x 128
-// part of this wavefront (wn, wm).  The k-steps of consecutive blocks form one stream through the ring of
-// kStages LDS buffers: while the last steps of a block are multiplied the first steps of the next one are
-// already being fetched, and its first fragments are read, so that a new block starts without refilling
-// the pipeline and its copies run under the epilogue of the previous one.  K >= kStages and even.
-// SPLIT: a work item is an output block over k-steps k0 .. k0 + Ks - 1 only (tile_at also names k0, the epilogue
-// gets it); the rows of W are still K k-steps long.  Ks >= kStages and even.
-template <bool SPLIT = false, typename TileAt, typename Epilogue>
-__device__ __forceinline__ void lds_gemm_stream(const uint8_t* Wt, const uint8_t* Xt, int n_tiles, int m_tiles, int K,
-                                                uint8_t* lds, int lane, int uwave, int wn, int wm, TileAt tile_at,
-                                                Epilogue epilogue, int Ks = 0) {
+// The matrix pipeline of a workgroup over a SEQUENCE of output blocks.  `tile_at(nt_base, mt_base, k0)` names the
+// next block and the k-step it starts at (false: no more), `epilogue(acc, nt_base, mt_base, k0)` consumes a finished one:
+// acc = the NB x MB accumulator blocks of this wavefront (wn, wm).  The k-steps of consecutive blocks form one stream
+// through the ring of ST LDS buffers: while the last steps of a block are multiplied the first steps of the next one are
+// already being fetched, and its first fragments are read, so that a new block starts without refilling the pipeline
+// and its copies run under the epilogue of the previous one.  A block is Ks k-steps of operands whose rows are
+// K steps long; Ks >= ST and even.
+template <class T, typename TileAt, typename Epilogue>
+__device__ __forceinline__ void lds_gemm_stream(const uint8_t* Wt, const uint8_t* Xt, int n_tiles, int m_tiles, int K, int Ks,
+                                                uint8_t* lds, int lane, int uwave, TileAt tile_at, Epilogue epilogue) {
+  constexpr int NB = T::NB, MB = T::MB, ST = T::ST, NL = T::NL, SB = T::kStage;
+  const int wn = uwave & 1, wm = uwave >> 1;
   int nt_base = 0, mt_base = 0, k0 = 0;
-  const int KL = SPLIT ? Ks : K;  // k-steps of a work item
-  bool any;
-  if constexpr (SPLIT) any = tile_at(0, nt_base, mt_base, k0);
-  else any = tile_at(0, nt_base, mt_base);
-  if (!any) return;  // whole workgroup
+  if (!tile_at(nt_base, mt_base, k0)) return;  // whole workgroup
   const size_t xstep = (size_t)m_tiles * 1024;
-  const uint32_t lane16 = lane * 16;
-  // A 32-row operand of the 32x32x16 MFMA (lane l: row l % 32, 8 consecutive k of half l / 32) is
-  // gathered from two adjacent 16-row blocks: lane -> (block (l % 32) / 16, row l % 16, k group
-  // 2 p + l / 32) for the p-th pair of k groups; the two pairs of a k-step are 512 bytes apart.
-  const int r32 = lane & 31;
-  const int lane_off = (r32 >> 4) * 1024 + (((lane >> 5) << 4) + (r32 & 15)) * 16;
-  // Fragments of one k-step: per 32-row block two operands (k groups 0,1 and 2,3).
-  struct Frags { v8h w[4][2], x[4][2]; };
-  auto read_frag = [&](Frags& f, const uint8_t* sb, int i) {  // i = 0..15
-    const int blk = (i >> 1) & 3, p = i & 1;
-    if (i < 8) f.x[blk][p] = *reinterpret_cast<const v8h*>(sb + (kBlkTiles + 8 * wm + 2 * blk) * 1024 + p * 512);
-    else f.w[blk][p] = *reinterpret_cast<const v8h*>(sb + (8 * wn + 2 * blk) * 1024 + p * 512);
+  const uint32_t l16 = lane * 16;
+  struct Frags { v8h w[NB], x[MB]; };
+  auto read_frag = [&](Frags& f, const uint8_t* sb, int i) {
+    if (i < MB) f.x[i] = *reinterpret_cast<const v8h*>(sb + (T::TN + MB * wm + i) * 1024);
+    else f.w[i - MB] = *reinterpret_cast<const v8h*>(sb + (NB * wn + i - MB) * 1024);
   };
-  auto issue_one = [&](const TileSrc& t, int kk, uint8_t* sb, int j) {  // j = 0..7; sb = this wavefront's part of a buffer
-    if (j < 4) copy_block_to_lds(t.w[j] + (size_t)kk * 1024 + lane16, sb + j * 1024);
-    else copy_block_to_lds(t.x[j - 4] + (size_t)kk * xstep + lane16, sb + (kBlkTiles + j - 4) * 1024);
+  auto issue_one = [&](const TileSrc<T>& s, int kk, uint8_t* sb, int j) {
+    if (j < T::LW) copy_block_to_lds(s.w + (size_t)kk * 1024, l16, s.wo[j], sb + (T::LW * uwave + j) * 1024);
+    else copy_block_to_lds(s.x + (size_t)kk * xstep, l16, s.xo[j - T::LW], sb + (T::TN + T::LX * uwave + j - T::LW) * 1024);
   };
-
-  TileSrc cur = tile_src(Wt, Xt, n_tiles, m_tiles, K, nt_base, mt_base, uwave, k0);
-  // ---- fill the ring with the first kStages steps of the first block, read its first fragments
+  TileSrc<T> cur = tile_src<T>(Wt, Xt, n_tiles, m_tiles, K, nt_base, mt_base, uwave, k0);
+  // ---- fill the ring with the first ST steps of the first block, read its first fragments
 #pragma unroll
-  for (int s = 0; s < kStages; ++s)
+  for (int s = 0; s < ST; ++s)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) issue_one(cur, s, lds + s * kStageBytes + uwave * 4096, j);
+    for (int j = 0; j < NL; ++j) issue_one(cur, s, lds + s * SB, j);
   Frags fa, fb;
-  wait_vmcnt<(kStages - 1) * kLoadsPerStage>();
+  wait_vmcnt<(ST - 1) * NL>();
   __builtin_amdgcn_s_barrier();
 #pragma unroll
-  for (int i = 0; i < 16; ++i) read_frag(fa, lds + lane_off, i);
+  for (int i = 0; i < NB + MB; ++i) read_frag(fa, lds + l16, i);
 
-  int g0 = 0;  // stream index of step 0 of the current block (step g lives in buffer g % kStages)
-  for (int ti = 0;; ++ti) {
+  int off = 0;  // LDS offset of the buffer that the step being multiplied was read from
+  for (;;) {
     int nt_next = 0, mt_next = 0, k0_next = 0;
-    bool has_next;
-    if constexpr (SPLIT) has_next = tile_at(ti + 1, nt_next, mt_next, k0_next);
-    else has_next = tile_at(ti + 1, nt_next, mt_next);
-    const TileSrc nxt = has_next ? tile_src(Wt, Xt, n_tiles, m_tiles, K, nt_next, mt_next, uwave, k0_next) : cur;
-    v16f acc[4][4];
+    const bool has_next = tile_at(nt_next, mt_next, k0_next);
+    const TileSrc<T> nxt = has_next ? tile_src<T>(Wt, Xt, n_tiles, m_tiles, K, nt_next, mt_next, uwave, k0_next) : cur;
+    v4f acc[NB][MB];
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) acc[nb][mb][j] = 0.f;
+      for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = v4f{0.f, 0.f, 0.f, 0.f};
     asm volatile("s_nop 7" ::: "memory");  // accumulator writes settle before the first (inline-asm) MFMA reads them
-    // Step kt multiplies the fragments already in registers; spread between its 32 MFMAs (which take 32
-    // cycles each and leave the issue slots free) are the 16 LDS reads of the fragments of stream step
-    // g + 1 and the 8 block fetches of stream step g + kStages, into the buffer step g was read from.
+    // Step kt multiplies the fragments already in registers; between its products go the LDS reads of the fragments
+    // of the next step (first half) and the block fetches of step kt + ST into the buffer step kt was read from.
     auto step = [&](const Frags& fc, Frags& fn, int kt) {
-      // own LDS reads done (they all feed `fc`); blocks of step g + 1 landed, g + 2 and g + 3 may fly
-      __builtin_amdgcn_s_waitcnt((((kStages - 2) * kLoadsPerStage) & 15) | ((((kStages - 2) * kLoadsPerStage) >> 4) << 14) |
-                                 (7 << 4) | (0 << 8));
+      constexpr int VM = (ST - 2) * NL;
+      // own LDS reads done (they all feed `fc`); blocks of the next step landed, those of later ones may fly
+      __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | (7 << 4) | (0 << 8));
       __builtin_amdgcn_s_barrier();
-      const int g = g0 + kt;
-      const uint8_t* rb = lds + ((g + 1) % kStages) * kStageBytes + lane_off;
-      uint8_t* fbuf = lds + (g % kStages) * kStageBytes + uwave * 4096;
-      // step g + kStages: of this block, else of the next one, else (nothing follows) a clamped copy nobody reads
-      const int ka = kt + kStages;
-      const bool own = ka < KL;
-      const TileSrc& src = own ? cur : nxt;
-      const int kk = own ? ka : (has_next ? ka - KL : KL - 1);
+      uint8_t* fbuf = lds + off;
+      off = off + SB == ST * SB ? 0 : off + SB;
+      const uint8_t* rb = lds + off + l16;
+      // step kt + ST: of this block, else of the next one, else (nothing follows) a clamped copy nobody reads
+      const int ka = kt + ST;
+      const bool own = ka < Ks;
+      const TileSrc<T>& src = own ? cur : nxt;
+      const int kk = own ? ka : (has_next ? ka - Ks : Ks - 1);
+      constexpr int NM = NB * MB, NR = NB + MB;
+      int ir = 0, ic = 0;
 #pragma unroll
-      for (int i = 0; i < 32; ++i) {
-        const int pp = i >> 4, nb = (i >> 2) & 3, mb = i & 3;
-        mfma32_acc(acc[nb][mb], fc.w[nb][pp], fc.x[mb][pp]);
-        if ((i & 1) == 0) read_frag(fn, rb, i >> 1);
-        if ((i & 3) == 1) issue_one(src, kk, fbuf, i >> 2);
+      for (int i = 0; i < NM; ++i) {
+        mfma16_acc(acc[i / MB][i % MB], fc.w[i / MB], fc.x[i % MB]);
+        if (ir < NR && 2 * i * NR >= ir * NM) { read_frag(fn, rb, ir); ++ir; }
+        if (ic < NL && i >= NM / 16 + ic * NM * 15 / 16 / NL) { issue_one(src, kk, fbuf, ic); ++ic; }
       }
     };
-    for (int kt = 0; kt < KL; kt += 2) {
+    for (int kt = 0; kt < Ks; kt += 2) {
       step(fa, fb, kt);
       step(fb, fa, kt + 1);
     }
-    g0 += KL;
-    // the last MFMAs were issued from inline assembly: give them time to retire before their accumulators
-    // are read (16 passes of 4 cycles cover the longest one)
-    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-    if constexpr (SPLIT) epilogue(acc, nt_base, mt_base, k0);
-    else epilogue(acc, nt_base, mt_base);
+    // the last MFMAs were issued from inline assembly: give them time to retire before their accumulators are read
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    epilogue(acc, nt_base, mt_base, k0);
     if (!has_next) break;
     // the epilogue's stores (and loads) share the counter with the copies: drain it so that the waits of the
     // next block count copies only (they have been flying under the epilogue)
@@ -231,159 +201,147 @@ __device__ __forceinline__ void lds_gemm_stream(const uint8_t* Wt, const uint8_t
   wait_vmcnt<0>();  // the clamped copies past the last step still target this workgroup's LDS
 }
 
-template <int EPI>
-__global__ __launch_bounds__(256, 1) void k_gemm_lds(LargeArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wn = wave & 1, wm = wave >> 1;
-  const int nb_n = (a.n_tiles + kBlkTiles - 1) / kBlkTiles;
-  int nb_m = (a.m_tiles + kBlkTiles - 1) / kBlkTiles;
-  // rows packed on the device: only the row blocks that hold tokens are walked (the operand layout keeps the
-  // stride of the full capacity)
-  if (a.d_rows) nb_m = min(nb_m, (*a.d_rows + kBlkTiles * 16 - 1) / (kBlkTiles * 16));
-  // persistent workgroup: gridDim.x is a multiple of 8, so this workgroup and the gridDim.x / 8 - 1 others of its
-  // XCD share out the blocks the XCD owns, in the order block_of_xcd gives them
-  const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3;
-  const int total = blocks_of_xcd(xcd, nb_n, nb_m);
-  int t = (int)(blockIdx.x >> 3) - stride;
-  auto tile_at = [&](int, int& nt_base, int& mt_base) {
-    t += stride;
-    if (t >= total) return false;
-    const Block blk = block_of_xcd(xcd, t, nb_n, nb_m);
-    nt_base = blk.nb * kBlkTiles;
-    mt_base = blk.mb * kBlkTiles;
-    return true;
+// acc[nb][mb] of lane l holds token 16 mb + l % 16 and features 16 nb + 4 (l / 16) + 0..3 of the wavefront's part of
+// the block.  fp32 forms: out[token][feature] = (ADD: +=) acc; the old values of the next 16 tokens are requested while
+// the current ones are stored (where the CU hosts a second workgroup, that one's products fill the wait instead).
+template <class T, bool ADD>
+__device__ __forceinline__ void store_f32(v4f (&acc)[T::NB][T::MB], float* out, int ld, int M, int N, int nt0, int mt0, int lane) {
+  constexpr int NB = T::NB, MB = T::MB;
+  const int m0 = mt0 * 16 + (lane & 15), n0 = nt0 * 16 + (lane >> 4) * 4;
+  const bool full = (mt0 + MB) * 16 <= M && (nt0 + NB) * 16 <= N;  // wavefront-uniform
+  constexpr int PF = T::PC == 1 ? 2 : 1;
+  v4f old[PF][NB];
+  auto fetch = [&](int mb) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int m = m0 + mb * 16, n = n0 + nb * 16;
+      old[mb % PF][nb] = v4f{0.f, 0.f, 0.f, 0.f};
+      if (full || (m < M && n < N)) old[mb % PF][nb] = *reinterpret_cast<const v4f*>(out + (size_t)m * ld + n);
+    }
   };
-  auto epilogue = [&](v16f (&acc)[4][4], int nt_base, int mt_base) {
-  // ---- epilogue: in a 32 x 32 block, lane holds token lane % 32 and features 8 q + 4 (lane / 32) + 0..3
-  // (q = 0..3) in registers 4 q .. 4 q + 3
-  const int col = lane & 31, rh = (lane >> 5) * 4;
-  const int Mpad = a.m_tiles * 16;
-  // accumulate form: the old values of a group of four blocks (one nb, the four mb) are requested while the
-  // group before it is worked on; pass by pass, each block would wait a whole memory round trip for them
-  v4f old[2][4][4];
-  const int f = (lane & 7) * 4, trow = lane >> 3;
-  auto fetch_old = [&](int nb, v4f (&dst)[4][4]) {
-    const int n = (nt_base + 8 * wn + 2 * nb) * 16 + f;
+  if (ADD && PF == 2) fetch(0);
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+  for (int mb = 0; mb < MB; ++mb) {
+    if (ADD && mb + PF - 1 < MB) fetch(mb + PF - 1);
 #pragma unroll
-      for (int pass = 0; pass < 4; ++pass) {
-        const int mm = (mt_base + 8 * wm + 2 * mb) * 16 + pass * 8 + trow;
-        dst[mb][pass] = v4f{0.f, 0.f, 0.f, 0.f};
-        if (mm < a.M && n < a.N) dst[mb][pass] = *reinterpret_cast<const v4f*>(a.out_f32 + (size_t)mm * a.ld_out + n);
-      }
-  };
-  if (EPI == LEPI_ADD) fetch_old(0, old[0]);
-  bool out_of_range = false;  // SwiGLU form: a product that does not fit fp16 (reported once per block, below)
-#pragma unroll
-  for (int nb = 0; nb < 4; ++nb) {
-    if (EPI == LEPI_ADD && nb + 1 < 4) fetch_old(nb + 1, old[(nb + 1) & 1]);
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      // one accumulator block at a time: it is taken from its registers here, not earlier (volatile statements
-      // keep their order), which keeps the 256 accumulators out of the VGPR half until they are needed
+    for (int nb = 0; nb < NB; ++nb) {
+      // one accumulator block at a time: it is taken from its registers here, not earlier (volatile statements keep
+      // their order), which keeps the accumulators out of the VGPR half until they are needed
       asm volatile("" : "+a"(acc[nb][mb])::"memory");
-      const int m = (mt_base + 8 * wm + 2 * mb) * 16 + col;
-      const int n0 = (nt_base + 8 * wn + 2 * nb) * 16;  // first feature row of the block
-      if (EPI == LEPI_SWIGLU) {
-        // rows 0..15 of the block are gate rows, rows 16..31 the matching up rows
-        if (m >= a.M || n0 >= a.n_tiles * 16) continue;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const int fo = (n0 >> 1) + 8 * q + rh;
-          uint2 pk;
-          pk.x = pack_h16x2_track(silu_l(acc[nb][mb][4 * q + 0]) * acc[nb][mb][4 * q + 8],
-                                  silu_l(acc[nb][mb][4 * q + 1]) * acc[nb][mb][4 * q + 9], out_of_range);
-          pk.y = pack_h16x2_track(silu_l(acc[nb][mb][4 * q + 2]) * acc[nb][mb][4 * q + 10],
-                                  silu_l(acc[nb][mb][4 * q + 3]) * acc[nb][mb][4 * q + 11], out_of_range);
-          *reinterpret_cast<uint2*>(a.out_bf16 + act_off(m, fo, Mpad)) = pk;
-        }
-      } else {
-        // fp32 output, row-major [token][feature]: a lane's 4 consecutive features of ONE token would make every
-        // store instruction touch 32 different rows; the 32 x 32 block is turned round in a wavefront-private
-        // LDS tile (behind the ring) so that an instruction covers 8 rows of 128 contiguous bytes
-        float* tb = reinterpret_cast<float*>(lds + kStages * kStageBytes) + wave * (32 * kTrRow);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<v4f*>(tb + col * kTrRow + 8 * q + rh) =
-              v4f{acc[nb][mb][4 * q], acc[nb][mb][4 * q + 1], acc[nb][mb][4 * q + 2], acc[nb][mb][4 * q + 3]};
-        __builtin_amdgcn_wave_barrier();
-        const int m0 = (mt_base + 8 * wm + 2 * mb) * 16, n = n0 + f;
-#pragma unroll
-        for (int pass = 0; pass < 4; ++pass) {
-          const int row = pass * 8 + trow, mm = m0 + row;
-          v4f v = *reinterpret_cast<const v4f*>(tb + row * kTrRow + f);
-          if (EPI == LEPI_ADD) v = v + old[nb & 1][mb][pass];
-          if (mm < a.M && n < a.N) *reinterpret_cast<v4f*>(a.out_f32 + (size_t)mm * a.ld_out + n) = v;
-        }
-        __builtin_amdgcn_wave_barrier();  // the tile is reused by the next accumulator block
-      }
+      const int m = m0 + mb * 16, n = n0 + nb * 16;
+      v4f v = acc[nb][mb];
+      if (ADD) v = v + old[mb % PF][nb];
+      if (full || (m < M && n < N)) *reinterpret_cast<v4f*>(out + (size_t)m * ld + n) = v;
     }
   }
-  if (EPI == LEPI_SWIGLU && out_of_range) atomicOr(a.err_flag, kErrFp16Range);
-};
-  lds_gemm_stream(reinterpret_cast<const uint8_t*>(a.Wt), reinterpret_cast<const uint8_t*>(a.Xt), a.n_tiles, a.m_tiles,
-                  a.k_tiles, lds, lane, __builtin_amdgcn_readfirstlane(wave), wn, wm, tile_at, epilogue);
+}
+
+// silu(gate) * up -> tiled fp16 operand; weight row tiles alternate gate / up.  The values are packed without a clamp and
+// the packed pairs are tested for an exponent of all ones (an infinity or a NaN: the value did not fit) with three
+// integer instructions per pair; only if one is found the block is packed again with the clamp, and the flag raised.
+template <class T>
+__device__ __forceinline__ void store_swiglu(v4f (&acc)[T::NB][T::MB], const LargeArgs& a, int nt0, int mt0, int lane) {
+  constexpr int NB = T::NB, MB = T::MB;
+  const int m0 = mt0 * 16 + (lane & 15), rq = (lane >> 4) * 4, Mpad = a.m_tiles * 16;
+  uint32_t bad = 0;
+  auto put = [&](int nb, int mb, bool clamp) {
+    const int m = m0 + mb * 16, nt = nt0 + nb;
+    if (m >= a.M || nt >= a.n_tiles) return;
+    const v4f g = acc[nb][mb], u = acc[nb + 1][mb];
+    float v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = silu_l(g[r]) * u[r];
+    uint2 pk;
+    if (clamp) {
+      bool out_of_range = false;
+      pk.x = pack_h16x2_track(v[0], v[1], out_of_range);
+      pk.y = pack_h16x2_track(v[2], v[3], out_of_range);
+      if (out_of_range) atomicOr(a.err_flag, kErrFp16Range);
+    } else {
+      pk.x = pack_h16x2_inrange(v[0], v[1]);
+      pk.y = pack_h16x2_inrange(v[2], v[3]);
+      bad |= (((pk.x & 0x7fff7fffu) + 0x04000400u) | ((pk.y & 0x7fff7fffu) + 0x04000400u)) & 0x80008000u;
+    }
+    *reinterpret_cast<uint2*>(a.out_bf16 + act_off(m, (nt >> 1) * 16 + rq, Mpad)) = pk;
+  };
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB; nb += 2) {
+      asm volatile("" : "+a"(acc[nb][mb]), "+a"(acc[nb + 1][mb])::"memory");
+      put(nb, mb, false);
+    }
+  if (__builtin_expect(__any(bad != 0), 0)) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; nb += 2) put(nb, mb, true);
+  }
+}
+
+// Blocks that hold tokens: rows packed on the device (d_rows) fill only part of the capacity the launch is sized for.
+// Whatever the block's height, all rows up to the next multiple of 256 are computed (from cleared inputs): a launch with
+// taller blocks reads them next.
+template <class T>
+__device__ __forceinline__ int row_blocks(int m_tiles, const int* d_rows) {
+  const int nb_m = (m_tiles + T::TM - 1) / T::TM;
+  return d_rows ? min(nb_m, (((*d_rows + 255) & ~255) + T::TM * 16 - 1) / (T::TM * 16)) : nb_m;
+}
+
+template <class T, int EPI>
+__global__ __launch_bounds__(256, T::PC) void k_gemm_lds(LargeArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  const int lane = threadIdx.x & 63, uwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb_n = (a.n_tiles + T::TN - 1) / T::TN, nb_m = row_blocks<T>(a.m_tiles, a.d_rows);
+  // persistent workgroup: gridDim.x is a multiple of 8, so this workgroup and the gridDim.x / 8 - 1 others of its
+  // XCD share out the XCD's run of blocks
+  const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3, end = run_of_xcd(xcd + 1, nb_n * nb_m);
+  int t = run_of_xcd(xcd, nb_n * nb_m) + (int)(blockIdx.x >> 3) - stride;
+  auto tile_at = [&](int& nt_base, int& mt_base, int&) {
+    t += stride;
+    if (t >= end) return false;
+    const Block blk = block_at(t, nb_n, nb_m);
+    nt_base = blk.nb * T::TN;
+    mt_base = blk.mb * T::TM;
+    return true;
+  };
+  auto epilogue = [&](v4f (&acc)[T::NB][T::MB], int nt_base, int mt_base, int) {
+    const int nt0 = nt_base + T::NB * (uwave & 1), mt0 = mt_base + T::MB * (uwave >> 1);
+    if (EPI == LEPI_SWIGLU) store_swiglu<T>(acc, a, nt0, mt0, lane);
+    else store_f32<T, EPI == LEPI_ADD>(acc, a.out_f32, a.ld_out, a.M, a.N, nt0, mt0, lane);
+  };
+  lds_gemm_stream<T>(reinterpret_cast<const uint8_t*>(a.Wt), reinterpret_cast<const uint8_t*>(a.Xt), a.n_tiles, a.m_tiles,
+                     a.k_tiles, a.k_tiles, lds, lane, uwave, tile_at, epilogue);
 }
 
 // Split-K form for outputs of few blocks and a long reduction (the O and down projections, and the QKV projection,
-// of a prompt or a few: 12-128 blocks for 256 CUs): a work item is one output block over one of a.k_split equal
-// ranges of k-steps, the items of a block are neighbours in an XCD's walk, and every item stores its sum as fp32
-// into its own slice of a.part ([k_split][M][N]); k_splitk_reduce then adds the slices in order, so the result does
-// not depend on which workgroup ran when.
-__global__ __launch_bounds__(256, 1) void k_gemm_lds_split(LargeArgs a) {
+// of a prompt or a few): a work item is one output block over one of a.k_split equal ranges of k-steps, the items of a
+// block are neighbours in an XCD's walk, and every item stores its sum as fp32 into its own slice of a.part
+// ([k_split][M][N]); k_splitk_reduce then adds the slices in order, so the result does not depend on which workgroup
+// ran when.
+template <class T>
+__global__ __launch_bounds__(256, T::PC) void k_gemm_lds_split(LargeArgs a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wn = wave & 1, wm = wave >> 1;
-  const int nb_n = (a.n_tiles + kBlkTiles - 1) / kBlkTiles;
-  int nb_m = (a.m_tiles + kBlkTiles - 1) / kBlkTiles;
-  if (a.d_rows) nb_m = min(nb_m, (*a.d_rows + kBlkTiles * 16 - 1) / (kBlkTiles * 16));
+  const int lane = threadIdx.x & 63, uwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb_n = (a.n_tiles + T::TN - 1) / T::TN, nb_m = row_blocks<T>(a.m_tiles, a.d_rows);
   const int S = a.k_split, Ks = a.k_tiles / S;
-  const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3;
-  const int total = blocks_of_xcd(xcd, nb_n, nb_m) * S;
-  int t = (int)(blockIdx.x >> 3) - stride;
-  auto tile_at = [&](int, int& nt_base, int& mt_base, int& k0) {
+  const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3, end = run_of_xcd(xcd + 1, nb_n * nb_m * S);
+  int t = run_of_xcd(xcd, nb_n * nb_m * S) + (int)(blockIdx.x >> 3) - stride;
+  auto tile_at = [&](int& nt_base, int& mt_base, int& k0) {
     t += stride;
-    if (t >= total) return false;
-    const Block blk = block_of_xcd(xcd, t / S, nb_n, nb_m);
-    nt_base = blk.nb * kBlkTiles;
-    mt_base = blk.mb * kBlkTiles;
+    if (t >= end) return false;
+    const Block blk = block_at(t / S, nb_n, nb_m);
+    nt_base = blk.nb * T::TN;
+    mt_base = blk.mb * T::TM;
     k0 = (t % S) * Ks;
     return true;
   };
-  auto epilogue = [&](v16f (&acc)[4][4], int nt_base, int mt_base, int k0) {
-    // as the store form of k_gemm_lds: every 32 x 32 block is turned round in a wavefront-private LDS tile so that
-    // a store instruction covers 8 rows of 128 contiguous bytes
-    float* out = a.part + (size_t)(k0 / Ks) * a.M * a.N;
-    const int col = lane & 31, rh = (lane >> 5) * 4;
-    const int f = (lane & 7) * 4, trow = lane >> 3;
-    float* tb = reinterpret_cast<float*>(lds + kStages * kStageBytes) + wave * (32 * kTrRow);
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        asm volatile("" : "+a"(acc[nb][mb])::"memory");
-        const int n0 = (nt_base + 8 * wn + 2 * nb) * 16;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<v4f*>(tb + col * kTrRow + 8 * q + rh) =
-              v4f{acc[nb][mb][4 * q], acc[nb][mb][4 * q + 1], acc[nb][mb][4 * q + 2], acc[nb][mb][4 * q + 3]};
-        __builtin_amdgcn_wave_barrier();
-        const int m0 = (mt_base + 8 * wm + 2 * mb) * 16, n = n0 + f;
-#pragma unroll
-        for (int pass = 0; pass < 4; ++pass) {
-          const int row = pass * 8 + trow, mm = m0 + row;
-          const v4f v = *reinterpret_cast<const v4f*>(tb + row * kTrRow + f);
-          if (mm < a.M && n < a.N) *reinterpret_cast<v4f*>(out + (size_t)mm * a.N + n) = v;
-        }
-        __builtin_amdgcn_wave_barrier();  // the tile is reused by the next accumulator block
-      }
-    }
+  auto epilogue = [&](v4f (&acc)[T::NB][T::MB], int nt_base, int mt_base, int k0) {
+    store_f32<T, false>(acc, a.part + (size_t)(k0 / Ks) * a.M * a.N, a.N, a.M, a.N, nt_base + T::NB * (uwave & 1),
+                        mt_base + T::MB * (uwave >> 1), lane);
   };
-  lds_gemm_stream<true>(reinterpret_cast<const uint8_t*>(a.Wt), reinterpret_cast<const uint8_t*>(a.Xt), a.n_tiles,
-                        a.m_tiles, a.k_tiles, lds, lane, __builtin_amdgcn_readfirstlane(wave), wn, wm, tile_at, epilogue,
-                        Ks);
+  lds_gemm_stream<T>(reinterpret_cast<const uint8_t*>(a.Wt), reinterpret_cast<const uint8_t*>(a.Xt), a.n_tiles, a.m_tiles,
+                     a.k_tiles, Ks, lds, lane, uwave, tile_at, epilogue);
 }
 
 // out (+)= part[0] + part[1] + ... in that order; four features per thread
@@ -400,178 +358,251 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(float* out, int ld_out, c
   *reinterpret_cast<v4f*>(o) = acc;
 }
 
-// Scoring LM head on the same engine: a workgroup owns 256 rows and one vocabulary slice (8 blocks of
-// 256 entries), computes the logits block by block and folds them into running per-row results
-// (log-sum-exp, two largest logits, logit of the target token); logits are never stored.
-__global__ __launch_bounds__(256, 1) void k_lmhead_lds(ScoreHeadArgs a, int slices) {
+// Scoring LM head on the same engine: a work item is one block of rows and one slice of the vocabulary (`bps` blocks of
+// 256 entries); the logits are computed block by block and folded into running per-row results (log-sum-exp, two
+// largest logits, logit of the target token), never stored.  Persistent: the items' blocks form one stream.
+// A block's 128 entries of a wavefront are reduced over the four lanes that share a row before they meet the running
+// result, so a row's state sits in ONE lane (row 16 mb + l % 16: the lanes l / 16 = mb % 4) and takes registers the
+// matrix loop does not need.
+template <class T, bool TOP>
+__global__ __launch_bounds__(256, T::PC) void k_lmhead_lds(ScoreHeadArgs a, int bps) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wn = wave & 1, wm = wave >> 1;
-  const int nb_m = (a.m_tiles + kBlkTiles - 1) / kBlkTiles;
-  const Block blk = block_of(blockIdx.x, slices, nb_m);
-  if (!blk.valid) return;  // whole workgroup
-  const int mt_base = blk.mb * kBlkTiles;
-  if (a.d_rows && mt_base * 16 >= *a.d_rows) return;  // rows packed on the device: this block holds no token
-  const int col = lane & 31, rh = (lane >> 5) * 4;
-  const int uwave = __builtin_amdgcn_readfirstlane(wave);
-  // The per-row running results live in LDS behind the ring (28 words per thread, word-interleaved over the
-  // threads) and are loaded only inside the epilogue, so that they take no registers from the matrix loop.
-  float* st_f = reinterpret_cast<float*>(lds + kStages * kStageBytes) + threadIdx.x;
-  int* st_i = reinterpret_cast<int*>(st_f);
-  constexpr int SM = 0, SS = 4, SV1 = 8, SI1 = 12, SV2 = 16, SZT = 20, STG = 24;  // word index + mb, x 256 threads
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
-    const int m = (mt_base + 8 * wm + 2 * mb) * 16 + col;
-    st_f[(SM + mb) * 256] = -INFINITY;
-    st_f[(SS + mb) * 256] = 0.f;
-    st_f[(SV1 + mb) * 256] = -INFINITY;
-    st_i[(SI1 + mb) * 256] = 0x7fffffff;
-    st_f[(SV2 + mb) * 256] = -INFINITY;
-    st_f[(SZT + mb) * 256] = -INFINITY;
-    st_i[(STG + mb) * 256] = (m < a.M) ? a.targets[m] : -1;
-  }
-  const int nb_n = (a.n_tiles + kBlkTiles - 1) / kBlkTiles;
-  const int vocab = a.n_tiles * 16;
-  const int nbk0 = blk.nb * 8, nbk1 = min(blk.nb * 8 + 8, nb_n);
-  auto tile_at = [&](int i, int& nt_base, int& mt_b) {
-    nt_base = (nbk0 + i) * kBlkTiles;
-    mt_b = mt_base;
-    return nbk0 + i < nbk1;
+  constexpr int NB = T::NB, MB = T::MB, H = MB / 4;
+  constexpr float kLog2e = 1.4426950408889634f;
+  const int lane = threadIdx.x & 63, uwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wn = uwave & 1, wm = uwave >> 1, col = lane & 15, lg = lane >> 4;
+  const int nb_n = (a.n_tiles + T::TN - 1) / T::TN, nb_m = row_blocks<T>(a.m_tiles, a.d_rows);
+  const int slices = (nb_n + bps - 1) / bps;
+  const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3, end = run_of_xcd(xcd + 1, slices * nb_m);
+  int t = run_of_xcd(xcd, slices * nb_m) + (int)(blockIdx.x >> 3) - stride;
+  int b_next = 0, b_end = 0, mt_item = 0;  // blocks of the item that tile_at is in
+  auto tile_at = [&](int& nt_base, int& mt_base, int&) {
+    if (b_next == b_end) {
+      t += stride;
+      if (t >= end) return false;
+      const Block blk = block_at(t, slices, nb_m);
+      b_next = blk.nb * bps;
+      b_end = min(b_next + bps, nb_n);
+      mt_item = blk.mb * T::TM;
+    }
+    nt_base = b_next++ * T::TN;
+    mt_base = mt_item;
+    return true;
   };
-  auto epilogue = [&](v16f (&acc)[4][4], int nt_base, int) {
-    const int nbk = nt_base / kBlkTiles;
-    const bool full = (nbk + 1) * kBlkTiles <= a.n_tiles;  // all 256 entries of the block exist (workgroup-uniform)
-    // one group of 32 rows (mb) at a time, so that only its running results and one accumulator block are live
+  Lse lse[H];
+  Top2 top[H];
+  float zt[H];
+  int target[H];
+  auto epilogue = [&](v4f (&acc)[NB][MB], int nt_base, int mt_base, int) {
+    const int blk = nt_base / T::TN, slice = blk / bps;
+    const int nt0 = nt_base + NB * wn, mt0 = mt_base + MB * wm;
+    if (blk == slice * bps) {  // a new item
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      Lse lse = Lse{st_f[(SM + mb) * 256], st_f[(SS + mb) * 256]};
-      Top2 top = Top2{st_f[(SV1 + mb) * 256], st_i[(SI1 + mb) * 256], st_f[(SV2 + mb) * 256]};
-      float zt = st_f[(SZT + mb) * 256];
-      const int target = st_i[(STG + mb) * 256];
+      for (int h = 0; h < H; ++h) {
+        const int m = (mt0 + 4 * h + lg) * 16 + col;
+        lse[h] = lse_empty();
+        top[h] = top2_empty();
+        zt[h] = -INFINITY;
+        target[h] = m < a.M ? a.targets[m] : -1;
+      }
+    }
+    const bool full = nt0 + NB <= a.n_tiles;  // all 128 entries exist (wavefront-uniform)
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb) {
-        // the accumulator block is taken from its registers here, not earlier (volatile statements keep their order)
+    for (int mb = 0; mb < MB; ++mb) {
+      const int h = mb >> 2, owner = (mb & 3) * 16 + col;
+      float z[NB * 4];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
         asm volatile("" : "+a"(acc[nb][mb])::"memory");
-        // this lane's 16 entries of the block: n0 + 8 q + r (q, r = 0..3) in register 4 q + r
-        const int n0 = (nbk * kBlkTiles + 8 * wn + 2 * nb) * 16 + rh;
-        v16f z = acc[nb][mb];
-        if (!full) {
 #pragma unroll
-          for (int j = 0; j < 16; ++j)
-            if (n0 + 8 * (j >> 2) + (j & 3) >= vocab) z[j] = -INFINITY;
+        for (int r = 0; r < 4; ++r) z[4 * nb + r] = (full || nt0 + nb < a.n_tiles) ? acc[nb][mb][r] : -INFINITY;
+      }
+      float bm = z[0];
+#pragma unroll
+      for (int j = 1; j < NB * 4; ++j) bm = fmaxf(bm, z[j]);
+      bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
+      bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
+      // no entry exists (or none compares): nothing to add; every other lane's terms are exp2(<= 0)
+      const float mk = (bm > -INFINITY ? bm : 0.f) * kLog2e;
+      float sum = 0.f;
+#pragma unroll
+      for (int j = 0; j < NB * 4; ++j) sum += __builtin_amdgcn_exp2f(fmaf(z[j], kLog2e, -mk));
+      sum += __shfl_xor(sum, 16, 64);
+      sum += __shfl_xor(sum, 32, 64);
+      const int d = __shfl(target[h], owner, 64) - nt0 * 16;  // the target's index among the wavefront's entries
+      float hit = -INFINITY;
+      const bool here = d >= 0 && d < NB * 16 && ((d >> 2) & 3) == lg;
+      if (__any(here)) {
+        const int idx = (d >> 4) * 4 + (d & 3);
+#pragma unroll
+        for (int j = 0; j < NB * 4; ++j)
+          if (here && j == idx) hit = z[j];
+        hit = fmaxf(hit, __shfl_xor(hit, 16, 64));
+        hit = fmaxf(hit, __shfl_xor(hit, 32, 64));
+      }
+      const bool own = lg == (mb & 3);
+      Top2 t2 = top2_empty();
+      if (TOP) {
+        // two largest of the block and the lowest index of the largest: three instructions per entry, then the indices
+        float v1 = -INFINITY, v2 = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < NB * 4; ++j) {
+          v2 = fmaxf(v2, fminf(v1, z[j]));
+          v1 = fmaxf(v1, z[j]);
         }
-        float bm = z[0];
+        int i1 = 0x7fffffff;
 #pragma unroll
-        for (int j = 1; j < 16; ++j) bm = fmaxf(bm, z[j]);
-        if (bm > lse.m) {  // -inf never gets here: an empty block leaves the state untouched
-          lse.s *= __expf(lse.m - bm);
-          lse.m = bm;
+        for (int j = NB * 4 - 1; j >= 0; --j)
+          if (z[j] == v1) i1 = (nt0 + (j >> 2)) * 16 + 4 * lg + (j & 3);
+        t2 = Top2{v1, i1, v2};
+#pragma unroll
+        for (int o = 16; o <= 32; o <<= 1)
+          t2 = top2_merge(t2, Top2{__shfl_xor(t2.v1, o, 64), __shfl_xor(t2.i1, o, 64), __shfl_xor(t2.v2, o, 64)});
+      }
+      if (own) {
+        const float m_new = fmaxf(lse[h].m, bm);
+        if (m_new > -INFINITY) {
+          lse[h].s = lse[h].s * __builtin_amdgcn_exp2f((lse[h].m - m_new) * kLog2e) +
+                     (bm > -INFINITY ? sum * __builtin_amdgcn_exp2f((bm - m_new) * kLog2e) : 0.f);
+          lse[h].m = m_new;
         }
-        if (lse.m > -INFINITY) {
-          const float mm = lse.m;
-          float add = 0.f;
+        zt[h] = fmaxf(zt[h], hit);
+        if (TOP) top[h] = top2_merge(top[h], t2);
+      }
+    }
+    if (blk + 1 == min(slice * bps + bps, nb_n)) {  // the item's last block
 #pragma unroll
-          for (int j = 0; j < 16; ++j) add += __expf(z[j] - mm);  // exp(-inf) = 0 for missing entries
-          lse.s += add;
-        }
-        if (a.want_top && (bm > top.v2 || bm == top.v1)) {  // only then can the two largest (or a tie) change
-#pragma unroll
-          for (int j = 0; j < 16; ++j) top2_push(top, z[j], n0 + 8 * (j >> 2) + (j & 3));
-        }
-        const int d = target - n0;
-        if (d >= 0 && d < 32 && (d & 4) == 0) {
-          const int idx = (d >> 3) * 4 + (d & 3);
-#pragma unroll
-          for (int j = 0; j < 16; ++j)
-            if (j == idx) zt = z[j];
+      for (int h = 0; h < H; ++h) {
+        const int m = (mt0 + 4 * h + lg) * 16 + col;
+        if (m < a.M) {
+          ScorePartial* p = reinterpret_cast<ScorePartial*>(a.part) + ((size_t)(slice * 2 + wn)) * a.M + m;
+          p->m = lse[h].m; p->s = lse[h].s; p->v1 = top[h].v1; p->i1 = top[h].i1; p->v2 = top[h].v2; p->zt = zt[h];
         }
       }
-      st_f[(SM + mb) * 256] = lse.m;
-      st_f[(SS + mb) * 256] = lse.s;
-      st_f[(SV1 + mb) * 256] = top.v1;
-      st_i[(SI1 + mb) * 256] = top.i1;
-      st_f[(SV2 + mb) * 256] = top.v2;
-      st_f[(SZT + mb) * 256] = zt;
     }
   };
-  lds_gemm_stream(reinterpret_cast<const uint8_t*>(a.Wt), reinterpret_cast<const uint8_t*>(a.Xt), a.n_tiles, a.m_tiles,
-                  a.k_tiles, lds, lane, uwave, wn, wm, tile_at, epilogue);
-  Lse lse[4];
-  Top2 top[4];
-  float zt[4];
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
-    lse[mb] = Lse{st_f[(SM + mb) * 256], st_f[(SS + mb) * 256]};
-    top[mb] = Top2{st_f[(SV1 + mb) * 256], st_i[(SI1 + mb) * 256], st_f[(SV2 + mb) * 256]};
-    zt[mb] = st_f[(SZT + mb) * 256];
-  }
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
-    const Lse ol = {__shfl_xor(lse[mb].m, 32, 64), __shfl_xor(lse[mb].s, 32, 64)};
-    const Top2 ot = {__shfl_xor(top[mb].v1, 32, 64), __shfl_xor(top[mb].i1, 32, 64), __shfl_xor(top[mb].v2, 32, 64)};
-    lse[mb] = lse_merge(lse[mb], ol);
-    top[mb] = top2_merge(top[mb], ot);
-    zt[mb] = fmaxf(zt[mb], __shfl_xor(zt[mb], 32, 64));
-    const int m = (mt_base + 8 * wm + 2 * mb) * 16 + col;
-    if (lane < 32 && m < a.M) {
-      ScorePartial* p = reinterpret_cast<ScorePartial*>(a.part) + ((size_t)(blk.nb * 2 + wn)) * a.M + m;
-      p->m = lse[mb].m; p->s = lse[mb].s; p->v1 = top[mb].v1; p->i1 = top[mb].i1; p->v2 = top[mb].v2;
-      p->zt = zt[mb];
-    }
-  }
+  lds_gemm_stream<T>(reinterpret_cast<const uint8_t*>(a.Wt), reinterpret_cast<const uint8_t*>(a.Xt), a.n_tiles, a.m_tiles,
+                     a.k_tiles, a.k_tiles, lds, lane, uwave, tile_at, epilogue);
 }
 
-template <int EPI>
-void launch_one(const LargeArgs& a, hipStream_t st) {
-  static bool configured = false;  // per process; the attribute is a property of the function
-  const int lds_bytes = kStages * kStageBytes + kTrBytes;
-  if (!configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_lds<EPI>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-    configured = true;
-  }
-  const int nb_n = (a.n_tiles + kBlkTiles - 1) / kBlkTiles, nb_m = (a.m_tiles + kBlkTiles - 1) / kBlkTiles;
-  // persistent: one workgroup per CU (the kernel fills a CU), each walks launch indices i, i + grid, ...
-  const int grid = std::min(grid_of(nb_n, nb_m), kPersistentGrid);
-  k_gemm_lds<EPI><<<grid, 256, lds_bytes, st>>>(a);
+// The runtime's limit on dynamic LDS is raised once per kernel.
+template <class T, typename Kernel>
+void allow_lds(Kernel* k) {
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLds);
 }
+// workgroups of a launch of `items` work items: one round of the CUs at most, a multiple of the XCDs
+template <class T>
+int grid_of(size_t items) { return (int)std::min<size_t>((items + kXcds - 1) / kXcds * kXcds, (size_t)kCus * T::PC); }
+template <class T>
+size_t blocks_of(const LargeArgs& a) {
+  return (size_t)((a.n_tiles + T::TN - 1) / T::TN) * ((a.m_tiles + T::TM - 1) / T::TM);
+}
+
+template <class T, int EPI>
+void launch_tile(const LargeArgs& a, hipStream_t st) {
+  static const bool configured = (allow_lds<T>(&k_gemm_lds<T, EPI>), true);
+  (void)configured;
+  k_gemm_lds<T, EPI><<<grid_of<T>(blocks_of<T>(a)), 256, T::kLds, st>>>(a);
+}
+template <class T>
+void launch_split(const LargeArgs& a, hipStream_t st) {
+  static const bool configured = (allow_lds<T>(&k_gemm_lds_split<T>), true);
+  (void)configured;
+  k_gemm_lds_split<T><<<grid_of<T>(blocks_of<T>(a) * a.k_split), 256, T::kLds, st>>>(a);
+}
+template <class T>
+void launch(const LargeArgs& a, int epi, hipStream_t st) {
+  if (a.k_split > 1) launch_split<T>(a, st);
+  else if (epi == LEPI_STORE) launch_tile<T, LEPI_STORE>(a, st);
+  else if (epi == LEPI_ADD) launch_tile<T, LEPI_ADD>(a, st);
+  else launch_tile<T, LEPI_SWIGLU>(a, st);
+}
+
+// The tiles, features x tokens per workgroup, and what they were measured to take: microseconds per k-step for a
+// workgroup that has its CU to itself, for the two of a CU that hosts two, and per block outside the k-steps (SwiGLU
+// form; the fp32 forms move four times the bytes and take 1.7 times as long).  Sums do not depend on the tile.
+struct TileCost {
+  int features, tokens, per_cu;
+  double alone, pair, block;
+  void (*run)(const LargeArgs&, int, hipStream_t);
+};
+const TileCost kTiles[] = {
+    {256, 256, 1, 0.74, 0.0, 9.0, &launch<Tile<8, 8, 4, 1>>},   // fewest bytes per product: the large passes
+    {192, 256, 1, 0.60, 0.0, 7.0, &launch<Tile<6, 8, 4, 1>>},
+    {256, 128, 2, 0.42, 0.76, 5.0, &launch<Tile<8, 4, 3, 2>>},
+    {192, 128, 2, 0.37, 0.62, 4.0, &launch<Tile<6, 4, 4, 2>>},
+    {128, 128, 2, 0.25, 0.44, 3.0, &launch<Tile<4, 4, 4, 2>>},
+    {128, 64, 2, 0.16, 0.30, 1.5, &launch<Tile<4, 2, 4, 2>>},   // a few dozen rows
+};
+
+// What a launch takes, by its busiest CU.  Measured against it: 4096 x 1536 x 8960 (features and tokens swapped) 183 us
+// in 96 blocks of 256 x 256, 104 us in 256 of 192 x 128; 512 tokens x 17 920 features 38.6 and 32.1 us; 800 tokens 73.6 and
+// 44.0 us; 98 304 tokens 4.46 ms in 256 x 256, 4.55-5.2 ms in the others.
+double cost_of(const TileCost& t, int features, int tokens, int k_steps, int splits, bool fp32) {
+  const long long items = (long long)((features + t.features - 1) / t.features) * ((tokens + t.tokens - 1) / t.tokens) * splits;
+  const long long per_cu = (items + kCus - 1) / kCus;
+  const double steps = (double)k_steps / splits, out = t.block * (fp32 ? 1.7 : 1.0);
+  if (t.per_cu == 1) return per_cu * (steps * t.alone + out);
+  return (per_cu / 2) * (steps * t.pair + 2 * out) + (per_cu % 2) * (steps * t.alone + out);
+}
+const TileCost& best_tile(int features, int tokens, int k_steps, int splits, bool fp32, double* cost) {
+  const TileCost* best = nullptr;
+  for (const TileCost& t : kTiles) {
+    const double c = cost_of(t, features, tokens, k_steps, splits, fp32);
+    if (!best || c < *cost) {
+      best = &t;
+      *cost = c;
+    }
+  }
+  return *best;
+}
+
+// rows a launch is expected to hold: where they are packed on the device the launch knows its capacity alone (candidate
+// actions of 1 .. A tokens fill about half of it)
+int expected_rows(const LargeArgs& a) { return a.d_rows ? (a.M + 1) / 2 : a.M; }
 
 }  // namespace
 
-void lmhead_score_lds(const ScoreHeadArgs& a, int slices, hipStream_t st) {
-  static bool configured = false;
-  const int lds_bytes = kStages * kStageBytes + 28 * 256 * 4;  // ring + per-thread running results
-  if (!configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lmhead_lds), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              lds_bytes);
-    configured = true;
-  }
-  k_lmhead_lds<<<grid_of(slices, (a.m_tiles + kBlkTiles - 1) / kBlkTiles), 256, lds_bytes, st>>>(a, slices);
+// Vocabulary blocks per slice of the scoring LM head for R rows: slices as long as they can be while a launch still
+// has several items per CU to even out (3332 rows x 128 256 entries: 882 items of 8 blocks on 256 CUs are four rounds where
+// 3.4 would do; 127 rows: 75 workgroups in all).
+int lmhead_lds_slice(int R) { return R <= 1024 ? 1 : R <= 4096 ? 2 : R <= 16384 ? 4 : 8; }
+int lmhead_lds_parts(int n_tiles, int R) {
+  const int blocks = (n_tiles + 15) / 16, bps = lmhead_lds_slice(R);
+  return 2 * ((blocks + bps - 1) / bps);
+}
+
+template <class T, bool TOP>
+static void launch_lmhead(const ScoreHeadArgs& a, hipStream_t st) {
+  static const bool configured = (allow_lds<T>(&k_lmhead_lds<T, TOP>), true);
+  (void)configured;
+  const int bps = lmhead_lds_slice(a.M);
+  const size_t items = (size_t)(((a.n_tiles + T::TN - 1) / T::TN + bps - 1) / bps) * ((a.m_tiles + T::TM - 1) / T::TM);
+  k_lmhead_lds<T, TOP><<<grid_of<T>(items), 256, T::kLds, st>>>(a, bps);
+}
+void lmhead_score_lds(const ScoreHeadArgs& a, hipStream_t st) {
+  // blocks of 128 rows where blocks of 256 would be padding for more than the 8 % that the smaller block costs
+  const bool narrow = 1.08 * ((a.m_tiles + 7) / 8) < 2 * ((a.m_tiles + 15) / 16);
+  if (narrow) a.want_top ? launch_lmhead<Tile<8, 4, 3, 2>, true>(a, st) : launch_lmhead<Tile<8, 4, 3, 2>, false>(a, st);
+  else a.want_top ? launch_lmhead<Tile<8, 8, 4, 1>, true>(a, st) : launch_lmhead<Tile<8, 8, 4, 1>, false>(a, st);
 }
 
 bool gemm_lds_split(const LargeArgs& a0, bool accumulate, float* part, size_t part_floats, hipStream_t st) {
-  const int nb_n = (a0.n_tiles + kBlkTiles - 1) / kBlkTiles, nb_m = (a0.m_tiles + kBlkTiles - 1) / kBlkTiles;
-  const int blocks = nb_n * nb_m;
-  if (!part || blocks > kPersistentGrid / 2 || a0.N % 4 != 0) return false;
-  // the most splits, up to 8 and to one round of workgroups, that leave every range even and at least 8 k-steps long
+  const int blocks = (a0.n_tiles + 15) / 16 * ((a0.m_tiles + 15) / 16);  // of 256 x 256
+  if (!part || blocks > kCus / 2 || a0.N % 4 != 0) return false;
+  // The most splits, up to 8 and to one round of blocks of 256 x 256, that leave every range even and at least 8 k-steps
+  // long.  Not by the tile that is chosen below: the order of the sums then follows from the sizes alone.
   int S = 0;
-  for (int s = std::min(8, kPersistentGrid / blocks); s >= 2 && !S; --s)
+  for (int s = std::min(8, kCus / blocks); s >= 2 && !S; --s)
     if (a0.k_tiles % s == 0 && (a0.k_tiles / s) % 2 == 0 && a0.k_tiles / s >= 8 &&
         (size_t)s * a0.M * a0.N <= part_floats)
       S = s;
   if (!S) return false;
-  static bool configured = false;
-  const int lds_bytes = kStages * kStageBytes + kTrBytes;
-  if (!configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_lds_split), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              lds_bytes);
-    configured = true;
-  }
   LargeArgs a = a0;
   a.k_split = S;
   a.part = part;
-  const int grid = std::min(kPersistentGrid, 8 * blocks_of_xcd(0, nb_n, nb_m) * S);
-  k_gemm_lds_split<<<grid, 256, lds_bytes, st>>>(a);
+  double cost = 0.0;
+  best_tile(a.N, expected_rows(a), a.k_tiles, S, true, &cost).run(a, LEPI_STORE, st);
   const size_t quads = (size_t)a.M * (a.N / 4);
   k_splitk_reduce<<<(unsigned)((quads + 255) / 256), 256, 0, st>>>(a.out_f32, a.ld_out, part, S, a.M, a.N,
                                                                   accumulate ? 1 : 0, a.d_rows);
@@ -579,9 +610,8 @@ bool gemm_lds_split(const LargeArgs& a0, bool accumulate, float* part, size_t pa
 }
 
 void gemm_lds(const LargeArgs& a, int epi, hipStream_t st) {
-  if (epi == LEPI_STORE) launch_one<LEPI_STORE>(a, st);
-  else if (epi == LEPI_ADD) launch_one<LEPI_ADD>(a, st);
-  else launch_one<LEPI_SWIGLU>(a, st);
+  double cost = 0.0;
+  best_tile(a.n_tiles * 16, expected_rows(a), a.k_tiles, 1, epi != LEPI_SWIGLU, &cost).run(a, epi, st);
 }
 
 }  // namespace bf16

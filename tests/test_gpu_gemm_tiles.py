@@ -1,0 +1,72 @@
+"""The LDS-staged matrix kernels over the sizes at which they choose another tile, at remainders of features, tokens
+and vocabulary: a sequence scored alone and in a call of many, and both against the direct kernels.  A block that is
+missed, taken twice or read from the wrong place moves logits by their own size."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from parity import LOGP_TOL_BF16
+from paper_2511_20100_amd import inputs
+
+# 512 / 256 / 1376 features (86 row tiles: remainders of 128, 192 and 256) and 2064 vocabulary entries (129 tiles)
+CFG = inputs.ModelConfig(1, 256, 2, 1, 128, 688, 2064, dtype="bf16")
+# The forms differ where a value falls on the other side of an fp16 rounding (the direct kernels' silu differs from the
+# staged ones' by 1e-6; the row norm of large calls adds its squares in another order than that of small ones).  Each form
+# is within LOGP_TOL_BF16 = 1e-2 of the exact value (what fp16 operands give), so that bounds their difference up to a factor
+# of two; with one block of layers it is an order smaller, and a wrong block gives differences of order 1.
+TOL = LOGP_TOL_BF16
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import torch
+    from paper_2511_20100_amd import mtmc
+    torch.cuda.set_device(0)
+    return mtmc
+
+
+@pytest.fixture(scope="module")
+def handle(lib):
+    w = inputs.make_weights(CFG, seed=0, std=0.05, gain_std=0.1)
+    handle = lib.mtmc_weights_create(lib.make_config(CFG, 512), w.blob())
+    yield handle
+    lib.mtmc_weights_destroy(handle)
+
+
+def _lds(lib, handle, on):
+    lib.mtmc_set_option(handle, lib.MTMC_OPT_GEMM_LDS_MIN_BLOCKS, 1 if on else 1 << 20)
+
+
+@pytest.mark.parametrize("n_seqs,seq_len,prompt_len", [(2, 33, 1), (2, 64, 60), (3, 85, 20), (3, 343, 2), (9, 233, 7), (16, 259, 3),
+                                                       (47, 128, 64), (63, 190, 90), (129, 257, 250), (260, 257, 200)])
+def test_scoring_is_the_same_in_every_tile(lib, handle, n_seqs, seq_len, prompt_len):
+    import torch
+    seqs = torch.from_numpy(inputs.make_sequences(n_seqs, seq_len, CFG.vocab, seed=4)).cuda()
+    _lds(lib, handle, True)
+    lp, top1, margin = lib.mtmc_score(handle, seqs, prompt_len, want_top1=True)
+    assert torch.equal(lib.mtmc_score(handle, seqs, prompt_len), lp)
+    for s in (0, n_seqs - 1):
+        one = lib.mtmc_score(handle, seqs[s:s + 1].contiguous(), prompt_len, want_top1=True)
+        assert float((one[0][0] - lp[s]).abs().max()) <= TOL and float((one[2][0] - margin[s]).abs().max()) <= 2 * TOL
+        clear = margin[s] > 2 * TOL
+        assert torch.equal(one[1][0][clear], top1[s][clear])
+    _lds(lib, handle, False)
+    direct = lib.mtmc_score(handle, seqs, prompt_len)
+    lib.mtmc_poll_errors(handle)
+    assert float((direct - lp).abs().max()) <= TOL
+
+
+@pytest.mark.parametrize("n_states,state_len,n_actions,max_len", [(1, 2, 3, 5), (3, 65, 7, 33), (8, 200, 40, 17)])
+def test_packed_candidates_are_the_same_in_every_tile(lib, handle, n_states, state_len, n_actions, max_len):
+    import torch
+    states = torch.from_numpy(inputs.make_prompts(n_states, state_len, CFG.vocab, seed=5)).cuda()
+    actions, lens = (torch.from_numpy(x).cuda() for x in inputs.make_actions(n_states, n_actions, max_len, CFG.vocab, 6, 0))
+    _lds(lib, handle, True)
+    tok, act, _ = lib.mtmc_score_actions(handle, states, actions, lens)
+    one = lib.mtmc_score_actions(handle, states[:1].contiguous(), actions[:1].contiguous(), lens[:1].contiguous())
+    assert float((one[0][0] - tok[0]).abs().max()) <= TOL
+    assert float((one[1][0] - act[0]).abs().max()) <= TOL * max_len
+    _lds(lib, handle, False)
+    direct = lib.mtmc_score_actions(handle, states, actions, lens)
+    lib.mtmc_poll_errors(handle)
+    assert float((direct[0] - tok).abs().max()) <= TOL
