@@ -1,6 +1,8 @@
 // Host-side engine: blob layout, workspace plans and the per-dtype schedulers.
 #pragma once
 
+#include <functional>
+
 #include "common.h"
 
 namespace mtmc {
@@ -219,6 +221,10 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
 int bf16_score(const mtmc_weights* w, const ScorePlan& p, const ScoreArgs& a, hipStream_t st);
 int f32_score_actions(const mtmc_weights* w, const ActionPlan& p, const ActionArgs& a, hipStream_t st);
 int bf16_score_actions(const mtmc_weights* w, const ActionPlan& p, const ActionArgs& a, hipStream_t st);
+// Returns in *out the instantiated graph of one decode step for this workspace and shape, capturing it if it is not cached
+// (nullptr when graphs are off or `st` is already capturing: launch the step directly).
+int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, const std::function<void(hipStream_t)>& step,
+                 hipGraphExec_t* out);
 void destroy_graph_cache(mtmc_weights* w);
 int kernel_timer_set(mtmc_weights* w, int cls, int every);
 int kernel_timer_read(mtmc_weights* w, hipStream_t st, double* total_ms, int64_t* launches, double* empty_pair_ms);

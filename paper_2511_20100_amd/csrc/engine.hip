@@ -1,6 +1,7 @@
 // Workspace plans, auxiliary tables and the fp32 schedulers.
 #include <cmath>
 
+#include "bf16_kernels.h"
 #include "engine.h"
 #include "kernels.h"
 
@@ -91,6 +92,7 @@ RolloutPlan plan_rollout(const mtmc_weights* w, int n_prompts, int prompt_len, i
   if (!bf) {
     p.gu = cv.take<float>((size_t)p.Tmax * 2 * F);
     p.logits = cv.take<float>((size_t)p.B * c.vocab);
+    p.ctl = cv.take<bf16::SampleCtl>(1);
   } else {
     bf16_plan_rollout_extra(w, p, cv);
   }
@@ -233,14 +235,15 @@ void f32_layers(const mtmc_weights* w, const F32Acts& A, int T, TokMap map, KvPo
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerWeights& L = w->layers[l];
     const int kvl = l * layer_stride;
-    f32::rmsnorm(A.x, A.h, L.attn_norm, c.rms_eps, T, d, st);
-    f32::gemm(A.qkv, nqkv, A.x, d, (const float*)L.wqkv, T, nqkv, d, false, st);
-    f32::rope_kv_write(A.qkv, T, Hq, Hkv, hd, w->rope_cos, w->rope_sin, map, pool, kvl, st);
-    f32::attention(A.o, A.qkv, T, Hq, Hkv, hd, map, pool, kvl, st);
+    f32::norm_gemm(A.qkv, nqkv, A.h, L.attn_norm, c.rms_eps, A.x, (const float*)L.wqkv, T, nqkv, d, st);
+    if (map.S == 1 && map.d_step) {  // a decode step
+      f32::attention_dec(A.o, A.qkv, T, Hq, Hkv, hd, w->rope_cos, w->rope_sin, map, pool, kvl, st);
+    } else {
+      f32::rope_kv_write(A.qkv, T, Hq, Hkv, hd, w->rope_cos, w->rope_sin, map, pool, kvl, st);
+      f32::attention(A.o, A.qkv, T, Hq, Hkv, hd, map, pool, kvl, st);
+    }
     f32::gemm(A.h, d, A.o, nq, (const float*)L.wo, T, d, nq, true, st);
-    f32::rmsnorm(A.x, A.h, L.ffn_norm, c.rms_eps, T, d, st);
-    f32::gemm(A.gu, 2 * F, A.x, d, (const float*)L.wgu, T, 2 * F, d, false, st);
-    f32::swiglu(A.a, A.gu, T, F, st);
+    f32::norm_swiglu(A.a, A.h, L.ffn_norm, c.rms_eps, A.x, A.gu, (const float*)L.wgu, T, F, d, st);
     f32::gemm(A.h, d, A.a, F, (const float*)L.wdown, T, d, F, true, st);
   }
 }
@@ -265,6 +268,7 @@ int f32_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts,
     launch_build_page_table(p.page_table, p.B, p.max_pages, p.n_samples, p.n_full, p.shared_total, st);
   }
   launch_set_int(p.d_step, 0, st);
+  launch_set_int(p.d_step + 1, 0, st);  // arrival counter of the sampler
   // ---- prefill: whole prompts, chunk by chunk; the prompt's pages are those of its first sample
   for (int p0 = 0; p0 < p.n_prompts; p0 += p.chunk_prompts) {
     const int np = std::min(p.chunk_prompts, p.n_prompts - p0);
@@ -287,18 +291,28 @@ int f32_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts,
     launch_fork_tail_pages(pool, c.n_layers, p.B, p.n_samples, p.n_full, 4, st);
   // ---- step 0 samples from the prompt's last position; step i > 0 first feeds token i-1
   TokMap dmap{1, 1, p.prompt_len - 1, p.d_step, ragged ? p.row_pos : nullptr};
-  int* done = (ragged && sa.stop_id >= 0) ? p.done : nullptr;
-  for (int i = 0; i < p.max_new; ++i) {
-    if (i > 0) {
-      f32::embed(p.hB, p.cur_ids, p.B, (const float*)w->embed, d, V, w->err_flag, st);
-      F32Acts D{p.hB, (float*)p.x, p.qkv, (float*)p.o, p.gu, (float*)p.a};
-      f32_layers(w, D, p.B, dmap, pool, 1, st);
-    }
-    f32::rmsnorm((float*)p.xB, p.hB, w->final_norm, c.rms_eps, p.B, d, st);
-    f32::gemm(p.logits, V, (const float*)p.xB, d, (const float*)w->lm_head, p.B, V, d, false, st);
-    f32::sample(p.logits, p.B, V, sa.inv_temp, sa.greedy, sa.seed, sa.seq_offset, p.d_step, sa.max_new,
-                p.cur_ids, sa.out_ids, sa.out_logprobs, sa.stop_id, done, sa.out_lens, st);
-    launch_add_int(p.d_step, 1, st);
+  // what changes between calls of one shape goes through the control block: a captured step stays valid
+  bf16::SampleCtl* ctl = (bf16::SampleCtl*)p.ctl;
+  bf16::set_sample_ctl(ctl, bf16::SampleCtl{sa.greedy, sa.inv_temp, (uint32_t)(sa.seed & 0xffffffffu), (uint32_t)(sa.seed >> 32),
+                                            sa.seq_offset, sa.max_new, sa.out_ids, sa.out_logprobs, sa.stop_id,
+                                            (ragged && sa.stop_id >= 0) ? p.done : nullptr, sa.out_lens, nullptr, nullptr}, st);
+  auto sample = [&](hipStream_t s) {
+    f32::norm_gemm(p.logits, V, p.hB, w->final_norm, c.rms_eps, (float*)p.xB, (const float*)w->lm_head, p.B, V, d, s);
+    f32::sample(p.logits, p.B, V, ctl, p.d_step, p.cur_ids, p.hB, (const float*)w->embed, d, w->err_flag, s);
+  };
+  auto decode_step = [&](hipStream_t s) {  // the sampler left the embeddings of the last tokens in hB
+    f32_layers(w, F32Acts{p.hB, (float*)p.x, p.qkv, (float*)p.o, p.gu, (float*)p.a}, p.B, dmap, pool, 1, s);
+    sample(s);
+  };
+  sample(st);
+  // a dozen small launches per step: replayed as a graph they follow each other without the host (capturing one takes
+  // about as long as a few steps launched one by one)
+  hipGraphExec_t exec = nullptr;
+  if (p.max_new >= 8)
+    if (int rc = decode_graph(w, p, st, decode_step, &exec)) return rc;
+  for (int i = 1; i < p.max_new; ++i) {
+    if (exec) MTMC_HIP_CHECK(hipGraphLaunch(exec, st));
+    else decode_step(st);
   }
   return MTMC_OK;
 }

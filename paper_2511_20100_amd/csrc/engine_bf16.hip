@@ -2,6 +2,7 @@
 // Weights and KV cache are bf16; the residual stream, norms, softmax and all accumulators fp32.
 #include <algorithm>
 #include <array>
+#include <functional>
 #include <mutex>
 
 #include "bf16_kernels.h"
@@ -36,6 +37,14 @@ struct GraphCache {
   hipEvent_t poll_events[2] = {nullptr, nullptr};
   int* host_slots = nullptr;            // pinned: which slots hold a sequence that still runs (a batch that takes in prompts)
 };
+
+// The handle's cache, made on first use (calls on one handle may come from several threads).
+static GraphCache& graph_cache(const mtmc_weights* w) {
+  mtmc_weights* mw = const_cast<mtmc_weights*>(w);
+  std::lock_guard<std::mutex> lock(*w->ragged_mu);
+  if (!mw->graphs) mw->graphs = new GraphCache();
+  return *mw->graphs;
+}
 
 // Brackets launches of one kernel class with HIP events while a decode step is launched directly.
 struct KernelTimer {
@@ -80,8 +89,7 @@ void destroy_graph_cache(mtmc_weights* w) {
 }
 
 int kernel_timer_set(mtmc_weights* w, int cls, int every) {
-  if (!w->graphs) w->graphs = new GraphCache();
-  std::lock_guard<std::mutex> lock(w->graphs->mu);
+  std::lock_guard<std::mutex> lock(graph_cache(w).mu);
   w->graphs->timer_class = cls;
   w->graphs->timer_every = every;
   w->graphs->events_used = 0;
@@ -470,10 +478,11 @@ void decode_layers(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, K
   *ss_old_out = ss[old];
 }
 
+}  // namespace
+
 // Returns in *out the instantiated graph of one decode step for this workspace and shape, capturing
 // it on a private stream if it is not cached (or nullptr when graphs are off or `st` is already capturing).
-template <class Step>
-int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, Step&& step,
+int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, const std::function<void(hipStream_t)>& step,
                  hipGraphExec_t* out) {
   *out = nullptr;
   if (!w->opt_hip_graph) return MTMC_OK;
@@ -482,9 +491,7 @@ int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, S
     (void)hipGetLastError();
     return MTMC_OK;
   }
-  mtmc_weights* mw = const_cast<mtmc_weights*>(w);
-  if (!mw->graphs) mw->graphs = new GraphCache();
-  GraphCache& gc = *mw->graphs;
+  GraphCache& gc = graph_cache(w);
   std::lock_guard<std::mutex> lock(gc.mu);
   if (!gc.capture_stream) {  // the caller's stream may be the default stream, which cannot capture
     hipError_t e = hipStreamCreateWithFlags(&gc.capture_stream, hipStreamNonBlocking);
@@ -521,9 +528,6 @@ int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, S
   *out = exec;
   return MTMC_OK;
 }
-
-
-}  // namespace
 
 int admission_plan(const int* live, const int* slot_region, int n_slots, int n_regions, int n_samples, int prompts_left,
                    int max_at_once, int wait_for, int* out_slots, int* out_regions) {
@@ -635,9 +639,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   };
   sample(st, (const h16_t*)p.xB, B, nullptr, nullptr, d_ctl, p.d_step, p.cur_ids, embed_args(gp));  // step 0 of the first prompts
 
-  mtmc_weights* mw = const_cast<mtmc_weights*>(w);
-  if (!mw->graphs) mw->graphs = new GraphCache();
-  GraphCache& gc = *mw->graphs;
+  GraphCache& gc = graph_cache(w);
   std::lock_guard<std::mutex> poll_lock(gc.poll_mu);
   if (!gc.host_slots) MTMC_HIP_CHECK(hipHostMalloc((void**)&gc.host_slots, 256 * sizeof(int), hipHostMallocDefault));
   const int* live = gc.host_slots;
@@ -858,9 +860,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
       }
     }
     if (p.max_new > 1 && poll > 0) {
-      mtmc_weights* mw = const_cast<mtmc_weights*>(w);
-      if (!mw->graphs) mw->graphs = new GraphCache();
-      GraphCache& gc = *mw->graphs;
+      GraphCache& gc = graph_cache(w);
       std::lock_guard<std::mutex> poll_lock(gc.poll_mu);
       if (!gc.host_live) {
         MTMC_HIP_CHECK(hipHostMalloc((void**)&gc.host_live, 64 * sizeof(int), hipHostMallocDefault));

@@ -4,6 +4,7 @@
 #include "common.h"
 
 namespace mtmc {
+namespace bf16 { struct SampleCtl; }
 
 // ---------------------------------------------------------------- shared (layout / control)
 // Page table of a rollout: row b, entry j -> shared page (b / n_samples) * n_full + j for
@@ -11,7 +12,6 @@ namespace mtmc {
 void launch_build_page_table(int* table, int rows, int max_pages, int n_samples, int n_full,
                              int shared_total, hipStream_t st);
 void launch_set_int(int* p, int v, hipStream_t st);
-void launch_add_int(int* p, int v, hipStream_t st);
 void launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
 void launch_copy_probe(void* dst, const void* src, size_t bytes, hipStream_t st);
 // dst[r, :] = src[(r / n_rep) * src_stride + src_offset + (r % n_rep) * rep_stride, :]
@@ -74,20 +74,29 @@ void rmsnorm(float* x, const float* h, const float* gain, float eps, int T, int 
 // C[M, N] (ldc) = or += A[M, K] (lda) * W[N, K]^T      (K % 16 == 0)
 void gemm(float* C, int ldc, const float* A, int lda, const float* W, int M, int N, int K,
           bool accumulate, hipStream_t st);
+// C[M, N] = norm(H[M, K]; gain) W[N, K]^T;  a[M, F] = silu(x Wg^T) * (x Wu^T) with x = norm(H; gain), W = [gate rows; up
+// rows].  x [M, K] and gu [M, 2 F] are scratch (large calls).
+void norm_gemm(float* C, int ldc, const float* H, const float* gain, float eps, float* x, const float* W, int M, int N,
+               int K, hipStream_t st);
+void norm_swiglu(float* a, const float* H, const float* gain, float eps, float* x, float* gu, const float* W, int M, int F,
+                 int K, hipStream_t st);
 // qkv [T, (Hq + 2 Hkv) hd]: rotates q in place, writes rotated k and v into the pages.
 void rope_kv_write(float* qkv, int T, int Hq, int Hkv, int hd, const float* cos, const float* sin,
                    TokMap map, KvPool pool, int layer, hipStream_t st);
 // o [T, Hq hd] = causal grouped-query attention of the (rotated) q in qkv over the pages.
 void attention(float* o, const float* qkv, int T, int Hq, int Hkv, int hd, TokMap map, KvPool pool,
                int layer, hipStream_t st);
+// One token per sequence (map.S == 1): rotates the q, k and v of qkv, appends k and v to their pages and attends.
+void attention_dec(float* o, const float* qkv, int B, int Hq, int Hkv, int hd, const float* cos, const float* sin, TokMap map,
+                   KvPool pool, int layer, hipStream_t st);
 void swiglu(float* a, const float* gu, int T, int F, hipStream_t st);  // gu [T, 2F] -> a [T, F]
-// Gumbel-max sampling from materialised logits [B, V] at step *d_step; writes out_ids[b, step],
-// out_logprobs[b, step] and cur_ids[b].
-// With done != NULL (stop token in use): a row whose done flag is set reports stop_id with log-prob 0; a row
-// that samples stop_id sets its flag and out_lens[b] = step + 1.
-void sample(const float* logits, int B, int V, float inv_temp, int greedy, uint64_t seed,
-            uint32_t seq_offset, const int* d_step, int max_new, int* cur_ids, int* out_ids,
-            float* out_logprobs, int stop_id, int* done, int* out_lens, hipStream_t st);
+// Gumbel-max sampling from materialised logits [B, V] at step *d_step by the call's control block; writes the id and
+// log-probability of every row and cur_ids[b], advances *d_step (d_step[1] is its arrival counter, 0 between launches) and
+// leaves the sampled tokens' embeddings (E [V, d]) in h [B, d].
+// With ctl->done (stop token in use): a row whose done flag is set reports stop_id with log-prob 0; a row that
+// samples stop_id sets its flag and out_lens[b] = step + 1.
+void sample(const float* logits, int B, int V, const bf16::SampleCtl* ctl, int* d_step, int* cur_ids, float* h,
+            const float* E, int d, int* err_flag, hipStream_t st);
 // Teacher-forced scoring from materialised logits [R, V].  Row r is position
 // i = first + (row0 + r) % n_scored of sequence n = seq0 + (row0 + r) / n_scored; its target is
 // seqs[n, i + 1] and its output slot [n, i] of the [*, S - 1] outputs.

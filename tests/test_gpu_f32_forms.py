@@ -1,0 +1,60 @@
+"""The fp32 path where its kernels change form: 8-row groups with a remainder, widths that are no multiple of a
+wavefront's 256 columns, more query heads per kv head than one workgroup of the decode attention takes, contexts beyond the 256
+keys it scores at once, outputs large enough for the tiled product, and decode steps replayed as a graph under other
+seeds and outputs.  Ids equal the oracle's up to its first near-tie; log-probabilities to the fp32 tolerance."""
+import numpy as np
+import pytest
+
+import mtmc_oracle as oracle
+from helpers import oracle_model
+from paper_2511_20100_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+LOGP_TOL_F32 = 1e-4  # as for the fp32 workload
+G6 = inputs.ModelConfig(2, 112, 6, 1, 64, 176, 1040, dtype="fp32")    # two workgroups of 4 and 2 heads per kv head
+G5 = inputs.ModelConfig(1, 272, 5, 1, 128, 304, 2064, dtype="fp32")
+
+
+def _check(got_ids, got_lp, ref):
+    ref_ids, ref_lp, margins = ref
+    ok = np.cumprod(margins > 1e-4, axis=1).astype(bool)
+    assert np.array_equal(got_ids.cpu().numpy()[ok], ref_ids[ok])
+    assert np.abs(got_lp.cpu().numpy() - ref_lp)[ok].max() <= LOGP_TOL_F32
+
+
+@pytest.mark.parametrize("cfg,n_prompts,plen,n_samples,max_new", [(G6, 3, 250, 3, 12), (G5, 1, 5, 1, 9), (G5, 2, 300, 4, 8),
+                                                                  (G6, 1, 600, 17, 2)])
+def test_rollouts_on_one_workspace(cfg, n_prompts, plen, n_samples, max_new):
+    import torch
+    from paper_2511_20100_amd import mtmc
+    w = inputs.make_weights(cfg, seed=0, std=0.06, gain_std=0.1)
+    handle = mtmc.mtmc_weights_create(mtmc.make_config(cfg, 704), w.blob())
+    try:
+        prompts = inputs.make_prompts(n_prompts, plen, cfg.vocab, seed=2)
+        dev = torch.from_numpy(prompts).cuda()
+        ws = torch.empty(mtmc.mtmc_rollout_workspace_bytes(handle, n_prompts, plen, n_samples, max_new), dtype=torch.uint8,
+                         device="cuda")
+        model = oracle_model(w, 704)
+        for seed, temp in ((1, 1.0), (9, 0.7), (1, 0.0)):
+            ids, lp = mtmc.mtmc_rollout(handle, dev, n_samples, max_new, temp, seed, workspace=ws)
+            mtmc.mtmc_poll_errors(handle)
+            _check(ids, lp, oracle.rollout(model, prompts, n_samples, max_new, temp, seed=seed))
+    finally:
+        mtmc.mtmc_weights_destroy(handle)
+
+
+@pytest.mark.parametrize("n_seqs,seq_len", [(1, 7), (4, 129), (5, 400)])
+def test_scoring(n_seqs, seq_len):
+    import torch
+    from paper_2511_20100_amd import mtmc
+    w = inputs.make_weights(G6, seed=0, std=0.06, gain_std=0.1)
+    handle = mtmc.mtmc_weights_create(mtmc.make_config(G6, 704), w.blob())
+    try:
+        seqs = inputs.make_sequences(n_seqs, seq_len, G6.vocab, seed=4)
+        lp = mtmc.mtmc_score(handle, torch.from_numpy(seqs).cuda(), 3)
+        mtmc.mtmc_poll_errors(handle)
+        ref = oracle.score(oracle_model(w, 704), seqs, prompt_len=3)[0]
+        assert np.abs(lp.cpu().numpy() - ref).max() <= LOGP_TOL_F32
+    finally:
+        mtmc.mtmc_weights_destroy(handle)
