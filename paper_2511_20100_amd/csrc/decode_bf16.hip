@@ -479,14 +479,22 @@ static void launch_dec_wide(const DecGemmArgs& a, int epi, hipStream_t st) {
   } else {
     // every workgroup reads the whole activation operand, so a CU that hosts two workgroups takes about
     // twice as long as one that hosts one: one round of workgroups with 6 row tiles beats 1.x rounds with 4
-    if (epi == DEPI_SWIGLU && a.n_tiles > 4 * 256 && a.n_tiles <= 6 * 256) launch_dec_t<6, MB, 8, 2, 2, 1, 2>(a, epi, st);
-    else if (epi == DEPI_PARTIAL && a.partial_nb == 3) {
+    if (epi == DEPI_SWIGLU && a.n_tiles > 4 * 256 && a.n_tiles <= 6 * 256) {
+      // up to 16 rows the activation operand is a sixth of the weights: pairs of tiles, several workgroups per CU and so
+      // more wavefronts that pull (1 row, 1.5 B shape: 15.1 -> 14.6 us; four tiles: 16.7); the same K ranges, the same sums
+      if constexpr (MB == 1) launch_dec_t<2, MB, 8, 2, 2, 1>(a, epi, st);
+      else launch_dec_t<6, MB, 8, 2, 2, 1, 2>(a, epi, st);
+    } else if (epi == DEPI_SWIGLU && MB == 2) {
+      launch_dec_t<4, MB, 8, 2, 2, 1>(a, epi, st);  // 17..32 rows, 7 B shape: 59.9 us with 4 wavefronts, 56.4 with 8
+    } else if (epi == DEPI_PARTIAL && a.partial_nb == 3) {
       // 8 K splits, one per XCD; three row tiles and 5 wavefronts per workgroup, rings three deep (1.5 B shape: down
       // projection 11.3 -> 10.6 us, HBM fetch of the launch 36.8 -> 29 MB; 7 wavefronts or rings two deep: 0.2 % slower)
       DecGemmArgs x = a;
       x.xcd_split = 1;
       x.row_pairs = 0;
-      k_gemm_dec<3, MB, 5, 3, 3, 1, DEPI_PARTIAL, 3><<<dim3(8 * ((a.n_tiles + 2) / 3)), 5 * 64, 0, st>>>(x);
+      // (up to 16 rows one tile per workgroup, three of them on a CU: 8.5 -> 8.0 us, the same sums)
+      if constexpr (MB == 1) k_gemm_dec<1, MB, 5, 3, 3, 1, DEPI_PARTIAL, 1><<<dim3(8 * a.n_tiles), 5 * 64, 0, st>>>(x);
+      else k_gemm_dec<3, MB, 5, 3, 3, 1, DEPI_PARTIAL, 3><<<dim3(8 * ((a.n_tiles + 2) / 3)), 5 * 64, 0, st>>>(x);
     } else if (epi == DEPI_PARTIAL && a.partial_nb == 2) launch_dec_t<2, MB, 8, 2, 2, 1>(a, epi, st);
     else if (epi == DEPI_SAMPLE) launch_dec_t<4, MB, 4, 2, 2, 3, 2>(a, epi, st);  // three workgroups per CU
     else launch_dec_t<4, MB, 4, 2, 2, 2>(a, epi, st);
@@ -518,11 +526,20 @@ void gemm_dec(const DecGemmArgs& a, int epi, hipStream_t st) {
   } else {
     switch (mb) {
       case 1: launch_dec_narrow<1>(a, epi, st); break;
-      case 2: launch_dec_narrow<1>(a, epi, st, 2); break;
+      // More row tiles than CUs (QKV of the wide shapes): with one tile per workgroup of 16 wavefronts a CU hosts two or
+      // three of them in turn; two tiles and 8 wavefronts (32 rows, 288 tiles: 14.7 -> 13.4 us; 48 rows, 384 tiles: 16.3 ->
+      // 11.3, 11.6 without the split of the rows, 12.8 with three tiles).
+      case 2:
+        if (a.n_tiles > 256 && epi == DEPI_STORE) launch_dec_t<2, 1, 8, 2, 2, 1>(a, epi, st, 2);
+        else launch_dec_narrow<1>(a, epi, st, 2);
+        break;
       // 33..64 rows: every workgroup reads the whole activation operand of its rows from L2, four times the bytes
       // of its weight tile, and with one workgroup per weight row tile only 100-odd CUs work: two workgroups per
       // row tile, 32 rows each (placed on the same XCD by the launch order, so the tile's second read hits L2)
-      case 4: launch_dec_narrow<2>(a, epi, st, 2); break;
+      case 4:
+        if (a.n_tiles > 256 && epi == DEPI_STORE) launch_dec_t<2, 2, 8, 2, 2, 1>(a, epi, st, 2);
+        else launch_dec_narrow<2>(a, epi, st, 2);
+        break;
       // 65..128 rows: two weight row tiles per workgroup (the activation operand outweighs the weights) and two
       // workgroups of 64 rows per pair of tiles; behind a context-split attention the form that combines chunks
       default:
