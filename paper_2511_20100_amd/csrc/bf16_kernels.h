@@ -182,18 +182,20 @@ void retile_gate_up(h16_t* dst, const bf16_t* gate, const bf16_t* up, int F, int
 // d_rows (device, may be NULL): the number of rows that hold tokens when it is known on the device only (rows
 // packed by a kernel); M and m_tiles then give the capacity the launch is sized for.
 // part (device, may be NULL) / part_floats: room for partial sums; with it, an output of few 256 x 256 blocks is
-// computed over several ranges of K at once (gemm_lds_split) and summed in a fixed order.
-void gemm_large_f32(float* C, int ldc, int N, bool accumulate, const h16_t* Wt, int n_tiles,
-                    int k_tiles, const h16_t* Xt, int M, int m_tiles, int lds_min_blocks, const int* d_rows,
-                    hipStream_t st, float* part = nullptr, size_t part_floats = 0);
+// computed over several ranges of K at once (gemm_lds_split) and summed in a fixed order.  leave_parts: that sum is left to
+// the consumer of the output; returns the number of slices [M][N] then found in `part` (0: the output is complete).
+int gemm_large_f32(float* C, int ldc, int N, bool accumulate, const h16_t* Wt, int n_tiles,
+                   int k_tiles, const h16_t* Xt, int M, int m_tiles, int lds_min_blocks, const int* d_rows,
+                   hipStream_t st, float* part = nullptr, size_t part_floats = 0, bool leave_parts = false);
 void gemm_large_swiglu(h16_t* act, const h16_t* Wt, int n_tiles, int k_tiles, const h16_t* Xt,
                        int M, int m_tiles, int lds_min_blocks, int* err_flag, const int* d_rows, hipStream_t st);
 // LDS-staged kernel behind the two launchers above (epi: 0 store, 1 accumulate, 2 SwiGLU); it chooses its block by the
 // sizes of the output and of K (even, at least 4 k-steps).
 void gemm_lds(const LargeArgs& a, int epi, hipStream_t st);
-// Split-K form of the store / accumulate GEMM for outputs of at most 128 blocks of 256 x 256: false when it does not apply
-// (no range count from 2 to 8 divides K into even ranges of at least 8 k-steps that fit `part`), and nothing was launched.
-bool gemm_lds_split(const LargeArgs& a, bool accumulate, float* part, size_t part_floats, hipStream_t st);
+// Split-K form of the store / accumulate GEMM for outputs of at most 128 blocks of 256 x 256: the number of ranges, or 0
+// when it does not apply (no count from 2 to 8 divides K into even ranges of at least 8 k-steps that fit `part`) and nothing
+// was launched.
+int gemm_lds_split(const LargeArgs& a, bool accumulate, float* part, size_t part_floats, bool leave_parts, hipStream_t st);
 // Partial results per row that lmhead_score leaves for M rows, and the room to plan for up to rows_max rows.
 int score_head_parts(int n_tiles, int k_tiles, int M, int lds_min_blocks);
 size_t score_head_part_floats(int n_tiles, int rows_max);
@@ -262,7 +264,9 @@ void compact_slots(const int* done, int B, int slots, const int* slot_row, const
                    int* row_step0_c, hipStream_t st);
 void embed(float* h, const int* ids, int T, const bf16_t* E, int d, int vocab, int* err_flag,
            hipStream_t st, const int* d_rows = nullptr);
-// h[m, :] += sum_s P[s][m][:] (n_split may be 0); x = bf16(RMSNorm(h; gain)) in tiled layout.
+// h[m, :] += sum_s P[s][m][:] (n_split may be 0); x = bf16(RMSNorm(h; gain)) in tiled layout.  From kNormTileRows rows on
+// (and without partial sums) the form that works on tiles of 16 rows.
+constexpr int kNormTileRows = 1024;
 void add_norm(float* h, const float* P, int n_split, int ldp, int Mpad_p, const float* gain, float eps,
               h16_t* x, int M, int m_tiles, int d, int* err_flag, hipStream_t st, const int* d_rows = nullptr);
 // qkv fp32 [T, (Hq + 2 Hkv) hd] (row stride ld), T = n_seqs * S tokens at positions map.pos_base + t % S: rotates q
@@ -270,9 +274,10 @@ void add_norm(float* h, const float* P, int n_split, int ldp, int Mpad_p, const 
 // seq_start (device, may be NULL): sequences of different lengths packed back to back: sequence s holds the
 // tokens seq_start[s] .. seq_start[s + 1] - 1 at positions map.pos_base + 0, 1, ...; S is then the longest
 // length a sequence can have and n_seqs the number of sequences (T is ignored).
+// n_split > 1: qkv is the sum, in order, of n_split arrays that lie split_stride floats apart.
 void rope_kv_write(h16_t* q, const float* qkv, int ld, int T, int S, int Hq, int Hkv, const float* cos,
                    const float* sin, TokMap map, KvPool pool, int layer, int* err_flag, hipStream_t st,
-                   const int* seq_start = nullptr, int n_seqs = 0);
+                   const int* seq_start = nullptr, int n_seqs = 0, int n_split = 1, size_t split_stride = 0);
 
 // ---- attention -----------------------------------------------------------------------------
 // Floats of the per-chunk partial results of the decode attention kernel.

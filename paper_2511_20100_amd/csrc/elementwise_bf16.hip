@@ -1,5 +1,7 @@
 // Row-wise and layout kernels of the bf16 path: weight re-tiling, embedding, residual-add +
 // RMSNorm (-> tiled bf16 GEMM operand), split-K sum + rotary embedding + KV page write.
+#include <algorithm>
+
 #include "bf16_kernels.h"
 #include "device_utils.h"
 #include "frag.h"
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(256) void k_norm_tile16(const float* __restrict__ h
 void add_norm(float* h, const float* P, int n_split, int ldp, int Mpad_p, const float* gain, float eps,
               h16_t* x, int M, int m_tiles, int d, int* err_flag, hipStream_t st, const int* d_rows) {
   if (M == 0) return;
-  if (n_split == 0 && M >= 1024 && d % 32 == 0 && d * 32 + 256 <= 160 * 1024) {
+  if (n_split == 0 && M >= kNormTileRows && d % 32 == 0 && d * 32 + 256 <= 160 * 1024) {
     static bool configured = false;
     if (!configured) {
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_norm_tile16), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -221,7 +223,8 @@ void add_norm(float* h, const float* P, int n_split, int ldp, int Mpad_p, const 
 template <int HD>
 __global__ __launch_bounds__(256) void k_rope_kv_page(h16_t* q, const float* qkv, int ld, int S, int Hq, int Hkv,
                                                       const float* cos, const float* sin, int row_stride, int pos_base,
-                                                      KvPool pool, int layer, int* err_flag, const int* seq_start) {
+                                                      KvPool pool, int layer, int* err_flag, const int* seq_start,
+                                                      int n_split, size_t split_stride) {
   constexpr int HALF = HD / 2, QUADS = HALF / 4;  // quads of rotation pairs per head
   constexpr int ROW = HD + 8;                     // LDS row stride in halfs: 16-byte reads down a column stay conflict-free
   __shared__ __attribute__((aligned(16))) h16_t k_s[kPageTokens][ROW];
@@ -241,15 +244,22 @@ __global__ __launch_bounds__(256) void k_rope_kv_page(h16_t* q, const float* qkv
   h16_t* kv = (h16_t*)pool.base;
   const size_t page_elems = (size_t)kPageTokens * HD;
   const int tid = threadIdx.x;
-  // ---- rotation of the q and k heads: unit = (slot, quad)
-  for (int head = 0; head < Hq + Hkv; ++head) {
+  // four values of the projection: the sum of its split-K slices, if it comes in slices
+  auto load4 = [&](const float* p) {
+    v4f v = *reinterpret_cast<const v4f*>(p);
+    for (int s = 1; s < n_split; ++s) v = v + *reinterpret_cast<const v4f*>(p + s * split_stride);
+    return v;
+  };
+  // ---- rotation of the q and k heads: unit = (slot, quad).  gridDim.z workgroups share out the heads of a page.
+  const int per_z = (Hq + Hkv + gridDim.z - 1) / gridDim.z, head0 = blockIdx.z * per_z;
+  for (int head = head0; head < min(head0 + per_z, Hq + Hkv); ++head) {
     for (int u = tid; u < kPageTokens * QUADS; u += 256) {
       const int slot = u / QUADS, i = (u % QUADS) * 4;
       const int pos = pg * kPageTokens + slot;
       if (pos < p_lo || pos >= p_hi) continue;
       const size_t t = tok0 + (pos - pos_base);
       const float* pr = qkv + t * ld + (size_t)head * HD;
-      const v4f a = *reinterpret_cast<const v4f*>(pr + i), b = *reinterpret_cast<const v4f*>(pr + i + HALF);
+      const v4f a = load4(pr + i), b = load4(pr + i + HALF);
       const v4f c = *reinterpret_cast<const v4f*>(cos + (size_t)pos * HALF + i);
       const v4f sn = *reinterpret_cast<const v4f*>(sin + (size_t)pos * HALF + i);
       const v4f ra = a * c - b * sn, rb = b * c + a * sn;
@@ -273,7 +283,7 @@ __global__ __launch_bounds__(256) void k_rope_kv_page(h16_t* q, const float* qkv
       const int pos = pg * kPageTokens + slot;
       if (pos < p_lo || pos >= p_hi) continue;
       const size_t t = tok0 + (pos - pos_base);
-      const v4f v = *reinterpret_cast<const v4f*>(qkv + t * ld + (size_t)(Hq + Hkv + g) * HD + i);
+      const v4f v = load4(qkv + t * ld + (size_t)(Hq + Hkv + g) * HD + i);
       uint2 pk;
       pk.x = pack_h16x2_flag(v[0], v[1], err_flag); pk.y = pack_h16x2_flag(v[2], v[3], err_flag);
       *reinterpret_cast<uint2*>(&v_s[slot][i]) = pk;
@@ -307,17 +317,20 @@ __global__ __launch_bounds__(256) void k_rope_kv_page(h16_t* q, const float* qkv
 }
 void rope_kv_write(h16_t* q, const float* qkv, int ld, int T, int S, int Hq, int Hkv, const float* cos,
                    const float* sin, TokMap map, KvPool pool, int layer, int* err_flag, hipStream_t st,
-                   const int* seq_start, int n_seqs) {
+                   const int* seq_start, int n_seqs, int n_split, size_t split_stride) {
   if (seq_start ? (n_seqs == 0 || S == 0) : T == 0) return;
   // pages that the positions pos_base .. pos_base + S - 1 of a sequence touch
   const int n_pg = (map.pos_base + S - 1) / kPageTokens - map.pos_base / kPageTokens + 1;
-  const dim3 grid(n_pg, seq_start ? n_seqs : T / S);
+  const int pages = n_pg * (seq_start ? n_seqs : T / S);
+  // few pages: the heads of a page are shared out until about 2048 workgroups are there (32 pages x 14 heads of 128 dims:
+  // 12.6 us with one workgroup per page)
+  const dim3 grid(n_pg, seq_start ? n_seqs : T / S, std::max(1, std::min(Hq + Hkv, 2048 / pages)));
   if (pool.head_dim == 64)
     k_rope_kv_page<64><<<grid, 256, 0, st>>>(q, qkv, ld, S, Hq, Hkv, cos, sin, map.row_stride, map.pos_base, pool, layer,
-                                             err_flag, seq_start);
+                                             err_flag, seq_start, n_split, split_stride);
   else
     k_rope_kv_page<128><<<grid, 256, 0, st>>>(q, qkv, ld, S, Hq, Hkv, cos, sin, map.row_stride, map.pos_base, pool,
-                                              layer, err_flag, seq_start);
+                                              layer, err_flag, seq_start, n_split, split_stride);
 }
 
 }  // namespace bf16

@@ -399,19 +399,27 @@ void prefill_layers(const mtmc_weights* w, const Dims& D, float* h, h16_t* x, fl
   const mtmc_config& c = w->cfg;
   const int T = n_seqs * S, mt = tiles16(T), lmb = w->opt_lds_min_blocks;
   const size_t pf = part ? kGemmPartFloats : 0;  // partial sums of the split-K GEMMs (a prompt or a few)
+  // Their slices are added up by the kernel that reads the output next, which saves a launch and a trip of the output
+  // through memory: rotary embedding + cache write, and the row norm in its form for few rows (the form for many works on
+  // tiles of 16 rows).  The same additions in the same order.
+  const bool leave = T < bf16::kNormTileRows && !d_rows;
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerWeights& L = w->layers[l];
     const int kvl = l * layer_stride;
-    bf16::gemm_large_f32(qkv, D.nqkv, D.nqkv, false, (const h16_t*)L.wqkv, D.nt_qkv, D.kt_d, x, T, mt, lmb, d_rows, st, part, pf);
-    bf16::rope_kv_write(qb, qkv, D.nqkv, T, S, D.Hq, D.Hkv, w->rope_cos, w->rope_sin, map, pool, kvl, w->err_flag, st,
-                        seq_start, n_seqs);
+    const int sq = bf16::gemm_large_f32(qkv, D.nqkv, D.nqkv, false, (const h16_t*)L.wqkv, D.nt_qkv, D.kt_d, x, T, mt, lmb,
+                                        d_rows, st, part, pf, leave);
+    bf16::rope_kv_write(qb, sq ? part : qkv, D.nqkv, T, S, D.Hq, D.Hkv, w->rope_cos, w->rope_sin, map, pool, kvl, w->err_flag,
+                        st, seq_start, n_seqs, std::max(sq, 1), (size_t)T * D.nqkv);
     bf16::attention_prefill(o, qb, n_seqs, S, mt, D.Hq, D.Hkv, map, pool, kvl, w->err_flag, st, seq_start);
-    bf16::gemm_large_f32(h, D.d, D.d, true, (const h16_t*)L.wo, D.nt_d, D.kt_nq, o, T, mt, lmb, d_rows, st, part, pf);
-    bf16::add_norm(h, nullptr, 0, 0, 0, L.ffn_norm, c.rms_eps, x, T, mt, D.d, w->err_flag, st, d_rows);
+    const int so = bf16::gemm_large_f32(h, D.d, D.d, true, (const h16_t*)L.wo, D.nt_d, D.kt_nq, o, T, mt, lmb, d_rows, st, part,
+                                        pf, leave);
+    bf16::add_norm(h, part, so, D.d, T, L.ffn_norm, c.rms_eps, x, T, mt, D.d, w->err_flag, st, d_rows);
     bf16::gemm_large_swiglu(a, (const h16_t*)L.wgu, D.nt_gu, D.kt_d, x, T, mt, lmb, w->err_flag, d_rows, st);
-    bf16::gemm_large_f32(h, D.d, D.d, true, (const h16_t*)L.wdown, D.nt_d, D.kt_F, a, T, mt, lmb, d_rows, st, part, pf);
-    if (l + 1 < c.n_layers)
-      bf16::add_norm(h, nullptr, 0, 0, 0, w->layers[l + 1].attn_norm, c.rms_eps, x, T, mt, D.d, w->err_flag, st, d_rows);
+    const bool last = l + 1 == c.n_layers;  // h is read as it is after the last block
+    const int sd = bf16::gemm_large_f32(h, D.d, D.d, true, (const h16_t*)L.wdown, D.nt_d, D.kt_F, a, T, mt, lmb, d_rows, st,
+                                        part, pf, leave && !last);
+    if (!last)
+      bf16::add_norm(h, part, sd, D.d, T, w->layers[l + 1].attn_norm, c.rms_eps, x, T, mt, D.d, w->err_flag, st, d_rows);
   }
 }
 

@@ -317,8 +317,8 @@ __global__ __launch_bounds__(256, T::PC) void k_gemm_lds(LargeArgs a) {
 // Split-K form for outputs of few blocks and a long reduction (the O and down projections, and the QKV projection,
 // of a prompt or a few): a work item is one output block over one of a.k_split equal ranges of k-steps, the items of a
 // block are neighbours in an XCD's walk, and every item stores its sum as fp32 into its own slice of a.part
-// ([k_split][M][N]); k_splitk_reduce then adds the slices in order, so the result does not depend on which workgroup
-// ran when.
+// ([k_split][M][N]); k_splitk_reduce, or the consumer of the output, then adds the slices in order, so the result does
+// not depend on which workgroup ran when.
 template <class T>
 __global__ __launch_bounds__(256, T::PC) void k_gemm_lds_split(LargeArgs a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
@@ -587,9 +587,9 @@ void lmhead_score_lds(const ScoreHeadArgs& a, hipStream_t st) {
   else a.want_top ? launch_lmhead<Tile<8, 8, 4, 1>, true>(a, st) : launch_lmhead<Tile<8, 8, 4, 1>, false>(a, st);
 }
 
-bool gemm_lds_split(const LargeArgs& a0, bool accumulate, float* part, size_t part_floats, hipStream_t st) {
+int gemm_lds_split(const LargeArgs& a0, bool accumulate, float* part, size_t part_floats, bool leave_parts, hipStream_t st) {
   const int blocks = (a0.n_tiles + 15) / 16 * ((a0.m_tiles + 15) / 16);  // of 256 x 256
-  if (!part || blocks > kCus / 2 || a0.N % 4 != 0) return false;
+  if (!part || blocks > kCus / 2 || a0.N % 4 != 0) return 0;
   // The most splits, up to 8 and to one round of blocks of 256 x 256, that leave every range even and at least 8 k-steps
   // long.  Not by the tile that is chosen below: the order of the sums then follows from the sizes alone.
   int S = 0;
@@ -597,16 +597,17 @@ bool gemm_lds_split(const LargeArgs& a0, bool accumulate, float* part, size_t pa
     if (a0.k_tiles % s == 0 && (a0.k_tiles / s) % 2 == 0 && a0.k_tiles / s >= 8 &&
         (size_t)s * a0.M * a0.N <= part_floats)
       S = s;
-  if (!S) return false;
+  if (!S) return 0;
   LargeArgs a = a0;
   a.k_split = S;
   a.part = part;
   double cost = 0.0;
   best_tile(a.N, expected_rows(a), a.k_tiles, S, true, &cost).run(a, LEPI_STORE, st);
+  if (leave_parts) return S;
   const size_t quads = (size_t)a.M * (a.N / 4);
   k_splitk_reduce<<<(unsigned)((quads + 255) / 256), 256, 0, st>>>(a.out_f32, a.ld_out, part, S, a.M, a.N,
                                                                   accumulate ? 1 : 0, a.d_rows);
-  return true;
+  return S;
 }
 
 void gemm_lds(const LargeArgs& a, int epi, hipStream_t st) {
