@@ -15,6 +15,8 @@
 // its update (a well-scaled fp16 value), together with the sum of squares of its 16 new columns.
 // The consumer sums those per-tile squares in a fixed order to get r_new and multiplies its
 // fp32 accumulators by r_new / r_old: W (h g r_new) = (W (h g r_old)) r_new / r_old.
+#include <algorithm>
+
 #include "attention_core.h"
 #include "bf16_kernels.h"
 #include "device_utils.h"
@@ -1048,6 +1050,184 @@ __global__ __launch_bounds__(AW * 64) void k_attn_dec(AttnDecArgs a) {
   }
 }
 
+// The samples of one prompt in one workgroup.  NS sequences that share their prompt's whole pages sit side by side in the
+// 16 columns of the matrix instruction (column c = query head c % G of sequence c / G; one sequence fills only G of
+// them): the shared pages are read once for all NS, then every sequence's own pages with the other columns masked, the
+// pairs of own pages handed to the wavefronts in turn.  All NS sequences are at the same position.  What bounds the plain
+// form at many (sequence, kv head) pairs is that a CU holds one workgroup (199 registers): 768 pairs are three rounds of a
+// 10 us chain.  48 rows x 16 kv heads, 4 samples per prompt: see the launcher for what it measured.
+constexpr int kOwnTab = 512;  // page-table entries of the sequences' own pages kept in LDS
+template <int DHD>
+constexpr int kSharedLds = AW * 16 * (DHD + 1) * (int)sizeof(float);
+template <int DHD>
+__global__ __launch_bounds__(AW * 64) void k_attn_dec_shared(AttnDecArgs a, int NS) {
+  constexpr int HALF = DHD / 2;
+  __shared__ __attribute__((aligned(16))) h16_t q_s[16][DHD];
+  extern __shared__ __attribute__((aligned(16))) float s_o_raw[];  // kSharedLds<DHD> bytes
+  float (*s_o)[16][DHD + 1] = reinterpret_cast<float (*)[16][DHD + 1]>(s_o_raw);
+  __shared__ float s_m[AW][16], s_l[AW][16];
+  __shared__ int s_table[ATAB], s_own[kOwnTab];
+  // workgroups of one prompt and kv head get launch indices that are congruent modulo 8 (one XCD, one L2)
+  const int GX = gridDim.x, sets = a.share / NS;  // workgroups that share a prompt
+  int bx = blockIdx.x, g = blockIdx.y;
+  {
+    const int total = GX * gridDim.y;
+    if (sets > 1 && total % (8 * sets) == 0) {
+      const int L = bx + GX * g, xcd = L & 7, slot = L >> 3;
+      const int item = ((slot / sets) * 8 + xcd) * sets + slot % sets;
+      g = item / GX;
+      bx = item - g * GX;
+    }
+  }
+  const int b0 = bx * NS;
+  const int Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv, n_col = NS * G;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int col = lane & 15, lg = lane >> 4;
+  const KvPool& pool = a.pool;
+  const int* table = pool.page_table + (size_t)b0 * pool.max_pages;
+  const int pos0 = a.row_pos ? a.row_pos[b0] : a.pos_base;
+  const int nb = ((pos0 + 1) / kPageTokens) & ~1;  // shared pages, taken in pairs
+  const int own_max = pool.max_pages - nb;
+  const int step = *a.d_step;
+  const h16_t* kbase = dec_page<DHD>(pool, a.layer, 0, 0, g);
+  const h16_t* vbase = dec_page<DHD>(pool, a.layer, 1, 0, g);
+  const size_t pstride = (size_t)pool.n_kv_heads * (kPageTokens * DHD);
+  // the wavefront's first pair of shared pages does not depend on the position: requested first (a wavefront that has none
+  // loads any two pages and drops them)
+  KvFrags<DHD> cur;
+  {
+    const int i0 = table[min(2 * wave, pool.max_pages - 1)], i1 = table[min(2 * wave + 1, pool.max_pages - 1)];
+    cur = load_kv<DHD>(kbase + i0 * pstride, kbase + i1 * pstride, vbase + i0 * pstride, vbase + i1 * pstride, lane);
+  }
+  for (int i = tid; i < nb; i += AW * 64) s_table[i] = table[i];
+  for (int i = tid; i < NS * own_max; i += AW * 64) s_own[i] = table[(size_t)(i / own_max) * pool.max_pages + nb + i % own_max];
+  const int row_w = (Hq + 2 * Hkv) * DHD;
+  const int pos = pos0 + step;
+  const float* cs = a.cos + (size_t)pos * HALF;
+  const float* sn = a.sin + (size_t)pos * HALF;
+  for (int e = tid; e < 16 * HALF; e += AW * 64) {
+    const int c = e / HALF, i = e % HALF;
+    float lo = 0.f, hi = 0.f;
+    if (c < n_col) {
+      const float* w = a.qkv + (size_t)(b0 + c / G) * row_w + (size_t)(g * G + c % G) * DHD;
+      lo = w[i];
+      hi = w[i + HALF];
+    }
+    q_s[c][i] = f32_to_h16_flag(lo * cs[i] - hi * sn[i], a.err_flag);
+    q_s[c][i + HALF] = f32_to_h16_flag(hi * cs[i] + lo * sn[i], a.err_flag);
+  }
+  // wavefront w appends the new key and value of sequence w (NS <= AW)
+  const int cur_page = pos / kPageTokens, slot = pos % kPageTokens;
+  if (wave < NS && lane < HALF) {
+    const float* row = a.qkv + (size_t)(b0 + wave) * row_w;
+    const int page = table[(size_t)wave * pool.max_pages + cur_page];
+    h16_t* kp = dec_page<DHD>(pool, a.layer, 0, page, g);
+    h16_t* vp = dec_page<DHD>(pool, a.layer, 1, page, g);
+    const float x0 = row[(size_t)(Hq + g) * DHD + lane], x1 = row[(size_t)(Hq + g) * DHD + lane + HALF];
+    const float v0 = row[(size_t)(Hq + Hkv + g) * DHD + lane], v1 = row[(size_t)(Hq + Hkv + g) * DHD + lane + HALF];
+    const float c = cs[lane], s = sn[lane];
+    const int c0 = lane, c1 = lane + HALF;
+    kp[(c0 >> 3) * 128 + slot * 8 + (c0 & 7)] = f32_to_h16_flag(x0 * c - x1 * s, a.err_flag);
+    kp[(c1 >> 3) * 128 + slot * 8 + (c1 & 7)] = f32_to_h16_flag(x1 * c + x0 * s, a.err_flag);
+    vp[c0 * kPageTokens + slot] = f32_to_h16_flag(v0, a.err_flag);
+    vp[c1 * kPageTokens + slot] = f32_to_h16_flag(v1, a.err_flag);
+  }
+  __syncthreads();  // q_s and the tables complete; this workgroup's K/V stores are visible to its own loads
+
+  v8h qf[DHD / 32];
+#pragma unroll
+  for (int kb = 0; kb < DHD / 32; ++kb) qf[kb] = __builtin_bit_cast(v8h, *reinterpret_cast<const v4u*>(&q_s[col][kb * 32 + 8 * lg]));
+  AttnState<DHD / 16> st;
+  attn_init(st);
+  const float scale2 = (DHD == 128 ? 0.08838834764831845f : 0.125f) * 1.4426950408889634f;  // log2(e) / sqrt(head_dim)
+  // Stages of this wavefront: the pairs wave, wave + AW, ... of shared pages, then the pairs of own pages (sequence s,
+  // pair i: item s P + i) wave, wave + AW, ...
+  const int own_pages = cur_page + 1 - nb, P = (own_pages + 1) / 2;  // own_pages >= 1: the current page is one
+  const int n_sh = nb / 2 > wave ? (nb / 2 - wave + AW - 1) / AW : 0;
+  const int n_own = NS * P > wave ? (NS * P - wave + AW - 1) / AW : 0;
+  const int n_st = n_sh + n_own, seq_of_col = col / G;
+  auto load_stage = [&](int j) {
+    int i0, i1;
+    if (j < n_sh) {
+      i0 = s_table[2 * (wave + AW * j)];
+      i1 = s_table[2 * (wave + AW * j) + 1];
+    } else {
+      const int item = wave + AW * (j - n_sh), s = item / P, pg = 2 * (item - s * P);
+      i0 = s_own[s * own_max + pg];
+      i1 = s_own[s * own_max + min(pg + 1, own_pages - 1)];
+    }
+    return load_kv<DHD>(kbase + i0 * pstride, kbase + i1 * pstride, vbase + i0 * pstride, vbase + i1 * pstride, lane);
+  };
+  auto attend = [&](const KvFrags<DHD>& f, int j) {
+    if (j < n_sh) {
+      attn_step1<DHD, false>(f, 0, qf, 0, scale2, st, lane);
+    } else {
+      const int item = wave + AW * (j - n_sh), s = item / P, pg = nb + 2 * (item - s * P);
+      attn_step1<DHD, true>(f, pg * kPageTokens, qf, seq_of_col == s ? pos : -1, scale2, st, lane);
+    }
+  };
+  // two register sets in turn; the stage behind the last one is a clamped copy of it that nobody uses
+  if (n_st > 0) {
+    KvFrags<DHD> alt;
+    if (n_sh == 0) cur = load_stage(0);
+    for (int j = 0; j < n_st; j += 2) {
+      alt = load_stage(min(j + 1, n_st - 1));
+      attend(cur, j);
+      cur = load_stage(min(j + 2, n_st - 1));
+      if (j + 1 < n_st) attend(alt, j + 1);
+    }
+  }
+  float l = st.l;
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+#pragma unroll
+  for (int cb = 0; cb < DHD / 16; ++cb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s_o[wave][col][cb * 16 + 4 * lg + r] = st.o[cb][r];
+  if (lg == 0) {
+    s_m[wave][col] = st.m;
+    s_l[wave][col] = l;
+  }
+  __syncthreads();
+  // ---- merge the wavefronts: thread t < 16 n_col (dims in eights) owns (column c, 8 consecutive dims)
+  if (tid < n_col * (DHD / 8)) {
+    const int c = tid / (DHD / 8), d0 = (tid % (DHD / 8)) * 8;
+    float mm = -INFINITY, ll = 0.f, acc[8] = {};
+#pragma unroll
+    for (int w = 0; w < AW; ++w) mm = fmaxf(mm, s_m[w][c]);
+#pragma unroll
+    for (int w = 0; w < AW; ++w) {
+      const float f = __builtin_amdgcn_exp2f(s_m[w][c] - mm);
+      ll += f * s_l[w][c];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += f * s_o[w][c][d0 + e];
+    }
+    const float inv = 1.0f / ll;  // the current position is visible to its own sequence
+    v4u pk;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pk[e] = pack_h16x2_flag(acc[2 * e] * inv, acc[2 * e + 1] * inv, a.err_flag);
+    *reinterpret_cast<v4u*>(a.o + act_off(b0 + c / G, (g * G + c % G) * DHD + d0, a.m_tiles * 16)) = pk;
+  }
+}
+
+template <int DHD>
+static void launch_shared(const AttnDecArgs& a, int B, int ns, hipStream_t st) {
+  static const bool configured = (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_dec_shared<DHD>),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kSharedLds<DHD>), true);
+  (void)configured;
+  k_attn_dec_shared<DHD><<<dim3(B / ns, a.Hkv), AW * 64, kSharedLds<DHD>, st>>>(a, ns);
+}
+// Sequences per workgroup of the shared form, or 1: more (sequence, kv head) pairs than CUs, several samples per prompt that
+// advance together, and tables that fit.  The fewest that make the launch one round, as far as the 16 columns hold them.
+static int shared_sequences(const AttnDecArgs& a, int B) {
+  const int G = a.Hq / a.Hkv, most = std::min(16 / G, AW);
+  if (a.n_chunks != 1 || a.row_step0 || a.share < 2 || B % a.share != 0 || B * a.Hkv <= 256 || a.pool.max_pages > ATAB) return 1;
+  int ns = 1;
+  for (int n = 2; n <= most && ns * 256 < B * a.Hkv; ++n)
+    if (a.share % n == 0 && n * (a.pool.max_pages - a.shared_pages) <= kOwnTab) ns = n;
+  return ns;
+}
+
 // ---------------------------------------------------------------- packing live rows into the leading slots
 __global__ void k_count_live(const int* done, int B, int* live) {
   __shared__ float red[16];
@@ -1194,6 +1374,11 @@ void compact_slots(const int* done, int B, int slots, const int* slot_row, const
 }
 
 void attention_dec(const AttnDecArgs& a, int B, hipStream_t st) {
+  if (const int ns = shared_sequences(a, B); ns > 1) {
+    if (a.pool.head_dim == 64) launch_shared<64>(a, B, ns, st);
+    else launch_shared<128>(a, B, ns, st);
+    return;
+  }
   const dim3 grid(B, a.Hkv, a.n_chunks);
   if (a.pool.head_dim == 64) k_attn_dec<64><<<grid, AW * 64, 0, st>>>(a);
   else k_attn_dec<128><<<grid, AW * 64, 0, st>>>(a);

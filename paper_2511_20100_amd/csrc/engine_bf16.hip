@@ -452,6 +452,7 @@ void decode_layers(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, K
     at.qkv = p.qkv; at.cos = w->rope_cos; at.sin = w->rope_sin; at.Hq = D.Hq; at.Hkv = D.Hkv; at.layer = l;
     at.pos_base = pos_base; at.row_pos = p.ragged ? p.row_pos : nullptr; at.d_step = p.d_step; at.pool = pool; at.chunk_pages = p.chunk_pages; at.split_at_prompt = p.split_at_prompt;
     at.n_chunks = p.n_chunks; at.m_tiles = bt; at.share = p.n_samples;
+    at.shared_pages = p.ragged ? 0 : p.prompt_len / kPageTokens & ~1;
     at.row_step0 = p.ragged == 3 ? p.row_step0 : nullptr; at.max_step = p.max_new - 1;
     at.o = (h16_t*)p.o_chunks; at.o_chunk_stride = (size_t)D.nq * bt * 16; at.ml = p.attn_ml; at.err_flag = w->err_flag;
     mark(MTMC_KERNEL_ATTENTION);
@@ -581,7 +582,6 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   const int S = p.prompt_len, ns = p.n_samples, B = p.B;
   const size_t total_rows = (size_t)p.total_prompts * ns;
   KvPool pool{p.kv, p.n_pages, c.n_kv_heads, c.head_dim, p.page_table, p.max_pages};
-  const size_t kv_words = (size_t)c.n_layers * 2 * p.n_pages * c.n_kv_heads * kPageTokens * c.head_dim / 2;
   RolloutPlan gp = p;
   gp.ragged = 3;  // the step graph of this form is its own (its launches carry row_step0)
   bf16::SampleCtl* d_ctl = (bf16::SampleCtl*)p.ctl;
@@ -599,7 +599,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   bf16::admit_init(p.slot_row, p.row_step0, B, p.bt * 16, st);
   launch_set_int(p.d_step, 0, st);
   launch_set_int(p.d_step + 1, 0, st);
-  launch_fill_u32((uint32_t*)p.kv, 0u, kv_words, st);
+  launch_clear_values(pool, c.n_layers, 2, st);
   // prefill of `np` prompts (ids [np, S], padding cleared) through the page-table rows from `table` on (one row
   // per sequence, n_samples rows per prompt, the prompt's pages being those of its first row)
   auto prefill = [&](const int* ids, int np, const int* table, int rows_per_prompt) {
@@ -767,7 +767,6 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
   }
   const Dims D = dims_of(w);
   KvPool pool{p.kv, p.n_pages, c.n_kv_heads, c.head_dim, p.page_table, p.max_pages};
-  const size_t kv_words = (size_t)c.n_layers * 2 * p.n_pages * c.n_kv_heads * kPageTokens * c.head_dim / 2;
   for (int g0 = 0; g0 < p.total_prompts; g0 += p.n_prompts) {
     const int np_group = std::min(p.n_prompts, p.total_prompts - g0);
     RolloutPlan gp = p;  // this group's shape (the last group may be smaller)
@@ -802,9 +801,9 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     }
     launch_set_int(p.d_step, 0, st);
     launch_set_int(p.d_step + 1, 0, st);  // arrival counter of the sampler merge
-    // stale or uninitialised cache slots must at least be finite: masked scores multiply them by 0 (with a cached
+    // stale or uninitialised value slots must at least be finite: masked weights multiply them by 0 (with a cached
     // prefix the pool holds the previous call's values: finite, and the prefix pages must stay)
-    if (R == 0) launch_fill_u32((uint32_t*)p.kv, 0u, kv_words, st);
+    if (R == 0) launch_clear_values(pool, c.n_layers, 2, st);
     // ---- prefill, whole prompts per chunk; a prompt's pages are those of its first sample
     for (int p0 = 0; p0 < np_group; p0 += p.chunk_prompts) {
       const int np = std::min(p.chunk_prompts, np_group - p0);
@@ -940,7 +939,7 @@ int bf16_score(const mtmc_weights* w, const ScorePlan& p, const ScoreArgs& a, hi
   if (a.out_margin) launch_fill_u32((uint32_t*)a.out_margin, 0u, n_out, st);
   KvPool pool{p.kv, p.n_pages, c.n_kv_heads, c.head_dim, p.page_table, p.pages_per_seq};
   launch_build_page_table(p.page_table, p.chunk_seqs, p.pages_per_seq, 1, 0, 0, st);
-  launch_fill_u32((uint32_t*)p.kv, 0u, (size_t)2 * p.n_pages * c.n_kv_heads * kPageTokens * c.head_dim / 2, st);
+  launch_clear_values(pool, 1, 2, st);
   TokMap map{S, 1, 0, nullptr};
   for (int s0 = 0; s0 < a.n_seqs; s0 += p.chunk_seqs) {
     const int ns = std::min(p.chunk_seqs, a.n_seqs - s0);
@@ -971,9 +970,8 @@ int bf16_score_actions(const mtmc_weights* w, const ActionPlan& p, const ActionA
   launch_build_action_seqs(p.vseq, p.prefix, a.states, a.actions, a.action_len, p.n_states, p.P, p.K, p.A,
                            w->err_flag, st);
   launch_fill_u32((uint32_t*)a.out_token, 0u, (size_t)p.B * p.A, st);
-  // stale or uninitialised cache slots must at least be finite: masked scores multiply them by 0
-  launch_fill_u32((uint32_t*)p.kv, 0u,
-                  (size_t)c.n_layers * 2 * p.n_pages * c.n_kv_heads * kPageTokens * c.head_dim / 2, st);
+  // stale or uninitialised value slots must at least be finite: masked weights multiply them by 0
+  launch_clear_values(pool, c.n_layers, 2, st);
   // ---- the states without their last token, once per state, into the pages of their first candidate
   if (p.Pp > 0) {
     for (int n0 = 0; n0 < p.n_states; n0 += p.chunk_states) {

@@ -40,6 +40,19 @@ void launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st) {
   k_fill_u32<<<blocks, 256, 0, st>>>(p, v, n);
 }
 
+// The value pages of a pool are cleared (16 bytes per thread), the key pages are not: a key slot that was never written only
+// ever gives a score that the mask replaces, a value slot is multiplied by its weight 0.
+__global__ void k_clear_values(uint4* kv, size_t plane, size_t total) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x)
+    kv[(2 * (i / plane) + 1) * plane + i % plane] = make_uint4(0, 0, 0, 0);
+}
+void launch_clear_values(const KvPool& pool, int n_layers, int elem_bytes, hipStream_t st) {
+  const size_t plane = (size_t)pool.n_pages * pool.n_kv_heads * kPageTokens * pool.head_dim * elem_bytes / 16;
+  const size_t total = plane * n_layers;
+  if (total == 0) return;
+  k_clear_values<<<(int)std::min<size_t>((total + 255) / 256, 4096), 256, 0, st>>>((uint4*)pool.base, plane, total);
+}
+
 // Plain 16-byte-per-lane copy: a kernel of exactly known traffic for calibrating byte counters.
 __global__ void k_copy_probe(uint4* dst, const uint4* src, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)

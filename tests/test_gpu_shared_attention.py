@@ -1,0 +1,90 @@
+"""The decode attention that takes several samples of a prompt in one workgroup (more (sequence, kv head) pairs than CUs):
+one to eight query heads per kv head, an even and an odd number of whole prompt pages and none, contexts of one pair of
+pages up to several per wavefront, prompts of different lengths.  Every row is replayed on the oracle, and agrees with
+the same prompt in a call too small for that form."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from parity import LOGP_TOL_BF16, check_ragged_by_replay, check_rollout_by_replay
+from paper_2511_20100_amd import inputs
+
+MHA8 = inputs.ModelConfig(1, 256, 8, 8, 64, 512, 1040, dtype="bf16")
+G2 = inputs.ModelConfig(1, 256, 16, 8, 128, 512, 1040, dtype="bf16")
+G4 = inputs.ModelConfig(1, 256, 16, 4, 64, 512, 1040, dtype="bf16")
+G7 = inputs.ModelConfig(1, 256, 28, 4, 128, 512, 1040, dtype="bf16")
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_2511_20100_amd import mtmc
+    return mtmc
+
+
+@pytest.mark.parametrize("name,cfg,n_prompts,plen,n_samples,max_new", [
+    ("mha-no-whole-page", MHA8, 5, 9, 8, 20),        # 320 pairs; all pages are the sequences' own, 2 of them at the end
+    ("mha-odd-pages", MHA8, 5, 55, 8, 12),           # 3 whole pages: two shared, the third taken with the own ones
+    ("mha-long", MHA8, 8, 330, 6, 6),                # 20 whole pages; two of the six samples per workgroup
+    ("g2", G2, 4, 40, 12, 10),
+    ("g4", G4, 12, 70, 8, 8),
+    ("g7-two-rounds", G7, 16, 37, 8, 8),             # 512 pairs, two sequences per workgroup
+], ids=lambda v: v if isinstance(v, str) else None)
+def test_samples_in_one_workgroup(lib, name, cfg, n_prompts, plen, n_samples, max_new):
+    import torch
+    w = inputs.make_weights(cfg, seed=0, std=0.05, gain_std=0.1)
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 512), w.blob())
+    try:
+        prompts = inputs.make_prompts(n_prompts, plen, cfg.vocab, seed=2)
+        last = (n_prompts - 1) * n_samples
+        rep = check_rollout_by_replay(handle, w, prompts, n_samples, max_new, 1.0, 1, max_positions=512,
+                                      rows=[0, 1, n_samples - 1, n_samples, last, last + n_samples - 1], label=name)
+        alone = lib.mtmc_rollout(handle, torch.from_numpy(prompts[-1:]).cuda(), n_samples, max_new, 1.0, 1, seq_offset=last)
+        same = (alone[0].cpu().numpy() == rep["ids"][last:]).all(axis=1)
+        assert same.any()
+        # each is within the tolerance of the exact value
+        assert np.abs(alone[1].cpu().numpy() - rep["logprobs"][last:])[same].max() <= 2 * LOGP_TOL_BF16
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
+def test_prompts_of_different_lengths(lib):
+    w = inputs.make_weights(MHA8, seed=0, std=0.05, gain_std=0.1)
+    handle = lib.mtmc_weights_create(lib.make_config(MHA8, 512), w.blob())
+    try:
+        lens = np.array([1, 16, 33, 100, 15, 64, 129, 77, 48, 32], dtype=np.int32)
+        prompts = inputs.make_prompts(len(lens), int(lens.max()), MHA8.vocab, seed=2)
+        check_ragged_by_replay(handle, w, prompts, lens, 4, 14, 1.0, 1, stop_id=3, max_positions=512, label="ragged")
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
+@pytest.mark.parametrize("cfg", [G7, MHA8], ids=["g7", "mha8"])
+def test_what_a_workspace_held_before_does_not_matter(lib, cfg):
+    """Value pages are cleared by the call, key pages are not: every slot a call has not written is masked.  A workspace full
+    of NaN patterns gives the bits that a cleared one gives."""
+    import torch
+    w = inputs.make_weights(cfg, seed=0, std=0.05, gain_std=0.1)
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 256), w.blob())
+    try:
+        prompts = torch.from_numpy(inputs.make_prompts(9, 53, cfg.vocab, seed=2)).cuda()
+        lens = torch.tensor([53, 1, 16, 40, 17, 33, 8, 52, 31], dtype=torch.int32, device="cuda")
+        actions, alens = (torch.from_numpy(x).cuda() for x in inputs.make_actions(9, 5, 20, cfg.vocab, 6, 0))
+        calls = [
+            (lib.mtmc_rollout_workspace_bytes(handle, 9, 53, 8, 21),
+             lambda ws: lib.mtmc_rollout(handle, prompts, 8, 21, 1.0, 1, workspace=ws)),
+            (lib.mtmc_rollout_ragged_workspace_bytes(handle, 9, 53, 2, 21),
+             lambda ws: lib.mtmc_rollout_ragged(handle, prompts, lens, 2, 21, 1.0, 1, workspace=ws)),
+            (lib.mtmc_score_workspace_bytes(handle, 9, 53), lambda ws: (lib.mtmc_score(handle, prompts, 5, workspace=ws),)),
+            (lib.mtmc_score_actions_workspace_bytes(handle, 9, 53, 5, 20),
+             lambda ws: lib.mtmc_score_actions(handle, prompts, actions, alens, workspace=ws)),
+        ]
+        for n, call in calls:
+            got = []
+            for fill in (0x00, 0xff):
+                ws = torch.full((n,), fill, dtype=torch.uint8, device="cuda")
+                got.append([t.clone() for t in call(ws)])
+                lib.mtmc_poll_errors(handle)
+            assert all(torch.equal(a, b) for a, b in zip(*got))
+    finally:
+        lib.mtmc_weights_destroy(handle)
