@@ -38,10 +38,19 @@ struct LargeArgs {
   float* out_f32;
   int ld_out;
   h16_t* out_bf16;
-  int* err_flag;         // SwiGLU epilogue: raised when a value does not fit fp16
+  int* err_flag;         // fp16 outputs: raised when a value does not fit
   const int* d_rows;     // optional (device): only the first *d_rows rows hold tokens; blocks of rows beyond are skipped
   int k_split;           // split-K form: ranges of k-steps, and the partial sums [k_split][M][N] (set by its launcher)
   float* part;
+};
+// Where the QKV projection of the prefill / scoring pass goes when its epilogue rotates: q heads to rows, k and v heads to
+// the cache pages.  Token t is token t % S of sequence t / S, at position pos_base + t % S.
+struct RopeOut {
+  h16_t* q;                // [T, Hq * hd]
+  const float* cos;
+  const float* sin;
+  int Hq, Hkv, S, row_stride, pos_base, layer;
+  KvPool pool;
 };
 
 struct ScoreHeadArgs {
@@ -190,6 +199,13 @@ int gemm_large_f32(float* C, int ldc, int N, bool accumulate, const h16_t* Wt, i
                    hipStream_t st, float* part = nullptr, size_t part_floats = 0, bool leave_parts = false);
 void gemm_large_swiglu(h16_t* act, const h16_t* Wt, int n_tiles, int k_tiles, const h16_t* Xt,
                        int M, int m_tiles, int lds_min_blocks, int* err_flag, const int* d_rows, hipStream_t st);
+// QKV projection with the rotary embedding and the cache write in its epilogue: false, and nothing was launched, for the
+// sizes that the separate kernels keep (those of the direct kernel and of the split reduction).
+bool gemm_large_rope(const RopeOut& r, const h16_t* Wt, int n_tiles, int k_tiles, const h16_t* Xt, int M, int m_tiles,
+                     int lds_min_blocks, int* err_flag, size_t part_floats, hipStream_t st);
+void gemm_lds_rope(const LargeArgs& a, const RopeOut& r, hipStream_t st);
+// ranges that gemm_lds_split would cut the reduction into (0: it would not)
+int gemm_lds_splits(const LargeArgs& a, size_t part_floats);
 // LDS-staged kernel behind the two launchers above (epi: 0 store, 1 accumulate, 2 SwiGLU); it chooses its block by the
 // sizes of the output and of K (even, at least 4 k-steps).
 void gemm_lds(const LargeArgs& a, int epi, hipStream_t st);

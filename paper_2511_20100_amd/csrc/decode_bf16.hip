@@ -1055,7 +1055,8 @@ __global__ __launch_bounds__(AW * 64) void k_attn_dec(AttnDecArgs a) {
 // them): the shared pages are read once for all NS, then every sequence's own pages with the other columns masked, the
 // pairs of own pages handed to the wavefronts in turn.  All NS sequences are at the same position.  What bounds the plain
 // form at many (sequence, kv head) pairs is that a CU holds one workgroup (199 registers): 768 pairs are three rounds of a
-// 10 us chain.  48 rows x 16 kv heads, 4 samples per prompt: see the launcher for what it measured.
+// 10 us chain.  48 rows x 16 kv heads, 4 samples per prompt: 31.0 -> 22.4 us;
+// 128 rows x 4 kv heads of 7 query heads, 8 samples per prompt: 27.3 -> 20.9.
 constexpr int kOwnTab = 512;  // page-table entries of the sequences' own pages kept in LDS
 template <int DHD>
 constexpr int kSharedLds = AW * 16 * (DHD + 1) * (int)sizeof(float);
@@ -1219,6 +1220,7 @@ static void launch_shared(const AttnDecArgs& a, int B, int ns, hipStream_t st) {
 }
 // Sequences per workgroup of the shared form, or 1: more (sequence, kv head) pairs than CUs, several samples per prompt that
 // advance together, and tables that fit.  The fewest that make the launch one round, as far as the 16 columns hold them.
+// Up to 256 pairs the plain form is one round already, and the shared form would leave CUs idle.
 static int shared_sequences(const AttnDecArgs& a, int B) {
   const int G = a.Hq / a.Hkv, most = std::min(16 / G, AW);
   if (a.n_chunks != 1 || a.row_step0 || a.share < 2 || B % a.share != 0 || B * a.Hkv <= 256 || a.pool.max_pages > ATAB) return 1;

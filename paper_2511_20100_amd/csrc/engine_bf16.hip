@@ -406,10 +406,14 @@ void prefill_layers(const mtmc_weights* w, const Dims& D, float* h, h16_t* x, fl
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerWeights& L = w->layers[l];
     const int kvl = l * layer_stride;
-    const int sq = bf16::gemm_large_f32(qkv, D.nqkv, D.nqkv, false, (const h16_t*)L.wqkv, D.nt_qkv, D.kt_d, x, T, mt, lmb,
-                                        d_rows, st, part, pf, leave);
-    bf16::rope_kv_write(qb, sq ? part : qkv, D.nqkv, T, S, D.Hq, D.Hkv, w->rope_cos, w->rope_sin, map, pool, kvl, w->err_flag,
-                        st, seq_start, n_seqs, std::max(sq, 1), (size_t)T * D.nqkv);
+    const bf16::RopeOut rope{qb, w->rope_cos, w->rope_sin, D.Hq, D.Hkv, S, map.row_stride, map.pos_base, kvl, pool};
+    if (seq_start || T < bf16::kNormTileRows ||
+        !bf16::gemm_large_rope(rope, (const h16_t*)L.wqkv, D.nt_qkv, D.kt_d, x, T, mt, lmb, w->err_flag, pf, st)) {
+      const int sq = bf16::gemm_large_f32(qkv, D.nqkv, D.nqkv, false, (const h16_t*)L.wqkv, D.nt_qkv, D.kt_d, x, T, mt, lmb,
+                                          d_rows, st, part, pf, leave);
+      bf16::rope_kv_write(qb, sq ? part : qkv, D.nqkv, T, S, D.Hq, D.Hkv, w->rope_cos, w->rope_sin, map, pool, kvl,
+                          w->err_flag, st, seq_start, n_seqs, std::max(sq, 1), (size_t)T * D.nqkv);
+    }
     bf16::attention_prefill(o, qb, n_seqs, S, mt, D.Hq, D.Hkv, map, pool, kvl, w->err_flag, st, seq_start);
     const int so = bf16::gemm_large_f32(h, D.d, D.d, true, (const h16_t*)L.wo, D.nt_d, D.kt_nq, o, T, mt, lmb, d_rows, st, part,
                                         pf, leave);

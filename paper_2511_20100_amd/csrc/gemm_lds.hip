@@ -86,7 +86,10 @@ __device__ __forceinline__ Block block_at(int t, int nb_n, int nb_m) {
 // first block of an XCD's run of `total`
 __device__ __forceinline__ int run_of_xcd(int xcd, int total) { return (int)((long long)total * xcd / kXcds); }
 
-enum { LEPI_STORE = 0, LEPI_ADD = 1, LEPI_SWIGLU = 2 };
+enum { LEPI_STORE = 0, LEPI_ADD = 1, LEPI_SWIGLU = 2, LEPI_ROPE64 = 3, LEPI_ROPE128 = 4 };
+struct RopeArgs : LargeArgs {
+  RopeOut rope;
+};
 
 // Where this wavefront's share of a block's copies comes from: one base per operand (k-step 0), advanced by k-steps,
 // and a 32-bit offset per piece (tile indices past the end are clamped: such blocks are multiplied but never stored).
@@ -279,6 +282,77 @@ __device__ __forceinline__ void store_swiglu(v4f (&acc)[T::NB][T::MB], const Lar
   }
 }
 
+// Rotary form: the wavefront's 8 feature tiles are one head of 128 dims or two of 64, and a lane holds dims i .. i + 3 and
+// i + hd / 2 .. of one token, so it rotates what it holds.  q goes to rows, k and v to the pages (layouts: attention_core.h).
+// The fp32 projection is never written and read back: 16 of the 20 KiB that a token of the 1.5 B shape moved, and a launch.
+// Projection and rotary kernel, before and now: 874 -> 645 us (98 304 tokens x 2048 features), 102 -> 89 (5439 x 3072, 64-dim
+// heads), 46.6 -> 36.0 (2048 x 2048).
+template <class T, int HD>
+__device__ __forceinline__ void store_rope(v4f (&acc)[T::NB][T::MB], const RopeArgs& a, int nt0, int mt0, int lane) {
+  constexpr int MB = T::MB, BPH = HD / 16, HB = BPH / 2;
+  static_assert(T::NB == 8, "a wavefront holds whole heads");
+  const RopeOut& r = a.rope;
+  const int col = lane & 15, rq = (lane >> 4) * 4;
+  h16_t* const kv = (h16_t*)r.pool.base;
+  bool out_of_range = false;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int t = (mt0 + mb) * 16 + col;
+    const bool live = t < a.M;
+    const int seq = min(t, a.M - 1) / r.S, pos = r.pos_base + min(t, a.M - 1) - seq * r.S;
+    const float* cs = r.cos + (size_t)pos * (HD / 2) + rq;
+    const float* sn = r.sin + (size_t)pos * (HD / 2) + rq;
+#pragma unroll
+    for (int hs = 0; hs < 8 / BPH; ++hs) {
+      const int head = nt0 / BPH + hs;  // wavefront-uniform
+#pragma unroll
+      for (int nb = 0; nb < BPH; ++nb) asm volatile("" : "+a"(acc[hs * BPH + nb][mb])::"memory");
+      if (!live || head >= r.Hq + 2 * r.Hkv) continue;
+      if (head < r.Hq + r.Hkv) {
+        h16_t *lo, *hi;  // where dims rq .. + 3 of the two halves go; + 16 nb dims: step elements
+        int step;
+        if (head < r.Hq) {
+          lo = r.q + ((size_t)t * r.Hq + head) * HD + rq;
+          hi = lo + HD / 2;
+          step = 16;
+        } else {
+          const int page = r.pool.page_table[(size_t)seq * r.row_stride * r.pool.max_pages + pos / kPageTokens];
+          lo = kv + ((((size_t)r.layer * 2) * r.pool.n_pages + page) * r.Hkv + head - r.Hq) * (kPageTokens * HD) +
+               (rq >> 3) * 128 + (pos % kPageTokens) * 8 + (rq & 7);
+          hi = lo + HD / 16 * 128;
+          step = 256;
+        }
+#pragma unroll
+        for (int nb = 0; nb < HB; ++nb) {
+          const v4f x = acc[hs * BPH + nb][mb], y = acc[hs * BPH + nb + HB][mb];
+          const v4f c = *reinterpret_cast<const v4f*>(cs + 16 * nb), s = *reinterpret_cast<const v4f*>(sn + 16 * nb);
+          const v4f rx = x * c - y * s, ry = y * c + x * s;
+          uint2 p, q;
+          p.x = pack_h16x2_track(rx[0], rx[1], out_of_range); p.y = pack_h16x2_track(rx[2], rx[3], out_of_range);
+          q.x = pack_h16x2_track(ry[0], ry[1], out_of_range); q.y = pack_h16x2_track(ry[2], ry[3], out_of_range);
+          *reinterpret_cast<uint2*>(lo + nb * step) = p;
+          *reinterpret_cast<uint2*>(hi + nb * step) = q;
+        }
+      } else {
+        const int g = head - r.Hq - r.Hkv;
+        const int page = r.pool.page_table[(size_t)seq * r.row_stride * r.pool.max_pages + pos / kPageTokens];
+        h16_t* vp = kv + ((((size_t)r.layer * 2 + 1) * r.pool.n_pages + page) * r.Hkv + g) * (kPageTokens * HD) +
+                    rq * kPageTokens + pos % kPageTokens;
+#pragma unroll
+        for (int nb = 0; nb < BPH; ++nb) {
+          const v4f v = acc[hs * BPH + nb][mb];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            out_of_range |= !fits_h16(v[e]);
+            vp[(16 * nb + e) * kPageTokens] = f32_to_h16(v[e]);
+          }
+        }
+      }
+    }
+  }
+  if (out_of_range) atomicOr(a.err_flag, kErrFp16Range);
+}
+
 // Blocks that hold tokens: rows packed on the device (d_rows) fill only part of the capacity the launch is sized for.
 // Whatever the block's height, all rows up to the next multiple of 256 are computed (from cleared inputs): a launch with
 // taller blocks reads them next.
@@ -288,8 +362,8 @@ __device__ __forceinline__ int row_blocks(int m_tiles, const int* d_rows) {
   return d_rows ? min(nb_m, (((*d_rows + 255) & ~255) + T::TM * 16 - 1) / (T::TM * 16)) : nb_m;
 }
 
-template <class T, int EPI>
-__global__ __launch_bounds__(256, T::PC) void k_gemm_lds(LargeArgs a) {
+template <class T, int EPI, class Args>
+__global__ __launch_bounds__(256, T::PC) void k_gemm_lds(Args a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int lane = threadIdx.x & 63, uwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb_n = (a.n_tiles + T::TN - 1) / T::TN, nb_m = row_blocks<T>(a.m_tiles, a.d_rows);
@@ -307,7 +381,9 @@ __global__ __launch_bounds__(256, T::PC) void k_gemm_lds(LargeArgs a) {
   };
   auto epilogue = [&](v4f (&acc)[T::NB][T::MB], int nt_base, int mt_base, int) {
     const int nt0 = nt_base + T::NB * (uwave & 1), mt0 = mt_base + T::MB * (uwave >> 1);
-    if (EPI == LEPI_SWIGLU) store_swiglu<T>(acc, a, nt0, mt0, lane);
+    if constexpr (EPI == LEPI_ROPE64) store_rope<T, 64>(acc, a, nt0, mt0, lane);
+    else if constexpr (EPI == LEPI_ROPE128) store_rope<T, 128>(acc, a, nt0, mt0, lane);
+    else if constexpr (EPI == LEPI_SWIGLU) store_swiglu<T>(acc, a, nt0, mt0, lane);
     else store_f32<T, EPI == LEPI_ADD>(acc, a.out_f32, a.ld_out, a.M, a.N, nt0, mt0, lane);
   };
   lds_gemm_stream<T>(reinterpret_cast<const uint8_t*>(a.Wt), reinterpret_cast<const uint8_t*>(a.Xt), a.n_tiles, a.m_tiles,
@@ -498,11 +574,11 @@ size_t blocks_of(const LargeArgs& a) {
   return (size_t)((a.n_tiles + T::TN - 1) / T::TN) * ((a.m_tiles + T::TM - 1) / T::TM);
 }
 
-template <class T, int EPI>
-void launch_tile(const LargeArgs& a, hipStream_t st) {
-  static const bool configured = (allow_lds<T>(&k_gemm_lds<T, EPI>), true);
+template <class T, int EPI, class Args>
+void launch_tile(const Args& a, hipStream_t st) {
+  static const bool configured = (allow_lds<T>(&k_gemm_lds<T, EPI, Args>), true);
   (void)configured;
-  k_gemm_lds<T, EPI><<<grid_of<T>(blocks_of<T>(a)), 256, T::kLds, st>>>(a);
+  k_gemm_lds<T, EPI, Args><<<grid_of<T>(blocks_of<T>(a)), 256, T::kLds, st>>>(a);
 }
 template <class T>
 void launch_split(const LargeArgs& a, hipStream_t st) {
@@ -587,16 +663,17 @@ void lmhead_score_lds(const ScoreHeadArgs& a, hipStream_t st) {
   else a.want_top ? launch_lmhead<Tile<8, 8, 4, 1>, true>(a, st) : launch_lmhead<Tile<8, 8, 4, 1>, false>(a, st);
 }
 
+// The most splits, up to 8 and to one round of blocks of 256 x 256, that leave every range even and at least 8 k-steps
+// long.  Not by the tile that the launch chooses: the order of the sums then follows from the sizes alone.
+int gemm_lds_splits(const LargeArgs& a, size_t part_floats) {
+  const int blocks = (a.n_tiles + 15) / 16 * ((a.m_tiles + 15) / 16);  // of 256 x 256
+  if (blocks > kCus / 2 || a.N % 4 != 0) return 0;
+  for (int s = std::min(8, kCus / blocks); s >= 2; --s)
+    if (a.k_tiles % s == 0 && (a.k_tiles / s) % 2 == 0 && a.k_tiles / s >= 8 && (size_t)s * a.M * a.N <= part_floats) return s;
+  return 0;
+}
 int gemm_lds_split(const LargeArgs& a0, bool accumulate, float* part, size_t part_floats, bool leave_parts, hipStream_t st) {
-  const int blocks = (a0.n_tiles + 15) / 16 * ((a0.m_tiles + 15) / 16);  // of 256 x 256
-  if (!part || blocks > kCus / 2 || a0.N % 4 != 0) return 0;
-  // The most splits, up to 8 and to one round of blocks of 256 x 256, that leave every range even and at least 8 k-steps
-  // long.  Not by the tile that is chosen below: the order of the sums then follows from the sizes alone.
-  int S = 0;
-  for (int s = std::min(8, kCus / blocks); s >= 2 && !S; --s)
-    if (a0.k_tiles % s == 0 && (a0.k_tiles / s) % 2 == 0 && a0.k_tiles / s >= 8 &&
-        (size_t)s * a0.M * a0.N <= part_floats)
-      S = s;
+  const int S = part ? gemm_lds_splits(a0, part_floats) : 0;
   if (!S) return 0;
   LargeArgs a = a0;
   a.k_split = S;
@@ -608,6 +685,21 @@ int gemm_lds_split(const LargeArgs& a0, bool accumulate, float* part, size_t par
   k_splitk_reduce<<<(unsigned)((quads + 255) / 256), 256, 0, st>>>(a.out_f32, a.ld_out, part, S, a.M, a.N,
                                                                   accumulate ? 1 : 0, a.d_rows);
   return S;
+}
+
+// A wavefront has to hold whole heads: the blocks of 256 features, of which the measured costs choose.  From 1024 tokens (the
+// caller); below, the separate rotary kernel adds up the slices of a split reduction, and a launch has too few such blocks.
+void gemm_lds_rope(const LargeArgs& a0, const RopeOut& r, hipStream_t st) {
+  const RopeArgs a{a0, r};
+  const int features = a.n_tiles * 16;
+  const bool wide = cost_of(kTiles[0], features, a.M, a.k_tiles, 1, true) <= cost_of(kTiles[2], features, a.M, a.k_tiles, 1, true);
+  if (a.rope.pool.head_dim == 64) {
+    if (wide) launch_tile<Tile<8, 8, 4, 1>, LEPI_ROPE64>(a, st);
+    else launch_tile<Tile<8, 4, 3, 2>, LEPI_ROPE64>(a, st);
+  } else {
+    if (wide) launch_tile<Tile<8, 8, 4, 1>, LEPI_ROPE128>(a, st);
+    else launch_tile<Tile<8, 4, 3, 2>, LEPI_ROPE128>(a, st);
+  }
 }
 
 void gemm_lds(const LargeArgs& a, int epi, hipStream_t st) {

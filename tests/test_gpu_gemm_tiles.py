@@ -70,3 +70,24 @@ def test_packed_candidates_are_the_same_in_every_tile(lib, handle, n_states, sta
     direct = lib.mtmc_score_actions(handle, states, actions, lens)
     lib.mtmc_poll_errors(handle)
     assert float((direct[0] - tok).abs().max()) <= TOL
+
+
+# q, k and v heads of both sizes, an odd number of them (a wavefront's last pair of 64-dim heads is half empty), sequences
+# that end inside a page and blocks that end inside a sequence: the projection that rotates and writes the cache in its
+# epilogue, against the separate kernels (few tokens or the direct kernels).
+@pytest.mark.parametrize("heads,kv_heads,head_dim", [(3, 1, 64), (4, 4, 64), (3, 1, 128), (12, 2, 128), (8, 8, 64)])
+@pytest.mark.parametrize("n_seqs,seq_len", [(8, 129), (1, 1025), (13, 190), (150, 97)])
+def test_rotary_epilogue_is_the_separate_kernels(lib, heads, kv_heads, head_dim, n_seqs, seq_len):
+    import torch
+    cfg = inputs.ModelConfig(2, heads * head_dim, heads, kv_heads, head_dim, 256, 512, dtype="bf16")
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 1280), inputs.make_weights(cfg, seed=1, std=0.04, gain_std=0.1).blob())
+    seqs = torch.from_numpy(inputs.make_sequences(n_seqs, seq_len, cfg.vocab, seed=7)).cuda()
+    _lds(lib, handle, True)
+    lp = lib.mtmc_score(handle, seqs, 1)
+    short = lib.mtmc_score(handle, seqs[-1:, :seq_len // 2].contiguous(), 1)
+    _lds(lib, handle, False)
+    direct = lib.mtmc_score(handle, seqs, 1)
+    lib.mtmc_poll_errors(handle)
+    lib.mtmc_weights_destroy(handle)
+    assert float((direct - lp).abs().max()) <= TOL
+    assert float((short[0] - lp[-1, :seq_len // 2 - 1]).abs().max()) <= TOL
