@@ -286,7 +286,7 @@ __device__ __forceinline__ void store_swiglu(v4f (&acc)[T::NB][T::MB], const Lar
 // i + hd / 2 .. of one token, so it rotates what it holds.  q goes to rows, k and v to the pages (layouts: attention_core.h).
 // The fp32 projection is never written and read back: 16 of the 20 KiB that a token of the 1.5 B shape moved, and a launch.
 // Projection and rotary kernel, before and now: 874 -> 645 us (98 304 tokens x 2048 features), 102 -> 89 (5439 x 3072, 64-dim
-// heads), 46.6 -> 36.0 (2048 x 2048).
+// heads), 46.6 -> 36.0 (4096 x 2048).
 template <class T, int HD>
 __device__ __forceinline__ void store_rope(v4f (&acc)[T::NB][T::MB], const RopeArgs& a, int nt0, int mt0, int lane) {
   constexpr int MB = T::MB, BPH = HD / 16, HB = BPH / 2;
@@ -561,6 +561,142 @@ __global__ __launch_bounds__(256, T::PC) void k_lmhead_lds(ScoreHeadArgs a, int 
                      a.k_tiles, a.k_tiles, lds, lane, uwave, tile_at, epilogue);
 }
 
+// Sampling LM head of 65 .. 128 rows on the same engine: the workgroups of the launch walk the vocabulary in blocks of 128
+// entries, and every lane folds its entries of 4 rows into a running (log-sum-exp, Gumbel arg-max) that leaves the kernel once,
+// as two partial results per row and workgroup.  The logits are those of k_gemm_rows128 (one accumulator over K in ascending
+// order) bit for bit.  That form starts a workgroup, with the row scales (100 KiB of sums of squares) and an empty pipeline, for
+// every 128 entries: 128 rows x 151 936 entries x 1536 139 us there and 105 here (76 at the rate of a large read), 152 064 x 3584
+// 245 and 222 (176).
+using SampleTile = Tile<4, 4, 4, 2>;
+__global__ __launch_bounds__(256, SampleTile::PC) void k_lmhead_sample_lds(DecGemmArgs a) {
+  using T = SampleTile;
+  constexpr int NB = T::NB, MB = T::MB, NT = 256, ROWS = T::TM * 16;
+  static_assert(ROWS == 128, "the rows of a launch are one block of tokens");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  __shared__ float s_scale[ROWS];
+  __shared__ int s_row[ROWS], s_step[ROWS];
+  __shared__ float s_part[2][NT];
+  const int tid = threadIdx.x, lane = tid & 63, uwave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = uwave & 1, wm = uwave >> 1, col = lane & 15, rq = (lane >> 4) * 4;
+  const int Mpad = a.m_tiles * 16;  // 80 .. 128
+  const SampleCtl ctl = *a.ctl;
+
+  // ---- row scales r_new / r_old: thread t sums the tiles part, part + P, ... of row t % Mpad, the P sums are added in index
+  // order (the operations and their order are those of the other forms: the same bits)
+  {
+    const int P = NT / Mpad, m = tid % Mpad, part = tid / Mpad;
+    const bool two = a.ss_cur && a.ss_old != a.ss_cur;
+    float sa = 0.f, sb = 0.f;
+    if (two && part < P) {
+      constexpr int BT = 16;
+      for (int t0 = part; t0 < a.ss_tiles; t0 += BT * P) {  // batches of independent loads
+        float fa[BT], fb[BT];
+#pragma unroll
+        for (int u = 0; u < BT; ++u) {
+          const int t = t0 + u * P;
+          fa[u] = t < a.ss_tiles ? a.ss_cur[(size_t)t * Mpad + m] : 0.f;
+          fb[u] = t < a.ss_tiles ? a.ss_old[(size_t)t * Mpad + m] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < BT; ++u) {
+          sa += fa[u];
+          sb += fb[u];
+        }
+      }
+    }
+    s_part[0][tid] = sa;
+    s_part[1][tid] = sb;
+    __syncthreads();
+    if (tid < ROWS) {
+      float sc = 1.f;
+      if (tid < Mpad && two) {
+        float ta = 0.f, tb = 0.f;
+        for (int q = 0; q < P; ++q) {
+          ta += s_part[0][q * Mpad + tid];
+          tb += s_part[1][q * Mpad + tid];
+        }
+        sc = 1.0f / sqrtf(ta * a.inv_d + a.eps);
+        sc *= sqrtf(tb * a.inv_d + a.eps);
+      }
+      s_scale[tid] = sc;
+      // the random numbers of a row follow the row and its own step (an empty slot draws row 0's: unused)
+      s_row[tid] = (ctl.slot_row && tid < a.M) ? max(ctl.slot_row[tid], 0) : tid;
+      s_step[tid] = *a.d_step - ((ctl.row_step0 && tid < a.M) ? ctl.row_step0[tid] : 0);
+    }
+    __syncthreads();
+  }
+
+  const int nb_n = (a.n_tiles + T::TN - 1) / T::TN;
+  const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3, end = run_of_xcd(xcd + 1, nb_n);
+  int t = run_of_xcd(xcd, nb_n) + (int)(blockIdx.x >> 3) - stride;
+  auto tile_at = [&](int& nt_base, int& mt_base, int&) {
+    t += stride;
+    if (t >= end) return false;
+    nt_base = t * T::TN;
+    mt_base = 0;
+    return true;
+  };
+  Lse lse[MB];
+  float by[MB], bz[MB];
+  int bi[MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    lse[mb] = lse_empty();
+    by[mb] = -INFINITY;
+    bz[mb] = 0.f;
+    bi[mb] = 0x7fffffff;
+  }
+  auto epilogue = [&](v4f (&acc)[NB][MB], int nt_base, int, int) {
+    const int nt0 = nt_base + NB * wn;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const int m = (MB * wm + mb) * 16 + col;
+      const float sc = s_scale[m];
+      const uint32_t row = (uint32_t)s_row[m], step = (uint32_t)s_step[m];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        asm volatile("" : "+a"(acc[nb][mb])::"memory");
+        if (nt0 + nb >= a.n_tiles) continue;
+        const int v0 = (nt0 + nb) * 16 + rq;  // multiple of 4: one generator block per 4 entries
+        uint4 rb = make_uint4(0, 0, 0, 0);
+        if (!ctl.greedy) rb = philox4x32_10(make_uint4((uint32_t)(v0 >> 2), step, ctl.seq_offset + row, 0u), ctl.key0, ctl.key1);
+        const uint32_t rr[4] = {rb.x, rb.y, rb.z, rb.w};
+        float zt[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float z = acc[nb][mb][r] * sc;
+          zt[r] = ctl.greedy ? z : z * ctl.inv_temp;
+        }
+        lse_push4(lse[mb], zt[0], zt[1], zt[2], zt[3]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float y = ctl.greedy ? zt[r] : zt[r] + gumbel_from_bits(rr[r]);
+          if (y > by[mb]) { by[mb] = y; bi[mb] = v0 + r; bz[mb] = zt[r]; }  // ascending index: the first maximum wins
+        }
+      }
+    }
+  };
+  lds_gemm_stream<T>(reinterpret_cast<const uint8_t*>(a.Wt), reinterpret_cast<const uint8_t*>(a.Xt), a.n_tiles, a.m_tiles,
+                     a.k_tiles, a.k_tiles, lds, lane, uwave, tile_at, epilogue);
+  // ---- a row's four column groups (lane / 16); a workgroup without a block leaves empty results
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int m = (MB * wm + mb) * 16 + col;
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+      const Lse ol = {__shfl_xor(lse[mb].m, o, 64), __shfl_xor(lse[mb].s, o, 64)};
+      const float oy = __shfl_xor(by[mb], o, 64), oz = __shfl_xor(bz[mb], o, 64);
+      const int oi = __shfl_xor(bi[mb], o, 64);
+      lse[mb] = lse_merge(lse[mb], ol);
+      if (oy > by[mb] || (oy == by[mb] && oi < bi[mb])) { by[mb] = oy; bi[mb] = oi; bz[mb] = oz; }
+    }
+    if (lane < 16 && m < a.M) {
+      DecSamplePartial* p = reinterpret_cast<DecSamplePartial*>(a.out_f32) + (size_t)m * (2 * gridDim.x) + 2 * blockIdx.x + wn;
+      p->m = lse[mb].m; p->s = lse[mb].s; p->y = by[mb]; p->idx = bi[mb]; p->zt = bz[mb];
+    }
+  }
+}
+
 // The runtime's limit on dynamic LDS is raised once per kernel.
 template <class T, typename Kernel>
 void allow_lds(Kernel* k) {
@@ -700,6 +836,21 @@ void gemm_lds_rope(const LargeArgs& a0, const RopeOut& r, hipStream_t st) {
     if (wide) launch_tile<Tile<8, 8, 4, 1>, LEPI_ROPE128>(a, st);
     else launch_tile<Tile<8, 4, 3, 2>, LEPI_ROPE128>(a, st);
   }
+}
+
+static int sample_lds_grid(int n_tiles) { return grid_of<SampleTile>((size_t)(n_tiles + SampleTile::TN - 1) / SampleTile::TN); }
+// Where a CU gets at least one block of 128 entries; the ring takes an even number of k-steps, no fewer than its stages.
+int lmhead_sample_lds_groups(int n_tiles, int k_tiles, int m_tiles) {
+  if (m_tiles <= 4 || m_tiles > SampleTile::TM || n_tiles < kCus * SampleTile::TN || k_tiles < SampleTile::ST || k_tiles % 2 != 0)
+    return 0;
+  return 2 * sample_lds_grid(n_tiles);
+}
+bool lmhead_sample_lds(const DecGemmArgs& a, hipStream_t st) {
+  if (!lmhead_sample_lds_groups(a.n_tiles, a.k_tiles, a.m_tiles)) return false;
+  static const bool configured = (allow_lds<SampleTile>(&k_lmhead_sample_lds), true);
+  (void)configured;
+  k_lmhead_sample_lds<<<sample_lds_grid(a.n_tiles), 256, SampleTile::kLds, st>>>(a);
+  return true;
 }
 
 void gemm_lds(const LargeArgs& a, int epi, hipStream_t st) {
