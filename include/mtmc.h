@@ -306,13 +306,15 @@ const char* mtmc_data_error_string(int bits);
 /*
  * Tuning switches.
  *   MTMC_OPT_HIP_GRAPH (default 1): mtmc_rollout captures one decode step into a HIP graph and
- *   replays it for every token.  Results do not depend on it (same kernels in the same order).
+ *   replays it for every token (MTMC_F32: calls of at least 8 new tokens).  Results do not depend on it (same kernels
+ *   in the same order).
  *   Instantiated graphs are cached inside `w`, keyed by workspace address and the call's shape; replacing
  *   a cached graph (more than 8 are never kept) synchronises the device once.  When `stream` is itself being captured the steps
  *   are launched directly.
  *   MTMC_OPT_GEMM_LDS_MIN_BLOCKS (default 32, value >= 1): prefill / scoring GEMMs (MTMC_BF16)
- *   whose output has at least this many 256 x 256 blocks run in the LDS-staged kernel, smaller
- *   ones in the direct 128 x 128 kernel.  Both sum over K in the same order; results agree to
+ *   whose output has at least this many 256 x 256 blocks run in the LDS-staged kernels (which choose
+ *   their own block size, 128 x 64 to 256 x 256, by the call's sizes), smaller ones in the direct
+ *   128 x 128 kernel.  Both sum over K in the same order; results agree to
  *   the fp32 rounding inside the matrix instruction.
  *   MTMC_OPT_STOP_POLL_STEPS (default 32, 0 = off): MTMC_BF16 rollouts with a stop token look at the rows'
  *   stop flags every this many decode steps.  The look itself is queued on the stream; the host reads it one
