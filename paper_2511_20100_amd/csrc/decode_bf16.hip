@@ -308,7 +308,7 @@ __global__ __launch_bounds__(WAVES * 64, MINW) void k_gemm_dec(DecGemmArgs a) {
   // Sum over the K slices: every wavefront publishes its accumulators; wavefront w then adds the WAVES
   // slices of token tiles w, w + WAVES, ... in index order and runs the epilogue for those tokens.
   // SAMPLE: a wavefront has at most one token tile (MB <= WAVES); its sampler state lives across the passes.
-  Lse smp_lse = lse_empty();
+  Lse2 smp_lse2 = lse2_empty();
   float smp_y = -INFINITY, smp_z = 0.f;
   int smp_i = 0x7fffffff;
 #pragma unroll
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(WAVES * 64, MINW) void k_gemm_dec(DecGemmArgs a) {
         const float z = sum[nb][r] * sc;
         zt[r] = ctl.greedy ? z : z * ctl.inv_temp;
       }
-      lse_push4(smp_lse, zt[0], zt[1], zt[2], zt[3]);
+      lse2_push4(smp_lse2, zt[0], zt[1], zt[2], zt[3]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float y = ctl.greedy ? zt[r] : zt[r] + gumbel_from_bits(rr[r]);
@@ -417,6 +417,7 @@ __global__ __launch_bounds__(WAVES * 64, MINW) void k_gemm_dec(DecGemmArgs a) {
   if (EPI == DEPI_SAMPLE) {
     if (wave < MB && mt0 + wave < a.m_tiles) {
       const int col = lane & 15, m = (mt0 + wave) * 16 + col;
+      Lse smp_lse = lse_of(smp_lse2);
 #pragma unroll
       for (int o = 16; o <= 32; o <<= 1) {
         const Lse ol = {__shfl_xor(smp_lse.m, o, 64), __shfl_xor(smp_lse.s, o, 64)};

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kLW * 64, 1) void k_lmhead_sample(DecGemmArgs a) {
   // (an empty slot draws row 0's: unused)
   const int smp_row = (ctl.slot_row && m < a.M) ? max(ctl.slot_row[m], 0) : m;
   const int step_no = *a.d_step - ((ctl.row_step0 && m < a.M) ? ctl.row_step0[m] : 0);
-  Lse lse = lse_empty();
+  Lse2 lse2 = lse2_empty();
   float by = -INFINITY, bz = 0.f;
   int bi = 0x7fffffff;
 
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kLW * 64, 1) void k_lmhead_sample(DecGemmArgs a) {
             const float z = sum[r] * sc;
             zt[r] = ctl.greedy ? z : z * ctl.inv_temp;
           }
-          lse_push4(lse, zt[0], zt[1], zt[2], zt[3]);
+          lse2_push4(lse2, zt[0], zt[1], zt[2], zt[3]);
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const float y = ctl.greedy ? zt[r] : zt[r] + gumbel_from_bits(rr[r]);
@@ -181,6 +181,7 @@ __global__ __launch_bounds__(kLW * 64, 1) void k_lmhead_sample(DecGemmArgs a) {
   }
 
   // ---- a row's four column groups (lane / 16), then the wavefronts that share its token tile, in column order
+  Lse lse = lse_of(lse2);
 #pragma unroll
   for (int o = 16; o <= 32; o <<= 1) {
     const Lse ol = {__shfl_xor(lse.m, o, 64), __shfl_xor(lse.s, o, 64)};

@@ -241,7 +241,7 @@ __global__ __launch_bounds__(WAVES * 64, MINB) void k_gemm_rows128(DecGemmArgs a
       const float sc = m < Mpad ? s_scale[m] : 1.f;
       const int row = (ctl.slot_row && m < a.M) ? max(ctl.slot_row[m], 0) : m;
       const int row_step = step - ((ctl.row_step0 && m < a.M) ? ctl.row_step0[m] : 0);  // a row that joined later
-      Lse lse = lse_empty();
+      Lse2 lse2 = lse2_empty();
       float by = -INFINITY, bz = 0.f;
       int bi = 0x7fffffff;
 #pragma unroll
@@ -258,13 +258,14 @@ __global__ __launch_bounds__(WAVES * 64, MINB) void k_gemm_rows128(DecGemmArgs a
           const float z = acc[nb][mb][r] * sc;
           zt[r] = ctl.greedy ? z : z * ctl.inv_temp;
         }
-        lse_push4(lse, zt[0], zt[1], zt[2], zt[3]);
+        lse2_push4(lse2, zt[0], zt[1], zt[2], zt[3]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float y = ctl.greedy ? zt[r] : zt[r] + gumbel_from_bits(rr[r]);
           if (y > by) { by = y; bi = v0 + r; bz = zt[r]; }  // ascending index: the first maximum wins
         }
       }
+      Lse lse = lse_of(lse2);
 #pragma unroll
       for (int o = 16; o <= 32; o <<= 1) {
         const Lse ol = {__shfl_xor(lse.m, o, 64), __shfl_xor(lse.s, o, 64)};

@@ -9,6 +9,7 @@
 namespace mtmc {
 
 constexpr int kWave = 64;
+constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
@@ -61,7 +62,6 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
 // Both logarithms are the hardware's base-2 logarithm (1 ulp) times ln 2: u and -ln u (6e-8 .. 16.7) are normal
 // numbers, so none of the library routine's range fix-ups is needed; g is within about 2e-6 of the exact value.
 __device__ __forceinline__ float gumbel_from_bits(uint32_t r) {
-  constexpr float kLn2 = 0.6931471805599453f;
   const float u = ((float)(r >> 9) + 0.5f) * 1.1920928955078125e-07f;
   const float l = -kLn2 * __builtin_amdgcn_logf(u);
   return -kLn2 * __builtin_amdgcn_logf(l);
@@ -80,21 +80,31 @@ __device__ __forceinline__ void lse_push(Lse& a, float x) {
     a.s += expf(x - a.m);
   }
 }
-// The same for four values at once, without branches: the new maximum first, then the old sum and the four terms
-// rescaled to it with the hardware's 2^x (relative error about 1e-7 per term; every argument is <= 0).  An empty
-// state (m = -inf, s = 0) and values of -inf contribute exp2(-inf) = 0; the four values must not all be -inf while
-// the state is empty.
-__device__ __forceinline__ void lse_push4(Lse& a, float x0, float x1, float x2, float x3) {
-  constexpr float kLog2e = 1.4426950408889634f;
-  const float m = fmaxf(fmaxf(a.m, fmaxf(x0, x1)), fmaxf(x2, x3));
-  const float mk = m * kLog2e;
-  float s = a.s * __builtin_amdgcn_exp2f(fmaf(a.m, kLog2e, -mk));
-  s += __builtin_amdgcn_exp2f(fmaf(x0, kLog2e, -mk));
-  s += __builtin_amdgcn_exp2f(fmaf(x1, kLog2e, -mk));
-  s += __builtin_amdgcn_exp2f(fmaf(x2, kLog2e, -mk));
-  s += __builtin_amdgcn_exp2f(fmaf(x3, kLog2e, -mk));
-  a.m = m;
+// The same for four values at once, without branches, in base 2: s = sum of 2^(x log2(e) - k).  The new k first, then the old
+// sum and the four terms rescaled to it with the hardware's 2^x (relative error about 1e-7 per term; every argument is <= 0
+// up to a rounding).  k is the state and not the maximum itself: what rounding x log2(e) to k loses (4e-6 at 64) would be a
+// factor of the whole sum, and so an error of either sign in a likely token's log-probability.  An empty state (k = -inf,
+// s = 0) and values of -inf contribute exp2(-inf) = 0; the four values must not all be -inf while the state is empty.
+struct Lse2 {
+  float k, s;
+};
+__device__ __forceinline__ Lse2 lse2_empty() { return {-INFINITY, 0.f}; }
+__device__ __forceinline__ void lse2_push4(Lse2& a, float x0, float x1, float x2, float x3) {
+  const float k = fmaxf(a.k, fmaxf(fmaxf(x0, x1), fmaxf(x2, x3)) * kLog2e);
+  float s = a.s * __builtin_amdgcn_exp2f(a.k - k);
+  s += __builtin_amdgcn_exp2f(fmaf(x0, kLog2e, -k));
+  s += __builtin_amdgcn_exp2f(fmaf(x1, kLog2e, -k));
+  s += __builtin_amdgcn_exp2f(fmaf(x2, kLog2e, -k));
+  s += __builtin_amdgcn_exp2f(fmaf(x3, kLog2e, -k));
+  a.k = k;
   a.s = s;
+}
+// In natural units: m within a few units in the last place of the largest value, and the sum relative to exactly that m (by
+// the same log2(e) as the terms, so that its rounding does not count).
+__device__ __forceinline__ Lse lse_of(Lse2 a) {
+  if (a.s == 0.f) return lse_empty();
+  const float m = a.k * kLn2;
+  return {m, a.s * __builtin_amdgcn_exp2f(fmaf(-m, kLog2e, a.k))};
 }
 __device__ __forceinline__ Lse lse_merge(Lse a, Lse b) {
   if (b.s == 0.f) return a;

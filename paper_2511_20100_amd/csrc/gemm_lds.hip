@@ -444,7 +444,6 @@ template <class T, bool TOP>
 __global__ __launch_bounds__(256, T::PC) void k_lmhead_lds(ScoreHeadArgs a, int bps) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   constexpr int NB = T::NB, MB = T::MB, H = MB / 4;
-  constexpr float kLog2e = 1.4426950408889634f;
   const int lane = threadIdx.x & 63, uwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wn = uwave & 1, wm = uwave >> 1, col = lane & 15, lg = lane >> 4;
   const int nb_n = (a.n_tiles + T::TN - 1) / T::TN, nb_m = row_blocks<T>(a.m_tiles, a.d_rows);
@@ -498,13 +497,15 @@ __global__ __launch_bounds__(256, T::PC) void k_lmhead_lds(ScoreHeadArgs a, int 
       for (int j = 1; j < NB * 4; ++j) bm = fmaxf(bm, z[j]);
       bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
       bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
-      // no entry exists (or none compares): nothing to add; every other lane's terms are exp2(<= 0)
-      const float mk = (bm > -INFINITY ? bm : 0.f) * kLog2e;
+      // no entry exists (or none compares): nothing to add.  The terms are exp2(z log2(e) - mk) with mk = bm log2(e) rounded;
+      // lo is what that rounding lost, a common factor 2^lo of the sum (left in, it stood in the log-probability)
+      const float ref = bm > -INFINITY ? bm : 0.f, mk = ref * kLog2e, lo = fmaf(ref, kLog2e, -mk);
       float sum = 0.f;
 #pragma unroll
       for (int j = 0; j < NB * 4; ++j) sum += __builtin_amdgcn_exp2f(fmaf(z[j], kLog2e, -mk));
       sum += __shfl_xor(sum, 16, 64);
       sum += __shfl_xor(sum, 32, 64);
+      sum *= __builtin_amdgcn_exp2f(-lo);
       const int d = __shfl(target[h], owner, 64) - nt0 * 16;  // the target's index among the wavefront's entries
       float hit = -INFINITY;
       const bool here = d >= 0 && d < NB * 16 && ((d >> 2) & 3) == lg;
@@ -636,12 +637,12 @@ __global__ __launch_bounds__(256, SampleTile::PC) void k_lmhead_sample_lds(DecGe
     mt_base = 0;
     return true;
   };
-  Lse lse[MB];
+  Lse2 lse2[MB];
   float by[MB], bz[MB];
   int bi[MB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
-    lse[mb] = lse_empty();
+    lse2[mb] = lse2_empty();
     by[mb] = -INFINITY;
     bz[mb] = 0.f;
     bi[mb] = 0x7fffffff;
@@ -667,7 +668,7 @@ __global__ __launch_bounds__(256, SampleTile::PC) void k_lmhead_sample_lds(DecGe
           const float z = acc[nb][mb][r] * sc;
           zt[r] = ctl.greedy ? z : z * ctl.inv_temp;
         }
-        lse_push4(lse[mb], zt[0], zt[1], zt[2], zt[3]);
+        lse2_push4(lse2[mb], zt[0], zt[1], zt[2], zt[3]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float y = ctl.greedy ? zt[r] : zt[r] + gumbel_from_bits(rr[r]);
@@ -682,17 +683,18 @@ __global__ __launch_bounds__(256, SampleTile::PC) void k_lmhead_sample_lds(DecGe
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     const int m = (MB * wm + mb) * 16 + col;
+    Lse lse = lse_of(lse2[mb]);
 #pragma unroll
     for (int o = 16; o <= 32; o <<= 1) {
-      const Lse ol = {__shfl_xor(lse[mb].m, o, 64), __shfl_xor(lse[mb].s, o, 64)};
+      const Lse ol = {__shfl_xor(lse.m, o, 64), __shfl_xor(lse.s, o, 64)};
       const float oy = __shfl_xor(by[mb], o, 64), oz = __shfl_xor(bz[mb], o, 64);
       const int oi = __shfl_xor(bi[mb], o, 64);
-      lse[mb] = lse_merge(lse[mb], ol);
+      lse = lse_merge(lse, ol);
       if (oy > by[mb] || (oy == by[mb] && oi < bi[mb])) { by[mb] = oy; bi[mb] = oi; bz[mb] = oz; }
     }
     if (lane < 16 && m < a.M) {
       DecSamplePartial* p = reinterpret_cast<DecSamplePartial*>(a.out_f32) + (size_t)m * (2 * gridDim.x) + 2 * blockIdx.x + wn;
-      p->m = lse[mb].m; p->s = lse[mb].s; p->y = by[mb]; p->idx = bi[mb]; p->zt = bz[mb];
+      p->m = lse.m; p->s = lse.s; p->y = by[mb]; p->idx = bi[mb]; p->zt = bz[mb];
     }
   }
 }
