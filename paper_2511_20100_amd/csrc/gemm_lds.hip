@@ -240,8 +240,9 @@ __device__ __forceinline__ void store_f32(v4f (&acc)[T::NB][T::MB], float* out, 
 }
 
 // silu(gate) * up -> tiled fp16 operand; weight row tiles alternate gate / up.  The values are packed without a clamp and
-// the packed pairs are tested for an exponent of all ones (an infinity or a NaN: the value did not fit) with three
-// integer instructions per pair; only if one is found the block is packed again with the clamp, and the flag raised.
+// the packed pairs are tested with three integer instructions per pair for a magnitude of 0x7bff or more: an infinity, a NaN,
+// or 65504, which magnitudes up to 65520 round to.  Only if one is found the block is packed again with the clamp, and the
+// values themselves decide on the flag.
 template <class T>
 __device__ __forceinline__ void store_swiglu(v4f (&acc)[T::NB][T::MB], const LargeArgs& a, int nt0, int mt0, int lane) {
   constexpr int NB = T::NB, MB = T::MB;
@@ -263,7 +264,7 @@ __device__ __forceinline__ void store_swiglu(v4f (&acc)[T::NB][T::MB], const Lar
     } else {
       pk.x = pack_h16x2_inrange(v[0], v[1]);
       pk.y = pack_h16x2_inrange(v[2], v[3]);
-      bad |= (((pk.x & 0x7fff7fffu) + 0x04000400u) | ((pk.y & 0x7fff7fffu) + 0x04000400u)) & 0x80008000u;
+      bad |= (((pk.x & 0x7fff7fffu) + 0x04010401u) | ((pk.y & 0x7fff7fffu) + 0x04010401u)) & 0x80008000u;
     }
     *reinterpret_cast<uint2*>(a.out_bf16 + act_off(m, (nt >> 1) * 16 + rq, Mpad)) = pk;
   };
