@@ -308,9 +308,9 @@ const char* mtmc_data_error_string(int bits);
  *   MTMC_OPT_HIP_GRAPH (default 1): mtmc_rollout captures one decode step into a HIP graph and
  *   replays it for every token (MTMC_F32: calls of at least 8 new tokens).  Results do not depend on it (same kernels
  *   in the same order).
- *   Instantiated graphs are cached inside `w`, keyed by workspace address and the call's shape; replacing
- *   a cached graph (more than 8 are never kept) synchronises the device once.  When `stream` is itself being captured the steps
- *   are launched directly.
+ *   Instantiated graphs are cached inside `w`, keyed by workspace address and the call's shape, the 8 used last;
+ *   one that makes room is destroyed once the calls that launched it have ended (a call waits for that only when 8 such
+ *   graphs are still at work).  When `stream` is itself being captured the steps are launched directly.
  *   MTMC_OPT_GEMM_LDS_MIN_BLOCKS (default 32, value >= 1): prefill / scoring GEMMs (MTMC_BF16)
  *   whose output has at least this many 256 x 256 blocks run in the LDS-staged kernels (which choose
  *   their own block size, 128 x 64 to 256 x 256, by the call's sizes), smaller ones in the direct

@@ -221,10 +221,30 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
 int bf16_score(const mtmc_weights* w, const ScorePlan& p, const ScoreArgs& a, hipStream_t st);
 int f32_score_actions(const mtmc_weights* w, const ActionPlan& p, const ActionArgs& a, hipStream_t st);
 int bf16_score_actions(const mtmc_weights* w, const ActionPlan& p, const ActionArgs& a, hipStream_t st);
-// Returns in *out the instantiated graph of one decode step for this workspace and shape, capturing it if it is not cached
-// (nullptr when graphs are off or `st` is already capturing: launch the step directly).
+// A decode-step graph of the handle's cache, held while its launches are enqueued: until it is let go (at the end of the
+// scope, or when another graph takes its place) the cache does not destroy it, whatever other threads bring.
+class StepGraph {
+ public:
+  StepGraph() = default;
+  StepGraph(const StepGraph&) = delete;
+  StepGraph& operator=(const StepGraph&) = delete;
+  ~StepGraph() { reset(); }
+  explicit operator bool() const { return entry_ != nullptr; }
+  hipError_t launch(hipStream_t st);
+  void reset();
+
+ private:
+  friend int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st,
+                          const std::function<void(hipStream_t)>& step, StepGraph* out);
+  GraphCache* cache_ = nullptr;
+  void* entry_ = nullptr;  // of the cache
+  hipStream_t st_ = nullptr;
+  bool launched_ = false;
+};
+// Lets *out hold the instantiated graph of one decode step for this workspace and shape, capturing it if it is not cached
+// (none when graphs are off or `st` is already capturing: launch the step directly).
 int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, const std::function<void(hipStream_t)>& step,
-                 hipGraphExec_t* out);
+                 StepGraph* out);
 void destroy_graph_cache(mtmc_weights* w);
 int kernel_timer_set(mtmc_weights* w, int cls, int every);
 int kernel_timer_read(mtmc_weights* w, hipStream_t st, double* total_ms, int64_t* launches, double* empty_pair_ms);

@@ -307,11 +307,11 @@ int f32_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts,
   sample(st);
   // a dozen small launches per step: replayed as a graph they follow each other without the host (capturing one takes
   // about as long as a few steps launched one by one)
-  hipGraphExec_t exec = nullptr;
+  StepGraph graph;
   if (p.max_new >= 8)
-    if (int rc = decode_graph(w, p, st, decode_step, &exec)) return rc;
+    if (int rc = decode_graph(w, p, st, decode_step, &graph)) return rc;
   for (int i = 1; i < p.max_new; ++i) {
-    if (exec) MTMC_HIP_CHECK(hipGraphLaunch(exec, st));
+    if (graph) MTMC_HIP_CHECK(graph.launch(st));
     else decode_step(st);
   }
   return MTMC_OK;

@@ -8,22 +8,49 @@
 #include "bf16_kernels.h"
 #include "engine.h"
 #include "kernels.h"
+#include "lease_cache.h"
 
 namespace mtmc {
 
 // Instantiated decode-step graphs.  A graph bakes in the workspace pointers and the group
 // shape; everything that changes between calls (seed, temperature, output pointers, step
 // counter) lives in device memory that the kernels read.
+struct StepKey {
+  // every pointer and split factor a captured launch holds follows from the workspace base and the shape of the
+  // WHOLE call (the plan), plus the rows of the group the step belongs to
+  const void* workspace;
+  int total_prompts, B, prompt_len, n_samples, max_new, ragged;
+  bool operator==(const StepKey& o) const {
+    return workspace == o.workspace && total_prompts == o.total_prompts && B == o.B && prompt_len == o.prompt_len &&
+           n_samples == o.n_samples && max_new == o.max_new && ragged == o.ragged;
+  }
+};
+struct StepExec {
+  hipGraphExec_t exec = nullptr;
+  // recorded behind the last launch of whoever let the graph go last.  One event is enough for all streams: every launch
+  // of a graph writes one workspace, so its callers order them.  It only tells that the work has ended, so it fences nothing
+  // (with the default event a call of the tiny fp32 shape took 8 us longer, of 2260; so made, 0 to 8).
+  hipEvent_t done = nullptr;
+  bool recorded = false;
+  StepExec(hipGraphExec_t x, hipEvent_t e) : exec(x), done(e) {}
+  StepExec(StepExec&& o) noexcept : exec(o.exec), done(o.done), recorded(o.recorded) { o.exec = nullptr; o.done = nullptr; }
+  ~StepExec() {
+    if (exec) (void)hipGraphExecDestroy(exec);
+    if (done) (void)hipEventDestroy(done);
+  }
+  bool idle() {
+    if (!recorded) return true;
+    if (hipEventQuery(done) != hipErrorNotReady) return true;
+    (void)hipGetLastError();
+    return false;
+  }
+  void wait() {
+    if (recorded) (void)hipEventSynchronize(done);
+  }
+};
 struct GraphCache {
-  struct Entry {
-    // every pointer and split factor a captured launch holds follows from the workspace base and the shape of the
-    // WHOLE call (the plan), plus the rows of the group the step belongs to
-    const void* workspace;
-    int total_prompts, B, prompt_len, n_samples, max_new, ragged;
-    hipGraphExec_t exec;
-  };
   std::mutex mu;
-  std::vector<Entry> entries;
+  LeaseCache<StepKey, StepExec> steps{8};
   hipStream_t capture_stream = nullptr;  // never runs work: launches on it are only recorded
   // kernel timer (diagnostics): event pairs recorded around one class of decode kernel
   int timer_class = 0, timer_every = 0;
@@ -76,7 +103,6 @@ struct KernelTimer {
 
 void destroy_graph_cache(mtmc_weights* w) {
   if (!w->graphs) return;
-  for (auto& e : w->graphs->entries) (void)hipGraphExecDestroy(e.exec);
   if (w->graphs->capture_stream) (void)hipStreamDestroy(w->graphs->capture_stream);
   for (hipEvent_t e : w->graphs->events) (void)hipEventDestroy(e);
   for (hipEvent_t e : w->graphs->empty_events) (void)hipEventDestroy(e);
@@ -493,11 +519,31 @@ void decode_layers(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, K
 
 }  // namespace
 
-// Returns in *out the instantiated graph of one decode step for this workspace and shape, capturing
-// it on a private stream if it is not cached (or nullptr when graphs are off or `st` is already capturing).
+using StepEntry = LeaseCache<StepKey, StepExec>::Entry;
+
+hipError_t StepGraph::launch(hipStream_t st) {
+  st_ = st;
+  launched_ = true;
+  return hipGraphLaunch(((StepEntry*)entry_)->item.exec, st);
+}
+
+void StepGraph::reset() {
+  if (!entry_) return;
+  std::lock_guard<std::mutex> lock(cache_->mu);
+  StepEntry* e = (StepEntry*)entry_;
+  if (launched_) {
+    if (hipEventRecord(e->item.done, st_) == hipSuccess) e->item.recorded = true;
+    else (void)hipStreamSynchronize(st_);
+  }
+  cache_->steps.release(e);
+  entry_ = nullptr;
+  launched_ = false;
+}
+
+// A new graph is captured on a private stream.
 int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, const std::function<void(hipStream_t)>& step,
-                 hipGraphExec_t* out) {
-  *out = nullptr;
+                 StepGraph* out) {
+  out->reset();
   if (!w->opt_hip_graph) return MTMC_OK;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
@@ -513,18 +559,10 @@ int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, c
       return MTMC_EHIP;
     }
   }
-  for (auto& e : gc.entries)
-    if (e.workspace == (const void*)gp.page_table && e.total_prompts == gp.total_prompts && e.B == gp.B &&
-        e.prompt_len == gp.prompt_len && e.n_samples == gp.n_samples && e.max_new == gp.max_new &&
-        e.ragged == gp.ragged) {
-      *out = e.exec;
-      return MTMC_OK;
-    }
-  if (gc.entries.size() >= 8) {  // evict the oldest; it may still be queued, on this stream or on another caller's
-    MTMC_HIP_CHECK(hipDeviceSynchronize());
-    (void)hipGraphExecDestroy(gc.entries.front().exec);
-    gc.entries.erase(gc.entries.begin());
-  }
+  const StepKey key{(const void*)gp.page_table, gp.total_prompts, gp.B, gp.prompt_len, gp.n_samples, gp.max_new, gp.ragged};
+  out->cache_ = &gc;
+  out->entry_ = gc.steps.acquire(key);
+  if (out->entry_) return MTMC_OK;
   hipGraph_t graph = nullptr;
   MTMC_HIP_CHECK(hipStreamBeginCapture(gc.capture_stream, hipStreamCaptureModeThreadLocal));
   step(gc.capture_stream);
@@ -536,9 +574,9 @@ int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, c
     set_error(std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
     return MTMC_EHIP;
   }
-  gc.entries.push_back({(const void*)gp.page_table, gp.total_prompts, gp.B, gp.prompt_len, gp.n_samples, gp.max_new,
-                        gp.ragged, exec});
-  *out = exec;
+  StepExec item(exec, nullptr);
+  MTMC_HIP_CHECK(hipEventCreateWithFlags(&item.done, hipEventDisableTiming | hipEventDisableSystemFence));
+  out->entry_ = gc.steps.insert(key, std::move(item));
   return MTMC_OK;
 }
 
@@ -655,8 +693,8 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   std::lock_guard<std::mutex> poll_lock(gc.poll_mu);
   if (!gc.host_slots) MTMC_HIP_CHECK(hipHostMalloc((void**)&gc.host_slots, 256 * sizeof(int), hipHostMallocDefault));
   const int* live = gc.host_slots;
-  hipGraphExec_t exec = nullptr;
-  if (int rc = decode_graph(w, cur, st, decode_step, &exec)) return rc;
+  StepGraph graph;
+  if (int rc = decode_graph(w, cur, st, decode_step, &graph)) return rc;
 
   std::vector<int> slot_region(B), regions(p.n_regions);  // slot_region: the region a slot's sequence reads
   for (int s = 0; s < B; ++s) slot_region[s] = s / ns;
@@ -669,7 +707,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   std::vector<int> free_slots(B);
   for (;;) {
     for (int j = 0; j < period; ++j) {
-      if (exec) MTMC_HIP_CHECK(hipGraphLaunch(exec, st));
+      if (graph) MTMC_HIP_CHECK(graph.launch(st));
       else decode_step(st);
     }
     steps += period;
@@ -746,7 +784,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
       cc.row_step0 = p.row_step0_c;
       bf16::set_sample_ctl(d_ctl, cc, st);
       bf16::embed_slots(p.slot_row_c, p.cur_ids, slots, embed_args(cur), st);
-      if (int rc = decode_graph(w, cur, st, decode_step, &exec)) return rc;
+      if (int rc = decode_graph(w, cur, st, decode_step, &graph)) return rc;
     }
   }
   return MTMC_OK;
@@ -880,14 +918,14 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
       RolloutPlan cur = gp;
       KvPool cur_pool = pool;
       auto step_cur = [&](hipStream_t s) { decode_step_in(s, nullptr, cur, cur_pool); };
-      hipGraphExec_t exec = nullptr;
-      if (int rc = decode_graph(w, cur, st, step_cur, &exec)) return rc;
+      StepGraph graph;
+      if (int rc = decode_graph(w, cur, st, step_cur, &graph)) return rc;
       int i = 1, slot = 0;
       bool have_prev = false;
       while (i < p.max_new) {
         const int n = std::min(poll, p.max_new - i);
         for (int j = 0; j < n; ++j) {
-          if (exec) MTMC_HIP_CHECK(hipGraphLaunch(exec, st));
+          if (graph) MTMC_HIP_CHECK(graph.launch(st));
           else step_cur(st);
         }
         i += n;
@@ -911,21 +949,21 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
             ctl.slot_row = p.slot_row;
             bf16::set_sample_ctl((bf16::SampleCtl*)p.ctl, ctl, st);
             bf16::embed_slots(p.slot_row, p.cur_ids, slots, embed_args(cur), st);
-            if (int rc = decode_graph(w, cur, st, step_cur, &exec)) return rc;
+            if (int rc = decode_graph(w, cur, st, step_cur, &graph)) return rc;
           }
         }
         have_prev = true;
         slot ^= 1;
       }
     } else if (p.max_new > 1) {
-      hipGraphExec_t exec = nullptr;
-      if (int rc = decode_graph(w, gp, st, decode_step, &exec)) return rc;
+      StepGraph graph;
+      if (int rc = decode_graph(w, gp, st, decode_step, &graph)) return rc;
       GraphCache* gc = w->graphs;
       KernelTimer tm{gc, gc ? gc->timer_class : 0, st};
       const int every = gc ? gc->timer_every : 0;
       for (int i = 1; i < p.max_new; ++i) {
         if (tm.cls && every > 0 && i % every == 1 % every) decode_step_timed(st, &tm);  // launched directly, with events
-        else if (exec) MTMC_HIP_CHECK(hipGraphLaunch(exec, st));
+        else if (graph) MTMC_HIP_CHECK(graph.launch(st));
         else decode_step(st);
       }
     }
