@@ -1060,7 +1060,10 @@ __global__ __launch_bounds__(AW * 64) void k_attn_dec(AttnDecArgs a) {
 // form at many (sequence, kv head) pairs is that a CU holds one workgroup (199 registers): 768 pairs are three rounds of a
 // 10 us chain.  48 rows x 16 kv heads, 4 samples per prompt: 31.0 -> 22.4 us;
 // 128 rows x 4 kv heads of 7 query heads, 8 samples per prompt: 27.3 -> 20.9.
-constexpr int kOwnTab = 512;  // page-table entries of the sequences' own pages kept in LDS
+// Page-table entries of the sequences' own pages kept in LDS: all that AW sequences can have, so that the choice of the form
+// does not depend on how much of a context is shared, which the host does not know where prompts differ in length.  (16 KiB; a
+// CU holds one workgroup of the 128-dim form by its registers, two of the 64-dim form by registers and LDS alike.)
+constexpr int kOwnTab = AW * ATAB;
 template <int DHD>
 constexpr int kSharedLds = AW * 16 * (DHD + 1) * (int)sizeof(float);
 template <int DHD>
@@ -1216,20 +1219,20 @@ __global__ __launch_bounds__(AW * 64) void k_attn_dec_shared(AttnDecArgs a, int 
 
 template <int DHD>
 static void launch_shared(const AttnDecArgs& a, int B, int ns, hipStream_t st) {
-  static const bool configured = (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_dec_shared<DHD>),
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kSharedLds<DHD>), true);
+  static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_dec_shared<DHD>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kSharedLds<DHD>);
   (void)configured;
   k_attn_dec_shared<DHD><<<dim3(B / ns, a.Hkv), AW * 64, kSharedLds<DHD>, st>>>(a, ns);
 }
 // Sequences per workgroup of the shared form, or 1: more (sequence, kv head) pairs than CUs, several samples per prompt that
-// advance together, and tables that fit.  The fewest that make the launch one round, as far as the 16 columns hold them.
+// advance together, and a context whose table fits.  The fewest that make the launch one round, as far as the 16 columns hold them.
 // Up to 256 pairs the plain form is one round already, and the shared form would leave CUs idle.
 static int shared_sequences(const AttnDecArgs& a, int B) {
   const int G = a.Hq / a.Hkv, most = std::min(16 / G, AW);
   if (a.n_chunks != 1 || a.row_step0 || a.share < 2 || B % a.share != 0 || B * a.Hkv <= 256 || a.pool.max_pages > ATAB) return 1;
   int ns = 1;
   for (int n = 2; n <= most && ns * 256 < B * a.Hkv; ++n)
-    if (a.share % n == 0 && n * (a.pool.max_pages - a.shared_pages) <= kOwnTab) ns = n;
+    if (a.share % n == 0) ns = n;
   return ns;
 }
 

@@ -88,3 +88,36 @@ def test_what_a_workspace_held_before_does_not_matter(lib, cfg):
             assert all(torch.equal(a, b) for a, b in zip(*got))
     finally:
         lib.mtmc_weights_destroy(handle)
+
+
+@pytest.mark.parametrize("name,cfg,n_prompts,plen,n_samples,max_new", [
+    ("mha8", MHA8, 5, 4200, 8, 20),                  # 264 pages: a table of one sequence's own pages for each of two sequences
+    ("g7", G7, 14, 1100, 8, 200),
+    ("g2", G2, 4, 2300, 9, 12),
+], ids=lambda v: v if isinstance(v, str) else None)
+def test_equal_lengths_are_mtmc_rollout(lib, name, cfg, n_prompts, plen, n_samples, max_new):
+    """Whether a prompt's length is known on the host or on the device only, the same sequences sit in a workgroup."""
+    import torch
+    w = inputs.make_weights(cfg, seed=0, std=0.05, gain_std=0.1)
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 4352), w.blob())
+    try:
+        prompts = torch.from_numpy(inputs.make_prompts(n_prompts, plen, cfg.vocab, seed=2)).cuda()
+        lens = torch.full((n_prompts,), plen, dtype=torch.int32, device="cuda")
+        a = lib.mtmc_rollout(handle, prompts, n_samples, max_new, 1.0, 1)
+        b = lib.mtmc_rollout_ragged(handle, prompts, lens, n_samples, max_new, 1.0, 1)
+        lib.mtmc_poll_errors(handle)
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
+def test_short_prompts_beside_a_long_one(lib):
+    """Nearly all pages of the short ones' page-table rows are their own: the table of a workgroup has several hundred entries."""
+    w = inputs.make_weights(MHA8, seed=0, std=0.05, gain_std=0.1)
+    handle = lib.mtmc_weights_create(lib.make_config(MHA8, 4352), w.blob())
+    try:
+        lens = np.array([1, 40, 2900, 333, 16], dtype=np.int32)
+        prompts = inputs.make_prompts(len(lens), 4200, MHA8.vocab, seed=2)
+        check_ragged_by_replay(handle, w, prompts, lens, 8, 40, 1.0, 1, stop_id=-1, max_positions=4352, label="short and long")
+    finally:
+        lib.mtmc_weights_destroy(handle)
