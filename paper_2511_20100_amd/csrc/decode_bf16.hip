@@ -15,9 +15,8 @@
 // its update (a well-scaled fp16 value), together with the sum of squares of its 16 new columns.
 // The consumer sums those per-tile squares in a fixed order to get r_new and multiplies its
 // fp32 accumulators by r_new / r_old: W (h g r_new) = (W (h g r_old)) r_new / r_old.
-#include <algorithm>
-
 #include "attention_core.h"
+#include "attention_plan.h"
 #include "bf16_kernels.h"
 #include "device_utils.h"
 #include "frag.h"
@@ -1224,16 +1223,10 @@ static void launch_shared(const AttnDecArgs& a, int B, int ns, hipStream_t st) {
   (void)configured;
   k_attn_dec_shared<DHD><<<dim3(B / ns, a.Hkv), AW * 64, kSharedLds<DHD>, st>>>(a, ns);
 }
-// Sequences per workgroup of the shared form, or 1: more (sequence, kv head) pairs than CUs, several samples per prompt that
-// advance together, and a context whose table fits.  The fewest that make the launch one round, as far as the 16 columns hold them.
-// Up to 256 pairs the plain form is one round already, and the shared form would leave CUs idle.
+// Sequences per workgroup (1: the plain form): where they advance together and a context's table fits.
 static int shared_sequences(const AttnDecArgs& a, int B) {
-  const int G = a.Hq / a.Hkv, most = std::min(16 / G, AW);
-  if (a.n_chunks != 1 || a.row_step0 || a.share < 2 || B % a.share != 0 || B * a.Hkv <= 256 || a.pool.max_pages > ATAB) return 1;
-  int ns = 1;
-  for (int n = 2; n <= most && ns * 256 < B * a.Hkv; ++n)
-    if (a.share % n == 0) ns = n;
-  return ns;
+  if (a.n_chunks != 1 || a.row_step0 || a.pool.max_pages > ATAB) return 1;
+  return attention_sequences(a.pool.head_dim, a.Hq, a.Hkv, B, a.share, a.prompt_len, a.max_new);
 }
 
 // ---------------------------------------------------------------- packing live rows into the leading slots

@@ -482,6 +482,7 @@ void decode_layers(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, K
     at.qkv = p.qkv; at.cos = w->rope_cos; at.sin = w->rope_sin; at.Hq = D.Hq; at.Hkv = D.Hkv; at.layer = l;
     at.pos_base = pos_base; at.row_pos = p.ragged ? p.row_pos : nullptr; at.d_step = p.d_step; at.pool = pool; at.chunk_pages = p.chunk_pages; at.split_at_prompt = p.split_at_prompt;
     at.n_chunks = p.n_chunks; at.m_tiles = bt; at.share = p.n_samples;
+    at.prompt_len = p.prompt_len; at.max_new = p.max_new;
     at.row_step0 = p.ragged == 3 ? p.row_step0 : nullptr; at.max_step = p.max_new - 1;
     at.o = (h16_t*)p.o_chunks; at.o_chunk_stride = (size_t)D.nq * bt * 16; at.ml = p.attn_ml; at.err_flag = w->err_flag;
     mark(MTMC_KERNEL_ATTENTION);

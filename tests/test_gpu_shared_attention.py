@@ -14,6 +14,8 @@ MHA8 = inputs.ModelConfig(1, 256, 8, 8, 64, 512, 1040, dtype="bf16")
 G2 = inputs.ModelConfig(1, 256, 16, 8, 128, 512, 1040, dtype="bf16")
 G4 = inputs.ModelConfig(1, 256, 16, 4, 64, 512, 1040, dtype="bf16")
 G7 = inputs.ModelConfig(1, 256, 28, 4, 128, 512, 1040, dtype="bf16")
+G4W = inputs.ModelConfig(1, 256, 32, 8, 64, 512, 1040, dtype="bf16")
+MHA16 = inputs.ModelConfig(1, 256, 16, 16, 128, 512, 1040, dtype="bf16")
 
 
 @pytest.fixture(scope="module")
@@ -23,8 +25,14 @@ def lib():
 
 
 @pytest.mark.parametrize("name,cfg,n_prompts,plen,n_samples,max_new", [
+    # the first two are one round of the plain form
     ("mha-no-whole-page", MHA8, 5, 9, 8, 20),        # 320 pairs; all pages are the sequences' own, 2 of them at the end
     ("mha-odd-pages", MHA8, 5, 55, 8, 12),           # 3 whole pages: two shared, the third taken with the own ones
+    ("mha-no-whole-page-four", MHA8, 16, 9, 8, 20),  # the same, four samples per workgroup
+    ("mha-odd-pages-four", MHA8, 16, 55, 8, 12),
+    ("g4-four", G4W, 9, 70, 12, 40),
+    ("mha-eight", MHA16, 16, 21, 8, 9),              # one sequence per wavefront to append for
+    ("mha-fifteen-columns", MHA16, 24, 100, 5, 30),
     ("mha-long", MHA8, 8, 330, 6, 6),                # 20 whole pages; two of the six samples per workgroup
     ("g2", G2, 4, 40, 12, 10),
     ("g4", G4, 12, 70, 8, 8),
@@ -86,6 +94,23 @@ def test_what_a_workspace_held_before_does_not_matter(lib, cfg):
                 got.append([t.clone() for t in call(ws)])
                 lib.mtmc_poll_errors(handle)
             assert all(torch.equal(a, b) for a, b in zip(*got))
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
+@pytest.mark.parametrize("poll", [2, 4])
+def test_rows_packed_after_steps_together(lib, poll):
+    """Samples of a prompt sit in one workgroup until the first look that frees a tile; from then on every row is alone."""
+    cfg = MHA8.with_(vocab=48)
+    w = inputs.make_weights(cfg, seed=0, std=0.05, gain_std=0.1)
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 512), w.blob())
+    try:
+        lib.mtmc_set_option(handle, lib.MTMC_OPT_STOP_POLL_STEPS, poll)
+        lens = (3 + np.arange(15) * 11 % 90).astype(np.int32)
+        prompts = inputs.make_prompts(len(lens), int(lens.max()), cfg.vocab, seed=2)
+        rep = check_ragged_by_replay(handle, w, prompts, lens, 8, 40, 1.0, 1, stop_id=3, max_positions=512, label="packed")
+        ends = np.sort(rep["lens"])
+        assert (ends < 40).sum() >= 32 and ends[-1] > 4 * poll  # tiles were freed while rows still ran
     finally:
         lib.mtmc_weights_destroy(handle)
 
