@@ -1225,7 +1225,7 @@ static void launch_shared(const AttnDecArgs& a, int B, int ns, hipStream_t st) {
 }
 // Sequences per workgroup (1: the plain form): where they advance together and a context's table fits.
 static int shared_sequences(const AttnDecArgs& a, int B) {
-  if (a.n_chunks != 1 || a.row_step0 || a.pool.max_pages > ATAB) return 1;
+  if (a.samples_alone || a.n_chunks != 1 || a.row_step0 || a.pool.max_pages > ATAB) return 1;
   return attention_sequences(a.pool.head_dim, a.Hq, a.Hkv, B, a.share, a.prompt_len, a.max_new);
 }
 

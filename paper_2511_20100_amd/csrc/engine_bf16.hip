@@ -20,9 +20,10 @@ struct StepKey {
   // WHOLE call (the plan), plus the rows of the group the step belongs to
   const void* workspace;
   int total_prompts, B, prompt_len, n_samples, max_new, ragged;
+  bool samples_alone;
   bool operator==(const StepKey& o) const {
     return workspace == o.workspace && total_prompts == o.total_prompts && B == o.B && prompt_len == o.prompt_len &&
-           n_samples == o.n_samples && max_new == o.max_new && ragged == o.ragged;
+           n_samples == o.n_samples && max_new == o.max_new && ragged == o.ragged && samples_alone == o.samples_alone;
   }
 };
 struct StepExec {
@@ -482,7 +483,7 @@ void decode_layers(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, K
     at.qkv = p.qkv; at.cos = w->rope_cos; at.sin = w->rope_sin; at.Hq = D.Hq; at.Hkv = D.Hkv; at.layer = l;
     at.pos_base = pos_base; at.row_pos = p.ragged ? p.row_pos : nullptr; at.d_step = p.d_step; at.pool = pool; at.chunk_pages = p.chunk_pages; at.split_at_prompt = p.split_at_prompt;
     at.n_chunks = p.n_chunks; at.m_tiles = bt; at.share = p.n_samples;
-    at.prompt_len = p.prompt_len; at.max_new = p.max_new;
+    at.prompt_len = p.prompt_len; at.max_new = p.max_new; at.samples_alone = p.samples_alone;
     at.row_step0 = p.ragged == 3 ? p.row_step0 : nullptr; at.max_step = p.max_new - 1;
     at.o = (h16_t*)p.o_chunks; at.o_chunk_stride = (size_t)D.nq * bt * 16; at.ml = p.attn_ml; at.err_flag = w->err_flag;
     mark(MTMC_KERNEL_ATTENTION);
@@ -559,7 +560,8 @@ int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, c
       return MTMC_EHIP;
     }
   }
-  const StepKey key{(const void*)gp.page_table, gp.total_prompts, gp.B, gp.prompt_len, gp.n_samples, gp.max_new, gp.ragged};
+  const StepKey key{(const void*)gp.page_table, gp.total_prompts, gp.B, gp.prompt_len, gp.n_samples, gp.max_new, gp.ragged,
+                    gp.samples_alone};
   out->cache_ = &gc;
   out->entry_ = gc.steps.acquire(key);
   if (out->entry_) return MTMC_OK;
@@ -817,6 +819,8 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     gp.bt = tiles16(gp.B);
     gp.shared_total = np_group * p.nf_max;
     const bool ragged = sa.prompt_lens != nullptr;
+    // a call whose prompts could join a running batch (where every sequence is alone) gives the same bits batch after batch
+    gp.samples_alone = ragged && sa.stop_id >= 0 && p.total_prompts > p.n_prompts;
     const int* glens = ragged ? sa.prompt_lens + g0 : nullptr;
     int* g_out_lens = ragged ? sa.out_lens + (size_t)g0 * p.n_samples : nullptr;
     const int* gprompts = prompts + (size_t)g0 * p.prompt_len;

@@ -115,6 +115,39 @@ def test_rows_packed_after_steps_together(lib, poll):
         lib.mtmc_weights_destroy(handle)
 
 
+@pytest.mark.parametrize("cfg", [MHA8, G7], ids=["mha8", "g7"])
+def test_first_batch_of_joining_prompts(lib, cfg):
+    """320 sequences through 128 slots: until the batch is packed, the sequences of the first batch get the same bits whether
+    the other prompts join it or follow batch after batch, also at sizes where a batch's samples are taken together."""
+    import torch
+    n_prompts, n_samples, max_new, period = 40, 8, 48, 4
+    cfg = cfg.with_(vocab=48)
+    w = inputs.make_weights(cfg, seed=0, std=0.05, gain_std=0.1)
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 512), w.blob())
+    try:
+        lens = torch.from_numpy((30 + np.arange(n_prompts) * 7 % 90).astype(np.int32)).cuda()
+        prompts = torch.from_numpy(inputs.make_prompts(n_prompts, int(lens.max()), cfg.vocab, seed=2)).cuda()
+        run = lambda stop: [t.cpu() for t in lib.mtmc_rollout_ragged(handle, prompts, lens, n_samples, max_new, 1.0, 1, stop_id=stop)]
+        lib.mtmc_set_option(handle, lib.MTMC_OPT_STOP_POLL_STEPS, period)
+        joined = run(3)
+        lib.mtmc_set_option(handle, lib.MTMC_OPT_ADMIT_PROMPTS, 0)
+        lib.mtmc_set_option(handle, lib.MTMC_OPT_STOP_POLL_STEPS, 0)
+        lib.mtmc_set_option(handle, lib.MTMC_OPT_HIP_GRAPH, 0)
+        free = run(-1)   # without a stop token nothing can join, and samples are taken together
+        lib.mtmc_set_option(handle, lib.MTMC_OPT_HIP_GRAPH, 1)
+        run(-1)
+        static = run(3)  # after a graph of that shape without a stop token
+        lib.mtmc_poll_errors(handle)
+        # the looks are `period` steps apart, one takes in at most 16 prompts, and the batch is packed one look after the last
+        first, steps = 128, period * (-(-(n_prompts - 16) // 16) + 1)
+        assert torch.equal(static[0][:first, :steps], joined[0][:first, :steps])
+        assert torch.equal(static[1][:first, :steps], joined[1][:first, :steps])
+        same = (free[0][:, :4] == static[0][:, :4]).all(dim=1)
+        assert (free[1] - static[1])[same][:, :4].abs().max() <= 2 * LOGP_TOL_BF16 and same.float().mean() > 0.5
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
 @pytest.mark.parametrize("name,cfg,n_prompts,plen,n_samples,max_new", [
     ("mha8", MHA8, 5, 4200, 8, 20),                  # 264 pages: a table of one sequence's own pages for each of two sequences
     ("g7", G7, 14, 1100, 8, 200),
