@@ -226,25 +226,26 @@ struct F32Acts {
 };
 
 // All residual blocks over T tokens (h in, h out).  `layer_stride` is 1 when every layer has
-// its own pages (rollout) and 0 when one layer's worth of pages is reused (scoring).
+// its own pages (rollout) and 0 when one layer's worth of pages is reused (scoring).  form_rows: the rows of the call that
+// these tokens are a part of, if it has more.
 void f32_layers(const mtmc_weights* w, const F32Acts& A, int T, TokMap map, KvPool pool,
-                int layer_stride, hipStream_t st) {
+                int layer_stride, hipStream_t st, int form_rows = 0) {
   const mtmc_config& c = w->cfg;
   const int d = c.d_model, Hq = c.n_q_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.d_ffn;
   const int nq = Hq * hd, nqkv = (Hq + 2 * Hkv) * hd;
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerWeights& L = w->layers[l];
     const int kvl = l * layer_stride;
-    f32::norm_gemm(A.qkv, nqkv, A.h, L.attn_norm, c.rms_eps, A.x, (const float*)L.wqkv, T, nqkv, d, st);
+    f32::norm_gemm(A.qkv, nqkv, A.h, L.attn_norm, c.rms_eps, A.x, (const float*)L.wqkv, T, nqkv, d, st, form_rows);
     if (map.S == 1 && map.d_step) {  // a decode step
       f32::attention_dec(A.o, A.qkv, T, Hq, Hkv, hd, w->rope_cos, w->rope_sin, map, pool, kvl, st);
     } else {
       f32::rope_kv_write(A.qkv, T, Hq, Hkv, hd, w->rope_cos, w->rope_sin, map, pool, kvl, st);
       f32::attention(A.o, A.qkv, T, Hq, Hkv, hd, map, pool, kvl, st);
     }
-    f32::gemm(A.h, d, A.o, nq, (const float*)L.wo, T, d, nq, true, st);
-    f32::norm_swiglu(A.a, A.h, L.ffn_norm, c.rms_eps, A.x, A.gu, (const float*)L.wgu, T, F, d, st);
-    f32::gemm(A.h, d, A.a, F, (const float*)L.wdown, T, d, F, true, st);
+    f32::gemm(A.h, d, A.o, nq, (const float*)L.wo, T, d, nq, true, st, form_rows);
+    f32::norm_swiglu(A.a, A.h, L.ffn_norm, c.rms_eps, A.x, A.gu, (const float*)L.wgu, T, F, d, st, form_rows);
+    f32::gemm(A.h, d, A.a, F, (const float*)L.wdown, T, d, F, true, st, form_rows);
   }
 }
 }  // namespace
@@ -277,7 +278,7 @@ int f32_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts,
     chunk_pool.page_table = p.page_table + (size_t)p0 * p.n_samples * p.max_pages;
     TokMap map{S, p.n_samples, R, nullptr};
     f32::embed(A.h, prompts + (size_t)p0 * S, T, (const float*)w->embed, d, V, w->err_flag, st);
-    f32_layers(w, A, T, map, chunk_pool, 1, st);
+    f32_layers(w, A, T, map, chunk_pool, 1, st, np * p.prompt_len);
     if (ragged)
       launch_gather_last_rows(p.hB + (size_t)p0 * p.n_samples * d, A.h, d, np, p.n_samples, p.prompt_len,
                               sa.prompt_lens + p0, R, st);

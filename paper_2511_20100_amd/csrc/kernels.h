@@ -74,14 +74,16 @@ void embed(float* h, const int* ids, int T, const float* E, int d, int vocab, in
            hipStream_t st);
 void rmsnorm(float* x, const float* h, const float* gain, float eps, int T, int d, hipStream_t st);
 // C[M, N] (ldc) = or += A[M, K] (lda) * W[N, K]^T      (K % 16 == 0)
+// form_rows (here and below; 0: M) chooses between the forms for few and for many rows, which add up in different orders: a
+// call that evaluates only some of a longer one's rows passes the longer one's count and gets the same bits.
 void gemm(float* C, int ldc, const float* A, int lda, const float* W, int M, int N, int K,
-          bool accumulate, hipStream_t st);
+          bool accumulate, hipStream_t st, int form_rows = 0);
 // C[M, N] = norm(H[M, K]; gain) W[N, K]^T;  a[M, F] = silu(x Wg^T) * (x Wu^T) with x = norm(H; gain), W = [gate rows; up
 // rows].  x [M, K] and gu [M, 2 F] are scratch (large calls).
 void norm_gemm(float* C, int ldc, const float* H, const float* gain, float eps, float* x, const float* W, int M, int N,
-               int K, hipStream_t st);
+               int K, hipStream_t st, int form_rows = 0);
 void norm_swiglu(float* a, const float* H, const float* gain, float eps, float* x, float* gu, const float* W, int M, int F,
-                 int K, hipStream_t st);
+                 int K, hipStream_t st, int form_rows = 0);
 // qkv [T, (Hq + 2 Hkv) hd]: rotates q in place, writes rotated k and v into the pages.
 void rope_kv_write(float* qkv, int T, int Hq, int Hkv, int hd, const float* cos, const float* sin,
                    TokMap map, KvPool pool, int layer, hipStream_t st);

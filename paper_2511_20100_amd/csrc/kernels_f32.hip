@@ -420,7 +420,9 @@ __global__ __launch_bounds__(256) void k_gemm_rows(float* C, int ldc, const floa
   }
 }
 // The form for few rows reads W once per 8 rows, from the caches: it is taken while the 64x64 tile has fewer blocks than
-// half the CUs and the rows are few (128 rows x 512 columns x 256: 18 us in 16 tiles, 6 us here).
+// half the CUs and the rows are few.  128 rows x 512 columns x 256: 18 us in 16 tiles, 6 us here.  At the upper end, 512 rows,
+// whole scoring passes of two blocks took (tiles, and these forms where the rule gives them): d 256 308 -> 155 us, d 512 505 ->
+// 261, d 960 (where the wider products stay on tiles) 956 -> 614; at 1024 rows the tiles have their blocks.
 static bool few_rows(int M, int N) { return M <= 512 && (M + 63) / 64 * ((N + 63) / 64) < 128; }
 template <int MODE>
 static void launch_rows(float* C, int ldc, const float* A, int lda, const float* W, int M, int N, int K, const float* gain,
@@ -429,9 +431,9 @@ static void launch_rows(float* C, int ldc, const float* A, int lda, const float*
   k_gemm_rows<MODE><<<dim3((N + 4 * NO - 1) / (4 * NO), (M + 7) / 8), 256, 0, st>>>(C, ldc, A, lda, W, M, N, K, gain, eps);
 }
 void gemm(float* C, int ldc, const float* A, int lda, const float* W, int M, int N, int K,
-          bool accumulate, hipStream_t st) {
+          bool accumulate, hipStream_t st, int form_rows) {
   if (M == 0 || N == 0) return;
-  if (few_rows(M, N)) {
+  if (few_rows(std::max(M, form_rows), N)) {
     if (accumulate) launch_rows<ROWS_ADD>(C, ldc, A, lda, W, M, N, K, nullptr, 0.f, st);
     else launch_rows<0>(C, ldc, A, lda, W, M, N, K, nullptr, 0.f, st);
     return;
@@ -440,24 +442,24 @@ void gemm(float* C, int ldc, const float* A, int lda, const float* W, int M, int
                                                             accumulate ? 1 : 0);
 }
 void norm_gemm(float* C, int ldc, const float* H, const float* gain, float eps, float* x, const float* W, int M, int N,
-               int K, hipStream_t st) {
+               int K, hipStream_t st, int form_rows) {
   if (M == 0 || N == 0) return;
-  if (few_rows(M, N)) {
+  if (few_rows(std::max(M, form_rows), N)) {
     launch_rows<ROWS_NORM>(C, ldc, H, K, W, M, N, K, gain, eps, st);
     return;
   }
   rmsnorm(x, H, gain, eps, M, K, st);
-  gemm(C, ldc, x, K, W, M, N, K, false, st);
+  gemm(C, ldc, x, K, W, M, N, K, false, st, form_rows);
 }
 void norm_swiglu(float* a, const float* H, const float* gain, float eps, float* x, float* gu, const float* W, int M, int F,
-                 int K, hipStream_t st) {
+                 int K, hipStream_t st, int form_rows) {
   if (M == 0) return;
-  if (few_rows(M, 2 * F)) {
+  if (few_rows(std::max(M, form_rows), 2 * F)) {
     launch_rows<ROWS_NORM | ROWS_SWIGLU>(a, F, H, K, W, M, F, K, gain, eps, st);
     return;
   }
   rmsnorm(x, H, gain, eps, M, K, st);
-  gemm(gu, 2 * F, x, K, W, M, 2 * F, K, false, st);
+  gemm(gu, 2 * F, x, K, W, M, 2 * F, K, false, st, form_rows);
   swiglu(a, gu, M, F, st);
 }
 

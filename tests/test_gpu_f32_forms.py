@@ -58,3 +58,25 @@ def test_scoring(n_seqs, seq_len):
         assert np.abs(lp.cpu().numpy() - ref).max() <= LOGP_TOL_F32
     finally:
         mtmc.mtmc_weights_destroy(handle)
+
+
+@pytest.mark.parametrize("lens,plen,reuse", [((400, 391), 400, 384), ((120, 113), 120, 112), ((600, 599), 600, 256)])
+def test_a_cached_prefix_gives_the_bits_of_a_fresh_call(lens, plen, reuse):
+    """The products of the few rows left to evaluate add up as those of the whole prompts would: in the form for many rows
+    (800 and 1200 of them), and in the form for few."""
+    import torch
+    from paper_2511_20100_amd import mtmc
+    handle = mtmc.mtmc_weights_create(mtmc.make_config(G6, 704), inputs.make_weights(G6, seed=0, std=0.06, gain_std=0.1).blob())
+    try:
+        prompts = torch.from_numpy(inputs.make_prompts(2, plen, G6.vocab, seed=2)).cuda()
+        n = torch.tensor(lens, dtype=torch.int32, device="cuda")
+        before = torch.full_like(n, reuse)
+        size = mtmc.mtmc_rollout_ragged_workspace_bytes(handle, 2, plen, 2, 10)
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        mtmc.mtmc_rollout_ragged(handle, prompts, before, 2, 10, 1.0, 5, workspace=ws)
+        cached = mtmc.mtmc_rollout_ragged_cached(handle, prompts, n, 2, 10, 1.0, 1, reuse, ws)
+        fresh = mtmc.mtmc_rollout_ragged(handle, prompts, n, 2, 10, 1.0, 1, workspace=torch.empty_like(ws))
+        mtmc.mtmc_poll_errors(handle)
+        assert all(torch.equal(a, b) for a, b in zip(cached, fresh))
+    finally:
+        mtmc.mtmc_weights_destroy(handle)
