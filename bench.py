@@ -135,7 +135,7 @@ def cpu_baseline(weights, cfg, prompts, max_positions, score_only=False):
 
 def attainable_rates(torch, mtmc, dev):
     """What this GPU sustains, measured here: a plain streaming read of 2 GiB (GB/s) and a register-only loop of
-    fp16 32x32x16 matrix instructions on every SIMD, with the register tile of the scoring GEMM and pseudo-random
+    fp16 16x16x32 matrix instructions on every SIMD, with the register tile of the scoring GEMM and pseudo-random
     operands (TFLOP/s)."""
     stream = torch.cuda.current_stream()
     buf = torch.ones(2 << 30, dtype=torch.uint8, device=dev)
@@ -394,7 +394,7 @@ def main() -> int:
     read_gbs, mfma_tflops = attainable_rates(torch, mtmc, dev)
     hbm_attainable = {"value": read_gbs, "unit": "GB/s", "how": "plain streaming read of 2 GiB, measured in this run"}
     mfma_attainable = {"value": mfma_tflops, "unit": "TFLOP/s",
-                       "how": "register-only loop of fp16 32x32x16 matrix instructions on all SIMDs (4 x 4 accumulator blocks per "
+                       "how": "register-only loop of fp16 16x16x32 matrix instructions on all SIMDs (8 x 8 accumulator blocks per "
                               "wavefront, pseudo-random operands), measured in this run"}
     if k_launches > 0:
         k_us = 1e3 * k_ms / k_launches
