@@ -91,3 +91,64 @@ def test_rotary_epilogue_is_the_separate_kernels(lib, heads, kv_heads, head_dim,
     lib.mtmc_weights_destroy(handle)
     assert float((direct - lp).abs().max()) <= TOL
     assert float((short[0] - lp[-1, :seq_len // 2 - 1]).abs().max()) <= TOL
+
+
+# ---- the same bits.  The calls compared below take the same row norm (from 1024 rows on) and the same number of vocabulary
+# slices in the LM head (by the scored rows), and split no reduction, so that only what a test is about differs.  (Where the
+# reader of a split reduction adds up its slices, no other call runs the same sums in separate launches: the tests above
+# bound that form by the tolerance alone.)
+def test_scoring_has_the_same_bits_in_every_tile(lib, handle):
+    import torch
+    seqs = torch.from_numpy(inputs.make_sequences(30, 233, CFG.vocab, seed=4)).cuda()
+    _lds(lib, handle, True)
+    ref = lib.mtmc_score(handle, seqs, 100)           # 6990 tokens, 3990 scored rows
+    for n in (8, 9, 11, 14, 19, 25):                  # from 1864 tokens and 1064 rows
+        assert torch.equal(lib.mtmc_score(handle, seqs[:n].contiguous(), 100), ref[:n]), n
+    lib.mtmc_poll_errors(handle)
+
+
+# The samples of a prompt scored as whole sequences, and as candidates of the prompt (packed rows, whose projection is stored and
+# rotated by a kernel of its own): 10 880 tokens in one pass, 1196 (on the pages of every eighth row) and 1280 in two.
+@pytest.mark.parametrize("heads,kv_heads,head_dim", [(4, 4, 64), (6, 2, 64), (3, 1, 128), (2, 2, 128)])
+def test_rotary_epilogue_has_the_bits_of_the_separate_kernels(lib, heads, kv_heads, head_dim):
+    import torch
+    cfg = inputs.ModelConfig(2, heads * head_dim, heads, kv_heads, head_dim, 688, 1040, dtype="bf16")
+    n_states, state_len, n_actions, max_len = 4, 300, 8, 40
+    w = inputs.make_weights(cfg, seed=1, std=0.04, gain_std=0.1)
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 1280), w.blob())
+    try:
+        _lds(lib, handle, True)
+        states = torch.from_numpy(inputs.make_prompts(n_states, state_len, cfg.vocab, seed=5)).cuda()
+        actions, _ = inputs.make_actions(n_states, n_actions, max_len, cfg.vocab, 6, 0)
+        actions = torch.from_numpy(actions).cuda()
+        lens = torch.full((n_states, n_actions), max_len, dtype=torch.int32, device="cuda")
+        tok = lib.mtmc_score_actions(handle, states, actions, lens)[0]
+        whole = torch.cat([states[:, None].expand(-1, n_actions, -1), actions], dim=2).reshape(n_states * n_actions, -1).contiguous()
+        lp = lib.mtmc_score(handle, whole, state_len)[:, state_len - 1:].reshape(n_states, n_actions, max_len)
+        lib.mtmc_poll_errors(handle)
+        assert torch.equal(tok, lp)
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
+# the epilogue behind a cached prefix: positions that start at 48 and 256, pages of every n_samples-th row, prompts that end
+# inside a page, before and behind the last new token of the others
+@pytest.mark.parametrize("heads,kv_heads,head_dim", [(4, 4, 64), (3, 1, 128)])
+@pytest.mark.parametrize("reuse,max_len,n_samples", [(48, 400, 4), (256, 517, 2)])
+def test_rotary_epilogue_behind_a_cached_prefix(lib, heads, kv_heads, head_dim, reuse, max_len, n_samples):
+    import torch
+    cfg = inputs.ModelConfig(2, heads * head_dim, heads, kv_heads, head_dim, 688, 1040, dtype="bf16")
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 640), inputs.make_weights(cfg, seed=1, std=0.04, gain_std=0.1).blob())
+    try:
+        _lds(lib, handle, True)
+        n = 5  # 1760 and 1305 new tokens
+        prompts = torch.from_numpy(inputs.make_prompts(n, max_len, cfg.vocab, seed=2)).cuda()
+        lens = torch.tensor([max_len, reuse + 1, max_len - 3, reuse + 16, max_len // 2 + reuse // 2], dtype=torch.int32, device="cuda")
+        ws = torch.empty(lib.mtmc_rollout_ragged_workspace_bytes(handle, n, max_len, n_samples, 20), dtype=torch.uint8, device="cuda")
+        lib.mtmc_rollout_ragged(handle, prompts, torch.full_like(lens, reuse), n_samples, 20, 1.0, 5, workspace=ws)
+        cached = lib.mtmc_rollout_ragged_cached(handle, prompts, lens, n_samples, 20, 1.0, 1, reuse, ws)
+        fresh = lib.mtmc_rollout_ragged(handle, prompts, lens, n_samples, 20, 1.0, 1, workspace=torch.empty_like(ws))
+        lib.mtmc_poll_errors(handle)
+        assert all(torch.equal(a, b) for a, b in zip(cached, fresh))
+    finally:
+        lib.mtmc_weights_destroy(handle)
