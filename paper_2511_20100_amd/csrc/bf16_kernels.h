@@ -203,10 +203,10 @@ int gemm_large_f32(float* C, int ldc, int N, bool accumulate, const h16_t* Wt, i
 void gemm_large_swiglu(h16_t* act, const h16_t* Wt, int n_tiles, int k_tiles, const h16_t* Xt,
                        int M, int m_tiles, int lds_min_blocks, int* err_flag, const int* d_rows, hipStream_t st);
 // QKV projection with the rotary embedding and the cache write in its epilogue: false, and nothing was launched, for the
-// sizes that the separate kernels keep (those of the direct kernel and of the split reduction).
+// sizes that the separate kernels keep (those of the direct kernel, of the split reduction, and where they cost less).
 bool gemm_large_rope(const RopeOut& r, const h16_t* Wt, int n_tiles, int k_tiles, const h16_t* Xt, int M, int m_tiles,
                      int lds_min_blocks, int* err_flag, size_t part_floats, hipStream_t st);
-void gemm_lds_rope(const LargeArgs& a, const RopeOut& r, hipStream_t st);
+bool gemm_lds_rope(const LargeArgs& a, const RopeOut& r, hipStream_t st);
 // ranges that gemm_lds_split would cut the reduction into (0: it would not)
 int gemm_lds_splits(const LargeArgs& a, size_t part_floats);
 // LDS-staged kernel behind the two launchers above (epi: 0 store, 1 accumulate, 2 SwiGLU); it chooses its block by the

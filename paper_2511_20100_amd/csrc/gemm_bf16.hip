@@ -188,9 +188,7 @@ bool gemm_large_rope(const RopeOut& r, const h16_t* Wt, int n_tiles, int k_tiles
   a.Wt = Wt; a.Xt = Xt; a.n_tiles = n_tiles; a.k_tiles = k_tiles; a.m_tiles = m_tiles; a.M = M;
   a.N = (r.Hq + 2 * r.Hkv) * r.pool.head_dim;
   a.err_flag = err_flag;
-  if (gemm_lds_splits(a, part_floats)) return false;
-  gemm_lds_rope(a, r, st);
-  return true;
+  return !gemm_lds_splits(a, part_floats) && gemm_lds_rope(a, r, st);
 }
 void gemm_large_swiglu(h16_t* act, const h16_t* Wt, int n_tiles, int k_tiles, const h16_t* Xt,
                        int M, int m_tiles, int lds_min_blocks, int* err_flag, const int* d_rows, hipStream_t st) {

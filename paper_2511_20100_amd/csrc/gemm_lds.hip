@@ -828,10 +828,17 @@ int gemm_lds_split(const LargeArgs& a0, bool accumulate, float* part, size_t par
 
 // A wavefront has to hold whole heads: the blocks of 256 features, of which the measured costs choose.  From 1024 tokens (the
 // caller); below, the separate rotary kernel adds up the slices of a split reduction, and a launch has too few such blocks.
-void gemm_lds_rope(const LargeArgs& a0, const RopeOut& r, hipStream_t st) {
+// Not where another block is so much better that the separate kernel (7 us, and 6 bytes per value at 4.8 TB/s) costs less than
+// the difference: 4608 features x 2048 tokens x 3584 take one round of 98 us in blocks of 256 x 256 and one of 79
+// in blocks of 192 x 256 (a layer of a scoring pass: 7 us longer with the epilogue, 12 us shorter at 3072 tokens).
+bool gemm_lds_rope(const LargeArgs& a0, const RopeOut& r, hipStream_t st) {
   const RopeArgs a{a0, r};
   const int features = a.n_tiles * 16;
-  const bool wide = cost_of(kTiles[0], features, a.M, a.k_tiles, 1, true) <= cost_of(kTiles[2], features, a.M, a.k_tiles, 1, true);
+  const double c256 = cost_of(kTiles[0], features, a.M, a.k_tiles, 1, true), c128 = cost_of(kTiles[2], features, a.M, a.k_tiles, 1, true);
+  double best = 0.0;
+  best_tile(features, a.M, a.k_tiles, 1, true, &best);
+  if (std::min(c256, c128) > best + 7.0 + 6.0 * features * a.M / 4.8e6) return false;
+  const bool wide = c256 <= c128;
   if (a.rope.pool.head_dim == 64) {
     if (wide) launch_tile<Tile<8, 8, 4, 1>, LEPI_ROPE64>(a, st);
     else launch_tile<Tile<8, 4, 3, 2>, LEPI_ROPE64>(a, st);
@@ -839,6 +846,7 @@ void gemm_lds_rope(const LargeArgs& a0, const RopeOut& r, hipStream_t st) {
     if (wide) launch_tile<Tile<8, 8, 4, 1>, LEPI_ROPE128>(a, st);
     else launch_tile<Tile<8, 4, 3, 2>, LEPI_ROPE128>(a, st);
   }
+  return true;
 }
 
 static int sample_lds_grid(int n_tiles) { return grid_of<SampleTile>((size_t)(n_tiles + SampleTile::TN - 1) / SampleTile::TN); }

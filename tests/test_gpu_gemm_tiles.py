@@ -93,6 +93,24 @@ def test_rotary_epilogue_is_the_separate_kernels(lib, heads, kv_heads, head_dim,
     assert float((short[0] - lp[-1, :seq_len // 2 - 1]).abs().max()) <= TOL
 
 
+def test_wide_projection_between_the_rotary_forms(lib):
+    """4608 features x 3584: 1998 tokens are stored by narrower blocks and rotated by the separate kernel, 2997 are rotated in
+    the epilogue of 256-feature blocks."""
+    import torch
+    cfg = inputs.ModelConfig(1, 3584, 28, 4, 128, 256, 512, dtype="bf16")
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 1024), inputs.make_weights(cfg, seed=1, std=0.015, gain_std=0.1).blob())
+    try:
+        seqs = torch.from_numpy(inputs.make_sequences(3, 1000, cfg.vocab, seed=7))[:, :999].contiguous().cuda()
+        _lds(lib, handle, True)
+        three, two = lib.mtmc_score(handle, seqs, 1), lib.mtmc_score(handle, seqs[:2].contiguous(), 1)
+        _lds(lib, handle, False)
+        direct = lib.mtmc_score(handle, seqs, 1)
+        lib.mtmc_poll_errors(handle)
+        assert float((direct - three).abs().max()) <= TOL and float((two - three[:2]).abs().max()) <= TOL
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
 # ---- the same bits.  The calls compared below take the same row norm (from 1024 rows on) and the same number of vocabulary
 # slices in the LM head (by the scored rows), and split no reduction, so that only what a test is about differs.  (Where the
 # reader of a split reduction adds up its slices, no other call runs the same sums in separate launches: the tests above
