@@ -161,11 +161,10 @@ static void launch_large(const LargeArgs& a, int epi, hipStream_t st) {
   else k_gemm_large<LEPI_SWIGLU><<<grid, 256, 0, st>>>(a);
 }
 
-// The LDS-staged kernel (256 x 256 blocks, one workgroup per CU) takes over once the output has
-// at least `lds_min_blocks` such blocks; smaller problems keep the 128 x 128 direct kernel, which
-// spreads them over more workgroups.
+// The LDS-staged kernels take over once the output has at least `lds_min_blocks` blocks of 256 x 256 (they then choose
+// their own block size by the call's sizes); smaller problems keep the 128 x 128 direct kernel.
 static bool use_lds_kernel(int n_tiles, int k_tiles, int m_tiles, int lds_min_blocks) {
-  // the LDS pipeline streams k-steps in pairs through a ring of four buffers
+  // the LDS pipeline streams k-steps in pairs through a ring of three or four buffers
   return k_tiles >= 4 && k_tiles % 2 == 0 && ((n_tiles + 15) / 16) * ((m_tiles + 15) / 16) >= lds_min_blocks;
 }
 int gemm_large_f32(float* C, int ldc, int N, bool accumulate, const h16_t* Wt, int n_tiles,

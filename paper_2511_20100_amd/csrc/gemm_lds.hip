@@ -2,9 +2,10 @@
 //
 // Workgroup tile: 32 NB output features x 32 MB tokens, full K.  Four wavefronts (one per SIMD and workgroup) in a
 // 2 x 2 arrangement own NB x MB accumulator blocks of v_mfma_f32_16x16x32_f16 each.  The 16x16x32 shape and not
-// 32x32x16: both are limited by power here, not by issue slots (a register-only loop on random operands reaches
-// 1.91 PFLOP/s with 16x16x32 and 1.67 with 32x32x16; the clock of the GEMM itself rose from 1.39 to 1.76 GHz), because
-// the smaller shape moves half as many accumulator bytes per product.  The sums are the same bit for bit.
+// 32x32x16: both are limited by power here, not by issue slots (a register-only loop on pseudo-random operands, the library's
+// matrix probe, attains 1.73 PFLOP/s with 16x16x32 and 1.60 with 32x32x16), because the smaller shape moves half as many
+// accumulator bytes per product: on one card the gate/up GEMM of the 1.5 B scoring pass ran at 1.70 GHz with the matrix pipes
+// occupied 0.69 of the cycles, and runs at 1.85 GHz and 0.68 now.  The sums are the same bit for bit.
 //
 // Both operands already sit in memory as 1 KiB MFMA operand blocks (frag.h), so staging is a plain copy: every k-step
 // (32 columns of K) needs 2 NB weight blocks and 2 MB activation blocks, which the wavefronts fetch with LDS-direct
@@ -13,10 +14,11 @@
 // blocks visible to every wavefront and at the same time guarantees that the buffer refilled next (read in the previous
 // step) is no longer in use.
 //
-// What bounds it (256 x 256 tiles, 98 304 tokens, same card): without the copies the loop runs at 1.57 PFLOP/s, with
-// them at 1.38, and with the epilogue's HBM traffic at 1.25 (down projection, 2.41 -> 2.17 ms; gate/up 4.70 -> 4.32 ms;
-// QKV 0.63 -> 0.59; before: 32x32x16, flat addresses).  The fragment reads of a step are issued in its first half: spread over
-// the whole step, their latency stood before the next step's first product (1.19 -> 1.28 PFLOP/s at 4096^2 x 8192).
+// What bounds it (256 x 256 tiles, 98 304 tokens, this file alone in a harness): without the copies the loop runs at 1.57
+// PFLOP/s, with them at 1.38, and with the epilogue's HBM traffic at 1.25 (down projection).  In the scoring pass, profiled in
+// turn on one card with the form of 32x32x16 and flat addresses before it: gate/up 4.65 -> 4.28 ms, O + down 2.70 -> 2.59,
+// LM head 26.1 -> 24.2.  The fragment reads of a step are issued in its first half: spread over the whole step, their latency
+// stood before the next step's first product (1.19 -> 1.28 PFLOP/s at 4096^2 x 8192).
 #include <algorithm>
 
 #include "bf16_kernels.h"
@@ -287,7 +289,8 @@ __device__ __forceinline__ void store_swiglu(v4f (&acc)[T::NB][T::MB], const Lar
 // i + hd / 2 .. of one token, so it rotates what it holds.  q goes to rows, k and v to the pages (layouts: attention_core.h).
 // The fp32 projection is never written and read back: 16 of the 20 KiB that a token of the 1.5 B shape moved, and a launch.
 // Projection and rotary kernel, before and now: 874 -> 645 us (98 304 tokens x 2048 features), 102 -> 89 (5439 x 3072, 64-dim
-// heads), 46.6 -> 36.0 (4096 x 2048).
+// heads), 46.6 -> 36.0 (4096 x 2048, in a pass without room for a split reduction: with it the projection of so few blocks is
+// split, and keeps the separate kernels).
 template <class T, int HD>
 __device__ __forceinline__ void store_rope(v4f (&acc)[T::NB][T::MB], const RopeArgs& a, int nt0, int mt0, int lane) {
   constexpr int MB = T::MB, BPH = HD / 16, HB = BPH / 2;
@@ -750,7 +753,7 @@ const TileCost kTiles[] = {
     {128, 64, 2, 0.16, 0.30, 1.5, &launch<Tile<4, 2, 4, 2>>},   // a few dozen rows
 };
 
-// What a launch takes, by its busiest CU.  Measured against it: 4096 x 1536 x 8960 (features and tokens swapped) 183 us
+// What a launch takes, by its busiest CU.  Measured against it (this file alone in a harness): 4096 x 1536 x 8960 (features and tokens swapped) 183 us
 // in 96 blocks of 256 x 256, 104 us in 256 of 192 x 128; 512 tokens x 17 920 features 38.6 and 32.1 us; 800 tokens 73.6 and
 // 44.0 us; 98 304 tokens 4.46 ms in 256 x 256, 4.55-5.2 ms in the others.
 double cost_of(const TileCost& t, int features, int tokens, int k_steps, int splits, bool fp32) {
