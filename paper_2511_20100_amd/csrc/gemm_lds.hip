@@ -3,9 +3,9 @@
 // Workgroup tile: 32 NB output features x 32 MB tokens, full K.  Four wavefronts (one per SIMD and workgroup) in a
 // 2 x 2 arrangement own NB x MB accumulator blocks of v_mfma_f32_16x16x32_f16 each.  The 16x16x32 shape and not
 // 32x32x16: both are limited by power here, not by issue slots (a register-only loop on pseudo-random operands, the library's
-// matrix probe, attains 1.73 PFLOP/s with 16x16x32 and 1.60 with 32x32x16), because the smaller shape moves half as many
-// accumulator bytes per product: on one card the gate/up GEMM of the 1.5 B scoring pass ran at 1.70 GHz with the matrix pipes
-// occupied 0.69 of the cycles, and runs at 1.85 GHz and 0.68 now.  The sums are the same bit for bit.
+// matrix probe, attains 1.68 PFLOP/s with 16x16x32 on the card where it read 1.56 with 32x32x16), because the smaller shape
+// moves half as many accumulator bytes per product: on that card the gate/up GEMM of the 1.5 B scoring pass ran at 1.70 GHz
+// with the matrix pipes occupied 0.69 of the cycles, and runs at 1.85 GHz and 0.68 now.  The sums are the same bit for bit.
 //
 // Both operands already sit in memory as 1 KiB MFMA operand blocks (frag.h), so staging is a plain copy: every k-step
 // (32 columns of K) needs 2 NB weight blocks and 2 MB activation blocks, which the wavefronts fetch with LDS-direct
