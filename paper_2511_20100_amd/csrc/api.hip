@@ -92,6 +92,7 @@ extern "C" int mtmc_weights_create(const mtmc_config* cfg, const void* blob, siz
   w->opt_lds_min_blocks = 32;
   w->opt_stop_poll = 32;
   w->opt_admit = 1;
+  w->opt_persistent_wait_us = 10000000;
   w->graphs = nullptr;
   w->ragged_mu = new (std::nothrow) std::mutex();
   if (!w->ragged_mu) { delete w; set_error("out of host memory"); return MTMC_ENOMEM; }
@@ -136,7 +137,8 @@ extern "C" int mtmc_admission_plan(const int32_t* live, const int32_t* slot_regi
 extern "C" int mtmc_set_option(mtmc_weights* w, int option, int value) {
   MTMC_REQUIRE(w != nullptr, "weights is NULL");
   MTMC_REQUIRE(option == MTMC_OPT_HIP_GRAPH || option == MTMC_OPT_GEMM_LDS_MIN_BLOCKS ||
-                   option == MTMC_OPT_STOP_POLL_STEPS || option == MTMC_OPT_ADMIT_PROMPTS,
+                   option == MTMC_OPT_STOP_POLL_STEPS || option == MTMC_OPT_ADMIT_PROMPTS ||
+                   option == MTMC_OPT_PERSISTENT_DECODE,
                "unknown option");
   if (option == MTMC_OPT_HIP_GRAPH) {
     w->opt_hip_graph = value ? 1 : 0;
@@ -145,6 +147,9 @@ extern "C" int mtmc_set_option(mtmc_weights* w, int option, int value) {
     w->opt_stop_poll = value;
   } else if (option == MTMC_OPT_ADMIT_PROMPTS) {
     w->opt_admit = value ? 1 : 0;
+  } else if (option == MTMC_OPT_PERSISTENT_DECODE) {
+    MTMC_REQUIRE(value >= 0 && value <= 60000000, "MTMC_OPT_PERSISTENT_DECODE needs a value in [0, 60 000 000]");
+    w->opt_persistent_wait_us = value;
   } else {
     MTMC_REQUIRE(value >= 1, "MTMC_OPT_GEMM_LDS_MIN_BLOCKS needs a value >= 1");
     w->opt_lds_min_blocks = value;
@@ -221,6 +226,9 @@ extern "C" const char* mtmc_data_error_string(int bits) {
   add(MTMC_DATA_FP16_RANGE,
       "an activation, key or value left the fp16 range (magnitude above 65504, or not finite) and was clamped: "
       "the results of the calls since the last poll are unreliable");
+  add(MTMC_DATA_STALLED,
+      "a persistent decode launch waited longer than its limit for workgroups that never became resident (another process "
+      "on the GPU?): the results of the calls since the last poll are wrong; MTMC_OPT_PERSISTENT_DECODE 0 avoids such launches");
   return text.c_str();
 }
 

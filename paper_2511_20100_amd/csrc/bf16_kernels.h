@@ -137,6 +137,7 @@ struct EmbedNextArgs {
   float* ss_out;
   int vocab;         // a chosen id outside [0, vocab) (every logit NaN) is replaced by 0 and reported
   int* err_flag;
+  uint32_t* sync;    // counters of the persistent step (PersistArgs), cleared for the next one by the sampler merge; or NULL
 };
 // Merges the sampler partials of a step, writes the outputs of step *d_step, advances *d_step (d_step[1] is the
 // kernel's arrival counter: zero before the first launch, left at zero by every launch) and embeds the chosen tokens.
@@ -167,6 +168,40 @@ struct AttnDecArgs {
   int* err_flag;         // raised when q, k, v or the output does not fit fp16
 };
 void attention_dec(const AttnDecArgs& a, int B, hipStream_t st);
+
+// ---- the blocks of a decode step of up to 16 rows as one launch (decode_persistent.hip) -------------
+constexpr int kPersistGrid = 256;        // workgroups, all resident at once: one per CU
+constexpr int kPersistSyncStride = 64;   // words between the arrival counters: 8 that are watched, 16 of groups of workgroups
+constexpr int kPersistTops = 8, kPersistCounters = kPersistTops + 16;
+constexpr int kPersistStalled = kPersistCounters * kPersistSyncStride;  // word that says that a wait has outlasted its limit
+constexpr int kPersistSyncWords = kPersistStalled + 64;
+struct PersistArgs {
+  int n_layers, B, d;
+  int nt_qkv, nt_d, nt_gu, kt_d, kt_nq, kt_F;
+  // weights of block 0; those of block l lie l * layer_stride bytes behind
+  const h16_t *wqkv, *wo, *wgu, *wdown;
+  const float *attn_norm, *ffn_norm, *final_norm;
+  size_t layer_stride;
+  float inv_d, eps;
+  float* h;
+  h16_t *x, *act;
+  float *qkv, *part;
+  float* ss[2];          // sums of squares [tile][16]: ss[0] those of the residual that comes in, and of the one that goes out
+  float* ss_in[2];       // the same inside the launch, [16][kPersistGrid]
+  int o_ranges;          // ranges of K in the O projection: 16 or 8; behind several context chunks 12 (two) or 8, by heads
+  int ks_down, dn_batches;
+  int attn_units;        // B * Hkv * n_chunks
+  AttnDecArgs at;        // layer is set by the kernel
+  uint32_t* sync;        // kPersistSyncWords, zero at the first launch; the sampler merge clears the counters after every step
+  long long wait_ticks;  // of the 100 MHz clock
+  int* err_flag;
+};
+struct PersistShape {
+  int m_tiles, head_dim, kt_d, nt_d, nt_gu, n_chunks, pairs;  // pairs: sequences x kv heads
+};
+bool decode_persistent_fits(const PersistShape& s);
+// down_nb: row tiles per workgroup of the down projection's own launch (2, 3 or 4), which tells its ranges of K
+void decode_persistent(const PersistArgs& a, int down_nb, hipStream_t st);
 
 // ---- packing the live rows of a batch with a stop token into the leading slots ------------------
 // live[0] = number of rows whose stop flag is clear.

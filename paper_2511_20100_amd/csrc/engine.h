@@ -90,6 +90,9 @@ struct RolloutPlan {
   float* rs_buf;      // 1/rms per row, handed from the split-K down projection to its reduction
   int chunk_pages, n_chunks;       // decode-attention context split
   int split_at_prompt;             // two chunks: the prompt's whole pages | the rest (else equal chunks)
+  bool persistent;       // the decode step's blocks run as one persistent launch
+  uint32_t* sync;        // its counters (kPersistSyncWords)
+  float* ss_in;          // its sums of squares
   bool samples_alone;    // the decode attention takes every sequence in a workgroup of its own
   int ks_qkv, ks_o, ks_down;       // split-K factors of the decode GEMMs
   int down_nb;                     // weight row tiles per workgroup of the down projection (2 or 4)

@@ -9,6 +9,7 @@
 #include "engine.h"
 #include "kernels.h"
 #include "lease_cache.h"
+#include "persistent_turn.h"
 
 namespace mtmc {
 
@@ -21,9 +22,11 @@ struct StepKey {
   const void* workspace;
   int total_prompts, B, prompt_len, n_samples, max_new, ragged;
   bool samples_alone;
+  int persistent_wait_us;  // 0: separate launches
   bool operator==(const StepKey& o) const {
     return workspace == o.workspace && total_prompts == o.total_prompts && B == o.B && prompt_len == o.prompt_len &&
-           n_samples == o.n_samples && max_new == o.max_new && ragged == o.ragged && samples_alone == o.samples_alone;
+           n_samples == o.n_samples && max_new == o.max_new && ragged == o.ragged && samples_alone == o.samples_alone &&
+           persistent_wait_us == o.persistent_wait_us;
   }
 };
 struct StepExec {
@@ -368,6 +371,8 @@ void bf16_plan_rollout_extra(const mtmc_weights* w, RolloutPlan& p, Carver& cv) 
   p.ssA = cv.take<float>((size_t)D.nt_d * Mpad);
   p.ssB = cv.take<float>((size_t)D.nt_d * Mpad);
   p.rs_buf = cv.take<float>(Mpad);
+  p.sync = cv.take<uint32_t>(bf16::kPersistSyncWords);
+  p.ss_in = cv.take<float>(2 * 16 * bf16::kPersistGrid);
   if (p.ragged) {
     p.slot_row = cv.take<int>(Mpad);
     p.page_table_c = cv.take<int>(Mpad * p.max_pages);
@@ -454,6 +459,43 @@ void prefill_layers(const mtmc_weights* w, const Dims& D, float* h, h16_t* x, fl
   }
 }
 
+// The decode step's blocks as one launch, where its shape fits and the weights lie as it reads them (bf16_store_weights carves
+// every block alike; the stride is checked all the same).
+bool persistent_shape(const mtmc_weights* w, const Dims& D, const RolloutPlan& p) {
+  if (w->opt_persistent_wait_us <= 0 || p.max_new < 2) return false;
+  const auto& L = w->layers;
+  auto at = [](const void* q) { return (const char*)q; };
+  const ptrdiff_t stride = L.size() > 1 ? at(L[1].wqkv) - at(L[0].wqkv) : 0;
+  for (size_t l = 1; l < L.size(); ++l) {
+    for (auto f : {&LayerWeights::wqkv, &LayerWeights::wo, &LayerWeights::wgu, &LayerWeights::wdown})
+      if (at(L[l].*f) - at(L[l - 1].*f) != stride) return false;
+    for (auto f : {&LayerWeights::attn_norm, &LayerWeights::ffn_norm})
+      if (at(L[l].*f) - at(L[l - 1].*f) != stride) return false;
+  }
+  return stride >= 0 && bf16::decode_persistent_fits(bf16::PersistShape{p.bt, w->cfg.head_dim, D.kt_d, D.nt_d, D.nt_gu, p.n_chunks,
+                                                                        p.B * D.Hkv});
+}
+
+bf16::PersistArgs persistent_args(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, const bf16::AttnDecArgs& at) {
+  const auto& L = w->layers;
+  bf16::PersistArgs a{};
+  a.n_layers = w->cfg.n_layers; a.B = p.B; a.d = D.d;
+  a.nt_qkv = D.nt_qkv; a.nt_d = D.nt_d; a.nt_gu = D.nt_gu; a.kt_d = D.kt_d; a.kt_nq = D.kt_nq; a.kt_F = D.kt_F;
+  a.wqkv = (const h16_t*)L[0].wqkv; a.wo = (const h16_t*)L[0].wo; a.wgu = (const h16_t*)L[0].wgu; a.wdown = (const h16_t*)L[0].wdown;
+  a.attn_norm = L[0].attn_norm; a.ffn_norm = L[0].ffn_norm; a.final_norm = w->final_norm;
+  a.layer_stride = L.size() > 1 ? (size_t)((const char*)L[1].wqkv - (const char*)L[0].wqkv) : 0;
+  a.inv_d = 1.0f / (float)D.d; a.eps = w->cfg.rms_eps;
+  a.h = p.hB; a.x = (h16_t*)p.xB; a.act = (h16_t*)p.a; a.qkv = p.qkv; a.part = p.part; a.ss[0] = p.ssA; a.ss[1] = p.ssB;
+  a.ss_in[0] = p.ss_in; a.ss_in[1] = p.ss_in + 16 * bf16::kPersistGrid;
+  a.o_ranges = p.n_chunks > 1 ? (p.n_chunks == 2 ? 12 : 8) : (D.kt_nq >= 48 ? 16 : 8);
+  a.ks_down = p.ks_down;
+  a.dn_batches = p.down_nb == 3 ? (D.nt_d * 8 + 3 * bf16::kPersistGrid - 1) / (3 * bf16::kPersistGrid) : 1;
+  a.attn_units = p.B * D.Hkv * p.n_chunks;
+  a.at = at;
+  a.sync = p.sync; a.wait_ticks = 100LL * w->opt_persistent_wait_us; a.err_flag = w->err_flag;
+  return a;
+}
+
 // One decode step over the B sequences of a group.  In: hB / xB / ssA hold the embedded and normalised tokens of
 // the step (the sampler merge of the previous step leaves them).  Runs the blocks (six launches each) against the
 // paged cache at position prompt_len - 1 + *d_step and leaves in xB the operand of the LM head together with the
@@ -469,6 +511,22 @@ void decode_layers(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, K
   h16_t* a = (h16_t*)p.a;
   float* ss[2] = {p.ssA, p.ssB};
   int cur = 0, old = 0;
+  auto attention_args = [&](int l) {
+    bf16::AttnDecArgs at{};
+    at.qkv = p.qkv; at.cos = w->rope_cos; at.sin = w->rope_sin; at.Hq = D.Hq; at.Hkv = D.Hkv; at.layer = l;
+    at.pos_base = pos_base; at.row_pos = p.ragged ? p.row_pos : nullptr; at.d_step = p.d_step; at.pool = pool; at.chunk_pages = p.chunk_pages; at.split_at_prompt = p.split_at_prompt;
+    at.n_chunks = p.n_chunks; at.m_tiles = bt; at.share = p.n_samples;
+    at.prompt_len = p.prompt_len; at.max_new = p.max_new; at.samples_alone = p.samples_alone;
+    at.row_step0 = p.ragged == 3 ? p.row_step0 : nullptr; at.max_step = p.max_new - 1;
+    at.o = (h16_t*)p.o_chunks; at.o_chunk_stride = (size_t)D.nq * bt * 16; at.ml = p.attn_ml; at.err_flag = w->err_flag;
+    return at;
+  };
+  if (p.persistent) {
+    bf16::decode_persistent(persistent_args(w, D, p, attention_args(0)), p.down_nb, st);
+    *ss_cur_out = p.ssA;
+    *ss_old_out = p.ssB;
+    return;
+  }
   bf16::DecGemmArgs g{};
   g.m_tiles = bt; g.M = B; g.ss_tiles = D.nt_d; g.inv_d = 1.0f / (float)D.d; g.eps = c.rms_eps; g.err_flag = w->err_flag;
   for (int l = 0; l < c.n_layers; ++l) {
@@ -479,13 +537,7 @@ void decode_layers(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, K
     mark(MTMC_KERNEL_QKV);
     bf16::gemm_dec(q, bf16::DEC_STORE, st);
     mark(MTMC_KERNEL_QKV);
-    bf16::AttnDecArgs at{};
-    at.qkv = p.qkv; at.cos = w->rope_cos; at.sin = w->rope_sin; at.Hq = D.Hq; at.Hkv = D.Hkv; at.layer = l;
-    at.pos_base = pos_base; at.row_pos = p.ragged ? p.row_pos : nullptr; at.d_step = p.d_step; at.pool = pool; at.chunk_pages = p.chunk_pages; at.split_at_prompt = p.split_at_prompt;
-    at.n_chunks = p.n_chunks; at.m_tiles = bt; at.share = p.n_samples;
-    at.prompt_len = p.prompt_len; at.max_new = p.max_new; at.samples_alone = p.samples_alone;
-    at.row_step0 = p.ragged == 3 ? p.row_step0 : nullptr; at.max_step = p.max_new - 1;
-    at.o = (h16_t*)p.o_chunks; at.o_chunk_stride = (size_t)D.nq * bt * 16; at.ml = p.attn_ml; at.err_flag = w->err_flag;
+    const bf16::AttnDecArgs at = attention_args(l);
     mark(MTMC_KERNEL_ATTENTION);
     bf16::attention_dec(at, B, st);
     mark(MTMC_KERNEL_ATTENTION);
@@ -561,7 +613,7 @@ int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, c
     }
   }
   const StepKey key{(const void*)gp.page_table, gp.total_prompts, gp.B, gp.prompt_len, gp.n_samples, gp.max_new, gp.ragged,
-                    gp.samples_alone};
+                    gp.samples_alone, gp.persistent ? w->opt_persistent_wait_us : 0};
   out->cache_ = &gc;
   out->entry_ = gc.steps.acquire(key);
   if (out->entry_) return MTMC_OK;
@@ -641,6 +693,8 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   launch_ragged_setup(p.page_table, p.row_pos, p.done, sa.out_lens, p.prompt_ids, p.suffix_ids, prompts, sa.prompt_lens,
                       p.n_prompts, ns, S, p.max_pages, p.nf_max, p.shared_total, p.max_new, 0, w->err_flag, st);
   bf16::admit_init(p.slot_row, p.row_step0, B, p.bt * 16, st);
+  launch_fill_u32(p.sync, 0u, bf16::kPersistSyncWords, st);
+  PersistentTurn turn;
   launch_set_int(p.d_step, 0, st);
   launch_set_int(p.d_step + 1, 0, st);
   launch_clear_values(pool, c.n_layers, 2, st);
@@ -668,7 +722,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   bf16::add_norm(p.hB, nullptr, 0, 0, 0, w->final_norm, c.rms_eps, (h16_t*)p.xB, B, gp.bt, D.d, w->err_flag, st);
   auto embed_args = [&](const RolloutPlan& q) {
     return bf16::EmbedNextArgs{p.hB, (const bf16_t*)w->embed, D.d, w->layers[0].attn_norm, c.rms_eps, (h16_t*)p.xB,
-                               q.bt * 16, p.ssA, D.V, w->err_flag};
+                               q.bt * 16, p.ssA, D.V, w->err_flag, p.sync};
   };
   // LM head + sampler over `rows` rows of the operand x; `dc` / `ds`: control block and step counter
   auto sample = [&](hipStream_t s, const h16_t* x, int rows, const float* ss_cur, const float* ss_old,
@@ -763,7 +817,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
         launch_set_int(p.d_step + 8, 0, st);
         launch_set_int(p.d_step + 9, 0, st);
         const bf16::EmbedNextArgs embT{p.hT, (const bf16_t*)w->embed, D.d, w->layers[0].attn_norm, c.rms_eps, (h16_t*)p.xT,
-                                       tiles16(rows) * 16, p.ssT, D.V, w->err_flag};
+                                       tiles16(rows) * 16, p.ssT, D.V, w->err_flag, nullptr};
         sample(st, (const h16_t*)p.xT, rows, nullptr, nullptr, d_ctl + 1, p.d_step + 8, p.cur_ids + (size_t)q0 * ns, embT);
       }
       // the first tokens of the new sequences become operands of the next step (the other slots get again what
@@ -780,6 +834,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
       cur.B = slots; cur.bt = slots / 16; cur.n_samples = 1;
       cur.row_pos = p.row_pos_c; cur.row_step0 = p.row_step0_c;
       apply_tune(cur, tune_decode(D, cur.B, cur.bt, p.max_pages));
+      cur.persistent = persistent_shape(w, D, cur) && turn.take(w->device, st);
       cur_pool.page_table = p.page_table_c;
       bf16::SampleCtl cc = ctl;
       cc.slot_row = p.slot_row_c;
@@ -810,6 +865,17 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     (void)hipGetLastError();
   }
   const Dims D = dims_of(w);
+  // a step as one persistent launch where it fits, the turn is free and the caller is not capturing the stream
+  bool may_persist = true;
+  {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      may_persist = false;
+    }
+  }
+  PersistentTurn turn;
+  launch_fill_u32(p.sync, 0u, bf16::kPersistSyncWords, st);
   KvPool pool{p.kv, p.n_pages, c.n_kv_heads, c.head_dim, p.page_table, p.max_pages};
   for (int g0 = 0; g0 < p.total_prompts; g0 += p.n_prompts) {
     const int np_group = std::min(p.n_prompts, p.total_prompts - g0);
@@ -821,6 +887,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     const bool ragged = sa.prompt_lens != nullptr;
     // a call whose prompts could join a running batch (where every sequence is alone) gives the same bits batch after batch
     gp.samples_alone = ragged && sa.stop_id >= 0 && p.total_prompts > p.n_prompts;
+    gp.persistent = may_persist && persistent_shape(w, D, gp) && turn.take(w->device, st);
     const int* glens = ragged ? sa.prompt_lens + g0 : nullptr;
     int* g_out_lens = ragged ? sa.out_lens + (size_t)g0 * p.n_samples : nullptr;
     const int* gprompts = prompts + (size_t)g0 * p.prompt_len;
@@ -877,7 +944,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     // q: the shape the step runs in (the group's rows, or the slots its live rows were packed into)
     auto embed_args = [&](const RolloutPlan& q) {
       return bf16::EmbedNextArgs{p.hB, (const bf16_t*)w->embed, D.d, w->layers[0].attn_norm, c.rms_eps, (h16_t*)p.xB,
-                                 q.bt * 16, p.ssA, D.V, w->err_flag};
+                                 q.bt * 16, p.ssA, D.V, w->err_flag, p.sync};
     };
     auto sample = [&](hipStream_t s, const float* ss_cur, const float* ss_old, const RolloutPlan& q) {
       bf16::DecGemmArgs lm{};
@@ -898,7 +965,11 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
       sample(s, ss_cur, ss_old, q);
       if (tm) tm->mark(MTMC_KERNEL_LM_HEAD);
     };
-    auto decode_step_timed = [&](hipStream_t s, KernelTimer* tm) { decode_step_in(s, tm, gp, pool); };
+    auto decode_step_timed = [&](hipStream_t s, KernelTimer* tm) {
+      RolloutPlan q = gp;
+      if (tm) q.persistent = false;  // the kernels that are timed one by one: the same bits
+      decode_step_in(s, tm, q, pool);
+    };
     auto decode_step = [&](hipStream_t s) { decode_step_timed(s, nullptr); };
     sample(st, nullptr, nullptr, gp);  // xB holds the exactly normalised last prompt position
     // A stop token: every `poll` steps the number of rows still running goes to the host, which reads it one
@@ -949,6 +1020,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
             cur.B = slots; cur.bt = slots / 16; cur.n_samples = 1; cur.ragged = 2;
             cur.row_pos = p.row_pos_c;
             apply_tune(cur, tune_decode(D, cur.B, cur.bt, p.max_pages));
+            cur.persistent = may_persist && persistent_shape(w, D, cur) && turn.take(w->device, st);
             cur_pool.page_table = p.page_table_c;
             ctl.slot_row = p.slot_row;
             bf16::set_sample_ctl((bf16::SampleCtl*)p.ctl, ctl, st);

@@ -1,0 +1,98 @@
+// The turn of the persistent launches on a device: see persistent_turn.h.
+#include "persistent_turn.h"
+
+#include <stddef.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+#include <sys/socket.h>
+#include <sys/un.h>
+#include <unistd.h>
+
+#include <mutex>
+
+#include "bf16_kernels.h"
+
+namespace mtmc {
+namespace {
+
+struct DeviceTurn {
+  std::mutex mu;
+  bool asked = false, usable = false;
+  hipEvent_t last = nullptr;  // behind the launches of the latest turn
+  hipStream_t stream = nullptr;
+  bool recorded = false;
+};
+constexpr int kMaxDevices = 64;
+DeviceTurn g_turns[kMaxDevices];  // events stay until the process ends
+
+// The name is held by a socket that is never closed: the lease ends with the process.
+bool lease_device(int device) {
+  char bus[32];
+  if (hipDeviceGetPCIBusId(bus, sizeof bus, device) != hipSuccess) return false;
+  const int fd = socket(AF_UNIX, SOCK_DGRAM | SOCK_CLOEXEC, 0);
+  if (fd < 0) return false;
+  sockaddr_un addr;
+  memset(&addr, 0, sizeof addr);
+  addr.sun_family = AF_UNIX;
+  const int n = snprintf(addr.sun_path + 1, sizeof addr.sun_path - 1, "mtmc-persistent-%s", bus);
+  if (bind(fd, (const sockaddr*)&addr, (socklen_t)(offsetof(sockaddr_un, sun_path) + 1 + n)) != 0) {
+    close(fd);
+    return false;
+  }
+  return true;
+}
+
+// Every CU has to be open to the stream.
+bool whole_device(hipStream_t st) {
+  if (getenv("HSA_CU_MASK") || getenv("ROC_GLOBAL_CU_MASK")) return false;
+  if (st == nullptr || st == hipStreamPerThread || st == hipStreamLegacy) return true;  // these have no mask of their own
+  uint32_t mask[16] = {};
+  if (hipExtStreamGetCUMask(st, 16, mask) != hipSuccess) return false;
+  int open = 0;
+  for (uint32_t m : mask) open += __builtin_popcount(m);
+  return open >= bf16::kPersistGrid;
+}
+
+bool usable(DeviceTurn& t, int device) {
+  if (t.asked) return t.usable;
+  t.asked = true;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < bf16::kPersistGrid)
+    return false;
+  if (hipEventCreateWithFlags(&t.last, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) return false;
+  t.usable = lease_device(device);
+  return t.usable;
+}
+
+}  // namespace
+
+bool PersistentTurn::take(int device, hipStream_t st) {
+  if (held_) return true;
+  if (device < 0 || device >= kMaxDevices || !whole_device(st)) return false;
+  DeviceTurn& t = g_turns[device];
+  if (!t.mu.try_lock()) return false;
+  bool ok = usable(t, device);
+  if (ok && t.recorded && hipEventQuery(t.last) == hipErrorNotReady)
+    ok = t.stream == st && hipStreamWaitEvent(st, t.last, 0) == hipSuccess;
+  (void)hipGetLastError();
+  if (!ok) {
+    t.mu.unlock();
+    return false;
+  }
+  held_ = &t;
+  st_ = st;
+  return true;
+}
+
+void PersistentTurn::release() {
+  if (!held_) return;
+  DeviceTurn& t = *(DeviceTurn*)held_;
+  t.recorded = hipEventRecord(t.last, st_) == hipSuccess;
+  if (!t.recorded) (void)hipStreamSynchronize(st_);
+  t.stream = st_;
+  t.mu.unlock();
+  held_ = nullptr;
+}
+
+}  // namespace mtmc

@@ -20,6 +20,7 @@ _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libmtmc.so
 MTMC_OK, MTMC_EINVAL, MTMC_ENOMEM, MTMC_EHIP, MTMC_EDATA = 0, -1, -2, -3, -4
 MTMC_F32, MTMC_BF16 = 0, 1
 MTMC_DATA_TOKEN_ID, MTMC_DATA_WEIGHT, MTMC_DATA_LENGTH, MTMC_DATA_FP16_RANGE, MTMC_DATA_PREFIX = 1, 2, 4, 8, 16
+MTMC_DATA_STALLED = 32
 
 
 class MtmcError(RuntimeError):
@@ -332,6 +333,7 @@ MTMC_OPT_HIP_GRAPH = 1
 MTMC_OPT_GEMM_LDS_MIN_BLOCKS = 2
 MTMC_OPT_STOP_POLL_STEPS = 3
 MTMC_OPT_ADMIT_PROMPTS = 4
+MTMC_OPT_PERSISTENT_DECODE = 5
 
 
 def mtmc_set_option(handle: int, option: int, value: int) -> None:
