@@ -339,7 +339,7 @@ const char* mtmc_data_error_string(int bits);
  *   of the fp32 sums (step 0 of a prompt that joins is sampled in a smaller batch, the packed batch runs other
  *   tilings): about 1e-3 in a log-probability, an id can differ where two candidates are that close.  Not used
  *   when `stream` is being captured, without a stop token, or with a cached prefix.
- *   MTMC_OPT_PERSISTENT_DECODE (default 10 000 000, 0 = off): MTMC_BF16 decode steps of up to 16 rows run all blocks as
+ *   MTMC_OPT_PERSISTENT_DECODE (default 10 000 000, 0 = off): MTMC_BF16 decode steps of up to 64 rows run all blocks as
  *   one launch of one workgroup per CU, whose workgroups wait for each other between phases, instead of six launches
  *   per block.  Results do not depend on it (the same sums in the same order).  The launch needs the whole device at once: it
  *   is used while no other such launch is under way from another stream or thread of the process, by one process per

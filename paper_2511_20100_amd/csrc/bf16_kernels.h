@@ -138,6 +138,7 @@ struct EmbedNextArgs {
   int vocab;         // a chosen id outside [0, vocab) (every logit NaN) is replaced by 0 and reported
   int* err_flag;
   uint32_t* sync;    // counters of the persistent step (PersistArgs), cleared for the next one by the sampler merge; or NULL
+  float* ss_rows;    // the sums of squares once more as the persistent step reads them, [row][kPersistGrid]; or NULL
 };
 // Merges the sampler partials of a step, writes the outputs of step *d_step, advances *d_step (d_step[1] is the
 // kernel's arrival counter: zero before the first launch, left at zero by every launch) and embeds the chosen tokens.
@@ -169,7 +170,7 @@ struct AttnDecArgs {
 };
 void attention_dec(const AttnDecArgs& a, int B, hipStream_t st);
 
-// ---- the blocks of a decode step of up to 16 rows as one launch (decode_persistent.hip) -------------
+// ---- the blocks of a decode step of up to 64 rows as one launch (decode_persistent.hip) -------------
 constexpr int kPersistGrid = 256;        // workgroups, all resident at once: one per CU
 constexpr int kPersistSyncStride = 64;   // words between the arrival counters: 8 that are watched, 16 of groups of workgroups
 constexpr int kPersistTops = 8, kPersistCounters = kPersistTops + 16;
@@ -184,12 +185,17 @@ struct PersistArgs {
   size_t layer_stride;
   float inv_d, eps;
   float* h;
-  h16_t *x, *act;
+  h16_t* x;              // operand that comes in, and the one that goes out (fragment-tiled)
+  // operands between the phases, one of each per block: behind the O projection and behind the block (x_stride elements apart),
+  // of the down projection (act_stride)
+  h16_t *xo, *xr, *act;
+  size_t x_stride, act_stride;
   float *qkv, *part;
-  float* ss[2];          // sums of squares [tile][16]: ss[0] those of the residual that comes in, and of the one that goes out
-  float* ss_in[2];       // the same inside the launch, [16][kPersistGrid]
-  int o_ranges;          // ranges of K in the O projection: 16 or 8; behind several context chunks 12 (two) or 8, by heads
-  int ks_down, dn_batches;
+  float* ss[2];          // sums of squares [tile][rows]: both go out, of the residual ss[0] and of the one before it
+  float* ss_in[2];       // the same [row][kPersistGrid]; ss_in[0] also comes in
+  int qkv_ranges;        // ranges of K in the QKV projection: 16 or 8
+  int o_ranges;          // in the O projection: 16 or 8; behind several context chunks 12 (two) or 8, by heads
+  int ks_down;
   int attn_units;        // B * Hkv * n_chunks
   AttnDecArgs at;        // layer is set by the kernel
   uint32_t* sync;        // kPersistSyncWords, zero at the first launch; the sampler merge clears the counters after every step
@@ -197,11 +203,11 @@ struct PersistArgs {
   int* err_flag;
 };
 struct PersistShape {
-  int m_tiles, head_dim, kt_d, nt_d, nt_gu, n_chunks, pairs;  // pairs: sequences x kv heads
+  int m_tiles, head_dim, kt_d, nt_d, nt_qkv, nt_gu, n_chunks, pairs;  // pairs: sequences x kv heads
+  int down_nb;  // row tiles per workgroup of the down projection's own launch (2, 3 or 4), which tells its ranges of K
 };
 bool decode_persistent_fits(const PersistShape& s);
-// down_nb: row tiles per workgroup of the down projection's own launch (2, 3 or 4), which tells its ranges of K
-void decode_persistent(const PersistArgs& a, int down_nb, hipStream_t st);
+void decode_persistent(const PersistArgs& a, int m_tiles, int down_nb, hipStream_t st);
 
 // ---- packing the live rows of a batch with a stop token into the leading slots ------------------
 // live[0] = number of rows whose stop flag is clear.

@@ -633,6 +633,7 @@ __device__ __forceinline__ void embed_row(const EmbedNextArgs& e, int m, int id,
     for (int i = 0; i < 16; i += 4)
       *reinterpret_cast<v4f*>(e.h + (size_t)m * d + k + i) = v4f{v[i], v[i + 1], v[i + 2], v[i + 3]};
     e.ss_out[(size_t)(k >> 4) * e.Mpad + m] = ss;
+    if (e.ss_rows) e.ss_rows[(size_t)m * kPersistGrid + (k >> 4)] = ss;
   }
   const float tot = block_sum(ss, red);
   const float r = 1.0f / sqrtf(tot / (float)d + e.eps);

@@ -93,6 +93,7 @@ struct RolloutPlan {
   bool persistent;       // the decode step's blocks run as one persistent launch
   uint32_t* sync;        // its counters (kPersistSyncWords)
   float* ss_in;          // its sums of squares
+  void *xo_l, *xr_l, *act_l;  // its operands, one of each per block
   bool samples_alone;    // the decode attention takes every sequence in a workgroup of its own
   int ks_qkv, ks_o, ks_down;       // split-K factors of the decode GEMMs
   int down_nb;                     // weight row tiles per workgroup of the down projection (2 or 4)

@@ -372,7 +372,12 @@ void bf16_plan_rollout_extra(const mtmc_weights* w, RolloutPlan& p, Carver& cv) 
   p.ssB = cv.take<float>((size_t)D.nt_d * Mpad);
   p.rs_buf = cv.take<float>(Mpad);
   p.sync = cv.take<uint32_t>(bf16::kPersistSyncWords);
-  p.ss_in = cv.take<float>(2 * 16 * bf16::kPersistGrid);
+  // what the persistent step hands from phase to phase, a buffer per block (sized for the row tiles it takes)
+  const size_t rows = std::min<size_t>(Mpad, 64), L = w->cfg.n_layers;
+  p.ss_in = cv.take<float>(2 * std::max<size_t>(Mpad, 64) * bf16::kPersistGrid);
+  p.xo_l = cv.take<h16_t>(L * rows * D.d);
+  p.xr_l = cv.take<h16_t>(L * rows * D.d);
+  p.act_l = cv.take<h16_t>(L * rows * D.F);
   if (p.ragged) {
     p.slot_row = cv.take<int>(Mpad);
     p.page_table_c = cv.take<int>(Mpad * p.max_pages);
@@ -472,8 +477,8 @@ bool persistent_shape(const mtmc_weights* w, const Dims& D, const RolloutPlan& p
     for (auto f : {&LayerWeights::attn_norm, &LayerWeights::ffn_norm})
       if (at(L[l].*f) - at(L[l - 1].*f) != stride) return false;
   }
-  return stride >= 0 && bf16::decode_persistent_fits(bf16::PersistShape{p.bt, w->cfg.head_dim, D.kt_d, D.nt_d, D.nt_gu, p.n_chunks,
-                                                                        p.B * D.Hkv});
+  return stride >= 0 && bf16::decode_persistent_fits(bf16::PersistShape{p.bt, w->cfg.head_dim, D.kt_d, D.nt_d, D.nt_qkv, D.nt_gu, p.n_chunks,
+                                                                        p.B * D.Hkv, p.down_nb});
 }
 
 bf16::PersistArgs persistent_args(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, const bf16::AttnDecArgs& at) {
@@ -485,12 +490,15 @@ bf16::PersistArgs persistent_args(const mtmc_weights* w, const Dims& D, const Ro
   a.attn_norm = L[0].attn_norm; a.ffn_norm = L[0].ffn_norm; a.final_norm = w->final_norm;
   a.layer_stride = L.size() > 1 ? (size_t)((const char*)L[1].wqkv - (const char*)L[0].wqkv) : 0;
   a.inv_d = 1.0f / (float)D.d; a.eps = w->cfg.rms_eps;
-  a.h = p.hB; a.x = (h16_t*)p.xB; a.act = (h16_t*)p.a; a.qkv = p.qkv; a.part = p.part; a.ss[0] = p.ssA; a.ss[1] = p.ssB;
-  a.ss_in[0] = p.ss_in; a.ss_in[1] = p.ss_in + 16 * bf16::kPersistGrid;
+  a.h = p.hB; a.x = (h16_t*)p.xB; a.qkv = p.qkv; a.part = p.part; a.ss[0] = p.ssA; a.ss[1] = p.ssB;
+  a.ss_in[0] = p.ss_in; a.ss_in[1] = p.ss_in + (size_t)std::max(p.bt * 16, 64) * bf16::kPersistGrid;
   a.o_ranges = p.n_chunks > 1 ? (p.n_chunks == 2 ? 12 : 8) : (D.kt_nq >= 48 ? 16 : 8);
+  a.qkv_ranges = p.bt > 1 && D.nt_qkv > 256 ? 8 : 16;  // as gemm_dec has them
   a.ks_down = p.ks_down;
-  a.dn_batches = p.down_nb == 3 ? (D.nt_d * 8 + 3 * bf16::kPersistGrid - 1) / (3 * bf16::kPersistGrid) : 1;
   a.attn_units = p.B * D.Hkv * p.n_chunks;
+  const size_t rows = (size_t)p.bt * 16;
+  a.xo = (h16_t*)p.xo_l; a.xr = (h16_t*)p.xr_l; a.act = (h16_t*)p.act_l;
+  a.x_stride = rows * D.d; a.act_stride = rows * D.F;
   a.at = at;
   a.sync = p.sync; a.wait_ticks = 100LL * w->opt_persistent_wait_us; a.err_flag = w->err_flag;
   return a;
@@ -522,7 +530,7 @@ void decode_layers(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, K
     return at;
   };
   if (p.persistent) {
-    bf16::decode_persistent(persistent_args(w, D, p, attention_args(0)), p.down_nb, st);
+    bf16::decode_persistent(persistent_args(w, D, p, attention_args(0)), bt, p.down_nb, st);
     *ss_cur_out = p.ssA;
     *ss_old_out = p.ssB;
     return;
@@ -722,7 +730,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   bf16::add_norm(p.hB, nullptr, 0, 0, 0, w->final_norm, c.rms_eps, (h16_t*)p.xB, B, gp.bt, D.d, w->err_flag, st);
   auto embed_args = [&](const RolloutPlan& q) {
     return bf16::EmbedNextArgs{p.hB, (const bf16_t*)w->embed, D.d, w->layers[0].attn_norm, c.rms_eps, (h16_t*)p.xB,
-                               q.bt * 16, p.ssA, D.V, w->err_flag, p.sync};
+                               q.bt * 16, p.ssA, D.V, w->err_flag, p.sync, p.ss_in};
   };
   // LM head + sampler over `rows` rows of the operand x; `dc` / `ds`: control block and step counter
   auto sample = [&](hipStream_t s, const h16_t* x, int rows, const float* ss_cur, const float* ss_old,
@@ -817,7 +825,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
         launch_set_int(p.d_step + 8, 0, st);
         launch_set_int(p.d_step + 9, 0, st);
         const bf16::EmbedNextArgs embT{p.hT, (const bf16_t*)w->embed, D.d, w->layers[0].attn_norm, c.rms_eps, (h16_t*)p.xT,
-                                       tiles16(rows) * 16, p.ssT, D.V, w->err_flag, nullptr};
+                                       tiles16(rows) * 16, p.ssT, D.V, w->err_flag, nullptr, nullptr};
         sample(st, (const h16_t*)p.xT, rows, nullptr, nullptr, d_ctl + 1, p.d_step + 8, p.cur_ids + (size_t)q0 * ns, embT);
       }
       // the first tokens of the new sequences become operands of the next step (the other slots get again what
@@ -944,7 +952,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     // q: the shape the step runs in (the group's rows, or the slots its live rows were packed into)
     auto embed_args = [&](const RolloutPlan& q) {
       return bf16::EmbedNextArgs{p.hB, (const bf16_t*)w->embed, D.d, w->layers[0].attn_norm, c.rms_eps, (h16_t*)p.xB,
-                                 q.bt * 16, p.ssA, D.V, w->err_flag, p.sync};
+                                 q.bt * 16, p.ssA, D.V, w->err_flag, p.sync, p.ss_in};
     };
     auto sample = [&](hipStream_t s, const float* ss_cur, const float* ss_old, const RolloutPlan& q) {
       bf16::DecGemmArgs lm{};

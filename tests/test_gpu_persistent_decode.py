@@ -1,6 +1,7 @@
-"""Decode steps of up to 16 rows as one persistent launch: the bits of the separate launches, at every split of the work that
+"""Decode steps of up to 64 rows as one persistent launch: the bits of the separate launches, at every split of the work that
 the launch knows (gate / up tiles per workgroup, ranges of the down projection, context chunks, one to four row tiles of the
-QKV projection per workgroup), from one row to a full tile, with empty slots, from two threads, and with a wait that gives up."""
+QKV projection per workgroup, one to four tiles of rows), from one row to full tiles, with empty slots, from two threads, and
+with a wait that gives up."""
 import threading
 
 import numpy as np
@@ -77,11 +78,40 @@ def test_the_bits_of_separate_launches(lib, policy, n_prompts, plen, n_samples, 
     _both(lib, handle, lambda: lib.mtmc_rollout(handle, prompts, n_samples, max_new, 1.0, 3))
 
 
+# more than one tile of rows: which shapes that form takes, and where its units are more than one round
+MANY_ROWS = {
+    "1p5b": SHAPES["1p5b"],
+    "7b": SHAPES["7b"],                                                             # up to 32 rows
+    "qkv-2-rounds": inputs.ModelConfig(2, 1536, 24, 4, 128, 8960, V, dtype="bf16"),  # 512 units of 16 ranges
+    "qkv-3-rounds": inputs.ModelConfig(2, 1536, 28, 4, 128, 8960, V, dtype="bf16"),  # 576 units of 8 ranges
+}
+
+
+@pytest.mark.parametrize("shape,calls", [
+    ("1p5b", [(3, 1, 6, 18), (17, 1100, 1, 5), (2, 2300, 9, 4), (4, 300, 8, 20),   # 18, 17, 18, 32 rows: 1, 3, 3, 2 chunks
+              (11, 127, 3, 4), (5, 700, 8, 18), (6, 20, 8, 12),                     # 33, 40, 48 rows
+              (7, 90, 7, 20), (8, 300, 8, 20), (4, 1500, 16, 3)]),                  # 49, 64, 64 rows
+    ("7b", [(17, 300, 1, 6), (4, 100, 8, 12), (3, 1500, 8, 4)]),
+    ("qkv-2-rounds", [(3, 40, 8, 6), (5, 140, 8, 6), (8, 40, 8, 6)]),
+    ("qkv-3-rounds", [(3, 40, 8, 6), (5, 140, 8, 6), (8, 40, 8, 6)]),
+])
+def test_the_bits_with_several_tiles_of_rows(lib, shape, calls):
+    import torch
+    cfg = MANY_ROWS[shape]
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 2400), inputs.make_weights(cfg, seed=0, std=0.04, gain_std=0.1).blob())
+    try:
+        for n_prompts, plen, n_samples, max_new in calls:
+            prompts = torch.from_numpy(inputs.make_prompts(n_prompts, plen, cfg.vocab, seed=plen)).cuda()
+            _both(lib, handle, lambda: lib.mtmc_rollout(handle, prompts, n_samples, max_new, 1.0, 3))
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
 def test_lengths_stop_tokens_and_empty_slots(lib, policy):
-    """Prompts of different lengths; sequences end, the rest is packed into one tile (from 24 rows and from 160)."""
+    """Prompts of different lengths; sequences end, the rest is packed into fewer tiles (from 24 rows, from 64 and from 160)."""
     import torch
     cfg, handle = policy
-    for n_prompts, n_samples, max_new in ((3, 8, 24), (20, 8, 24)):
+    for n_prompts, n_samples, max_new in ((3, 8, 24), (8, 8, 24), (20, 8, 24)):
         lens = torch.from_numpy(np.random.default_rng(n_prompts).integers(1, 90, n_prompts).astype(np.int32)).cuda()
         prompts = torch.from_numpy(inputs.make_prompts(n_prompts, 90, cfg.vocab, seed=5)).cuda()
         free = lib.mtmc_rollout_ragged(handle, prompts, lens, n_samples, max_new, 1.0, 4)[0].cpu().numpy()
