@@ -344,7 +344,8 @@ const char* mtmc_data_error_string(int bits);
  *   per block.  Results do not depend on it (the same sums in the same order).  The launch needs the whole device at once: it
  *   is used while no other such launch is under way from another stream or thread of the process, by one process per
  *   device, and not while `stream` is being captured; every other step runs as separate launches.  The value is the longest
- *   time in microseconds that a workgroup waits for the others before the launch gives up (MTMC_DATA_STALLED).
+ *   time in microseconds that a workgroup waits for the others before the launch gives up (MTMC_DATA_STALLED).  MTMC_FP32
+ *   generations of few rows of a small model run all of their steps as one such launch.
  */
 #define MTMC_OPT_HIP_GRAPH 1
 #define MTMC_OPT_GEMM_LDS_MIN_BLOCKS 2

@@ -7,6 +7,7 @@
 
 #include "attention_decode.h"
 #include "bf16_kernels.h"
+#include "device_scope.h"
 #include "device_utils.h"
 #include "frag.h"
 
@@ -16,29 +17,7 @@ namespace persist {
 
 constexpr int kHeadDim = 128;
 
-// ---- device-scope accesses
-using Rsrc = __amdgpu_buffer_rsrc_t;
-constexpr int kDeviceScope = 16;  // sc1
-constexpr int kReach = 0x40000000;  // bytes that a descriptor covers; every buffer of a step is smaller
-__device__ __forceinline__ Rsrc rsrc_of(const void* p) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, kReach, 0x00027000);
-}
-__device__ __forceinline__ v4u ld16(Rsrc r, int lane_off, int off) {
-  return __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, off, kDeviceScope));
-}
-__device__ __forceinline__ v4f ld16f(Rsrc r, int lane_off, int off) { return __builtin_bit_cast(v4f, ld16(r, lane_off, off)); }
-__device__ __forceinline__ void st16(Rsrc r, int lane_off, int off, v4u v) {
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, lane_off, off, kDeviceScope);
-}
-__device__ __forceinline__ float ld4(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void st4(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ uint2 ld8(const void* p) {
-  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
-}
-__device__ __forceinline__ void st8(void* p, uint2 v) {
-  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), (uint64_t)v.y << 32 | v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+using namespace device_scope;  // every buffer of a step is smaller than a descriptor's reach
 
 // Weights: read once per step, past what the caches hold for the rest (one row: 64.0 -> 62.7 ms of 63 steps, 16 rows 77.0 ->
 // 74.9, together with the fourth k tile in flight of the gate / up stream).

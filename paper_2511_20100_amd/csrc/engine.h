@@ -77,6 +77,8 @@ struct RolloutPlan {
   float* hB;      // [B, d]
   void* xB;       // [B, d]
   float* logits;  // fp32 path: [B, V]
+  float* sets;    // fp32 path: what the steps of a persistent generation hand on (f32::RolloutArgs), and its stall flag
+  uint32_t* stalled;
   // bf16 path scratch
   float* part;        // split-K partial sums
   void* o_chunks;     // decode-attention output per context chunk: n_chunks tiled fp16 operands [Hq*hd, bt*16]

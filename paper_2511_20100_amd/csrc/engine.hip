@@ -4,6 +4,7 @@
 #include "bf16_kernels.h"
 #include "engine.h"
 #include "kernels.h"
+#include "persistent_turn.h"
 
 namespace mtmc {
 
@@ -93,6 +94,9 @@ RolloutPlan plan_rollout(const mtmc_weights* w, int n_prompts, int prompt_len, i
     p.gu = cv.take<float>((size_t)p.Tmax * 2 * F);
     p.logits = cv.take<float>((size_t)p.B * c.vocab);
     p.ctl = cv.take<bf16::SampleCtl>(1);
+    p.sets = cv.take<float>(f32::kRolloutSets * p.B * f32::rollout_row_floats(c.n_layers, c.d_model, c.n_q_heads, c.n_kv_heads, c.head_dim,
+                                                                         c.d_ffn, c.vocab));
+    p.stalled = cv.take<uint32_t>(1);
   } else {
     bf16_plan_rollout_extra(w, p, cv);
   }
@@ -306,6 +310,38 @@ int f32_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts,
     sample(s);
   };
   sample(st);
+  if (p.max_new < 2) return MTMC_OK;
+  // all steps as one launch where it fits, the turn is free and the caller is not capturing the stream
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
+  else if (cs == hipStreamCaptureStatusNone && w->opt_persistent_wait_us > 0) {
+    const auto& L = w->layers;
+    auto at = [](const void* q) { return (const char*)q; };
+    const ptrdiff_t stride = L.size() > 1 ? at(L[1].wqkv) - at(L[0].wqkv) : 0;
+    bool even = stride >= 0;
+    for (size_t l = 1; l < L.size(); ++l) {
+      for (auto f : {&LayerWeights::wqkv, &LayerWeights::wo, &LayerWeights::wgu, &LayerWeights::wdown})
+        even = even && at(L[l].*f) - at(L[l - 1].*f) == stride;
+      for (auto f : {&LayerWeights::attn_norm, &LayerWeights::ffn_norm}) even = even && at(L[l].*f) - at(L[l - 1].*f) == stride;
+    }
+    f32::RolloutArgs a{};
+    a.n_layers = c.n_layers; a.B = p.B; a.d = d; a.Hq = c.n_q_heads; a.F = c.d_ffn; a.V = V; a.first_step = 1; a.last_step = p.max_new;
+    a.wqkv = (const float*)L[0].wqkv; a.wo = (const float*)L[0].wo; a.wgu = (const float*)L[0].wgu; a.wdown = (const float*)L[0].wdown;
+    a.attn_norm = L[0].attn_norm; a.ffn_norm = L[0].ffn_norm; a.layer_stride = (size_t)stride;
+    a.final_norm = w->final_norm; a.lm_head = (const float*)w->lm_head; a.embed = (const float*)w->embed;
+    a.cos = w->rope_cos; a.sin = w->rope_sin; a.eps = c.rms_eps;
+    a.pos_base = p.prompt_len - 1; a.row_pos = ragged ? p.row_pos : nullptr; a.pool = pool;
+    a.h0 = p.hB; a.sets = p.sets;
+    a.row_floats = (int)f32::rollout_row_floats(c.n_layers, d, c.n_q_heads, c.n_kv_heads, c.head_dim, c.d_ffn, V);
+    a.ctl = ctl; a.cur_ids = p.cur_ids; a.err_flag = w->err_flag; a.stalled = p.stalled;
+    a.wait_ticks = 100LL * w->opt_persistent_wait_us;
+    PersistentTurn turn;
+    if (even && f32::rollout_fits(a) && turn.take(w->device, st)) {
+      f32::rollout(a, st);
+      MTMC_HIP_CHECK(hipGetLastError());
+      return MTMC_OK;
+    }
+  }
   // a dozen small launches per step: replayed as a graph they follow each other without the host (capturing one takes
   // about as long as a few steps launched one by one)
   StepGraph graph;

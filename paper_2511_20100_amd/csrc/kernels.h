@@ -73,6 +73,8 @@ namespace f32 {
 void embed(float* h, const int* ids, int T, const float* E, int d, int vocab, int* err_flag,
            hipStream_t st);
 void rmsnorm(float* x, const float* h, const float* gain, float eps, int T, int d, hipStream_t st);
+// whether a product of M rows and N columns takes the form for few rows
+bool few_rows(int M, int N);
 // C[M, N] (ldc) = or += A[M, K] (lda) * W[N, K]^T      (K % 16 == 0)
 // form_rows (here and below; 0: M) chooses between the forms for few and for many rows, which add up in different orders: a
 // call that evaluates only some of a longer one's rows passes the longer one's count and gets the same bits.
@@ -101,6 +103,31 @@ void swiglu(float* a, const float* gu, int T, int F, hipStream_t st);  // gu [T,
 // samples stop_id sets its flag and out_lens[b] = step + 1.
 void sample(const float* logits, int B, int V, const bf16::SampleCtl* ctl, int* d_step, int* cur_ids, float* h,
             const float* E, int d, int* err_flag, hipStream_t st);
+// The steps first_step .. last_step - 1 of a generation as one launch (rollout_f32.hip): the blocks, the LM head and the sampler
+// of every step, with the results of the launches of their own.  h0 [B, d]: the residual that the first of them starts from.
+constexpr int kRolloutGrid = 256;  // one workgroup per CU; they wait for each other
+constexpr int kRolloutSets = 3;
+struct RolloutArgs {
+  int n_layers, B, d, Hq, F, V, first_step, last_step;
+  // weights of block 0; those of block l lie l * layer_stride bytes behind
+  const float *wqkv, *wo, *wgu, *wdown, *attn_norm, *ffn_norm;
+  size_t layer_stride;
+  const float *final_norm, *lm_head, *embed, *cos, *sin;
+  float eps;
+  int pos_base;
+  const int* row_pos;
+  KvPool pool;
+  float* h0;
+  float* sets;     // kRolloutSets x [B, row_floats]
+  int row_floats;  // rollout_row_floats()
+  const bf16::SampleCtl* ctl;
+  int *cur_ids, *err_flag;
+  uint32_t* stalled;
+  long long wait_ticks;  // of the 100 MHz clock
+};
+size_t rollout_row_floats(int n_layers, int d, int Hq, int Hkv, int hd, int F, int V);
+bool rollout_fits(const RolloutArgs& a);
+void rollout(const RolloutArgs& a, hipStream_t st);
 // Teacher-forced scoring from materialised logits [R, V].  Row r is position
 // i = first + (row0 + r) % n_scored of sequence n = seq0 + (row0 + r) / n_scored; its target is
 // seqs[n, i + 1] and its output slot [n, i] of the [*, S - 1] outputs.

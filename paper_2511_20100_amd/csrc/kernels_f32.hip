@@ -4,6 +4,7 @@
 
 #include "bf16_kernels.h"
 #include "device_utils.h"
+#include "f32_device.h"
 #include "kernels.h"
 
 namespace mtmc {
@@ -350,72 +351,34 @@ __global__ __launch_bounds__(256) void k_gemm(float* C, int ldc, const float* A,
 // is issued at once, and what bounds the launch is one trip to memory.  (8 rows x 256 columns x 688 on the 64x64 tile: 4
 // workgroups and 43 serial trips through a barrier, 49 us; here 64 wavefronts, 4-5 us.)  The row norm in front of a
 // product and the SwiGLU behind it are part of the launch.
-//   ROWS_NORM    A is the residual: row m is scaled by gain[k] and, after the sum, by 1 / rms of the row
-//   ROWS_SWIGLU  weight rows n and N + n are gate and up of output column n: C = silu(gate) * up
-// 2 HALF values per lane: lanes OFF apart exchange halves and add, then OFF / 2 apart, ... down to one value per lane,
-// the one whose index the lane's bits from OFF downwards spell
-template <int HALF, int OFF, int N>
-__device__ __forceinline__ void fold_lanes(float (&v)[N], int lane) {
-  const bool hi = lane & OFF;
-#pragma unroll
-  for (int i = 0; i < HALF; ++i) {
-    const float send = hi ? v[i] : v[i + HALF];
-    v[i] = (hi ? v[i + HALF] : v[i]) + __shfl_xor(send, OFF, 64);
-  }
-  if constexpr (HALF > 1) fold_lanes<HALF / 2, OFF / 2>(v, lane);
-}
-enum { ROWS_ADD = 1, ROWS_NORM = 2, ROWS_SWIGLU = 4 };
 template <int MODE>
 __global__ __launch_bounds__(256) void k_gemm_rows(float* C, int ldc, const float* A, int lda, const float* W, int M, int N,
                                                    int K, const float* gain, float eps) {
-  constexpr int MR = 8, NC = 4, NO = (MODE & ROWS_SWIGLU) ? 2 : 4;  // output columns per wavefront
+  using Tile = RowsTile<MODE>;
+  constexpr int MR = Tile::MR, NC = Tile::NC;
+  Tile t;
   const int lane = threadIdx.x & 63;
-  const int n0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * NO, m0 = blockIdx.y * MR;
+  const int n0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * t.columns(), m0 = blockIdx.y * MR;
   if (n0 >= N) return;
   const float* ap[MR];
   const float* wp[NC];
 #pragma unroll
   for (int i = 0; i < MR; ++i) ap[i] = A + (size_t)min(m0 + i, M - 1) * lda;
 #pragma unroll
-  for (int c = 0; c < NC; ++c) wp[c] = W + (size_t)(min(n0 + c % NO, N - 1) + (c / NO) * N) * K;
-  float v[NC * MR] = {}, ss[MR] = {};
+  for (int c = 0; c < NC; ++c) wp[c] = W + (size_t)t.weight_row(n0, c, N) * K;
   for (int k = lane * 4; k < K; k += 256) {
-    float4 a[MR], w[NC];
+    float4 a[MR], w[NC], g = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int c = 0; c < NC; ++c) w[c] = *(const float4*)(wp[c] + k);
 #pragma unroll
     for (int i = 0; i < MR; ++i) a[i] = *(const float4*)(ap[i] + k);
-    if (MODE & ROWS_NORM) {
-      const float4 g = *(const float4*)(gain + k);
-#pragma unroll
-      for (int i = 0; i < MR; ++i) {
-        ss[i] += (a[i].x * a[i].x + a[i].y * a[i].y) + (a[i].z * a[i].z + a[i].w * a[i].w);
-        a[i].x *= g.x; a[i].y *= g.y; a[i].z *= g.z; a[i].w *= g.w;
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int i = 0; i < MR; ++i)
-        v[c * MR + i] += (a[i].x * w[c].x + a[i].y * w[c].y) + (a[i].z * w[c].z + a[i].w * w[c].w);
+    if (MODE & ROWS_NORM) g = *(const float4*)(gain + k);
+    t.add(a, w, g);
   }
-  fold_lanes<16, 32>(v, lane);
-  float sum = v[0] + __shfl_xor(v[0], 1, 64);
-  const int idx = lane >> 1;  // the sum this lane ended up with: the first exchange decided its highest bit
-  const int c = idx / MR, i = idx % MR, m = m0 + i;
-  if (MODE & ROWS_NORM) {
-    fold_lanes<4, 32>(ss, lane);
-    float t = ss[0];
-#pragma unroll
-    for (int off = 4; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
-    t = __shfl(t, i * 8, 64);  // row i's total sits in lanes 8 i .. 8 i + 7
-    sum *= 1.0f / sqrtf(t / (float)K + eps);
-  }
-  if (MODE & ROWS_SWIGLU) {
-    const float up = __shfl_xor(sum, 32, 64);  // columns 2 and 3 (upper lanes) are the up rows of columns 0 and 1
-    if (lane < 32 && !(lane & 1) && m < M && n0 + c < N) C[(size_t)m * ldc + n0 + c] = sum / (1.0f + expf(-sum)) * up;
-  } else if (!(lane & 1) && m < M && n0 + c < N) {
-    float* o = C + (size_t)m * ldc + n0 + c;
+  const float sum = t.finish(lane, K, eps);
+  const int m = m0 + Tile::row(lane), n = n0 + Tile::column(lane);
+  if (t.owns(lane) && m < M && n < N) {
+    float* o = C + (size_t)m * ldc + n;
     *o = (MODE & ROWS_ADD) ? *o + sum : sum;
   }
 }
@@ -423,7 +386,7 @@ __global__ __launch_bounds__(256) void k_gemm_rows(float* C, int ldc, const floa
 // half the CUs and the rows are few.  128 rows x 512 columns x 256: 18 us in 16 tiles, 6 us here.  At the upper end, 512 rows,
 // whole scoring passes of two blocks took (tiles, and these forms where the rule gives them): d 256 308 -> 155 us, d 512 505 ->
 // 261, d 960 (where the wider products stay on tiles) 956 -> 614; at 1024 rows the tiles have their blocks.
-static bool few_rows(int M, int N) { return M <= 512 && (M + 63) / 64 * ((N + 63) / 64) < 128; }
+bool few_rows(int M, int N) { return M <= 512 && (M + 63) / 64 * ((N + 63) / 64) < 128; }
 template <int MODE>
 static void launch_rows(float* C, int ldc, const float* A, int lda, const float* W, int M, int N, int K, const float* gain,
                         float eps, hipStream_t st) {
@@ -466,12 +429,6 @@ void norm_swiglu(float* a, const float* H, const float* gain, float eps, float* 
 // =====================================================================================
 // rotary embedding + KV page write; attention over the pages
 // =====================================================================================
-__device__ __forceinline__ float* page_ptr(const KvPool& pool, int layer, int which, int page, int g) {
-  return (float*)pool.base +
-         ((((size_t)layer * 2 + which) * pool.n_pages + page) * pool.n_kv_heads + g) *
-             (size_t)(kPageTokens * pool.head_dim);
-}
-
 __global__ void k_rope_kv_write(float* qkv, int Hq, int Hkv, int hd, const float* cos,
                                 const float* sin, TokMap map, KvPool pool, int layer) {
   const int t = blockIdx.x;
@@ -561,128 +518,23 @@ void attention(float* o, const float* qkv, int T, int Hq, int Hkv, int hd, TokMa
   k_attention<<<dim3(T, Hq), 128, 0, st>>>(o, qkv, Hq, Hkv, hd, map, pool, layer);
 }
 
-// Decode form (one token per sequence): rotary embedding, append and attention in one launch.  One block of 256 threads
-// per (sequence, kv head, up to kDecHeads of its query heads): the new key and value are used from LDS (the first block
-// of a kv head also writes them to their page).  Keys are taken 256 at a time: every thread scores one for all heads, then
-// wavefront h does the online softmax of head h and adds up its values (lane = dims 4 c .. + 3 and a part of the keys):
-// two barriers per 256 keys.
-constexpr int kDecHeads = 4;
 template <int HD>
 __global__ __launch_bounds__(256) void k_attention_dec(float* o, const float* qkv, int Hq, int Hkv, const float* cos,
                                                        const float* sin, TokMap map, KvPool pool, int layer) {
-  constexpr int HALF = HD / 2, C4 = HD / 4, PARTS = 64 / C4;  // 4 parts at 64 dims, 2 at 128
-  __shared__ __attribute__((aligned(16))) float q[kDecHeads][HD];
-  __shared__ __attribute__((aligned(16))) float kn[HD], vn[HD];
-  __shared__ float p[kDecHeads][256];
-  __shared__ __attribute__((aligned(16))) float part[PARTS][kDecHeads][HD];
-  __shared__ float s_l[kDecHeads];
+  __shared__ AttnDecLds<HD> sm;
   const int G = Hq / Hkv, groups = (G + kDecHeads - 1) / kDecHeads;
   const int t = blockIdx.x, g = blockIdx.y / groups, j0 = (blockIdx.y % groups) * kDecHeads;
-  const int nh = min(kDecHeads, G - j0);
-  const int pos = tok_pos(map, t), tid = threadIdx.x;
   const int* table = pool.page_table + (size_t)tok_seq(map, t) * map.row_stride * pool.max_pages;
   const float* base = qkv + (size_t)t * (Hq + 2 * Hkv) * HD;
-  const float* cs = cos + (size_t)pos * HALF;
-  const float* sn = sin + (size_t)pos * HALF;
-  for (int e = tid; e < kDecHeads * HALF; e += 256) {
-    const int h = e / HALF, i = e % HALF;
-    float lo = 0.f, hi = 0.f;
-    if (h < nh) {
-      const float* w = base + (size_t)(g * G + j0 + h) * HD;
-      lo = w[i];
-      hi = w[i + HALF];
-    }
-    q[h][i] = lo * cs[i] - hi * sn[i];
-    q[h][i + HALF] = hi * cs[i] + lo * sn[i];
-  }
-  const int page = table[pos / kPageTokens], slot = pos % kPageTokens;
-  if (tid < HALF) {
-    const float* w = base + (size_t)(Hq + g) * HD;
-    const float lo = w[tid], hi = w[tid + HALF];
-    const float ra = lo * cs[tid] - hi * sn[tid], rb = hi * cs[tid] + lo * sn[tid];
-    kn[tid] = ra;
-    kn[tid + HALF] = rb;
-    if (j0 == 0) {
-      float* kp = page_ptr(pool, layer, 0, page, g) + (size_t)slot * HD;
-      kp[tid] = ra;
-      kp[tid + HALF] = rb;
-    }
-  } else if (tid >= 64 && tid < 64 + HALF) {
-    const float* w = base + (size_t)(Hq + Hkv + g) * HD;
-    for (int i = tid - 64; i < HD; i += HALF) {
-      vn[i] = w[i];
-      if (j0 == 0) page_ptr(pool, layer, 1, page, g)[(size_t)slot * HD + i] = w[i];
-    }
-  }
-  __syncthreads();
-  const float scale = 1.0f / sqrtf((float)HD);
-  const int lane = tid & 63, ah = tid >> 6, ac = lane / PARTS, apart = lane % PARTS;
-  float m = -INFINITY, l = 0.f;  // of head ah
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  const int n_ctx = pos + 1;
-  for (int c0 = 0; c0 < n_ctx; c0 += 256) {
-    const int key = c0 + tid;
-    if (key < n_ctx) {
-      const float* kp = key == pos ? kn
-                                   : page_ptr(pool, layer, 0, table[key / kPageTokens], g) + (size_t)(key % kPageTokens) * HD;
-      float d[kDecHeads] = {};
-#pragma unroll
-      for (int c = 0; c < C4; ++c) {
-        const float4 kv = *(const float4*)(kp + 4 * c);
-#pragma unroll
-        for (int h = 0; h < kDecHeads; ++h) {
-          const float4 qv = *(const float4*)(&q[h][4 * c]);
-          d[h] += (qv.x * kv.x + qv.y * kv.y) + (qv.z * kv.z + qv.w * kv.w);
-        }
-      }
-#pragma unroll
-      for (int h = 0; h < kDecHeads; ++h) p[h][tid] = d[h] * scale;
-    } else {
-#pragma unroll
-      for (int h = 0; h < kDecHeads; ++h) p[h][tid] = -INFINITY;
-    }
-    __syncthreads();
-    float s[4], mx = m;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      s[i] = p[ah][lane + 64 * i];
-      mx = fmaxf(mx, s[i]);
-    }
-    mx = wave_max(mx);
-    const float corr = expf(m - mx);  // exp(-inf) = 0 on the first chunk
-    float sum = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float e = c0 + lane + 64 * i < n_ctx ? expf(s[i] - mx) : 0.f;
-      p[ah][lane + 64 * i] = e;  // read back by this wavefront only
-      sum += e;
-    }
-    l = l * corr + wave_sum(sum);
-    m = mx;
-    acc.x *= corr; acc.y *= corr; acc.z *= corr; acc.w *= corr;
-    __builtin_amdgcn_wave_barrier();
-    const int n_here = min(256, n_ctx - c0);
-#pragma unroll 4
-    for (int i = apart; i < n_here; i += PARTS) {
-      const int kk = c0 + i;
-      const float* vp = kk == pos ? vn
-                                  : page_ptr(pool, layer, 1, table[kk / kPageTokens], g) + (size_t)(kk % kPageTokens) * HD;
-      const float4 vv = *(const float4*)(vp + 4 * ac);
-      const float w = p[ah][i];
-      acc.x = fmaf(w, vv.x, acc.x); acc.y = fmaf(w, vv.y, acc.y); acc.z = fmaf(w, vv.z, acc.z); acc.w = fmaf(w, vv.w, acc.w);
-    }
-    __syncthreads();  // the scores make room for the next keys'
-  }
-  if (lane == 0) s_l[ah] = l;
-  *(float4*)(&part[apart][ah][4 * ac]) = acc;
-  __syncthreads();
-  for (int e = tid; e < nh * HD; e += 256) {
-    const int h = e / HD, c = e % HD;
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < PARTS; ++w) sum += part[w][h][c];
-    o[(size_t)t * Hq * HD + (size_t)(g * G + j0 + h) * HD + c] = sum / s_l[h];
-  }
+  const float* q = base + (size_t)(g * G + j0) * HD;
+  const float* k = base + (size_t)(Hq + g) * HD;
+  const float* v = base + (size_t)(Hq + Hkv + g) * HD;
+  float* out = o + (size_t)t * Hq * HD + (size_t)(g * G + j0) * HD;
+  const int pos = tok_pos(map, t);
+  const AttnDecHeld<HD> held = attention_dec_hold<HD>(threadIdx.x, pos, table, cos, sin, pool, layer, g);
+  attention_dec_unit<HD>(sm, threadIdx.x, min(kDecHeads, G - j0), j0 == 0, pos, table, pool, layer, g, held,
+                         [&](int h, int i) { return q[h * HD + i]; }, [&](int i) { return k[i]; }, [&](int i) { return v[i]; },
+                         [&](int h, int c, float x) { out[h * HD + c] = x; });
 }
 void attention_dec(float* o, const float* qkv, int B, int Hq, int Hkv, int hd, const float* cos, const float* sin, TokMap map,
                    KvPool pool, int layer, hipStream_t st) {
@@ -694,67 +546,28 @@ void attention_dec(float* o, const float* qkv, int B, int Hq, int Hkv, int hd, c
 // =====================================================================================
 // sampling and scoring from materialised logits
 // =====================================================================================
-constexpr int kSampleThreads = 1024;  // a row is one workgroup's: 4096 logits are one trip of four per thread
+constexpr int kSampleThreads = kSampleWaves * 64;  // a row is one workgroup's: 4096 logits are one trip of four per thread
 __global__ __launch_bounds__(kSampleThreads) void k_sample(const float* logits, int V, const bf16::SampleCtl* ctlp,
                                                            int* d_step, int* cur_ids, float* h, const float* E, int d,
                                                            int* err_flag) {
-  __shared__ int s_tok;
-  __shared__ Lse s_lse[kSampleThreads / 64];
-  __shared__ Best s_best[kSampleThreads / 64];
+  __shared__ SampleLds sm;
   const int b = blockIdx.x;
   const bf16::SampleCtl ctl = *ctlp;
   const int step = *d_step;
   const float* z = logits + (size_t)b * V;
-  Lse lse = lse_empty();
-  Best best = best_empty();
+  SampleState st;
   for (int v4 = threadIdx.x; v4 * 4 < V; v4 += blockDim.x) {
-    uint4 r = make_uint4(0, 0, 0, 0);
-    if (!ctl.greedy) r = philox4x32_10(make_uint4((uint32_t)v4, (uint32_t)step, ctl.seq_offset + b, 0u), ctl.key0, ctl.key1);
-    const uint32_t rr[4] = {r.x, r.y, r.z, r.w};
+    float zs[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int v = v4 * 4 + k;
-      if (v >= V) break;
-      const float zt = ctl.greedy ? z[v] : z[v] * ctl.inv_temp;
-      lse_push(lse, zt);
-      const float y = ctl.greedy ? zt : zt + gumbel_from_bits(rr[k]);
-      best = best_merge(best, Best{y, v});
-    }
+    for (int k = 0; k < 4; ++k) zs[k] = z[min(v4 * 4 + k, V - 1)];
+    st.push(zs, sample_noise(v4, ctl, step, b), v4, V, ctl);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    Lse ol = {__shfl_xor(lse.m, o, 64), __shfl_xor(lse.s, o, 64)};
-    Best ob = {__shfl_xor(best.y, o, 64), __shfl_xor(best.idx, o, 64)};
-    lse = lse_merge(lse, ol);
-    best = best_merge(best, ob);
-  }
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane == 0) { s_lse[wid] = lse; s_best[wid] = best; }
+  st.publish(sm, threadIdx.x >> 6, threadIdx.x & 63);
   __syncthreads();
+  int tok = 0;
+  if (threadIdx.x < 64) tok = sample_row(sm, ctl, b, step, V, threadIdx.x, cur_ids, err_flag, [&](int v) { return z[v]; });
   if (threadIdx.x == 0) {
-    for (int i = 1; i < kSampleThreads / 64; ++i) { lse = lse_merge(lse, s_lse[i]); best = best_merge(best, s_best[i]); }
-    // no logit compared greater than -inf: the token is out of range, which its embedding reports
-    const float zb = best.idx < V ? z[best.idx] : NAN;
-    const float zt = ctl.greedy ? zb : zb * ctl.inv_temp;
-    int tok = best.idx;
-    float lp = zt - (lse.m + logf(lse.s));
-    if (ctl.done) {
-      if (ctl.done[b]) {
-        tok = ctl.stop_id;
-        lp = 0.f;
-      } else if (tok == ctl.stop_id) {
-        ctl.done[b] = 1;
-        ctl.out_lens[b] = step + 1;
-      }
-    }
-    cur_ids[b] = tok;
-    ctl.out_ids[(size_t)b * ctl.max_new + step] = tok;
-    ctl.out_logprobs[(size_t)b * ctl.max_new + step] = lp;
-    if (tok < 0 || tok >= V) {
-      atomicOr(err_flag, 1);
-      tok = tok < 0 ? 0 : V - 1;
-    }
-    s_tok = tok;
+    sm.tok = tok;
     // the last row to get here advances the step counter: by then every row has read it (d_step[1] counts
     // arrivals and is left at zero for the next launch)
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -764,7 +577,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample(const float* logits, 
     }
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < d; c += blockDim.x) h[(size_t)b * d + c] = E[(size_t)s_tok * d + c];
+  for (int c = threadIdx.x; c < d; c += blockDim.x) h[(size_t)b * d + c] = E[(size_t)sm.tok * d + c];
 }
 void sample(const float* logits, int B, int V, const bf16::SampleCtl* ctl, int* d_step, int* cur_ids, float* h,
             const float* E, int d, int* err_flag, hipStream_t st) {
