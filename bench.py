@@ -403,7 +403,8 @@ def main() -> int:
                     "attainable": hbm_attainable,
                     "traffic": gate_up_traffic_from_profile(args.workload),
                     "kernel": "gate/up projection of a decode step, one launch per layer (k_gemm_dec<..., SWIGLU> up to "
-                              "64 rows, k_gemm_rows128<..., SWIGLU> at 65..128)",
+                              "64 rows, k_gemm_rows128<..., SWIGLU> at 65..128); up to 64 rows on the timed steps only, "
+                              "every 32nd: the others run all blocks as one launch",
                     "bytes_per_launch": gate_up_bytes, "us_per_launch": k_us, "timed_launches": k_launches,
                     "empty_event_pair_us": 1e3 * k_empty_ms}
     else:
