@@ -1,4 +1,5 @@
 // Decode-step kernels of the bf16 path: six launches per residual block.
+// (up to 64 rows, where decode_persistent_fits() says so, the same sums run as one launch: decode_persistent.hip)
 //
 //   qkv   = W_qkv x'                      k_gemm_dec<STORE>
 //   o     = attention(rope(q), cache)     k_attn_dec   (also rotates/writes the new K, V; output per context chunk)
