@@ -335,6 +335,7 @@ int f32_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts,
     a.row_floats = (int)f32::rollout_row_floats(c.n_layers, d, c.n_q_heads, c.n_kv_heads, c.head_dim, c.d_ffn, V);
     a.ctl = ctl; a.cur_ids = p.cur_ids; a.err_flag = w->err_flag; a.stalled = p.stalled;
     a.wait_ticks = 100LL * w->opt_persistent_wait_us;
+    static_assert(f32::kRolloutGrid == PersistentTurn::kWorkgroups, "");
     PersistentTurn turn;
     if (even && f32::rollout_fits(a) && turn.take(w->device, st)) {
       f32::rollout(a, st);

@@ -466,6 +466,7 @@ void prefill_layers(const mtmc_weights* w, const Dims& D, float* h, h16_t* x, fl
 
 // The decode step's blocks as one launch, where its shape fits and the weights lie as it reads them (bf16_store_weights carves
 // every block alike; the stride is checked all the same).
+static_assert(bf16::kPersistGrid == PersistentTurn::kWorkgroups, "");
 bool persistent_shape(const mtmc_weights* w, const Dims& D, const RolloutPlan& p) {
   if (w->opt_persistent_wait_us <= 0 || p.max_new < 2) return false;
   const auto& L = w->layers;

@@ -5,7 +5,7 @@
 // or streams, and a call that does not get it runs the same step as separate launches, which give the same bits.
 //   - threads: a mutex that is only ever tried;
 //   - streams: an event behind the last launch of the turn before.  While that is still at work, only the stream it went to
-//     may take the next turn (and waits for it on the device);
+//     may take the next turn (and waits for it on the device); where the runtime does not say, nobody;
 //   - processes: the first that asks for a device keeps it until it ends (an abstract socket name of the host's network
 //     namespace, given back by the kernel whatever ends the process).
 #pragma once
@@ -16,6 +16,7 @@ namespace mtmc {
 
 class PersistentTurn {
  public:
+  static constexpr int kWorkgroups = 256;  // of a persistent launch, one per CU
   PersistentTurn() = default;
   PersistentTurn(const PersistentTurn&) = delete;
   PersistentTurn& operator=(const PersistentTurn&) = delete;

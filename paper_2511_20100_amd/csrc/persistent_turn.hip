@@ -11,8 +11,6 @@
 
 #include <mutex>
 
-#include "bf16_kernels.h"
-
 namespace mtmc {
 namespace {
 
@@ -23,6 +21,20 @@ struct DeviceTurn {
   hipStream_t stream = nullptr;
   bool recorded = false;
 };
+// Another thread may be capturing a stream in global mode, which refuses other threads' queries of an event and can end with
+// them.  What a turn asks is no part of such a capture.
+class OutsideCaptures {
+ public:
+  OutsideCaptures() { swap(); }
+  OutsideCaptures(const OutsideCaptures&) = delete;
+  OutsideCaptures& operator=(const OutsideCaptures&) = delete;
+  ~OutsideCaptures() { swap(); }
+
+ private:
+  void swap() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+};
+
 constexpr int kMaxDevices = 64;
 DeviceTurn g_turns[kMaxDevices];  // events stay until the process ends
 
@@ -51,32 +63,43 @@ bool whole_device(hipStream_t st) {
   if (hipExtStreamGetCUMask(st, 16, mask) != hipSuccess) return false;
   int open = 0;
   for (uint32_t m : mask) open += __builtin_popcount(m);
-  return open >= bf16::kPersistGrid;
+  return open >= PersistentTurn::kWorkgroups;
 }
 
 bool usable(DeviceTurn& t, int device) {
   if (t.asked) return t.usable;
   t.asked = true;
   int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < bf16::kPersistGrid)
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < PersistentTurn::kWorkgroups)
     return false;
   if (hipEventCreateWithFlags(&t.last, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) return false;
   t.usable = lease_device(device);
   return t.usable;
 }
 
+// Whether the launches of the latest turn have ended, or st (theirs) waits for them.  Any other answer than "ended" or "not yet"
+// says nothing about them: they may be under way.
+bool clear_for(DeviceTurn& t, hipStream_t st) {
+  if (!t.recorded) return true;
+  const hipError_t e = hipEventQuery(t.last);
+  if (e == hipSuccess) return true;
+  (void)hipGetLastError();
+  if (e != hipErrorNotReady || t.stream != st) return false;
+  if (hipStreamWaitEvent(st, t.last, 0) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
 }  // namespace
 
 bool PersistentTurn::take(int device, hipStream_t st) {
   if (held_) return true;
-  if (device < 0 || device >= kMaxDevices || !whole_device(st)) return false;
+  if (device < 0 || device >= kMaxDevices) return false;
+  OutsideCaptures outside;
+  if (!whole_device(st)) return false;
   DeviceTurn& t = g_turns[device];
   if (!t.mu.try_lock()) return false;
-  bool ok = usable(t, device);
-  if (ok && t.recorded && hipEventQuery(t.last) == hipErrorNotReady)
-    ok = t.stream == st && hipStreamWaitEvent(st, t.last, 0) == hipSuccess;
-  (void)hipGetLastError();
-  if (!ok) {
+  if (!usable(t, device) || !clear_for(t, st)) {
     t.mu.unlock();
     return false;
   }
@@ -87,9 +110,11 @@ bool PersistentTurn::take(int device, hipStream_t st) {
 
 void PersistentTurn::release() {
   if (!held_) return;
+  OutsideCaptures outside;
   DeviceTurn& t = *(DeviceTurn*)held_;
   t.recorded = hipEventRecord(t.last, st_) == hipSuccess;
-  if (!t.recorded) (void)hipStreamSynchronize(st_);
+  // no event to wait for: wait here, or nobody takes a turn any more
+  if (!t.recorded && hipStreamSynchronize(st_) != hipSuccess) t.usable = false;
   t.stream = st_;
   t.mu.unlock();
   held_ = nullptr;
