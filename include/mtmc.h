@@ -277,8 +277,10 @@ int mtmc_ppo_clip_loss_static(const float* new_logprobs, const float* old_logpro
  *                         had to be clamped to +-65504 (a NaN becomes -65504) where it is stored as fp16, or
  *                         every logit of a row was NaN (token 0 is then reported).  Outputs of the calls
  *                         since the last poll are unreliable.
- *   MTMC_DATA_STALLED     MTMC_BF16: a persistent decode launch gave up a wait (MTMC_OPT_PERSISTENT_DECODE); the
- *                         outputs of that rollout are wrong.
+ *   MTMC_DATA_STALLED     a persistent launch waited longer than the limit that the caller set with
+ *                         MTMC_OPT_PERSISTENT_DECODE; the outputs of that rollout are right, it took longer.
+ *   MTMC_DATA_UNFINISHED  a persistent launch whose workgroups were all there has ended all the same, after a minute; the outputs of
+ *                         that rollout are wrong.
  * mtmc_data_error_string returns the text for a set of bits (valid until the thread's next call of it).
  */
 #define MTMC_DATA_TOKEN_ID   1
@@ -287,6 +289,7 @@ int mtmc_ppo_clip_loss_static(const float* new_logprobs, const float* old_logpro
 #define MTMC_DATA_FP16_RANGE 8
 #define MTMC_DATA_PREFIX     16
 #define MTMC_DATA_STALLED    32
+#define MTMC_DATA_UNFINISHED 64
 /*
  * Host logic of the rollout that takes in prompts as it runs (MTMC_OPT_ADMIT_PROMPTS), exposed so that it can be
  * checked without a GPU; makes no GPU call.  Which of the call's remaining prompts join the batch at one look:
@@ -339,13 +342,15 @@ const char* mtmc_data_error_string(int bits);
  *   of the fp32 sums (step 0 of a prompt that joins is sampled in a smaller batch, the packed batch runs other
  *   tilings): about 1e-3 in a log-probability, an id can differ where two candidates are that close.  Not used
  *   when `stream` is being captured, without a stop token, or with a cached prefix.
- *   MTMC_OPT_PERSISTENT_DECODE (default 10 000 000, 0 = off): MTMC_BF16 decode steps of up to 64 rows run all blocks as
+ *   MTMC_OPT_PERSISTENT_DECODE (default 2 000, 0 = off): MTMC_BF16 decode steps of up to 64 rows run all blocks as
  *   one launch of one workgroup per CU, whose workgroups wait for each other between phases, instead of six launches
  *   per block.  Results do not depend on it (the same sums in the same order).  The launch needs the whole device at once: it
  *   is used while no other such launch is under way from another stream or thread of the process, by one process per
- *   device, and not while `stream` is being captured; every other step runs as separate launches.  The value is the longest
- *   time in microseconds that a workgroup waits for the others before the launch gives up (MTMC_DATA_STALLED).  MTMC_FP32
- *   generations of few rows of a small model run all of their steps as one such launch.
+ *   device, and not while `stream` is being captured; every other step runs as separate launches.  MTMC_FP32 generations of
+ *   few rows of a small model run all of their steps as one such launch.  The value is the longest time in microseconds that
+ *   such a launch waits for a place on the device for all of its workgroups (1: not at all).  Where other work keeps it from that, the
+ *   work is done by the workgroups that do get a place, with the same results, slower.  A caller that has set a
+ *   value is told (MTMC_DATA_STALLED).
  */
 #define MTMC_OPT_HIP_GRAPH 1
 #define MTMC_OPT_GEMM_LDS_MIN_BLOCKS 2

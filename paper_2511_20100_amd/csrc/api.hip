@@ -92,7 +92,8 @@ extern "C" int mtmc_weights_create(const mtmc_config* cfg, const void* blob, siz
   w->opt_lds_min_blocks = 32;
   w->opt_stop_poll = 32;
   w->opt_admit = 1;
-  w->opt_persistent_wait_us = 10000000;
+  w->opt_persistent_wait_us = 2000;
+  w->opt_persistent_told = false;
   w->graphs = nullptr;
   w->ragged_mu = new (std::nothrow) std::mutex();
   if (!w->ragged_mu) { delete w; set_error("out of host memory"); return MTMC_ENOMEM; }
@@ -150,6 +151,7 @@ extern "C" int mtmc_set_option(mtmc_weights* w, int option, int value) {
   } else if (option == MTMC_OPT_PERSISTENT_DECODE) {
     MTMC_REQUIRE(value >= 0 && value <= 60000000, "MTMC_OPT_PERSISTENT_DECODE needs a value in [0, 60 000 000]");
     w->opt_persistent_wait_us = value;
+    w->opt_persistent_told = true;
   } else {
     MTMC_REQUIRE(value >= 1, "MTMC_OPT_GEMM_LDS_MIN_BLOCKS needs a value >= 1");
     w->opt_lds_min_blocks = value;
@@ -227,8 +229,10 @@ extern "C" const char* mtmc_data_error_string(int bits) {
       "an activation, key or value left the fp16 range (magnitude above 65504, or not finite) and was clamped: "
       "the results of the calls since the last poll are unreliable");
   add(MTMC_DATA_STALLED,
-      "a persistent decode launch waited longer than its limit for workgroups that never became resident (another process "
-      "on the GPU?): the results of the calls since the last poll are wrong; MTMC_OPT_PERSISTENT_DECODE 0 avoids such launches");
+      "a persistent launch waited longer than the limit set with MTMC_OPT_PERSISTENT_DECODE for workgroups that found no place on "
+      "the GPU (other work on it?): the calls since the last poll took longer, their results are right");
+  add(MTMC_DATA_UNFINISHED,
+      "a persistent launch ended before its work was done: the results of the calls since the last poll are wrong");
   return text.c_str();
 }
 

@@ -172,10 +172,14 @@ void attention_dec(const AttnDecArgs& a, int B, hipStream_t st);
 
 // ---- the blocks of a decode step of up to 64 rows as one launch (decode_persistent.hip) -------------
 constexpr int kPersistGrid = 256;        // workgroups, all resident at once: one per CU
-constexpr int kPersistSyncStride = 64;   // words between the arrival counters: 8 that are watched, 16 of groups of workgroups
-constexpr int kPersistTops = 8, kPersistCounters = kPersistTops + 16;
-constexpr int kPersistStalled = kPersistCounters * kPersistSyncStride;  // word that says that a wait has outlasted its limit
-constexpr int kPersistSyncWords = kPersistStalled + 64;
+constexpr int kPersistSyncStride = 64;   // words between the words below
+constexpr int kPersistTops = 8, kPersistGroups = 16;  // arrival counters: 8 that are watched, 16 of groups of workgroups
+constexpr int kPersistEnded = kPersistTops + kPersistGroups;  // what became of the launch (PersistEnd)
+constexpr int kPersistSeats = kPersistEnded + 1, kPersistList = kPersistSeats + 1, kPersistMet = kPersistList + 1;  // of the other form
+constexpr int kPersistCounters = kPersistMet + 1;
+constexpr int kPersistGaveUp = kPersistCounters * kPersistSyncStride;  // word that says that a launch of this call has been given up
+constexpr int kPersistSyncWords = kPersistGaveUp + 64;
+enum PersistEnd { kPersistSkipped = 1, kPersistLost = 2 };
 struct PersistArgs {
   int n_layers, B, d;
   int nt_qkv, nt_d, nt_gu, kt_d, kt_nq, kt_F;
@@ -198,8 +202,10 @@ struct PersistArgs {
   int ks_down;
   int attn_units;        // B * Hkv * n_chunks
   AttnDecArgs at;        // layer is set by the kernel
+  int gu_ranges, dn_ranges;  // of the gate / up and of the down projection; decode_persistent() sets them
   uint32_t* sync;        // kPersistSyncWords, zero at the first launch; the sampler merge clears the counters after every step
-  long long wait_ticks;  // of the 100 MHz clock
+  long long roll_ticks;  // how long a workgroup waits for all of them to be there, of the 100 MHz clock
+  bool told;             // ... and whether a longer wait is reported (kErrStalled)
   int* err_flag;
 };
 struct PersistShape {
@@ -207,6 +213,7 @@ struct PersistShape {
   int down_nb;  // row tiles per workgroup of the down projection's own launch (2, 3 or 4), which tells its ranges of K
 };
 bool decode_persistent_fits(const PersistShape& s);
+// Two launches: the persistent one, and one that does the step where that was given up before it began (else nothing).
 void decode_persistent(const PersistArgs& a, int m_tiles, int down_nb, hipStream_t st);
 
 // ---- packing the live rows of a batch with a stop token into the leading slots ------------------

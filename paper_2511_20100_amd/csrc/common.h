@@ -96,7 +96,8 @@ struct mtmc_weights {
   int opt_stop_poll;       // decode steps between two looks at the stop flags of a rollout with a stop token (0: never)
   int opt_admit;           // a rollout with a stop token and more sequences than one batch holds runs as one batch
                            // that takes in the next prompts as sequences finish and leave slots (0: batch after batch)
-  int opt_persistent_wait_us;  // longest wait inside a persistent decode launch (0: steps run as separate launches)
+  int opt_persistent_wait_us;  // how long a persistent launch waits for its workgroups (0: steps run as separate launches)
+  bool opt_persistent_told;    // the caller has set that limit: a longer wait is reported
   mtmc::GraphCache* graphs;  // instantiated decode-step graphs, keyed by workspace and shape
   std::mutex* ragged_mu;     // guards ragged_calls
   std::vector<mtmc::RaggedCallRecord> ragged_calls;  // at most 16, oldest dropped first

@@ -10,6 +10,7 @@
 #include "device_scope.h"
 #include "device_utils.h"
 #include "frag.h"
+#include "roll_call.h"
 
 namespace mtmc {
 namespace bf16 {
@@ -187,32 +188,32 @@ __device__ __forceinline__ Ctx fresh(int wave) {
   return Ctx{*(const PersistArgs*)k, wg, wave, lane};
 }
 
+constexpr uint32_t kGroupOf = kPersistGrid / kPersistGroups;  // workgroups in a group
+constexpr long long kWaitTicks = 60 * 100000000ll;  // what is waited for once all workgroups are there always comes
+constexpr long long kAgainTicks = 2000;             // the roll call of a step after one that was given up
+__device__ __forceinline__ Word word_of(const PersistArgs& a, int i) { return {a.sync + i * kPersistSyncStride}; }
+
 // Counts the workgroup in (one lane): the last of a group of 16 workgroups counts the group in, on eight words of which every
 // workgroup watches one.  (Watchers and arrivals on the same words delay each other: with 128 workgroups that come 3 us after
 // the others, a flat form of eight counters takes 2.7 us from the last arrival, this one 1.5; all at once 1.5 either way.)
 __device__ __forceinline__ void count_in(const Ctx& c, uint32_t phase) {
-  uint32_t* group = c.a.sync + (kPersistTops + (c.wg & 15)) * kPersistSyncStride;
-  const uint32_t n = __hip_atomic_fetch_add(group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (n + 1 == (phase + 1) * (kPersistGrid / 16)) {
+  if (!roll_call::count_in(word_of(c.a, kPersistTops + (c.wg & (kPersistGroups - 1))), kGroupOf, phase + 1)) return;
 #pragma unroll
-    for (int t = 0; t < kPersistTops; ++t)
-      __hip_atomic_fetch_add(c.a.sync + t * kPersistSyncStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  for (int t = 0; t < kPersistTops; ++t) word_of(c.a, t).add(1);
 }
-// One wavefront: until every workgroup has been counted `phase` times, or the wait's limit has passed anywhere (then false).
+__device__ __forceinline__ uint32_t look(Word word) { return __builtin_amdgcn_readfirstlane(word.load()); }
+// One wavefront: until every workgroup has been counted `phase` times, or the launch is over (then false).
 __device__ __forceinline__ bool wait_grid(const Ctx& c, uint32_t phase) {
-  const uint32_t want = phase * 16;
-  const uint32_t* p = c.a.sync + (c.wg % kPersistTops) * kPersistSyncStride;
-  uint32_t* stalled = c.a.sync + kPersistStalled;
+  const uint32_t want = phase * kPersistGroups;
+  const Word mine = word_of(c.a, c.wg % kPersistTops), ended = word_of(c.a, kPersistEnded);
   const long long t0 = wall_clock64();
   bool ok = true;
-  for (int i = 0;; ++i) {
-    if ((uint32_t)__builtin_amdgcn_readfirstlane(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >= want) break;
-    if (wall_clock64() - t0 > c.a.wait_ticks ||
-        (i % 16 == 15 && __builtin_amdgcn_readfirstlane(__hip_atomic_load(stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))) {
-      if (c.lane == 0) {
-        __hip_atomic_store(stalled, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        atomicOr(c.a.err_flag, kErrStalled);
+  for (int i = 0; look(mine) < want; ++i) {
+    const bool late = wall_clock64() - t0 > kWaitTicks;
+    if (late || (i % 16 == 15 && look(ended))) {
+      if (late && c.lane == 0) {
+        ended.store(kPersistLost);
+        atomicOr(c.a.err_flag, kErrUnfinished);
       }
       ok = false;
       break;
@@ -220,6 +221,32 @@ __device__ __forceinline__ bool wait_grid(const Ctx& c, uint32_t phase) {
   }
   asm volatile("" ::: "memory");
   return ok;
+}
+// The same behind the first phase, which hands nothing on but the rows of qkv: one workgroup that waits longer than the limit gives the
+// launch up for all of them, unless all are there.  It is over then for whoever waits now or comes later.
+__device__ __forceinline__ bool answer_roll(const Ctx& c) {
+  const Word mine = word_of(c.a, c.wg % kPersistTops), ended = word_of(c.a, kPersistEnded),
+                              before = {c.a.sync + kPersistGaveUp};
+  const long long t0 = wall_clock64();
+  long long limit = c.a.roll_ticks;
+  for (int i = 0; look(mine) < kPersistGroups; ++i) {
+    if (i % 16 == 15) {
+      if (look(ended)) return false;
+      if (look(before)) limit = min(limit, kAgainTicks);
+    }
+    if (wall_clock64() - t0 <= limit) continue;
+    int closed = 0;
+    if (c.lane == 0) {
+      if (c.a.told) atomicOr(c.a.err_flag, kErrStalled);
+      closed = roll_call::close([&](int g) { return word_of(c.a, kPersistTops + g); }, kPersistGroups, kGroupOf);
+      if (closed) {
+        before.store(1);
+        ended.store(kPersistSkipped);
+      }
+    }
+    return !__builtin_amdgcn_readfirstlane(closed);
+  }
+  return true;
 }
 
 // 1/rms of the current residual and, where the operand was divided by an older one, times that one's rms
@@ -502,6 +529,9 @@ __device__ __forceinline__ bool attend(const AttnHeld& u, AttnLds& at, const int
 // Buffers of block l (see Operand): what its QKV projection reads, and what it leaves for the next one.
 __device__ __forceinline__ h16_t* x_of(const PersistArgs& a, int l) { return l == 0 ? a.x : a.xr + (size_t)(l - 1) * a.x_stride; }
 __device__ __forceinline__ h16_t* x_behind(const PersistArgs& a, int l) { return l + 1 == a.n_layers ? a.x : a.xr + (size_t)l * a.x_stride; }
+
+// decode_persistent_some.hip: the step by the workgroups that are there, after a launch that was given up
+void launch_some(const PersistArgs& a, int bt, hipStream_t st);
 
 // decode_persistent_rows.hip, bt tiles of 16 rows (2 to 4): which instances there are, and the launch of one that is there
 bool rows_fit(int bt, int gu_tiles, int dn_ranges);

@@ -23,8 +23,10 @@
 // earlier steps) is read as usual.  Every sum has the ranges and the order of the launches of decode_bf16.hip, so the
 // results are theirs bit for bit.
 //
-// All kPersistGrid workgroups have to be resident at once.  The host sees to that: one workgroup per CU, no second persistent launch
-// under way on the device (PersistentTurn), and a wait that outlasts its limit ends the launch with MTMC_DATA_STALLED.
+// All kPersistGrid workgroups have to be resident at once: one per CU, and no second persistent launch of the process under way
+// (PersistentTurn).  What else holds a CU, and for how long, nobody here knows.  So the first wait of a launch is its roll call
+// (roll_call.h): the phase before it changes nothing that a step starts from, and where not all workgroups come within the limit, the
+// launch ends there and decode_persistent_some.hip does the step.
 #include <type_traits>
 
 #include "decode_persistent.h"
@@ -193,6 +195,7 @@ __device__ __forceinline__ void control(Shared& sh, int wave) {
     // ---- attention
     {
       const Ctx c = fresh(wave);
+      if (lead && l == 0 && !answer_roll(c)) sh.stop = 1;
       if (!go(c)) return;
       if (attends) {
         if (attn_active) {
@@ -667,10 +670,14 @@ bool decode_persistent_fits(const PersistShape& s) {
          (s.m_tiles == 1 || persist::rows_fit(s.m_tiles, gu, dn));
 }
 
-void decode_persistent(const PersistArgs& a, int m_tiles, int down_nb, hipStream_t st) {
-  const int gu = gu_tiles(a.nt_gu), dn = dn_ranges(down_nb);
+void decode_persistent(const PersistArgs& args, int m_tiles, int down_nb, hipStream_t st) {
+  const int gu = gu_tiles(args.nt_gu), dn = dn_ranges(down_nb);
+  PersistArgs a = args;
+  a.gu_ranges = m_tiles > 1 || gu == 6 ? 8 : 4;
+  a.dn_ranges = dn;
   if (m_tiles == 1) persist::launch_one_tile(a, gu, dn, st);
   else persist::launch_rows(a, m_tiles, gu, st);
+  persist::launch_some(a, m_tiles, st);
 }
 
 }  // namespace bf16

@@ -188,6 +188,7 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
       leave();
     }
     // ---- attention
+    if (watches && l == 0 && !answer_roll(fresh(wave))) sh.stop = 1;
     if (!unit.active) {
       if (!enter([] {})) return;
     } else {

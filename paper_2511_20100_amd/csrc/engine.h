@@ -77,8 +77,7 @@ struct RolloutPlan {
   float* hB;      // [B, d]
   void* xB;       // [B, d]
   float* logits;  // fp32 path: [B, V]
-  float* sets;    // fp32 path: what the steps of a persistent generation hand on (f32::RolloutArgs), and its stall flag
-  uint32_t* stalled;
+  float* sets;    // fp32 path: what the steps of a persistent generation hand on (f32::RolloutArgs)
   // bf16 path scratch
   float* part;        // split-K partial sums
   void* o_chunks;     // decode-attention output per context chunk: n_chunks tiled fp16 operands [Hq*hd, bt*16]
@@ -93,7 +92,7 @@ struct RolloutPlan {
   int chunk_pages, n_chunks;       // decode-attention context split
   int split_at_prompt;             // two chunks: the prompt's whole pages | the rest (else equal chunks)
   bool persistent;       // the decode step's blocks run as one persistent launch
-  uint32_t* sync;        // its counters (kPersistSyncWords)
+  uint32_t* sync;        // its counters (kPersistSyncWords; fp32 path: f32::kRolloutSyncWords)
   float* ss_in;          // its sums of squares
   void *xo_l, *xr_l, *act_l;  // its operands, one of each per block
   bool samples_alone;    // the decode attention takes every sequence in a workgroup of its own

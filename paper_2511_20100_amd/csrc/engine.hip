@@ -96,7 +96,7 @@ RolloutPlan plan_rollout(const mtmc_weights* w, int n_prompts, int prompt_len, i
     p.ctl = cv.take<bf16::SampleCtl>(1);
     p.sets = cv.take<float>(f32::kRolloutSets * p.B * f32::rollout_row_floats(c.n_layers, c.d_model, c.n_q_heads, c.n_kv_heads, c.head_dim,
                                                                          c.d_ffn, c.vocab));
-    p.stalled = cv.take<uint32_t>(1);
+    p.sync = cv.take<uint32_t>(f32::kRolloutSyncWords);
   } else {
     bf16_plan_rollout_extra(w, p, cv);
   }
@@ -333,8 +333,8 @@ int f32_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts,
     a.pos_base = p.prompt_len - 1; a.row_pos = ragged ? p.row_pos : nullptr; a.pool = pool;
     a.h0 = p.hB; a.sets = p.sets;
     a.row_floats = (int)f32::rollout_row_floats(c.n_layers, d, c.n_q_heads, c.n_kv_heads, c.head_dim, c.d_ffn, V);
-    a.ctl = ctl; a.cur_ids = p.cur_ids; a.err_flag = w->err_flag; a.stalled = p.stalled;
-    a.wait_ticks = 100LL * w->opt_persistent_wait_us;
+    a.ctl = ctl; a.cur_ids = p.cur_ids; a.err_flag = w->err_flag; a.sync = p.sync;
+    a.roll_ticks = 100LL * (w->opt_persistent_wait_us - 1); a.told = w->opt_persistent_told;
     static_assert(f32::kRolloutGrid == PersistentTurn::kWorkgroups, "");
     PersistentTurn turn;
     if (even && f32::rollout_fits(a) && turn.take(w->device, st)) {

@@ -22,7 +22,7 @@ struct StepKey {
   const void* workspace;
   int total_prompts, B, prompt_len, n_samples, max_new, ragged;
   bool samples_alone;
-  int persistent_wait_us;  // 0: separate launches
+  int persistent_wait_us;  // 0: separate launches; negative: reported when it is passed
   bool operator==(const StepKey& o) const {
     return workspace == o.workspace && total_prompts == o.total_prompts && B == o.B && prompt_len == o.prompt_len &&
            n_samples == o.n_samples && max_new == o.max_new && ragged == o.ragged && samples_alone == o.samples_alone &&
@@ -464,7 +464,7 @@ void prefill_layers(const mtmc_weights* w, const Dims& D, float* h, h16_t* x, fl
   }
 }
 
-// The decode step's blocks as one launch, where its shape fits and the weights lie as it reads them (bf16_store_weights carves
+// The decode step's blocks as one launch (a second one stands by for it: decode_persistent()), where its shape fits and the weights lie as it reads them (bf16_store_weights carves
 // every block alike; the stride is checked all the same).
 static_assert(bf16::kPersistGrid == PersistentTurn::kWorkgroups, "");
 bool persistent_shape(const mtmc_weights* w, const Dims& D, const RolloutPlan& p) {
@@ -501,7 +501,8 @@ bf16::PersistArgs persistent_args(const mtmc_weights* w, const Dims& D, const Ro
   a.xo = (h16_t*)p.xo_l; a.xr = (h16_t*)p.xr_l; a.act = (h16_t*)p.act_l;
   a.x_stride = rows * D.d; a.act_stride = rows * D.F;
   a.at = at;
-  a.sync = p.sync; a.wait_ticks = 100LL * w->opt_persistent_wait_us; a.err_flag = w->err_flag;
+  a.sync = p.sync; a.roll_ticks = 100LL * (w->opt_persistent_wait_us - 1); a.told = w->opt_persistent_told;
+  a.err_flag = w->err_flag;
   return a;
 }
 
@@ -622,7 +623,8 @@ int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, c
     }
   }
   const StepKey key{(const void*)gp.page_table, gp.total_prompts, gp.B, gp.prompt_len, gp.n_samples, gp.max_new, gp.ragged,
-                    gp.samples_alone, gp.persistent ? w->opt_persistent_wait_us : 0};
+                    gp.samples_alone,
+                    !gp.persistent ? 0 : w->opt_persistent_told ? -w->opt_persistent_wait_us : w->opt_persistent_wait_us};
   out->cache_ = &gc;
   out->entry_ = gc.steps.acquire(key);
   if (out->entry_) return MTMC_OK;

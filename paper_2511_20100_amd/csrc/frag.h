@@ -44,7 +44,8 @@ __device__ __forceinline__ uint32_t pack_h16x2(float lo, float hi) {
 // not finite or exceeds the fp16 range (the stored value is then the clamped one, -65504 for a NaN): the results
 // of the call are unreliable and the next poll of the flag reports it.
 constexpr int kErrFp16Range = 8;
-constexpr int kErrStalled = 32;  // a persistent launch waited longer than its limit for workgroups that were not there
+constexpr int kErrStalled = 32;     // a persistent launch waited longer than the caller's limit for workgroups that were not there
+constexpr int kErrUnfinished = 64;  // a launch whose workgroups were all there ended before its work was done
 __device__ __forceinline__ bool fits_h16(float f) { return fabsf(f) <= 65504.f; }  // false for NaN
 // The converters every activation / KV-cache producer uses: same values as above, and the flag on a clamp.
 __device__ __forceinline__ h16_t f32_to_h16_flag(float f, int* err_flag) {

@@ -105,7 +105,8 @@ void sample(const float* logits, int B, int V, const bf16::SampleCtl* ctl, int* 
             const float* E, int d, int* err_flag, hipStream_t st);
 // The steps first_step .. last_step - 1 of a generation as one launch (rollout_f32.hip): the blocks, the LM head and the sampler
 // of every step, with the results of the launches of their own.  h0 [B, d]: the residual that the first of them starts from.
-constexpr int kRolloutGrid = 256;  // one workgroup per CU; they wait for each other
+constexpr int kRolloutGrid = 256;  // one workgroup per CU; those that are there wait for each other
+constexpr int kRolloutSyncWords = 3 * 64;
 constexpr int kRolloutSets = 3;
 struct RolloutArgs {
   int n_layers, B, d, Hq, F, V, first_step, last_step;
@@ -122,8 +123,9 @@ struct RolloutArgs {
   int row_floats;  // rollout_row_floats()
   const bf16::SampleCtl* ctl;
   int *cur_ids, *err_flag;
-  uint32_t* stalled;
-  long long wait_ticks;  // of the 100 MHz clock
+  uint32_t* sync;        // kRolloutSyncWords
+  long long roll_ticks;  // how long the workgroups wait for all of them to be there, of the 100 MHz clock
+  bool told;             // ... and whether a longer wait is reported (kErrStalled)
 };
 size_t rollout_row_floats(int n_layers, int d, int Hq, int Hkv, int hd, int F, int V);
 bool rollout_fits(const RolloutArgs& a);

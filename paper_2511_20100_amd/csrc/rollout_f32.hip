@@ -15,13 +15,15 @@
 // with every one of its logits.  (With two sets a workgroup that has no tile of the LM head could come back before it is
 // cleared.)  All of that holds for each block of eight rows by itself: blocks never wait for each other.
 //
-// All workgroups have to be resident at once (PersistentTurn), and a wait that outlasts its limit ends the launch.
+// The workgroups that find a place on the device in time share out the tiles, 256 as a rule, however few there are (roll_call.h);
+// they all stay, so that every wait ends.
 #include <algorithm>
 
 #include "device_scope.h"
 #include "f32_device.h"
 #include "frag.h"
 #include "kernels.h"
+#include "roll_call.h"
 
 namespace mtmc {
 namespace f32 {
@@ -32,6 +34,7 @@ using namespace device_scope;
 constexpr int kThreads = 256, kRows = 8, kSets = kRolloutSets;
 constexpr uint32_t kAbsent = 0xffffffffu;
 constexpr int kMaxK = 2040;  // eight rows of the operand in LDS
+constexpr long long kWaitTicks = 60 * 100000000ll;  // what is waited for always comes
 
 __device__ __forceinline__ bool absent(float x) { return __float_as_uint(x) == kAbsent; }
 __device__ __forceinline__ bool absent(v4f x) { return absent(x[0]) || absent(x[1]) || absent(x[2]) || absent(x[3]); }
@@ -45,13 +48,13 @@ struct Shared {
     SampleLds sample;
   };
   float raw[(kDecHeads + 2) * HD];  // the position's projections: queries, key, value
+  roll_call::Roster who;
   int stop;
 };
 
-// How long this launch still waits.
+// Where this launch waits.
 struct Patience {
-  long long limit;
-  uint32_t* stalled;
+  uint32_t* lost;  // somebody has given up
   int* err_flag;
   // asks again until done(): the values are there; false: given up, here or elsewhere
   template <class Ask, class Done>
@@ -60,9 +63,9 @@ struct Patience {
     for (int i = 0;; ++i) {
       ask();
       if (!__any(!done())) return true;
-      if (wall_clock64() - t0 > limit || (i % 16 == 15 && __hip_atomic_load(stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
-        __hip_atomic_store(stalled, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        atomicOr(err_flag, kErrStalled);
+      if (wall_clock64() - t0 > kWaitTicks || (i % 16 == 15 && __hip_atomic_load(lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+        __hip_atomic_store(lost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        atomicOr(err_flag, kErrUnfinished);
         return false;
       }
     }
@@ -116,18 +119,22 @@ struct Place {
   int off, stride;  // bytes
 };
 
-// The tiles of a phase go round the grid from workgroup `first` (0 .. kRolloutGrid - 1) on: the first tile of this workgroup.
-// first moves on by the phase's tiles, so that the next one finds workgroups that have its weights.
-__device__ __forceinline__ int first_tile(int& first, int total) {
-  const int at = ((int)blockIdx.x + kRolloutGrid - first) % kRolloutGrid;
-  first = (first + total) % kRolloutGrid;
-  return at;
-}
+// The tiles of a phase go round the n workgroups that are there, from workgroup `first` (0 .. n - 1) on.
+struct Share {
+  int id, n, first;
+  // The first tile of this workgroup; its next ones are n apart.  first moves on by the phase's tiles, so that the next one finds
+  // workgroups that have its weights.
+  __device__ __forceinline__ int first_tile(int total) {
+    const int at = id < first ? id + n - first : id - first;
+    first = n == kRolloutGrid ? (first + total) % kRolloutGrid : (first + total) % n;
+    return at;
+  }
+};
 
 // C[m, n] = product of the rows at A with W [N, K]: of the norm (gain: not NULL) or of the rows themselves plus the value at R.
 // behind(m0, nb, n_nb, columns): what else a tile does between operand and result.
 template <int NC_, int HD, class Behind>
-__device__ __forceinline__ bool product_of(Shared<HD>& sh, const Patience& wait, int& first, const Place& A, const Place& C, const Place& R,
+__device__ __forceinline__ bool product_of(Shared<HD>& sh, const Patience& wait, Share& work, const Place& A, const Place& C, const Place& R,
                                         const float* W, const float* gain, bool swiglu, int B, int N, int K, float eps,
                                         Behind behind) {
   using Tile = RowsTile<ROWS_ANY, NC_>;
@@ -135,7 +142,7 @@ __device__ __forceinline__ bool product_of(Shared<HD>& sh, const Patience& wait,
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, columns = swiglu ? NC / 2 : NC;
   const int n_nb = (N + 4 * columns - 1) / (4 * columns), total = n_nb * ((B + kRows - 1) / kRows);
   int held = -1;
-  for (int u = first_tile(first, total); u < total; u += kRolloutGrid) {
+  for (int u = work.first_tile(total); u < total; u += work.n) {
     Tile t;
     t.any_norm = gain != nullptr;
     t.any_swiglu = swiglu;
@@ -188,20 +195,20 @@ __device__ __forceinline__ bool product_of(Shared<HD>& sh, const Patience& wait,
 // Two weight rows per wavefront while that is one round: what a wavefront multiplies and folds is half of a phase (8 rows, d 256:
 // 47.6 us a step with four, 44.6 with two).
 template <int HD, class Behind>
-__device__ __forceinline__ bool product(Shared<HD>& sh, const Patience& wait, int& first, const Place& A, const Place& C, const Place& R,
+__device__ __forceinline__ bool product(Shared<HD>& sh, const Patience& wait, Share& work, const Place& A, const Place& C, const Place& R,
                                         const float* W, const float* gain, bool swiglu, int B, int N, int K, float eps,
                                         Behind behind) {
   const int per = swiglu ? 4 : 8;
   return (N + per - 1) / per * ((B + kRows - 1) / kRows) <= kRolloutGrid
-             ? product_of<2>(sh, wait, first, A, C, R, W, gain, swiglu, B, N, K, eps, behind)
-             : product_of<4>(sh, wait, first, A, C, R, W, gain, swiglu, B, N, K, eps, behind);
+             ? product_of<2>(sh, wait, work, A, C, R, W, gain, swiglu, B, N, K, eps, behind)
+             : product_of<4>(sh, wait, work, A, C, R, W, gain, swiglu, B, N, K, eps, behind);
 }
 
 template <int HD>
-__device__ __forceinline__ bool attention_step(Shared<HD>& sh, const Patience& wait, int& first, const RolloutArgs& a,
+__device__ __forceinline__ bool attention_step(Shared<HD>& sh, const Patience& wait, Share& work, const RolloutArgs& a,
                                                const Place& qkv, const Place& o, int layer, int step) {
   const int tid = threadIdx.x, Hq = a.Hq, Hkv = a.pool.n_kv_heads, G = Hq / Hkv, total = a.B * Hkv;
-  for (int u = first_tile(first, total); u < total; u += kRolloutGrid) {
+  for (int u = work.first_tile(total); u < total; u += work.n) {
     const int t = u / Hkv, g = u % Hkv, pos = (a.row_pos ? a.row_pos[t] : a.pos_base) + step;
     const int* table = a.pool.page_table + (size_t)t * a.pool.max_pages;
     const AttnDecHeld<HD> held = attention_dec_hold<HD>(tid, pos, table, a.cos, a.sin, a.pool, layer, g);
@@ -239,11 +246,11 @@ __device__ __forceinline__ bool attention_step(Shared<HD>& sh, const Patience& w
 }
 
 template <int HD>
-__device__ __forceinline__ bool sample_step(Shared<HD>& sh, const Patience& wait, int& first, const RolloutArgs& a, const bf16::SampleCtl& ctl,
+__device__ __forceinline__ bool sample_step(Shared<HD>& sh, const Patience& wait, Share& work, const RolloutArgs& a, const bf16::SampleCtl& ctl,
                                             const Place& logits, const Place& next, int step) {
   constexpr int kShare = kSampleWaves * 64 / kThreads;  // wavefronts of k_sample per wavefront here
   const int tid = threadIdx.x, V = a.V;
-  for (int b = first_tile(first, a.B); b < a.B; b += kRolloutGrid) {
+  for (int b = work.first_tile(a.B); b < a.B; b += work.n) {
     SampleState st[kShare];
     bool ok = true;
     const int row = logits.off + b * logits.stride;
@@ -298,14 +305,23 @@ template <int HD>
 __global__ __launch_bounds__(kThreads) void k_rollout(RolloutArgs a) {
   __shared__ Shared<HD> sh;
   const int tid = threadIdx.x;
-  if (tid == 0) sh.stop = 0;
+  if (tid == 0) {
+    sh.stop = 0;
+    const long long t0 = wall_clock64();
+    auto expired = [&] { return wall_clock64() - t0 > a.roll_ticks; };
+    sh.who = roll_call::join(Word{a.sync}, Word{a.sync + 64}, kRolloutGrid, expired);
+    if (sh.who.n == kRolloutGrid) sh.who.id = blockIdx.x;  // neighbouring tiles on different dies
+    if (a.told && expired()) atomicOr(a.err_flag, kErrStalled);
+  }
   __syncthreads();
+  Share work{__builtin_amdgcn_readfirstlane(sh.who.id), __builtin_amdgcn_readfirstlane(sh.who.n), 0};
+  if (work.id < 0) return;
   const bf16::SampleCtl ctl = *a.ctl;
-  const Patience wait{a.wait_ticks, a.stalled, a.err_flag};
+  const Patience wait{a.sync + 128, a.err_flag};
   const int nq = a.Hq * HD, nqkv = nq + 2 * a.pool.n_kv_heads * HD, per_layer = nqkv + nq + 2 * a.d + a.F;
   const int stride = a.row_floats * 4;
   const Rsrc all = rsrc_of(a.sets);
-  for (int b = blockIdx.x; b < a.B; b += kRolloutGrid)  // what the sampler before this launch has left
+  for (int b = work.id; b < a.B; b += work.n)  // what the sampler before this launch has left
     for (int c = tid; c < a.d; c += kThreads)
       st4(a.sets + ((size_t)(a.first_step % kSets) * a.B + b) * a.row_floats + c, present(a.h0[(size_t)b * a.d + c]));
   for (int step = a.first_step; step < a.last_step; ++step) {
@@ -313,7 +329,7 @@ __global__ __launch_bounds__(kThreads) void k_rollout(RolloutArgs a) {
     auto place = [&](int off) { return Place{all, a.sets, set + off * 4, stride}; };
     Place h = place(0);
     const Place logits = place(a.d + a.n_layers * per_layer);
-    int first = 0;
+    work.first = 0;
     for (int l = 0, phase = 0;; phase = (phase + 1) & 3, l += phase == 0) {
       const bool head = l == a.n_layers;
       const int at = a.d + l * per_layer;
@@ -340,12 +356,12 @@ __global__ __launch_bounds__(kThreads) void k_rollout(RolloutArgs a) {
         for (int e = nb * share + tid; tid < threads && e < min(quads, (nb + 1) * share); e += threads)
           st16(all, last + m0 * stride + e * 16, 0, v4u{kAbsent, kAbsent, kAbsent, kAbsent});
       };
-      if (!product(sh, wait, first, A, C, phase == 3 ? h1 : h, W, gain, phase == 2, a.B, N, K, a.eps, clear)) return;
+      if (!product(sh, wait, work, A, C, phase == 3 ? h1 : h, W, gain, phase == 2, a.B, N, K, a.eps, clear)) return;
       if (head) break;
-      if (phase == 0 && !attention_step<HD>(sh, wait, first, a, qkv, o, l, step)) return;
+      if (phase == 0 && !attention_step<HD>(sh, wait, work, a, qkv, o, l, step)) return;
       if (phase == 3) h = h2;
     }
-    if (!sample_step(sh, wait, first, a, ctl, logits, Place{all, a.sets, next, stride}, step)) return;
+    if (!sample_step(sh, wait, work, a, ctl, logits, Place{all, a.sets, next, stride}, step)) return;
   }
 }
 
@@ -372,7 +388,7 @@ bool rollout_fits(const RolloutArgs& a) {
 }
 void rollout(const RolloutArgs& a, hipStream_t st) {
   launch_fill_u32((uint32_t*)a.sets, kAbsent, kSets * (size_t)a.B * a.row_floats, st);
-  launch_set_int((int*)a.stalled, 0, st);
+  launch_fill_u32(a.sync, 0u, kRolloutSyncWords, st);
   if (a.pool.head_dim == 64) k_rollout<64><<<kRolloutGrid, kThreads, 0, st>>>(a);
   else k_rollout<128><<<kRolloutGrid, kThreads, 0, st>>>(a);
 }

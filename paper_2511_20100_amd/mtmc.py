@@ -20,7 +20,7 @@ _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libmtmc.so
 MTMC_OK, MTMC_EINVAL, MTMC_ENOMEM, MTMC_EHIP, MTMC_EDATA = 0, -1, -2, -3, -4
 MTMC_F32, MTMC_BF16 = 0, 1
 MTMC_DATA_TOKEN_ID, MTMC_DATA_WEIGHT, MTMC_DATA_LENGTH, MTMC_DATA_FP16_RANGE, MTMC_DATA_PREFIX = 1, 2, 4, 8, 16
-MTMC_DATA_STALLED = 32
+MTMC_DATA_STALLED, MTMC_DATA_UNFINISHED = 32, 64
 
 
 class MtmcError(RuntimeError):

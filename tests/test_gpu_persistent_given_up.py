@@ -1,0 +1,94 @@
+"""Persistent launches that do not get the whole device in time: the workgroups that are there do the work, with the bits of the
+separate launches.  Forced by a limit of a microsecond, and by another stream's kernel that holds a part of the device for a while."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2511_20100_amd import inputs
+
+V = 1040
+SHAPES = {
+    "narrow": inputs.ModelConfig(3, 1536, 12, 2, 128, 512, V, dtype="bf16"),
+    "1p5b": inputs.POLICY_1P5B.with_(n_layers=2, vocab=V),
+    "7b": inputs.POLICY_7B.with_(n_layers=1, vocab=V),
+    "mha": inputs.POLICY_1P3B_MHA.with_(n_layers=2, vocab=V),
+    "wide-kv": inputs.ModelConfig(2, 1600, 16, 8, 128, 1104, V, dtype="bf16"),
+    "fp32": inputs.TINY,
+    "fp32-hd128": inputs.ModelConfig(3, 272, 2, 2, 128, 2032, 1040, dtype="fp32"),
+}
+ONE_TILE = [(1, 1, 1, 12), (1, 300, 2, 9), (2, 1100, 1, 5), (5, 90, 3, 20)]
+CALLS = {
+    "narrow": ONE_TILE,
+    # also 18, 32, 33, 48, 49 and 64 rows, one to three context chunks
+    "1p5b": ONE_TILE + [(3, 1, 6, 6), (4, 300, 8, 6), (11, 127, 3, 4), (6, 20, 8, 5), (7, 90, 7, 6), (8, 300, 8, 6), (4, 1500, 16, 3)],
+    "7b": ONE_TILE + [(17, 300, 1, 6), (4, 100, 8, 5), (3, 1500, 8, 4)],
+    "mha": ONE_TILE,
+    "wide-kv": ONE_TILE,
+    "fp32": [(1, 1, 1, 3), (4, 32, 2, 20), (4, 17, 4, 9)],
+    "fp32-hd128": [(2, 20, 3, 10)],
+}
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_2511_20100_amd import mtmc
+    return mtmc
+
+
+def _policy(lib, name):
+    cfg = SHAPES[name]
+    return cfg, lib.mtmc_weights_create(lib.make_config(cfg, 2400), inputs.make_weights(cfg, seed=0, std=0.04, gain_std=0.1).blob())
+
+
+def _rollout(lib, handle, prompts, n_samples, max_new, limit, **kw):
+    lib.mtmc_set_option(handle, lib.MTMC_OPT_PERSISTENT_DECODE, limit)
+    return [t.cpu() for t in lib.mtmc_rollout(handle, prompts, n_samples, max_new, 1.0, 3, **kw)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_the_bits_of_separate_launches(lib, shape):
+    import torch
+    cfg, handle = _policy(lib, shape)
+    try:
+        for n_prompts, plen, n_samples, max_new in CALLS[shape]:
+            prompts = torch.from_numpy(inputs.make_prompts(n_prompts, plen, cfg.vocab, seed=plen)).cuda()
+            want = _rollout(lib, handle, prompts, n_samples, max_new, 0)
+            lib.mtmc_poll_errors(handle)
+            got = _rollout(lib, handle, prompts, n_samples, max_new, 1)
+            with pytest.raises(lib.MtmcError, match="persistent launch waited longer.*results are right"):
+                lib.mtmc_poll_errors(handle)
+            again = _rollout(lib, handle, prompts, n_samples, max_new, 10_000_000)
+            lib.mtmc_poll_errors(handle)
+            for other in (got, again):
+                assert all(torch.equal(a, b) for a, b in zip(want, other)), (n_prompts, plen, n_samples, max_new)
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
+@pytest.mark.parametrize("shape,call", [("1p5b", (2, 100, 2, 12)), ("1p5b", (3, 100, 8, 6)), ("1p5b", (6, 100, 8, 6)),
+                                        ("1p5b", (8, 100, 8, 6)), ("7b", (4, 100, 8, 5)), ("fp32", (4, 32, 2, 20))])
+@pytest.mark.parametrize("held", [16, 200, 512])  # workgroups of the other kernel; up to two of them share a CU
+def test_beside_another_stream(lib, shape, call, held):
+    import torch
+    cfg, handle = _policy(lib, shape)
+    n_prompts, plen, n_samples, max_new = call
+    try:
+        prompts = torch.from_numpy(inputs.make_prompts(n_prompts, plen, cfg.vocab, seed=plen)).cuda()
+        ws = torch.empty(lib.mtmc_rollout_workspace_bytes(handle, *call), dtype=torch.uint8, device="cuda")
+        want = _rollout(lib, handle, prompts, n_samples, max_new, 0, workspace=ws)
+        out = torch.empty(held * 256, dtype=torch.float32, device="cuda")
+        mine, other = torch.cuda.Stream(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        for limit in (300, 10_000_000):  # microseconds; the other kernel takes about 13 000
+            lib.mtmc_set_option(handle, lib.MTMC_OPT_PERSISTENT_DECODE, limit)
+            lib.mtmc_mfma_probe(out, held, 60_000, stream=other)
+            with torch.cuda.stream(mine):
+                got = lib.mtmc_rollout(handle, prompts, n_samples, max_new, 1.0, 3, workspace=ws, stream=mine)
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b.cpu()) for a, b in zip(want, got)), (held, limit)
+            try:
+                lib.mtmc_poll_errors(handle)
+            except lib.MtmcError as e:  # whether the other kernel was in the way is up to the device
+                assert limit == 300 and "results are right" in str(e)
+    finally:
+        lib.mtmc_weights_destroy(handle)
