@@ -94,10 +94,16 @@ extern "C" int mtmc_weights_create(const mtmc_config* cfg, const void* blob, siz
   w->opt_admit = 1;
   w->opt_persistent_wait_us = 2000;
   w->opt_persistent_told = false;
+  w->gave_up = nullptr;
   w->graphs = nullptr;
   w->ragged_mu = new (std::nothrow) std::mutex();
   if (!w->ragged_mu) { delete w; set_error("out of host memory"); return MTMC_ENOMEM; }
   int rc = hipGetDevice(&w->device) == hipSuccess ? MTMC_OK : MTMC_EHIP;
+  if (rc == MTMC_OK && hipHostMalloc((void**)&w->gave_up, sizeof(int), hipHostMallocDefault) != hipSuccess) {
+    set_error("hipHostMalloc failed");
+    rc = MTMC_ENOMEM;
+  }
+  if (rc == MTMC_OK) *w->gave_up = 0;
   if (rc == MTMC_OK) rc = build_aux(w, st);
   if (rc == MTMC_OK)
     rc = cfg->dtype == MTMC_F32 ? f32_store_weights(w, lay, blob, blob_on_device != 0, st)
@@ -119,6 +125,7 @@ extern "C" void mtmc_weights_destroy(mtmc_weights* w) {
   destroy_graph_cache(w);
   if (w->storage) (void)hipFree(w->storage);
   if (w->aux) (void)hipFree(w->aux);
+  if (w->gave_up) (void)hipHostFree(w->gave_up);
   delete w->ragged_mu;
   delete w;
 }
@@ -152,6 +159,7 @@ extern "C" int mtmc_set_option(mtmc_weights* w, int option, int value) {
     MTMC_REQUIRE(value >= 0 && value <= 60000000, "MTMC_OPT_PERSISTENT_DECODE needs a value in [0, 60 000 000]");
     w->opt_persistent_wait_us = value;
     w->opt_persistent_told = true;
+    w->backoff.forget(w->gave_up);
   } else {
     MTMC_REQUIRE(value >= 1, "MTMC_OPT_GEMM_LDS_MIN_BLOCKS needs a value >= 1");
     w->opt_lds_min_blocks = value;

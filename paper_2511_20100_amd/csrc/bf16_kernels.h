@@ -206,6 +206,7 @@ struct PersistArgs {
   uint32_t* sync;        // kPersistSyncWords, zero at the first launch; the sampler merge clears the counters after every step
   long long roll_ticks;  // how long a workgroup waits for all of them to be there, of the 100 MHz clock
   bool told;             // ... and whether a longer wait is reported (kErrStalled)
+  int* gave_up;          // pinned host word, set when a launch was given up
   int* err_flag;
 };
 struct PersistShape {

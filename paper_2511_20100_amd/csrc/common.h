@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "mtmc.h"
+#include "persistent_turn.h"
 
 namespace mtmc {
 
@@ -98,6 +99,8 @@ struct mtmc_weights {
                            // that takes in the next prompts as sequences finish and leave slots (0: batch after batch)
   int opt_persistent_wait_us;  // how long a persistent launch waits for its workgroups (0: steps run as separate launches)
   bool opt_persistent_told;    // the caller has set that limit: a longer wait is reported
+  int* gave_up;                // pinned host word, set by a persistent launch that was given up
+  mutable mtmc::PersistentBackoff backoff;
   mtmc::GraphCache* graphs;  // instantiated decode-step graphs, keyed by workspace and shape
   std::mutex* ragged_mu;     // guards ragged_calls
   std::vector<mtmc::RaggedCallRecord> ragged_calls;  // at most 16, oldest dropped first

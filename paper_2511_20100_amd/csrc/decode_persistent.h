@@ -241,6 +241,7 @@ __device__ __forceinline__ bool answer_roll(const Ctx& c) {
       closed = roll_call::close([&](int g) { return word_of(c.a, kPersistTops + g); }, kPersistGroups, kGroupOf);
       if (closed) {
         before.store(1);
+        __hip_atomic_store(c.a.gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         ended.store(kPersistSkipped);
       }
     }

@@ -334,10 +334,10 @@ int f32_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts,
     a.h0 = p.hB; a.sets = p.sets;
     a.row_floats = (int)f32::rollout_row_floats(c.n_layers, d, c.n_q_heads, c.n_kv_heads, c.head_dim, c.d_ffn, V);
     a.ctl = ctl; a.cur_ids = p.cur_ids; a.err_flag = w->err_flag; a.sync = p.sync;
-    a.roll_ticks = 100LL * (w->opt_persistent_wait_us - 1); a.told = w->opt_persistent_told;
+    a.roll_ticks = 100LL * (w->opt_persistent_wait_us - 1); a.told = w->opt_persistent_told; a.gave_up = w->gave_up;
     static_assert(f32::kRolloutGrid == PersistentTurn::kWorkgroups, "");
     PersistentTurn turn;
-    if (even && f32::rollout_fits(a) && turn.take(w->device, st)) {
+    if (even && f32::rollout_fits(a) && w->backoff.allows(w->gave_up) && turn.take(w->device, st)) {
       f32::rollout(a, st);
       MTMC_HIP_CHECK(hipGetLastError());
       return MTMC_OK;

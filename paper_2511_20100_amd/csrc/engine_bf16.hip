@@ -502,7 +502,7 @@ bf16::PersistArgs persistent_args(const mtmc_weights* w, const Dims& D, const Ro
   a.x_stride = rows * D.d; a.act_stride = rows * D.F;
   a.at = at;
   a.sync = p.sync; a.roll_ticks = 100LL * (w->opt_persistent_wait_us - 1); a.told = w->opt_persistent_told;
-  a.err_flag = w->err_flag;
+  a.gave_up = w->gave_up; a.err_flag = w->err_flag;
   return a;
 }
 
@@ -705,6 +705,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
                       p.n_prompts, ns, S, p.max_pages, p.nf_max, p.shared_total, p.max_new, 0, w->err_flag, st);
   bf16::admit_init(p.slot_row, p.row_step0, B, p.bt * 16, st);
   launch_fill_u32(p.sync, 0u, bf16::kPersistSyncWords, st);
+  const bool may_persist = w->backoff.allows(w->gave_up);
   PersistentTurn turn;
   launch_set_int(p.d_step, 0, st);
   launch_set_int(p.d_step + 1, 0, st);
@@ -845,7 +846,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
       cur.B = slots; cur.bt = slots / 16; cur.n_samples = 1;
       cur.row_pos = p.row_pos_c; cur.row_step0 = p.row_step0_c;
       apply_tune(cur, tune_decode(D, cur.B, cur.bt, p.max_pages));
-      cur.persistent = persistent_shape(w, D, cur) && turn.take(w->device, st);
+      cur.persistent = may_persist && persistent_shape(w, D, cur) && turn.take(w->device, st);
       cur_pool.page_table = p.page_table_c;
       bf16::SampleCtl cc = ctl;
       cc.slot_row = p.slot_row_c;
@@ -877,7 +878,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
   }
   const Dims D = dims_of(w);
   // a step as one persistent launch where it fits, the turn is free and the caller is not capturing the stream
-  bool may_persist = true;
+  bool may_persist = w->backoff.allows(w->gave_up);
   {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {

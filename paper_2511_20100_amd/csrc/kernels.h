@@ -126,6 +126,7 @@ struct RolloutArgs {
   uint32_t* sync;        // kRolloutSyncWords
   long long roll_ticks;  // how long the workgroups wait for all of them to be there, of the 100 MHz clock
   bool told;             // ... and whether a longer wait is reported (kErrStalled)
+  int* gave_up;          // pinned host word, set when they did not all come
 };
 size_t rollout_row_floats(int n_layers, int d, int Hq, int Hkv, int hd, int F, int V);
 bool rollout_fits(const RolloutArgs& a);

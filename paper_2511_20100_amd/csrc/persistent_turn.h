@@ -12,6 +12,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <mutex>
+
 namespace mtmc {
 
 class PersistentTurn {
@@ -28,6 +30,21 @@ class PersistentTurn {
  private:
   void* held_ = nullptr;
   hipStream_t st_ = nullptr;
+};
+
+// Whether the calls on a weights handle try persistent launches at all.  A launch that was given up says that other work shares the
+// device; its call took longer than with separate launches and so would the next ones.  These run separate launches then: 16
+// calls, twice as many after each further time (1024 at most), half as many after each call that was allowed and went well.
+class PersistentBackoff {
+ public:
+  // gave_up: the pinned word that a launch sets when it is given up; taken back here.
+  bool allows(int* gave_up);
+  void forget(int* gave_up);
+
+ private:
+  static constexpr int kFewest = 16, kMost = 1024;
+  std::mutex mu_;
+  int left_ = 0, next_ = kFewest;
 };
 
 }  // namespace mtmc

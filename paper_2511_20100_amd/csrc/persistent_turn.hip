@@ -9,7 +9,7 @@
 #include <sys/un.h>
 #include <unistd.h>
 
-#include <mutex>
+#include <algorithm>
 
 namespace mtmc {
 namespace {
@@ -118,6 +118,26 @@ void PersistentTurn::release() {
   t.stream = st_;
   t.mu.unlock();
   held_ = nullptr;
+}
+
+bool PersistentBackoff::allows(int* gave_up) {
+  std::lock_guard<std::mutex> lock(mu_);
+  if (__atomic_exchange_n(gave_up, 0, __ATOMIC_RELAXED)) {
+    left_ = next_;
+    next_ = std::min(2 * next_, kMost);
+  } else if (left_ == 0) {
+    next_ = std::max(next_ / 2, kFewest);
+  }
+  if (left_ == 0) return true;
+  --left_;
+  return false;
+}
+
+void PersistentBackoff::forget(int* gave_up) {
+  std::lock_guard<std::mutex> lock(mu_);
+  __atomic_store_n(gave_up, 0, __ATOMIC_RELAXED);
+  left_ = 0;
+  next_ = kFewest;
 }
 
 }  // namespace mtmc

@@ -311,6 +311,7 @@ __global__ __launch_bounds__(kThreads) void k_rollout(RolloutArgs a) {
     auto expired = [&] { return wall_clock64() - t0 > a.roll_ticks; };
     sh.who = roll_call::join(Word{a.sync}, Word{a.sync + 64}, kRolloutGrid, expired);
     if (sh.who.n == kRolloutGrid) sh.who.id = blockIdx.x;  // neighbouring tiles on different dies
+    else if (sh.who.id == 0) __hip_atomic_store(a.gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (a.told && expired()) atomicOr(a.err_flag, kErrStalled);
   }
   __syncthreads();

@@ -94,11 +94,41 @@ static void not_the_whole_device() {
   g_cus = 256;
 }
 
+// A launch that was given up: 16 calls without, then 32, ... 1024; fewer again when it goes well.
+static void after_a_launch_that_was_given_up() {
+  mtmc::PersistentBackoff b;
+  int word = 0;
+  auto without = [&] {  // calls until one is allowed
+    int n = 0;
+    while (!b.allows(&word)) ++n;
+    return n;
+  };
+  CHECK(without() == 0 && without() == 0);
+  for (int want : {16, 32, 64, 128, 256, 512, 1024, 1024}) {
+    word = 1;
+    CHECK(!b.allows(&word) && word == 0);
+    // the call that is allowed again has the next strike at once, which the pause is doubled by
+    int n = 1;
+    for (; n < want; ++n) CHECK(!b.allows(&word));
+  }
+  CHECK(b.allows(&word) && b.allows(&word));
+  word = 1;
+  CHECK(without() == 256);
+  word = 1;
+  CHECK(!b.allows(&word));
+  word = 1;
+  b.forget(&word);
+  CHECK(word == 0 && b.allows(&word));
+  word = 1;
+  CHECK(without() == 16);
+}
+
 int main() {
   what_the_last_turn_left();
   one_at_a_time();
   without_an_event();
   not_the_whole_device();
+  after_a_launch_that_was_given_up();
   std::printf("ok\n");
   return 0;
 }

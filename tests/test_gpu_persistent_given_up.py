@@ -65,6 +65,32 @@ def test_the_bits_of_separate_launches(lib, shape):
         lib.mtmc_weights_destroy(handle)
 
 
+@pytest.mark.parametrize("shape", ["1p5b", "fp32"])
+def test_calls_after_one_that_gave_up(lib, shape):
+    """16 of them run separate launches, unless the limit is set again."""
+    import torch
+    cfg, handle = _policy(lib, shape)
+
+    def told():
+        got.append([t.cpu() for t in lib.mtmc_rollout(handle, prompts, 2, 6, 1.0, 3)])
+        try:
+            lib.mtmc_poll_errors(handle)
+        except lib.MtmcError as e:
+            assert "results are right" in str(e)
+            return True
+        return False
+
+    try:
+        prompts, got = torch.from_numpy(inputs.make_prompts(2, 20, cfg.vocab, seed=1)).cuda(), []
+        lib.mtmc_set_option(handle, lib.MTMC_OPT_PERSISTENT_DECODE, 1)
+        assert [told() for _ in range(18)] == [True] + 16 * [False] + [True]
+        lib.mtmc_set_option(handle, lib.MTMC_OPT_PERSISTENT_DECODE, 1)
+        assert [told() for _ in range(2)] == [True, False]
+        assert all(torch.equal(a, b) for other in got[1:] for a, b in zip(got[0], other))
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
 @pytest.mark.parametrize("shape,call", [("1p5b", (2, 100, 2, 12)), ("1p5b", (3, 100, 8, 6)), ("1p5b", (6, 100, 8, 6)),
                                         ("1p5b", (8, 100, 8, 6)), ("7b", (4, 100, 8, 5)), ("fp32", (4, 32, 2, 20))])
 @pytest.mark.parametrize("held", [16, 200, 512])  # workgroups of the other kernel; up to two of them share a CU
