@@ -346,7 +346,7 @@ const char* mtmc_data_error_string(int bits);
  *   one launch of one workgroup per CU, whose workgroups wait for each other between phases, instead of six launches
  *   per block.  Results do not depend on it (the same sums in the same order).  The launch needs the whole device at once: it
  *   is used while no other such launch is under way from another stream or thread of the process, by one process per
- *   device, and not while `stream` is being captured; every other step runs as separate launches.  MTMC_FP32 generations of
+ *   device (of those that share a network namespace), and not while `stream` is being captured; every other step runs as separate launches.  MTMC_FP32 generations of
  *   few rows of a small model run all of their steps as one such launch.  The value is the longest time in microseconds that
  *   such a launch waits for a place on the device for all of its workgroups (1: not at all).  Where other work keeps it from that, the
  *   work is done by the workgroups that do get a place, with the same results, slower.  The next 16 calls on `w` (more if it happens again) run separate

@@ -6,8 +6,10 @@
 //   - threads: a mutex that is only ever tried;
 //   - streams: an event behind the last launch of the turn before.  While that is still at work, only the stream it went to
 //     may take the next turn (and waits for it on the device); where the runtime does not say, nobody;
-//   - processes: the first that asks for a device keeps it until it ends (an abstract socket name of the host's network
-//     namespace, given back by the kernel whatever ends the process).
+//   - processes: the first that asks for a device keeps it until it ends, and then the next (an abstract socket name, given back
+//     by the kernel whatever ends the process and what it has forked).  Processes of different network namespaces, as in two
+//     containers, do not see each other's: each takes its own turns, and launches of both that are in each other's way are given up at
+//     their roll call (roll_call.h).
 #pragma once
 
 #include <hip/hip_runtime.h>

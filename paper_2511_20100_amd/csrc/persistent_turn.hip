@@ -16,7 +16,7 @@ namespace {
 
 struct DeviceTurn {
   std::mutex mu;
-  bool asked = false, usable = false;
+  bool asked = false, able = false, leased = false;
   hipEvent_t last = nullptr;  // behind the launches of the latest turn
   hipStream_t stream = nullptr;
   bool recorded = false;
@@ -67,14 +67,15 @@ bool whole_device(hipStream_t st) {
 }
 
 bool usable(DeviceTurn& t, int device) {
-  if (t.asked) return t.usable;
-  t.asked = true;
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < PersistentTurn::kWorkgroups)
-    return false;
-  if (hipEventCreateWithFlags(&t.last, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) return false;
-  t.usable = lease_device(device);
-  return t.usable;
+  if (!t.asked) {
+    t.asked = true;
+    int cus = 0;
+    t.able = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess &&
+             cus >= PersistentTurn::kWorkgroups &&
+             hipEventCreateWithFlags(&t.last, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
+  }
+  if (t.able && !t.leased) t.leased = lease_device(device);  // at every turn: whoever has the device may end
+  return t.able && t.leased;
 }
 
 // Whether the launches of the latest turn have ended, or st (theirs) waits for them.  Any other answer than "ended" or "not yet"
@@ -114,7 +115,7 @@ void PersistentTurn::release() {
   DeviceTurn& t = *(DeviceTurn*)held_;
   t.recorded = hipEventRecord(t.last, st_) == hipSuccess;
   // no event to wait for: wait here, or nobody takes a turn any more
-  if (!t.recorded && hipStreamSynchronize(st_) != hipSuccess) t.usable = false;
+  if (!t.recorded && hipStreamSynchronize(st_) != hipSuccess) t.able = false;
   t.stream = st_;
   t.mu.unlock();
   held_ = nullptr;

@@ -1,5 +1,6 @@
 // Who gets the turn of the persistent launches, with a runtime whose answers are set here.  Compiled (with persistent_turn.hip)
 // and run by test_persistent_turn.py; exits non-zero at the first claim that does not hold.
+#include <sys/wait.h>
 #include <unistd.h>
 
 #include <cstdio>
@@ -123,7 +124,29 @@ static void after_a_launch_that_was_given_up() {
   CHECK(without() == 16);
 }
 
+// Two processes on one device: whoever asked first, and the other one when that has ended.
+static void one_process_at_a_time() {
+  static char name[64];
+  std::snprintf(name, sizeof name, "check-shared-%d", (int)getpid());
+  g_bus = name;
+  int has[2], end[2];
+  CHECK(pipe(has) == 0 && pipe(end) == 0);
+  const pid_t pid = fork();
+  char c = 0;
+  if (pid == 0) {
+    const bool got = takes(7, kA) && takes(7, kB);
+    CHECK(write(has[1], got ? "y" : "n", 1) == 1 && read(end[0], &c, 1) == 1);
+    _exit(0);
+  }
+  CHECK(pid > 0 && read(has[0], &c, 1) == 1 && c == 'y');
+  CHECK(!takes(7, kA) && !takes(7, kB));
+  CHECK(write(end[1], "e", 1) == 1 && waitpid(pid, nullptr, 0) == pid);
+  CHECK(takes(7, kA) && takes(7, kB));
+  g_bus = nullptr;
+}
+
 int main() {
+  one_process_at_a_time();
   what_the_last_turn_left();
   one_at_a_time();
   without_an_event();

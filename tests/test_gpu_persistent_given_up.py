@@ -118,3 +118,46 @@ def test_beside_another_stream(lib, shape, call, held):
                 assert limit == 300 and "results are right" in str(e)
     finally:
         lib.mtmc_weights_destroy(handle)
+
+
+OTHER_PROCESS = """
+import sys
+import torch
+from paper_2511_20100_amd import inputs, mtmc as lib
+import test_gpu_persistent_given_up as here
+cfg, handle = here._policy(lib, "1p5b")
+prompts = torch.from_numpy(inputs.make_prompts(2, 20, cfg.vocab, seed=1)).cuda()
+print("ready", flush=True)
+for _ in range(20):
+    out = here._rollout(lib, handle, prompts, 8, 12, 1)  # a persistent launch would be told of
+    lib.mtmc_poll_errors(handle)
+torch.save(out, sys.argv[1])
+"""
+
+
+def test_two_processes(lib, tmp_path):
+    """The one that came first has the persistent launches, the other one separate ones, at the same time."""
+    import os
+    import subprocess
+    import sys
+    import torch
+    cfg, handle = _policy(lib, "1p5b")
+    try:
+        prompts = torch.from_numpy(inputs.make_prompts(2, 20, cfg.vocab, seed=1)).cuda()
+        want = _rollout(lib, handle, prompts, 8, 12, 0)
+        with pytest.raises(lib.MtmcError, match="results are right"):  # this process has them
+            _rollout(lib, handle, prompts, 8, 12, 1)
+            lib.mtmc_poll_errors(handle)
+        root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+        env = dict(os.environ, PYTHONPATH=os.pathsep.join([root, os.path.join(root, "tests"), os.environ.get("PYTHONPATH", "")]))
+        path = str(tmp_path / "out.pt")
+        with subprocess.Popen([sys.executable, "-c", OTHER_PROCESS, path], stdout=subprocess.PIPE, text=True, env=env) as other:
+            assert other.stdout.readline().strip() == "ready"
+            while other.poll() is None:
+                got = _rollout(lib, handle, prompts, 8, 12, 10_000_000)
+                assert all(torch.equal(a, b) for a, b in zip(want, got))
+            assert other.returncode == 0
+        lib.mtmc_poll_errors(handle)
+        assert all(torch.equal(a, b) for a, b in zip(want, torch.load(path)))
+    finally:
+        lib.mtmc_weights_destroy(handle)
