@@ -3,6 +3,7 @@
 
 #include "common.h"
 #include "frag.h"
+#include "persistent_cut.h"
 
 namespace mtmc {
 namespace bf16 {
@@ -171,7 +172,6 @@ struct AttnDecArgs {
 void attention_dec(const AttnDecArgs& a, int B, hipStream_t st);
 
 // ---- the blocks of a decode step of up to 64 rows as one launch (decode_persistent.hip) -------------
-constexpr int kPersistGrid = 256;        // workgroups, all resident at once: one per CU
 constexpr int kPersistSyncStride = 64;   // words between the words below
 constexpr int kPersistTops = 8, kPersistGroups = 16;  // arrival counters: 8 that are watched, 16 of groups of workgroups
 constexpr int kPersistEnded = kPersistTops + kPersistGroups;  // what became of the launch (PersistEnd)
@@ -209,11 +209,6 @@ struct PersistArgs {
   int* gave_up;          // pinned host word, set when a launch was given up
   int* err_flag;
 };
-struct PersistShape {
-  int m_tiles, head_dim, kt_d, nt_d, nt_qkv, nt_gu, n_chunks, pairs;  // pairs: sequences x kv heads
-  int down_nb;  // row tiles per workgroup of the down projection's own launch (2, 3 or 4), which tells its ranges of K
-};
-bool decode_persistent_fits(const PersistShape& s);
 // Two launches: the persistent one, and one that does the step where that was given up before it began (else nothing).
 void decode_persistent(const PersistArgs& a, int m_tiles, int down_nb, hipStream_t st);
 

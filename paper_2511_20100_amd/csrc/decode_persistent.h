@@ -534,8 +534,7 @@ __device__ __forceinline__ h16_t* x_behind(const PersistArgs& a, int l) { return
 // decode_persistent_some.hip: the step by the workgroups that are there, after a launch that was given up
 void launch_some(const PersistArgs& a, int bt, hipStream_t st);
 
-// decode_persistent_rows.hip, bt tiles of 16 rows (2 to 4): which instances there are, and the launch of one that is there
-bool rows_fit(int bt, int gu_tiles, int dn_ranges);
+// decode_persistent_rows.hip, bt tiles of 16 rows (2 to 4), where persist_rows_fit()
 void launch_rows(const PersistArgs& a, int bt, int gu_tiles, hipStream_t st);
 
 }  // namespace persist

@@ -657,21 +657,8 @@ void launch_one_tile(const PersistArgs& a, int gu_tiles, int dn_ranges, hipStrea
 
 }  // namespace persist
 
-// Gate / up row tiles per workgroup: one round on the 256 CUs with the ranges of K of the launch of its own.
-static int gu_tiles(int nt_gu) { return nt_gu <= 4 * 256 ? 4 : nt_gu <= 6 * 256 ? 6 : nt_gu <= 10 * 256 ? 10 : 0; }
-static int dn_ranges(int down_nb) { return down_nb == 3 ? 5 : down_nb == 2 ? 8 : 4; }
-
-bool decode_persistent_fits(const PersistShape& s) {
-  // 16 ranges of K in the QKV projection (d from 1536), matrices within a descriptor's reach, a row tile of the sum of the
-  // splits per workgroup, a unit of the attention per workgroup
-  const int gu = gu_tiles(s.nt_gu), dn = dn_ranges(s.down_nb);
-  return s.head_dim == persist::kHeadDim && s.kt_d >= 48 && s.nt_d <= kPersistGrid && s.nt_qkv <= 4096 && s.n_chunks <= 8 &&
-         s.pairs * s.n_chunks <= kPersistGrid && gu > 0 && (dn != 5 || s.nt_d <= 96) &&
-         (s.m_tiles == 1 || persist::rows_fit(s.m_tiles, gu, dn));
-}
-
 void decode_persistent(const PersistArgs& args, int m_tiles, int down_nb, hipStream_t st) {
-  const int gu = gu_tiles(args.nt_gu), dn = dn_ranges(down_nb);
+  const int gu = persist_gu_tiles(args.nt_gu), dn = persist_dn_ranges(down_nb);
   PersistArgs a = args;
   a.gu_ranges = m_tiles > 1 || gu == 6 ? 8 : 4;
   a.dn_ranges = dn;

@@ -558,13 +558,6 @@ __global__ __launch_bounds__(kThreads, 2) void k_decode_layers_rows(PersistArgs)
 
 }  // namespace
 
-// 6 row tiles x 64 rows or 10 x 32 are what the accumulators hold.  The other cuts (at most 4 gate / up tiles per workgroup, a
-// down projection without ranges of 5 below d 1552) are not built: no configuration has them with more than 16 rows.
-bool rows_fit(int bt, int gu_tiles, int dn_ranges) {
-  return bt == 2 ? (gu_tiles == 6 && dn_ranges == 5) || (gu_tiles == 10 && dn_ranges == 4)
-                 : (bt == 3 || bt == 4) && gu_tiles == 6 && dn_ranges == 5;
-}
-
 void launch_rows(const PersistArgs& a, int bt, int gu_tiles, hipStream_t st) {
   if (bt == 2 && gu_tiles == 6) k_decode_layers_rows<2, 6, 5><<<kPersistGrid, kThreads, 0, st>>>(a);
   else if (bt == 2) k_decode_layers_rows<2, 10, 4><<<kPersistGrid, kThreads, 0, st>>>(a);

@@ -479,7 +479,7 @@ bool persistent_shape(const mtmc_weights* w, const Dims& D, const RolloutPlan& p
       if (at(L[l].*f) - at(L[l - 1].*f) != stride) return false;
   }
   return stride >= 0 && bf16::decode_persistent_fits(bf16::PersistShape{p.bt, w->cfg.head_dim, D.kt_d, D.nt_d, D.nt_qkv, D.nt_gu, p.n_chunks,
-                                                                        p.B * D.Hkv, p.down_nb});
+                                                                        p.B * D.Hkv, p.down_nb, p.ks_down});
 }
 
 bf16::PersistArgs persistent_args(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, const bf16::AttnDecArgs& at) {

@@ -1,5 +1,5 @@
-"""Who may have a persistent launch under way, and whether its workgroups are all there (no GPU: the runtime's answers are made
-up by the first check, the second one's workgroups are threads)."""
+"""Who may have a persistent launch under way, whether its workgroups are all there, and that they share out all of the work (no
+GPU: the runtime's answers are made up by the first check, the second one's workgroups are threads)."""
 import os
 import subprocess
 
@@ -22,3 +22,7 @@ def test_one_turn_and_none_while_launches_may_be_under_way(tmp_path):
 
 def test_a_launch_runs_with_all_of_its_workgroups_or_with_those_on_the_list(tmp_path):
     _run(tmp_path, "roll_call_check")
+
+
+def test_the_workgroups_of_a_step_share_out_all_of_its_work(tmp_path):
+    _run(tmp_path, "persistent_cut_check")
