@@ -77,7 +77,7 @@ struct RolloutPlan {
   float* hB;      // [B, d]
   void* xB;       // [B, d]
   float* logits;  // fp32 path: [B, V]
-  float* sets;    // fp32 path: what the steps of a persistent generation hand on (f32::RolloutArgs)
+  float* sets;    // fp32 path: what the steps of a persistent generation hand on (f32::RolloutArgs); NULL where it does not fit
   // bf16 path scratch
   float* part;        // split-K partial sums
   void* o_chunks;     // decode-attention output per context chunk: n_chunks tiled fp16 operands [Hq*hd, bt*16]
@@ -92,6 +92,7 @@ struct RolloutPlan {
   int chunk_pages, n_chunks;       // decode-attention context split
   int split_at_prompt;             // two chunks: the prompt's whole pages | the rest (else equal chunks)
   bool persistent;       // the decode step's blocks run as one persistent launch
+  int persist_rows;      // rows of the largest batch of the call that may (0: none, and what follows is NULL)
   uint32_t* sync;        // its counters (kPersistSyncWords; fp32 path: f32::kRolloutSyncWords)
   float* ss_in;          // its sums of squares
   void *xo_l, *xr_l, *act_l;  // its operands, one of each per block

@@ -46,6 +46,17 @@ int build_aux(mtmc_weights* w, hipStream_t st) {
   return MTMC_OK;
 }
 
+// The sizes of the one-launch generation, which tell whether it fits.
+static f32::RolloutArgs f32_one_launch(const mtmc_weights* w, const RolloutPlan& p) {
+  const mtmc_config& c = w->cfg;
+  f32::RolloutArgs a{};
+  a.n_layers = c.n_layers; a.B = p.B; a.d = c.d_model; a.Hq = c.n_q_heads; a.F = c.d_ffn; a.V = c.vocab;
+  a.first_step = 1; a.last_step = p.max_new;
+  a.pool = KvPool{p.kv, p.n_pages, c.n_kv_heads, c.head_dim, p.page_table, p.max_pages};
+  a.row_floats = (int)f32::rollout_row_floats(c.n_layers, c.d_model, c.n_q_heads, c.n_kv_heads, c.head_dim, c.d_ffn, c.vocab);
+  return a;
+}
+
 RolloutPlan plan_rollout(const mtmc_weights* w, int n_prompts, int prompt_len, int n_samples,
                          int max_new, char* base, bool ragged) {
   const mtmc_config& c = w->cfg;
@@ -94,9 +105,11 @@ RolloutPlan plan_rollout(const mtmc_weights* w, int n_prompts, int prompt_len, i
     p.gu = cv.take<float>((size_t)p.Tmax * 2 * F);
     p.logits = cv.take<float>((size_t)p.B * c.vocab);
     p.ctl = cv.take<bf16::SampleCtl>(1);
-    p.sets = cv.take<float>(f32::kRolloutSets * p.B * f32::rollout_row_floats(c.n_layers, c.d_model, c.n_q_heads, c.n_kv_heads, c.head_dim,
-                                                                         c.d_ffn, c.vocab));
-    p.sync = cv.take<uint32_t>(f32::kRolloutSyncWords);
+    const f32::RolloutArgs one = f32_one_launch(w, p);
+    if (p.max_new > 1 && f32::rollout_fits(one)) {
+      p.sets = cv.take<float>(f32::kRolloutSets * (size_t)p.B * one.row_floats);
+      p.sync = cv.take<uint32_t>(f32::kRolloutSyncWords);
+    }
   } else {
     bf16_plan_rollout_extra(w, p, cv);
   }
@@ -314,7 +327,7 @@ int f32_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts,
   // all steps as one launch where it fits, the turn is free and the caller is not capturing the stream
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
-  else if (cs == hipStreamCaptureStatusNone && w->opt_persistent_wait_us > 0) {
+  else if (cs == hipStreamCaptureStatusNone && p.sets && w->opt_persistent_wait_us > 0) {
     const auto& L = w->layers;
     auto at = [](const void* q) { return (const char*)q; };
     const ptrdiff_t stride = L.size() > 1 ? at(L[1].wqkv) - at(L[0].wqkv) : 0;
@@ -324,20 +337,18 @@ int f32_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts,
         even = even && at(L[l].*f) - at(L[l - 1].*f) == stride;
       for (auto f : {&LayerWeights::attn_norm, &LayerWeights::ffn_norm}) even = even && at(L[l].*f) - at(L[l - 1].*f) == stride;
     }
-    f32::RolloutArgs a{};
-    a.n_layers = c.n_layers; a.B = p.B; a.d = d; a.Hq = c.n_q_heads; a.F = c.d_ffn; a.V = V; a.first_step = 1; a.last_step = p.max_new;
+    f32::RolloutArgs a = f32_one_launch(w, p);
     a.wqkv = (const float*)L[0].wqkv; a.wo = (const float*)L[0].wo; a.wgu = (const float*)L[0].wgu; a.wdown = (const float*)L[0].wdown;
     a.attn_norm = L[0].attn_norm; a.ffn_norm = L[0].ffn_norm; a.layer_stride = (size_t)stride;
     a.final_norm = w->final_norm; a.lm_head = (const float*)w->lm_head; a.embed = (const float*)w->embed;
     a.cos = w->rope_cos; a.sin = w->rope_sin; a.eps = c.rms_eps;
-    a.pos_base = p.prompt_len - 1; a.row_pos = ragged ? p.row_pos : nullptr; a.pool = pool;
+    a.pos_base = p.prompt_len - 1; a.row_pos = ragged ? p.row_pos : nullptr;
     a.h0 = p.hB; a.sets = p.sets;
-    a.row_floats = (int)f32::rollout_row_floats(c.n_layers, d, c.n_q_heads, c.n_kv_heads, c.head_dim, c.d_ffn, V);
     a.ctl = ctl; a.cur_ids = p.cur_ids; a.err_flag = w->err_flag; a.sync = p.sync;
     a.roll_ticks = 100LL * (w->opt_persistent_wait_us - 1); a.told = w->opt_persistent_told; a.gave_up = w->gave_up;
     static_assert(f32::kRolloutGrid == PersistentTurn::kWorkgroups, "");
     PersistentTurn turn;
-    if (even && f32::rollout_fits(a) && w->backoff.allows(w->gave_up) && turn.take(w->device, st)) {
+    if (even && w->backoff.allows(w->gave_up) && turn.take(w->device, st)) {
       f32::rollout(a, st);
       MTMC_HIP_CHECK(hipGetLastError());
       return MTMC_OK;

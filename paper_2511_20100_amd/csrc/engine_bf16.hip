@@ -344,6 +344,24 @@ void apply_tune(RolloutPlan& p, const DecodeTune& t) {
   p.ks_qkv = t.ks_qkv; p.ks_o = t.ks_o; p.ks_down = t.ks_down; p.down_nb = t.down_nb;
   p.n_chunks = t.n_chunks; p.chunk_pages = t.chunk_pages; p.split_at_prompt = t.split_at_prompt;
 }
+static_assert(bf16::kPersistGrid == PersistentTurn::kWorkgroups, "");
+bool persistent_fits(const mtmc_weights* w, const Dims& D, int B, int bt, int n_chunks, int down_nb, int ks_down) {
+  return bf16::decode_persistent_fits(
+      bf16::PersistShape{bt, w->cfg.head_dim, D.kt_d, D.nt_d, D.nt_qkv, D.nt_gu, n_chunks, B * D.Hkv, down_nb, ks_down});
+}
+// Rows of the largest batch of the call whose steps may run as one launch: its groups of prompts, the last one with the launch
+// shape of the others, and (prompts of different lengths) the slots that live rows are packed into.
+int persistent_rows(const mtmc_weights* w, const Dims& D, const RolloutPlan& p) {
+  int most = 0;
+  if (p.max_new < 2) return most;
+  for (int B : {p.B, ((p.total_prompts - 1) % p.n_prompts + 1) * p.n_samples})
+    if (persistent_fits(w, D, B, tiles16(B), p.n_chunks, p.down_nb, p.ks_down)) most = std::max(most, tiles16(B));
+  for (int bt = 1; p.ragged && bt < p.bt; ++bt) {
+    const DecodeTune t = tune_decode(D, bt * 16, bt, p.max_pages);
+    if (persistent_fits(w, D, bt * 16, bt, t.n_chunks, t.down_nb, t.ks_down)) most = std::max(most, bt);
+  }
+  return most * 16;
+}
 }  // namespace
 
 void bf16_plan_rollout_extra(const mtmc_weights* w, RolloutPlan& p, Carver& cv) {
@@ -371,13 +389,15 @@ void bf16_plan_rollout_extra(const mtmc_weights* w, RolloutPlan& p, Carver& cv) 
   p.ssA = cv.take<float>((size_t)D.nt_d * Mpad);
   p.ssB = cv.take<float>((size_t)D.nt_d * Mpad);
   p.rs_buf = cv.take<float>(Mpad);
-  p.sync = cv.take<uint32_t>(bf16::kPersistSyncWords);
-  // what the persistent step hands from phase to phase, a buffer per block (sized for the row tiles it takes)
-  const size_t rows = std::min<size_t>(Mpad, 64), L = w->cfg.n_layers;
-  p.ss_in = cv.take<float>(2 * std::max<size_t>(Mpad, 64) * bf16::kPersistGrid);
-  p.xo_l = cv.take<h16_t>(L * rows * D.d);
-  p.xr_l = cv.take<h16_t>(L * rows * D.d);
-  p.act_l = cv.take<h16_t>(L * rows * D.F);
+  p.persist_rows = persistent_rows(w, D, p);
+  if (p.persist_rows > 0) {  // what the persistent step hands from phase to phase, a buffer per block
+    const size_t rows = p.persist_rows, L = w->cfg.n_layers;
+    p.sync = cv.take<uint32_t>(bf16::kPersistSyncWords);
+    p.ss_in = cv.take<float>(2 * std::max<size_t>(Mpad, 64) * bf16::kPersistGrid);
+    p.xo_l = cv.take<h16_t>(L * rows * D.d);
+    p.xr_l = cv.take<h16_t>(L * rows * D.d);
+    p.act_l = cv.take<h16_t>(L * rows * D.F);
+  }
   if (p.ragged) {
     p.slot_row = cv.take<int>(Mpad);
     p.page_table_c = cv.take<int>(Mpad * p.max_pages);
@@ -466,9 +486,8 @@ void prefill_layers(const mtmc_weights* w, const Dims& D, float* h, h16_t* x, fl
 
 // The decode step's blocks as one launch (a second one stands by for it: decode_persistent()), where its shape fits and the weights lie as it reads them (bf16_store_weights carves
 // every block alike; the stride is checked all the same).
-static_assert(bf16::kPersistGrid == PersistentTurn::kWorkgroups, "");
 bool persistent_shape(const mtmc_weights* w, const Dims& D, const RolloutPlan& p) {
-  if (w->opt_persistent_wait_us <= 0 || p.max_new < 2) return false;
+  if (w->opt_persistent_wait_us <= 0 || p.bt * 16 > p.persist_rows) return false;
   const auto& L = w->layers;
   auto at = [](const void* q) { return (const char*)q; };
   const ptrdiff_t stride = L.size() > 1 ? at(L[1].wqkv) - at(L[0].wqkv) : 0;
@@ -478,8 +497,7 @@ bool persistent_shape(const mtmc_weights* w, const Dims& D, const RolloutPlan& p
     for (auto f : {&LayerWeights::attn_norm, &LayerWeights::ffn_norm})
       if (at(L[l].*f) - at(L[l - 1].*f) != stride) return false;
   }
-  return stride >= 0 && bf16::decode_persistent_fits(bf16::PersistShape{p.bt, w->cfg.head_dim, D.kt_d, D.nt_d, D.nt_qkv, D.nt_gu, p.n_chunks,
-                                                                        p.B * D.Hkv, p.down_nb, p.ks_down});
+  return stride >= 0 && persistent_fits(w, D, p.B, p.bt, p.n_chunks, p.down_nb, p.ks_down);
 }
 
 bf16::PersistArgs persistent_args(const mtmc_weights* w, const Dims& D, const RolloutPlan& p, const bf16::AttnDecArgs& at) {
@@ -704,7 +722,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   launch_ragged_setup(p.page_table, p.row_pos, p.done, sa.out_lens, p.prompt_ids, p.suffix_ids, prompts, sa.prompt_lens,
                       p.n_prompts, ns, S, p.max_pages, p.nf_max, p.shared_total, p.max_new, 0, w->err_flag, st);
   bf16::admit_init(p.slot_row, p.row_step0, B, p.bt * 16, st);
-  launch_fill_u32(p.sync, 0u, bf16::kPersistSyncWords, st);
+  if (p.sync) launch_fill_u32(p.sync, 0u, bf16::kPersistSyncWords, st);
   const bool may_persist = w->backoff.allows(w->gave_up);
   PersistentTurn turn;
   launch_set_int(p.d_step, 0, st);
@@ -887,7 +905,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     }
   }
   PersistentTurn turn;
-  launch_fill_u32(p.sync, 0u, bf16::kPersistSyncWords, st);
+  if (p.sync) launch_fill_u32(p.sync, 0u, bf16::kPersistSyncWords, st);
   KvPool pool{p.kv, p.n_pages, c.n_kv_heads, c.head_dim, p.page_table, p.max_pages};
   for (int g0 = 0; g0 < p.total_prompts; g0 += p.n_prompts) {
     const int np_group = std::min(p.n_prompts, p.total_prompts - g0);
