@@ -2,11 +2,15 @@
 // Per-workgroup partial sums in double, then one workgroup adds the partials; both reductions run in a fixed order, so the result
 // does not depend on scheduling.
 //
-// What bounds a call of few samples is its launches.  One instead of two (65536 samples: 14.5 -> 11.5 us a call) takes a tag beside
-// every partial sum: the call's own 64-bit number, stored when the sum is where others see it.  A workgroup that has stored its tag looks at all of
-// them; the last one to store does see them all.  (Two that see them write the same result.)  It clears the tags behind
-// itself, so that a launch that is replayed with the number it was recorded with starts without them.  Nobody waits.  Up to kPpoAlone workgroups, whose tags are one look of a wavefront: with 256 a call
-// that is waited for takes 26.9 us against 24.9, and with 1024 that all look at 1024 tags it took 79 against 26.5.
+// What bounds calls of few samples that follow each other is the host: a launch costs it 2.5 us.  One instead of two takes a tag
+// beside every partial sum: the call's own 64-bit number, stored when the sum is where others see it.  A workgroup that has stored
+// its tag looks at all of them; the last one to store does see them all.  (Two that see them write the same result.)  It clears
+// the tags behind itself, so that a launch that is replayed with the number it was recorded with starts without them.  Nobody
+// waits.  The device pays for that with two trips to memory, and more the more workgroups look.  us a call, two launches -> one:
+//   workgroups (1024 samples)      8            32           64           96           128          192          256          512
+//   calls that follow each other   10.6 -> 7.9  10.6 -> 8.2  10.7 -> 8.3  10.9 -> 8.2  10.9 -> 8.3  10.9 -> 11.5 10.9 -> 8.8  10.9 -> 41
+//   a call that is waited for      22.0 -> 21.8 21.8 -> 22.3 21.9 -> 23.0 21.6 -> 23.3 21.7 -> 23.7 21.7 -> 25.6 21.8 -> 24.3 22.6 -> 58
+// Up to kPpoAlone the former gain more than the latter lose.
 #include <atomic>
 #include <chrono>
 #include <mutex>
@@ -21,7 +25,7 @@ namespace {
 
 constexpr int kPpoBlocks = 1024;   // partial results at most
 constexpr int kPpoThreads = 256;
-constexpr int kPpoAlone = 64;      // ... that one launch adds up
+constexpr int kPpoAlone = 128;     // ... that one launch adds up
 
 struct PpoSums {
   double surrogate, clipped, kl, count;

@@ -1,5 +1,5 @@
 """The clipped loss as one launch: the workgroup that finds every partial sum tagged adds them up.  A recorded launch has the
-same tag at every replay, with new inputs and other calls on the same array between them; from one workgroup to the 64 that
+same tag at every replay, with new inputs and other calls on the same array between them; from one workgroup to the 128 that
 one launch takes, and two launches beyond."""
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ import mtmc_oracle as oracle
 from paper_2511_20100_amd import inputs
 
 
-@pytest.mark.parametrize("n", [1024, 1025, 65_536, 65_537])  # 1, 2, 64 and 65 workgroups
+@pytest.mark.parametrize("n", [1024, 1025, 65_536, 65_537, 131_072, 131_073])  # 1, 2, 64, 65, 128 and 129 workgroups
 def test_replays_of_a_recorded_call(n):
     import torch
     from paper_2511_20100_amd import mtmc
