@@ -50,6 +50,9 @@ int main() {
   CHECK(decode_persistent_fits({4, 128, 48, 96, 128, 1120, 2, 128, 3, 8}) && decode_persistent_fits({1, 128, 48, 96, 128, 1120, 8, 2, 3, 8}));
   CHECK(decode_persistent_fits({2, 128, 112, 224, 288, 2368, 1, 128, 4, 4}));
   CHECK(!decode_persistent_fits({1, 128, 48, 96, 128, 1120, 1, 2, 4, 21}) && !decode_persistent_fits({2, 128, 112, 224, 288, 2368, 1, 128, 4, 9}));
+  // row tiles of a workgroup and ranges of the down projection of the widths that test_gpu_persistent_given_up.py names after them
+  struct { int gu, dn, F, down_nb; } named[] = {{4, 5, 6144, 3}, {4, 4, 8192, 4}, {6, 8, 11008, 2}, {6, 4, 12288, 4}, {10, 5, 16384, 3}, {10, 8, 14336, 2}};
+  for (auto& n : named) CHECK(persist_gu_tiles(n.F / 8) == n.gu && persist_dn_ranges(n.down_nb) == n.dn);
   std::printf("ok\n");
   return 0;
 }

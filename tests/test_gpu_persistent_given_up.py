@@ -13,6 +13,13 @@ SHAPES = {
     "7b": inputs.POLICY_7B.with_(n_layers=1, vocab=V),
     "mha": inputs.POLICY_1P3B_MHA.with_(n_layers=2, vocab=V),
     "wide-kv": inputs.ModelConfig(2, 1600, 16, 8, 128, 1104, V, dtype="bf16"),
+    # one tile of rows, the other cuts: gate / up tiles per workgroup and ranges of the down projection
+    "4x5": inputs.ModelConfig(2, 1536, 12, 2, 128, 6144, V, dtype="bf16"),
+    "4x4": inputs.ModelConfig(2, 3584, 28, 4, 128, 8192, V, dtype="bf16"),
+    "6x8": inputs.ModelConfig(2, 2048, 16, 2, 128, 11008, V, dtype="bf16"),
+    "6x4": inputs.ModelConfig(2, 3072, 24, 8, 128, 12288, V, dtype="bf16"),
+    "10x5": inputs.ModelConfig(2, 1536, 12, 2, 128, 16384, V, dtype="bf16"),
+    "10x8": inputs.ModelConfig(2, 2048, 16, 2, 128, 14336, V, dtype="bf16"),
     "fp32": inputs.TINY,
     "fp32-hd128": inputs.ModelConfig(3, 272, 2, 2, 128, 2032, 1040, dtype="fp32"),
 }
@@ -24,6 +31,7 @@ CALLS = {
     "7b": ONE_TILE + [(17, 300, 1, 6), (4, 100, 8, 5), (3, 1500, 8, 4)],
     "mha": ONE_TILE,
     "wide-kv": ONE_TILE,
+    **{cut: ONE_TILE + [(2, 40, 8, 5)] for cut in ("4x5", "4x4", "6x8", "6x4", "10x5", "10x8")},
     "fp32": [(1, 1, 1, 3), (4, 32, 2, 20), (4, 17, 4, 9)],
     "fp32-hd128": [(2, 20, 3, 10)],
 }
