@@ -362,8 +362,8 @@ int mtmc_set_option(mtmc_weights* w, int option, int value);
 /*
  * Diagnostics for measurement: HIP-event timing of one class of decode kernel inside mtmc_rollout
  * (MTMC_BF16).  While a class is selected, every `every_n_steps`-th decode step is launched
- * directly instead of through the captured graph, with an event pair around each launch of
- * that class (same kernels, same results).  mtmc_kernel_timer_read synchronises `stream` and
+ * directly instead of through the captured graph, as separate launches, with an event pair around each launch of
+ * that class (the same results; the other steps may run all blocks as one launch).  mtmc_kernel_timer_read synchronises `stream` and
  * returns the summed duration and the number of timed launches since the last read; if
  * `empty_pair_ms` is not NULL it receives the mean duration of event pairs recorded back to back
  * with nothing between them (one such pair per timed step: what the bracketing itself adds).

@@ -7,8 +7,8 @@
 // from the last arrival), and the weights of the next phase are on their way to registers while it waits: they depend on
 // nothing.  One row 47.7 -> 31 us per block (63 steps 89.5 -> 63.1 ms), 16 rows 51 -> 37 (96.6 -> 74.0 ms).
 //
-// What is left of a block's 31 us are five dependent phases of about 1 us to the first operand, 0.5 for sums and epilogue, 0.5
-// to 1 for the stores to drain and 1.5 for the counters, the sum of the splits, and the 10 us in which the gate / up and
+// What is left of a block's 31 us are six dependent phases (the sixth adds up the splits) of about 1 us to the first operand, 0.5
+// for sums and epilogue, 0.5 to 1 for the stores to drain and 1.5 for the counters, and the 10 us in which the gate / up and
 // down weights come at 5 TB/s.
 //
 //   wavefronts 0 .. 7    stream weights and multiply; their sums per range of K go to LDS.  They ask for the next weights only

@@ -2,7 +2,7 @@
 // for what a persistent step saves and for what it asks of the device.
 //
 // What bounds it: a CU takes in about 50 GB/s, weights from memory or operand from the cache.  At 64 rows the gate / up phase
-// needs 192 KB of operand beside 288 KB of weights per CU, 9 of a block's 56 us; in all a block spends 20 us on its five
+// needs 192 KB of operand beside 288 KB of weights per CU, 9 of a block's 56 us; in all a block spends 20 us on its six
 // hand-overs (stores drained 1 us, counters 1.5, stragglers), 10 on sums and epilogues, 26 on streams.  So the operand is
 // taken in as seldom as registers allow: the gate / up projection holds 6 row tiles x 64 rows in accumulators, which takes 256
 // registers and hence eight wavefronts in all (with the twelve of the one-tile form, two sets of workgroups per row tile,

@@ -17,9 +17,10 @@ inline int persist_gu_tiles(int nt_gu) { return nt_gu <= 4 * 256 ? 4 : nt_gu <= 
 inline int persist_dn_ranges(int down_nb) { return down_nb == 3 ? 5 : down_nb == 2 ? 8 : 4; }
 inline int persist_dn_tiles(int dn_ranges) { return dn_ranges == 5 ? 3 : dn_ranges == 8 ? 2 : 4; }
 
-// More than one tile of rows: 6 row tiles x 64 rows or 10 x 32 are what the accumulators hold.  The other cuts (at most 4 gate / up
-// tiles per workgroup, a down projection without ranges of 5 below d 1552) are not built: no configuration has them with more
-// than 16 rows.
+// More than one tile of rows: 6 row tiles x 64 rows or 10 x 32 are what the accumulators hold.  Each cut is an instance of its own,
+// and these are built: d 1536 with feed-forward widths of 8208 to 12288, and to 32 rows those of 10 gate / up tiles with 4 ranges of
+// the down projection (d 3584, F 18944).  Other widths that would fit the registers (d 2048, F 11008: 6 tiles and 8 ranges) run
+// separate launches from 17 rows on.
 inline bool persist_rows_fit(int bt, int gu_tiles, int dn_ranges) {
   return bt == 2 ? (gu_tiles == 6 && dn_ranges == 5) || (gu_tiles == 10 && dn_ranges == 4)
                  : (bt == 3 || bt == 4) && gu_tiles == 6 && dn_ranges == 5;
