@@ -30,7 +30,9 @@ MFMA_PEAK_TFLOPS = 2500.0   # MI355X published dense 16-bit MFMA rate
 # (FETCH_SIZE / WRITE_SIZE runs scaled by the library's copy kernel), with the hash of the kernel sources the
 # counters were taken on: `traffic` is reported only while those sources are unchanged.
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "decode_kernels_{workload}_hbm_counters.txt")
-DECODE_KERNEL_SOURCES = ("decode_bf16.hip", "decode_rows128.hip", "decode_lmhead.hip", "frag.h", "bf16_kernels.h", "attention_core.h",
+DECODE_KERNEL_SOURCES = ("decode_bf16.hip", "decode_rows128.hip", "decode_lmhead.hip", "decode_persistent.hip",
+                         "decode_persistent_rows.hip", "decode_persistent_some.hip", "decode_persistent.h", "persistent_cut.h",
+                         "attention_decode.h", "device_scope.h", "roll_call.h", "frag.h", "bf16_kernels.h", "attention_core.h",
                          "device_utils.h")
 
 
@@ -284,6 +286,8 @@ def main() -> int:
     ap.add_argument("--no-inference-legs", action="store_true",
                     help="skip the stop-token and cached-prefix legs (reported beside the step, 1p5b workload only)")
     ap.add_argument("--no-graph", action="store_true", help="launch decode steps directly (for counter runs)")
+    ap.add_argument("--persistent-decode", type=int, default=None, metavar="MICROSECONDS",
+                    help="MTMC_OPT_PERSISTENT_DECODE (0: the blocks of a step as separate launches, for counter runs)")
     ap.add_argument("--progress", action="store_true", help="print a line to stderr as each stage ends")
     ap.add_argument("--no-kernel-timer", action="store_true", help="do not bracket the gate/up launches with events")
     ap.add_argument("--copy-probe-mib", type=int, default=0,
@@ -319,6 +323,8 @@ def main() -> int:
     del blob
     if args.no_graph:
         mtmc.mtmc_set_option(handle, mtmc.MTMC_OPT_HIP_GRAPH, 0)
+    if args.persistent_decode is not None:
+        mtmc.mtmc_set_option(handle, mtmc.MTMC_OPT_PERSISTENT_DECODE, args.persistent_decode)
     if args.copy_probe_mib > 0:
         src = torch.ones(args.copy_probe_mib << 20, dtype=torch.uint8, device=dev)
         dst = torch.empty_like(src)
@@ -404,7 +410,7 @@ def main() -> int:
                     "traffic": gate_up_traffic_from_profile(args.workload),
                     "kernel": "gate/up projection of a decode step, one launch per layer (k_gemm_dec<..., SWIGLU> up to "
                               "64 rows, k_gemm_rows128<..., SWIGLU> at 65..128); up to 64 rows on the timed steps only, "
-                              "every 32nd: the others run all blocks as one launch",
+                              "every 32nd: the others run all blocks as one launch (decode_step has the step as a whole)",
                     "bytes_per_launch": gate_up_bytes, "us_per_launch": k_us, "timed_launches": k_launches,
                     "empty_event_pair_us": 1e3 * k_empty_ms}
     else:
