@@ -187,12 +187,19 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
       }
       leave();
     }
-    // ---- attention
-    if (watches && l == 0 && !answer_roll(fresh(wave))) sh.stop = 1;
+    // ---- attention; the first one is behind the roll call
+    auto enter_attention = [&] {
+      if (watches) {
+        const Ctx c = fresh(wave);
+        if (!(l == 0 ? answer_roll(c) : wait_grid(c, phase))) sh.stop = 1;
+      }
+      lds_barrier();
+      return __builtin_amdgcn_readfirstlane(sh.stop) == 0;
+    };
     if (!unit.active) {
-      if (!enter([] {})) return;
+      if (!enter_attention()) return;
     } else {
-      if (!attend<true>(unit, sh.at, sh.table, l, wave, 16 * BT, [&] { return enter([] {}); })) return;
+      if (!attend<true>(unit, sh.at, sh.table, l, wave, 16 * BT, enter_attention)) return;
     }
     leave();
     // ---- O projection: at most one unit per workgroup
