@@ -20,6 +20,13 @@ SHAPES = {
     "6x4": inputs.ModelConfig(2, 3072, 24, 8, 128, 12288, V, dtype="bf16"),
     "10x5": inputs.ModelConfig(2, 1536, 12, 2, 128, 16384, V, dtype="bf16"),
     "10x8": inputs.ModelConfig(2, 2048, 16, 2, 128, 14336, V, dtype="bf16"),
+    # the widest and narrowest that take the cuts for more than one tile of rows
+    "d4096": inputs.ModelConfig(1, 4096, 32, 8, 128, 20480, V, dtype="bf16"),
+    "d2560": inputs.ModelConfig(2, 2560, 20, 4, 128, 18944, V, dtype="bf16"),
+    "F8208": inputs.ModelConfig(2, 1536, 12, 4, 128, 8208, V, dtype="bf16"),
+    "F12288": inputs.ModelConfig(2, 1536, 12, 2, 128, 12288, V, dtype="bf16"),
+    # few units of the attention: up to eight context chunks with one tile of rows, seven with two, three with three
+    "one-kv-head": inputs.ModelConfig(2, 1536, 8, 1, 128, 8960, V, dtype="bf16"),
     "fp32": inputs.TINY,
     "fp32-hd128": inputs.ModelConfig(3, 272, 2, 2, 128, 2032, 1040, dtype="fp32"),
 }
@@ -32,6 +39,9 @@ CALLS = {
     "mha": ONE_TILE,
     "wide-kv": ONE_TILE,
     **{cut: ONE_TILE + [(2, 40, 8, 5)] for cut in ("4x5", "4x4", "6x8", "6x4", "10x5", "10x8")},
+    **{shape: [(1, 300, 2, 5), (4, 100, 8, 5), (17, 20, 1, 4)] for shape in ("d4096", "d2560")},
+    **{shape: [(1, 300, 2, 5), (4, 100, 8, 5), (6, 100, 8, 4), (8, 100, 8, 4), (33, 20, 1, 4)] for shape in ("F8208", "F12288")},
+    "one-kv-head": [(1, 1100, 1, 4), (2, 1100, 8, 4), (17, 900, 1, 3), (5, 700, 4, 3), (33, 500, 1, 3), (6, 500, 7, 3), (8, 300, 8, 3)],
     "fp32": [(1, 1, 1, 3), (4, 32, 2, 20), (4, 17, 4, 9)],
     "fp32-hd128": [(2, 20, 3, 10)],
 }
