@@ -350,7 +350,8 @@ const char* mtmc_data_error_string(int bits);
  *   few rows of a small model run all of their steps as one such launch.  The value is the longest time in microseconds that
  *   such a launch waits for a place on the device for all of its workgroups (1: not at all).  Where other work keeps it from that, the
  *   work is done by the workgroups that do get a place, with the same results, slower.  The next 16 calls on `w` (more if it happens again) run separate
- *   launches then.  A caller that has set a value is told (MTMC_DATA_STALLED); setting one also ends such a pause.
+ *   launches then.  Kernels of other streams mostly run between such launches: a caller whose other work is not to wait for a
+ *   step's end switches them off.  A caller that has set a value is told (MTMC_DATA_STALLED); setting one also ends such a pause.
  */
 #define MTMC_OPT_HIP_GRAPH 1
 #define MTMC_OPT_GEMM_LDS_MIN_BLOCKS 2
