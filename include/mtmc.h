@@ -344,14 +344,16 @@ const char* mtmc_data_error_string(int bits);
  *   when `stream` is being captured, without a stop token, or with a cached prefix.
  *   MTMC_OPT_PERSISTENT_DECODE (default 2 000, 0 = off): MTMC_BF16 decode steps of up to 64 rows run all blocks as
  *   one launch of one workgroup per CU, whose workgroups wait for each other between phases, instead of six launches
- *   per block.  Results do not depend on it (the same sums in the same order).  The launch needs the whole device at once: it
- *   is used while no other such launch is under way from another stream or thread of the process, by one process per
- *   device (of those that share a network namespace), and not while `stream` is being captured; every other step runs as separate launches.  MTMC_FP32 generations of
- *   few rows of a small model run all of their steps as one such launch.  The value is the longest time in microseconds that
- *   such a launch waits for a place on the device for all of its workgroups (1: not at all).  Where other work keeps it from that, the
- *   work is done by the workgroups that do get a place, with the same results, slower.  The next 16 calls on `w` (more if it happens again) run separate
- *   launches then.  Kernels of other streams mostly run between such launches: a caller whose other work is not to wait for a
- *   step's end switches them off.  A caller that has set a value is told (MTMC_DATA_STALLED); setting one also ends such a pause.
+ *   per block; MTMC_FP32 generations of few rows of a small model run all of their steps as one such launch.  Results do
+ *   not depend on it (the same sums in the same order).  The launch needs the whole device at once: it is used while no
+ *   other such launch is under way from another stream or thread of the process, by one process per device (of those
+ *   that share a network namespace), and not while `stream` is being captured; every other step runs as separate
+ *   launches.  Kernels of other streams mostly run between such launches: a caller whose other work is not to wait for
+ *   a step's end switches them off.
+ *   The value is the longest time in microseconds that such a launch waits for a place on the device for all of its
+ *   workgroups (1: not at all).  Where other work keeps it from that, the work is done by the workgroups that do get a
+ *   place, with the same results, slower, and the next 16 calls on `w` (more if it happens again) run separate launches.
+ *   A caller that has set a value is told (MTMC_DATA_STALLED); setting one also ends such a pause.
  */
 #define MTMC_OPT_HIP_GRAPH 1
 #define MTMC_OPT_GEMM_LDS_MIN_BLOCKS 2

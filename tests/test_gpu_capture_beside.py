@@ -1,0 +1,59 @@
+"""A rollout on one thread while another thread captures a graph of its own: neither disturbs the other."""
+import threading
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2511_20100_amd import inputs
+
+
+@pytest.mark.parametrize("cfg", [inputs.POLICY_1P5B.with_(n_layers=2, vocab=1040), inputs.TINY], ids=["bf16", "fp32"])
+def test_another_threads_capture(cfg):
+    import torch
+    from paper_2511_20100_amd import mtmc as lib
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 256), inputs.make_weights(cfg, seed=0, std=0.04).blob())
+    try:
+        prompts = torch.from_numpy(inputs.make_prompts(2, 20, cfg.vocab, seed=1)).cuda()
+        ws = torch.empty(lib.mtmc_rollout_workspace_bytes(handle, 2, 20, 2, 12), dtype=torch.uint8, device="cuda")
+        ids = torch.empty(4, 12, dtype=torch.int32, device="cuda")
+        lp = torch.empty(4, 12, dtype=torch.float32, device="cuda")
+        stream = torch.cuda.Stream()
+
+        def rollout():
+            lib.mtmc_rollout(handle, prompts, 2, 12, 1.0, 3, workspace=ws, out_ids=ids, out_logprobs=lp, stream=stream)
+
+        for _ in range(2):  # its step graph is there
+            rollout()
+        torch.cuda.synchronize()
+        want = ids.clone(), lp.clone()
+        ids.zero_()
+        x, y = torch.ones(1000, device="cuda"), torch.zeros(1000, device="cuda")
+        torch.cuda.synchronize()
+        go, done, failed = threading.Event(), threading.Event(), []
+
+        def other():
+            go.wait(60)
+            try:
+                for _ in range(3):  # the second finds the first one's launches under way, or ended
+                    rollout()
+            except Exception as e:  # noqa: BLE001  (reported by the test's own thread)
+                failed.append(e)
+            done.set()
+
+        thread = threading.Thread(target=other)
+        thread.start()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            y.add_(x)
+            go.set()
+            assert done.wait(60)
+            y.add_(x)
+        thread.join()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert not failed, failed
+        assert torch.equal(ids, want[0]) and torch.equal(lp, want[1]) and (y == 2).all()
+        lib.mtmc_poll_errors(handle)
+    finally:
+        lib.mtmc_weights_destroy(handle)
