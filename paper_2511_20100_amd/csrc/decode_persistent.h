@@ -222,38 +222,20 @@ __device__ __forceinline__ bool wait_grid(const Ctx& c, uint32_t phase) {
   asm volatile("" ::: "memory");
   return ok;
 }
-// The same behind the first phase, which hands nothing on but the rows of qkv: one workgroup that waits longer than the limit gives the
-// launch up for all of them, unless all are there.  It is over then for whoever waits now or comes later.
-__device__ __forceinline__ bool answer_roll(const Ctx& c) {
-  const Word mine = word_of(c.a, c.wg % kPersistTops), ended = word_of(c.a, kPersistEnded), before = {c.a.sync + kPersistGaveUp};
-  const long long t0 = wall_clock64();
-  long long limit = c.a.roll_ticks;
-  bool there = false;
-  for (int i = 0;; ++i) {
-    there = look(mine) >= kPersistGroups;
-    if (there || wall_clock64() - t0 > limit) break;
-    if (i % 16 == 15) {
-      if (look(ended)) return false;
-      if (look(before)) limit = min(limit, kAgainTicks);
-    }
-  }
-  asm volatile("" ::: "memory");
-  if (wall_clock64() - t0 <= limit) return true;
+// Behind the first phase, which hands nothing on but the rows of qkv, a workgroup that has waited longer than the limit gives the
+// launch up for all of them, unless all are there (false).  It is over then for whoever waits now or comes later.
+__device__ __forceinline__ bool give_up(const Ctx& c) {
   int closed = 0;
   if (c.lane == 0) {
-    if (c.a.told && wall_clock64() - t0 > c.a.roll_ticks) atomicOr(c.a.err_flag, kErrStalled);
-    if (!there) closed = roll_call::close([&](int g) { return word_of(c.a, kPersistTops + g); }, kPersistGroups, kGroupOf);
+    if (c.a.told) atomicOr(c.a.err_flag, kErrStalled);
+    closed = roll_call::close([&](int g) { return word_of(c.a, kPersistTops + g); }, kPersistGroups, kGroupOf);
     if (closed) {
-      before.store(1);
+      Word{c.a.sync + kPersistGaveUp}.store(1);
       __hip_atomic_store(c.a.gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      ended.store(kPersistSkipped);
+      word_of(c.a, kPersistEnded).store(kPersistSkipped);
     }
   }
-  if (__builtin_amdgcn_readfirstlane(closed)) return false;
-  while (look(mine) < kPersistGroups) {  // every group is full: the last of them are about to say so
-  }
-  asm volatile("" ::: "memory");
-  return true;
+  return __builtin_amdgcn_readfirstlane(closed);
 }
 
 // 1/rms of the current residual and, where the operand was divided by an older one, times that one's rms

@@ -112,6 +112,24 @@ __device__ __forceinline__ void row_scales(Shared& sh, const Ctx& c, const float
   }
 }
 
+// wait_grid() behind the first phase: the roll call.
+__device__ __forceinline__ bool answer_roll(const Ctx& c) {
+  const Word mine = word_of(c.a, c.wg % kPersistTops), ended = word_of(c.a, kPersistEnded), before = {c.a.sync + kPersistGaveUp};
+  const long long t0 = wall_clock64();
+  long long limit = c.a.roll_ticks;
+  for (int i = 0; look(mine) < kPersistGroups; ++i) {
+    if (i % 16 == 15) {
+      if (look(ended)) return false;
+      if (look(before)) limit = min(limit, kAgainTicks);
+    }
+    if (wall_clock64() - t0 <= limit) continue;
+    if (give_up(c)) return false;
+    limit = kWaitTicks;  // every group is full: the last of them are about to say so
+  }
+  asm volatile("" ::: "memory");
+  return true;
+}
+
 // ---- which workgroup does what.  The O projection and the sum of the splits have a row tile for workgroups 0 .. nt_d - 1; the
 // QKV tiles go to the others first (from the top down), the attention to those that start behind nt_d, and of the gate / up
 // tiles a workgroup with an O tile takes one pair where the others can take the rest: it comes to them last.

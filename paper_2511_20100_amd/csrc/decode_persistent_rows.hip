@@ -86,6 +86,29 @@ struct RowSums {
   }
 };
 
+// wait_grid() behind the first phase: the roll call.  The watch's first look comes back behind its keys and values: if that took longer
+// than the limit, callers who have set one are told, also where all are there by then.
+__device__ __forceinline__ bool answer_roll(const Ctx& c) {
+  const Word mine = word_of(c.a, c.wg % kPersistTops), ended = word_of(c.a, kPersistEnded), before = {c.a.sync + kPersistGaveUp};
+  const long long t0 = wall_clock64();
+  long long limit = c.a.roll_ticks;
+  for (int i = 0;; ++i) {
+    const bool there = look(mine) >= kPersistGroups;
+    if (wall_clock64() - t0 <= limit) {
+      if (there) break;
+      if (i % 16 == 15) {
+        if (look(ended)) return false;
+        if (look(before)) limit = min(limit, kAgainTicks);
+      }
+      continue;
+    }
+    if (give_up(c)) return false;
+    limit = kWaitTicks;  // every group is full: the last of them are about to say so
+  }
+  asm volatile("" ::: "memory");
+  return true;
+}
+
 // GU_TILES row tiles of the gate / up projection per workgroup, 8 ranges of K, one per wavefront; the sums go over in rounds of
 // kGroup tiles of 16 rows.
 template <int BT, int GU_TILES>

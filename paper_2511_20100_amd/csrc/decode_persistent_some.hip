@@ -1,7 +1,7 @@
 // The residual blocks of a decode step by whatever workgroups are there: what does the step when the persistent launch before
 // it (decode_persistent.hip, decode_persistent_rows.hip) was given up because something else held a part of the device.  Behind one that
-// was not, which is the rule, its workgroups look at a word and leave.  With the roll call that costs 2 to 5 us a step (63 steps of
-// one row 62.52 -> 62.75 ms, 127 of 64 rows 219.5 -> 220.1), by as many workgroups as there are CUs or by 16.
+// was not, which is the rule, its workgroups look at a word and leave.  With the roll call that costs up to 4 us a step (63 steps of
+// one row 62.64 -> 62.66 ms, 127 of 64 rows 219.5 -> 220.0), by as many workgroups as there are CUs or by 16.
 //
 // The workgroups that come within 20 us share all units of each phase out among themselves, one after the other, and wait for each
 // other alone (roll_call.h), so it ends however few they are.  Every sum has the ranges and the order of the launches it
