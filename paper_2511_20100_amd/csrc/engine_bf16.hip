@@ -9,6 +9,7 @@
 #include "engine.h"
 #include "kernels.h"
 #include "lease_cache.h"
+#include "outside_captures.h"
 #include "persistent_turn.h"
 
 namespace mtmc {
@@ -43,9 +44,8 @@ struct StepExec {
     if (done) (void)hipEventDestroy(done);
   }
   bool idle() {
-    if (!recorded) return true;
-    if (hipEventQuery(done) != hipErrorNotReady) return true;
-    (void)hipGetLastError();
+    if (!recorded || hipEventQuery(done) == hipSuccess) return true;
+    (void)hipGetLastError();  // any other answer says nothing about the work
     return false;
   }
   void wait() {
@@ -631,6 +631,7 @@ int decode_graph(const mtmc_weights* w, const RolloutPlan& gp, hipStream_t st, c
     (void)hipGetLastError();
     return MTMC_OK;
   }
+  OutsideCaptures outside;
   GraphCache& gc = graph_cache(w);
   std::lock_guard<std::mutex> lock(gc.mu);
   if (!gc.capture_stream) {  // the caller's stream may be the default stream, which cannot capture

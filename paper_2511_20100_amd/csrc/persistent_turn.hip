@@ -11,6 +11,8 @@
 
 #include <algorithm>
 
+#include "outside_captures.h"
+
 namespace mtmc {
 namespace {
 
@@ -21,20 +23,6 @@ struct DeviceTurn {
   hipStream_t stream = nullptr;
   bool recorded = false;
 };
-// Another thread may be capturing a stream in global mode, which refuses other threads' queries of an event and can end with
-// them.  What a turn asks is no part of such a capture.
-class OutsideCaptures {
- public:
-  OutsideCaptures() { swap(); }
-  OutsideCaptures(const OutsideCaptures&) = delete;
-  OutsideCaptures& operator=(const OutsideCaptures&) = delete;
-  ~OutsideCaptures() { swap(); }
-
- private:
-  void swap() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
-  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
-};
-
 constexpr int kMaxDevices = 64;
 DeviceTurn g_turns[kMaxDevices];  // events stay until the process ends
 

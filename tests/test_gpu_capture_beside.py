@@ -23,6 +23,16 @@ def test_another_threads_capture(cfg):
         def rollout():
             lib.mtmc_rollout(handle, prompts, 2, 12, 1.0, 3, workspace=ws, out_ids=ids, out_logprobs=lp, stream=stream)
 
+        # calls of other shapes: each records a step graph of its own, and from the ninth on one makes room for another
+        # (all memory is there beforehand: allocating is not for while a thread captures)
+        shapes = [dict(max_new=n, workspace=torch.empty(lib.mtmc_rollout_workspace_bytes(handle, 2, 20, 1, n), dtype=torch.uint8, device="cuda"),
+                       out_ids=torch.empty(2, n, dtype=torch.int32, device="cuda"),
+                       out_logprobs=torch.empty(2, n, dtype=torch.float32, device="cuda")) for n in range(9, 27)]
+
+        def rollouts_of_other_shapes():
+            for shape in shapes:
+                lib.mtmc_rollout(handle, prompts, n_samples=1, temperature=1.0, seed=3, stream=stream, **shape)
+
         for _ in range(2):  # its step graph is there
             rollout()
         torch.cuda.synchronize()
@@ -37,6 +47,8 @@ def test_another_threads_capture(cfg):
             try:
                 for _ in range(3):  # the second finds the first one's launches under way, or ended
                     rollout()
+                rollouts_of_other_shapes()
+                rollout()
             except Exception as e:  # noqa: BLE001  (reported by the test's own thread)
                 failed.append(e)
             done.set()
