@@ -179,12 +179,15 @@ struct Ctx {
   int wg, wave, lane;
 };
 // The same as new to the compiler: it would otherwise work out the addresses of all phases ahead of the loop over the blocks
-// and keep them, a thousand registers of them.
+// and keep them, a thousand registers of them.  The lane is a statement of its own: together with it the other outputs count as
+// different from lane to lane, and every buffer load whose place depends on the wavefront becomes a loop over the lanes' values
+// (162 such loops in the one-tile kernels, 294 in the others; 1.5 B blocks, 64 rows: 1533 -> 1521 us a step).
 using KernArgs = const __attribute__((address_space(4))) PersistArgs*;
 __device__ __forceinline__ Ctx fresh(int wave) {
   KernArgs k = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
   int lane = threadIdx.x & 63, wg = blockIdx.x;
-  asm volatile("" : "+s"(k), "+s"(wg), "+s"(wave), "+v"(lane));
+  asm volatile("" : "+s"(k), "+s"(wg), "+s"(wave));
+  asm volatile("" : "+v"(lane));
   return Ctx{*(const PersistArgs*)k, wg, wave, lane};
 }
 
