@@ -2,7 +2,8 @@
 // how its workgroups hand data to each other, how they wait for each other, and the sums that both forms make alike.
 //
 // What one workgroup writes and another reads goes past the caches that are not coherent between the dies: device-scope (sc1)
-// stores, drained before the workgroup is counted in, and device-scope loads, or plain ones where Operand says why.
+// stores, drained before the workgroup is counted in (where readers wait for the counters), and device-scope loads, or plain ones
+// where Operand says why.
 #pragma once
 
 #include "attention_decode.h"
@@ -43,6 +44,17 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// ---- readers that ask for the data themselves.  A word that nobody has written yet holds kNotThere, and a reader asks again, past
+// the caches, until no word of what it needs does.  An fp16 pair is never that word (the converters saturate), an fp32 value
+// only as a NaN that no instruction makes; written() turns that one into another NaN.
+constexpr uint32_t kNotThere = 0xffffffffu;
+__device__ __forceinline__ uint32_t written(uint32_t w) { return min(w, kNotThere - 1); }
+__device__ __forceinline__ v4u written(v4f v) {
+  const v4u w = __builtin_bit_cast(v4u, v);
+  return v4u{written(w[0]), written(w[1]), written(w[2]), written(w[3])};
+}
+__device__ __forceinline__ uint32_t largest(v4u w) { return max(max(w[0], w[1]), max(w[2], w[3])); }
+
 // The operand of MU tiles of 16 rows, fragment-tiled.  The operands of the QKV, gate / up and down projections are read through
 // the caches (SCOPE 0): every block of the step has buffers of its own for them, so no line of them is in a cache before it has
 // been written, and no line is written by two workgroups (a row tile's 16 columns of 16 rows are 512 bytes).  Past the caches
@@ -62,6 +74,15 @@ struct Operand {
     for (int i = 0; i < MU; ++i) x.off[i] = (mt0 + i) * 16 + (lane & 15) < B ? (mt0 + i) * 1024 + lane * 16 : kReach;
     return x;
   }
+  // one tile whose pieces hold `rows` rows (16: as tiled()); rows of fewer lie closer, fewer lines to ask for
+  __device__ __forceinline__ static Operand packed(const void* p, int rows, int lane, int B) {
+    static_assert(MU == 1, "");
+    Operand x;
+    x.r = rsrc_of(p);
+    x.step = rows * 64;
+    x.off[0] = (lane & 15) < B ? (lane >> 4) * (rows * 16) + (lane & 15) * 16 : kReach;
+    return x;
+  }
   __device__ __forceinline__ v8h load(int i, int at) const {
     return __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(r, off[i], at, SCOPE));
   }
@@ -76,6 +97,7 @@ struct Operand {
 template <int NB, int MU, int PF, int PFX>
 struct Stream {
   static_assert(PF % PFX == 0, "the weight ring must be a multiple of the operand ring");
+  static constexpr int kOperandsAhead = PFX;
   Rsrc w;
   int rows[NB];
   int k0, k1, n0, n, last, lane;
@@ -117,6 +139,60 @@ struct Stream {
 #pragma unroll
       for (int mu = 0; mu < MU; ++mu) y.off[mu] = s < n ? x.off[mu] : kReach;
       operand(y, s, s);
+    }
+  }
+  __device__ __forceinline__ uint32_t largest_of(int s) const {
+    uint32_t top = 0;
+#pragma unroll
+    for (int mu = 0; mu < MU; ++mu) top = max(top, largest(__builtin_bit_cast(v4u, xr[s][mu])));
+    return top;
+  }
+  __device__ __forceinline__ uint32_t largest_ahead() const {
+    uint32_t top = 0;
+#pragma unroll
+    for (int s = 0; s < PFX; ++s) top = max(top, largest_of(s));
+    return top;
+  }
+  // operands() and run() over all steps, of an operand that is asked for until it is there; `asked`: the steps that ask() saw to
+  template <int SCOPE, class Asker>
+  __device__ __forceinline__ void ask(const Operand<MU, SCOPE>& x, const Asker& asker) {
+    asker([&] {
+      operands(x);
+      return largest_ahead();
+    });
+  }
+  template <int SCOPE, class Asker>
+  __device__ __forceinline__ void run_asking(const Operand<MU, SCOPE>& x, const Asker& asker, v4f (&acc)[NB][MU], int asked) {
+    auto ready = [&](int s, int i) {
+      if (i >= asked && asker.missing(largest_of(s % PFX))) {
+        asker([&] {
+          operand(x, s % PFX, i);
+          return largest_of(s % PFX);
+        });
+      }
+    };
+    int i = 0;
+    for (; i + 2 * PF <= n; i += PF) {
+#pragma unroll
+      for (int s = 0; s < PF; ++s) {
+        ready(s, i + s);
+        multiply(s, acc);
+        __builtin_amdgcn_sched_barrier(0);
+        weights(s, i + s + PF, lane * 16);
+        operand(x, s % PFX, i + s + PFX);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    for (; i < n; i += PF) {
+#pragma unroll
+      for (int s = 0; s < PF; ++s) {
+        if (i + s < n) {
+          ready(s, i + s);
+          multiply(s, acc);
+          if (i + s + PF < n) weights(s, i + s + PF, lane * 16);
+          if (i + s + PFX < n) operand(x, s % PFX, i + s + PFX);
+        }
+      }
     }
   }
   __device__ __forceinline__ void multiply(int s, v4f (&acc)[NB][MU]) {
@@ -225,6 +301,36 @@ __device__ __forceinline__ bool wait_grid(const Ctx& c, uint32_t phase) {
   asm volatile("" ::: "memory");
   return ok;
 }
+// One wavefront asks until what load() brings is all there (load() gives the largest word of it), or the launch is over; *stop then.
+struct Asker {
+  const PersistArgs& a;
+  int* stop;
+  __device__ __forceinline__ static bool missing(uint32_t top) { return __builtin_amdgcn_ballot_w64(top == kNotThere) != 0; }
+  template <class Load>
+  __device__ __forceinline__ void operator()(Load load) const {
+    long long t0 = 0;
+    for (int i = 0; missing(load()); ++i) {
+      if (i == 0) t0 = wall_clock64();
+      if (i % 64 != 63) continue;
+      const Word ended = word_of(a, kPersistEnded);
+      const bool late = wall_clock64() - t0 > kWaitTicks;
+      if (late || look(ended)) {
+        if (late) {
+          ended.store(kPersistLost);
+          atomicOr(a.err_flag, kErrUnfinished);
+        }
+        *stop = 1;
+        break;
+      }
+    }
+  }
+};
+// Where nothing has to be asked for: the readers have waited for the counters.
+struct Known {
+  __device__ __forceinline__ static bool missing(uint32_t) { return false; }
+  template <class Load>
+  __device__ __forceinline__ void operator()(Load load) const { load(); }
+};
 // Behind the first phase, which hands nothing on but the rows of qkv, a workgroup that has waited longer than the limit gives the
 // launch up for all of them, unless all are there (false).  It is over then for whoever waits now or comes later.
 __device__ __forceinline__ bool give_up(const Ctx& c) {
@@ -256,13 +362,36 @@ struct TileOut {
   float* ss_out;  // the same for the launches that follow, or NULL
   int* err_flag;
   int d, B;
+  // the one-tile form: rows of a piece of x, and how often x and ss are written, each time that many bytes further on
+  int x_rows, copies, x_copy, ss_copy;
+  // ... the columns of a tile that have no row write the copies, at_once of them at a time: this lane those of `row` from `first` on
+  int row, first, at_once;
+  __device__ __forceinline__ TileOut(const PersistArgs& a, h16_t* x_, float* ss_, int which, int rows, int copies_, bool last, int lane)
+      : h(rsrc_of(nullptr)), x(keep(x_)), ss(keep(ss_)), ss_out(last ? a.ss[which] : nullptr),
+        err_flag(keep(a.err_flag)), d(keep(a.d)), B(keep(a.B)), x_rows(keep(rows)), copies(copies_), x_copy(a.at_hand.x_copy),
+        ss_copy(a.at_hand.ss_copy), row((lane & 15) % B), first((lane & 15) / B), at_once(16 / B) {}
   __device__ __forceinline__ TileOut(const PersistArgs& a, h16_t* x_, int which, bool last)
       : h(rsrc_of(keep(a.h))), x(keep(x_)), ss(keep(a.ss_in[which])), ss_out(last ? a.ss[which] : nullptr),
-        err_flag(keep(a.err_flag)), d(keep(a.d)), B(keep(a.B)) {}
+        err_flag(keep(a.err_flag)), d(keep(a.d)), B(keep(a.B)), x_rows(0), copies(1), x_copy(0), ss_copy(0), row(0), first(0), at_once(1) {}
 };
+// Place of row m, column n of an operand whose pieces hold `rows` rows (16: the layout of act_off()).
+__device__ __forceinline__ int packed_off(int m, int n, int rows) {
+  return (n >> 5) * (rows * 32) + ((n & 31) >> 3) * (rows * 8) + m * 8 + (n & 7);
+}
+// Where a tile's operand and squares will go in a later block: nothing is written there yet.
+__device__ __forceinline__ void not_there(const TileOut& to, int nt, int lane) {
+  const int n = nt * 16 + (lane >> 4) * 4;
+  const uint2 none = make_uint2(kNotThere, kNotThere);
+  for (int c = 0; c < to.copies; c += to.at_once) {
+    if (to.first >= min(to.at_once, to.copies - c)) continue;
+    st8((char*)(to.x + packed_off(to.row, n, to.x_rows)) + (c + to.first) * to.x_copy, none);
+    if (lane < 16) st4((float*)((char*)(to.ss + to.row * kPersistGrid + nt) + (c + to.first) * to.ss_copy), __uint_as_float(kNotThere));
+  }
+}
 // h += sum; x' = fp16(h gain r); the squares' sum of the tile.  Lane: row m, columns n = 16 nt + 4 (lane / 16) ..
-template <int BT>
-__device__ __forceinline__ void residual_tile(const TileOut& to, int nt, int mt, int lane, v4f sum, v4f h_old, v4f gain, float sc) {
+// PACKED: x in pieces of to.x_rows rows, and h stays with the caller (returned).
+template <int BT, bool PACKED = false>
+__device__ __forceinline__ v4f residual_tile(const TileOut& to, int nt, int mt, int lane, v4f sum, v4f h_old, v4f gain, float sc) {
   const int m = mt * 16 + (lane & 15), n = nt * 16 + (lane >> 4) * 4;
   const bool live = m < to.B;
   v4f hv = h_old + sum;
@@ -271,18 +400,34 @@ __device__ __forceinline__ void residual_tile(const TileOut& to, int nt, int mt,
   uint2 pk;
   pk.x = pack_h16x2_track(hv[0] * gain[0] * sc, hv[1] * gain[1] * sc, out_of_range);
   pk.y = pack_h16x2_track(hv[2] * gain[2] * sc, hv[3] * gain[3] * sc, out_of_range);
-  if (live) {
-    st16(to.h, (m * to.d + n) * 4, 0, __builtin_bit_cast(v4u, hv));
-    st8(to.x + act_off(m, n, 16 * BT), pk);
+  if (live && !PACKED) st16(to.h, (m * to.d + n) * 4, 0, __builtin_bit_cast(v4u, hv));
+  if constexpr (!PACKED) {
+    if (live) st8(to.x + act_off(m, n, 16 * BT), pk);
+  } else if (to.copies == 1) {
+    if (live) st8(to.x + packed_off(m, n, to.x_rows), pk);
+  } else {
+    const int from = (lane & 48) + to.row;
+    const uint2 mine = make_uint2(__shfl(pk.x, from, 64), __shfl(pk.y, from, 64));
+    for (int c = 0; c < to.copies; c += to.at_once)
+      if (to.first < min(to.at_once, to.copies - c))
+        st8((char*)(to.x + packed_off(to.row, n, to.x_rows)) + (c + to.first) * to.x_copy, mine);
   }
   float ss = fmaf(hv[0], hv[0], hv[1] * hv[1]) + fmaf(hv[2], hv[2], hv[3] * hv[3]);  // rounded as in the separate launches
   ss += __shfl_xor(ss, 16, 64);
   ss += __shfl_xor(ss, 32, 64);
+  const float s = __uint_as_float(written(__float_as_uint(ss)));
+  if (PACKED && to.copies > 1) {
+    const float mine = __shfl(s, to.row, 64);
+    for (int c = 0; c < to.copies; c += to.at_once)
+      if (lane < 16 && to.first < min(to.at_once, to.copies - c))
+        st4((float*)((char*)(to.ss + to.row * kPersistGrid + nt) + (c + to.first) * to.ss_copy), mine);
+  }
   if (lane < 16 && live) {
-    st4(to.ss + m * kPersistGrid + nt, ss);
+    if (!PACKED || to.copies == 1) st4(to.ss + m * kPersistGrid + nt, s);
     if (to.ss_out) st4(to.ss_out + nt * 16 * BT + m, ss);
   }
   if (live && out_of_range) atomicOr(to.err_flag, kErrFp16Range);
+  return hv;
 }
 
 // The unit of a workgroup in the attention phase, the same in every block: (sequence, kv head, chunk) and its place in the cache.
@@ -322,6 +467,7 @@ struct AttnHeld {
   int b, g, chunk, pos, lo, hi, id0, id1;
   bool there, active;
   float rope_c, rope_s;
+  // Mpad: rows of the operand that the output goes to; 0: the caller clears the part of a unit that is not active
   __device__ __forceinline__ AttnHeld(const PersistArgs& a, int place, int wave, int lane, int* table, int Mpad) {
     const AttnUnit u(a, place);
     b = u.b; g = u.g; chunk = u.chunk; pos = u.r.pos; lo = u.r.lo; hi = u.r.hi;
@@ -336,7 +482,7 @@ struct AttnHeld {
     const size_t at = (size_t)max(pos, 0) * (kHeadDim / 2) + lane;
     rope_c = a.at.cos[at];
     rope_s = a.at.sin[at];
-    if (there && !active) {
+    if (there && !active && Mpad) {
       // a chunk beyond the context contributes nothing, which its consumer learns from a zero sum; its part of the operand
       // is cleared so that stale bits never meet a zero weight.  Once: nobody writes it in this launch.
       const int G = a.at.Hq / a.at.Hkv;
@@ -350,11 +496,32 @@ struct AttnHeld {
     }
   }
 };
-// The active unit in block l, by wavefronts 0 .. AW - 1; two barriers of the workgroup.  enter() lets the wavefront into the
-// phase: the rows of qkv are there (false: the launch ends).  The stores are left to be drained.
+// How the rows of qkv come to a unit and where its output goes: enter() lets the wavefront into the phase, where the rows of qkv are there
+// (false: the launch ends).
+template <class Enter>
+struct CountedUnit {
+  int Mpad;
+  Enter enter;
+  __device__ __forceinline__ const float* qkv(const PersistArgs& a) const { return keep(a.at.qkv); }
+  __device__ __forceinline__ h16_t* out(const PersistArgs& a, int chunk) const { return keep(a.at.o) + chunk * a.at.o_chunk_stride; }
+  __device__ __forceinline__ float* ml(const PersistArgs& a) const { return keep(a.at.ml); }
+  __device__ __forceinline__ size_t place(int m, int k) const { return act_off(m, k, Mpad); }
+  __device__ __forceinline__ void before_stores() const {}
+  // load() once the rows are there
+  template <class Load>
+  __device__ __forceinline__ bool operator()(const PersistArgs&, Load load) const {
+    if (!enter()) return false;
+    load();
+    return true;
+  }
+};
+template <class Enter>
+__device__ __forceinline__ CountedUnit<Enter> counted_unit(int Mpad, Enter enter) { return {Mpad, enter}; }
+
+// The active unit in block l, by wavefronts 0 .. AW - 1; two barriers of the workgroup.  The stores are left to be drained.
 // TWO_SETS: two sets of registers for keys and values, the next pair of pages on its way while one is multiplied.
-template <bool TWO_SETS, class Enter>
-__device__ __forceinline__ bool attend(const AttnHeld& u, AttnLds& at, const int* table, int l, int wave, int Mpad, Enter enter) {
+template <bool TWO_SETS, class Hand>
+__device__ __forceinline__ bool attend(const AttnHeld& u, AttnLds& at, const int* table, int l, int wave, const Hand& hand) {
         const Ctx c = fresh(wave);
         const PersistArgs& a = c.a;
         const int w = c.wave, lane = c.lane, tid = w * 64 + lane, col = lane & 15, lg = lane >> 4;
@@ -378,12 +545,11 @@ __device__ __forceinline__ bool attend(const AttnHeld& u, AttnLds& at, const int
         if constexpr (TWO_SETS) {
           if (n_st > 1) alt = load_stage(1);
         }
-        const float* row = keep(a.at.qkv) + (size_t)u.b * (Hq + 2 * Hkv) * kHeadDim;
+        const float* row = hand.qkv(a) + (size_t)u.b * (Hq + 2 * Hkv) * kHeadDim;
         int* const err_flag = keep(a.err_flag);
         const int n_chunks = keep(a.at.n_chunks);
-        h16_t* const out = keep(a.at.o) + u.chunk * a.at.o_chunk_stride;
-        float* const ml = keep(a.at.ml);
-        if (!enter()) return false;
+        h16_t* const out = hand.out(a, u.chunk);
+        float* const ml = hand.ml(a);
         const int cur_page = u.pos / kPageTokens, slot = u.pos % kPageTokens;
         const bool owner = cur_page >= u.lo && cur_page < u.hi;
         const bool appends = owner && w == AW - 1;
@@ -392,9 +558,17 @@ __device__ __forceinline__ bool attend(const AttnHeld& u, AttnLds& at, const int
           const float* qp = row + (size_t)(u.g * G + min(w, G - 1)) * kHeadDim;
           const float* kp = row + (size_t)(Hq + u.g) * kHeadDim;
           const float* vp = kp + (size_t)Hkv * kHeadDim;
-          const float q0 = ld4(qp + lane), q1 = ld4(qp + lane + 64);
+          float q0, q1, x0 = 0.f, x1 = 0.f, v0 = 0.f, v1 = 0.f;
+          if (!hand(a, [&] {
+                q0 = ld4(qp + lane); q1 = ld4(qp + lane + 64);
+                if (appends) {
+                  x0 = ld4(kp + lane); x1 = ld4(kp + lane + 64);
+                  v0 = ld4(vp + lane); v1 = ld4(vp + lane + 64);
+                }
+                return max(largest(__builtin_bit_cast(v4u, v4f{q0, q1, x0, x1})), max(__float_as_uint(v0), __float_as_uint(v1)));
+              }))
+            return false;
           if (appends) {
-            const float x0 = ld4(kp + lane), x1 = ld4(kp + lane + 64), v0 = ld4(vp + lane), v1 = ld4(vp + lane + 64);
             const h16_t k0 = f32_to_h16_flag(rot(x0, x1, -u.rope_s), err_flag), k1 = f32_to_h16_flag(rot(x1, x0, u.rope_s), err_flag);
             const h16_t y0 = f32_to_h16_flag(v0, err_flag), y1 = f32_to_h16_flag(v1, err_flag);
             at.k[lane] = k0; at.k[lane + 64] = k1;
@@ -491,6 +665,7 @@ __device__ __forceinline__ bool attend(const AttnHeld& u, AttnLds& at, const int
           at.l[w][col] = sum_l;
         }
         lds_barrier();
+        hand.before_stores();
         // merge the wavefronts: thread t < 16 G owns (head h, 8 consecutive dims)
         if (tid < G * (kHeadDim / 8)) {
           const int h = tid / (kHeadDim / 8), d0 = (tid % (kHeadDim / 8)) * 8;
@@ -508,7 +683,7 @@ __device__ __forceinline__ bool attend(const AttnHeld& u, AttnLds& at, const int
           uint32_t pk[4];
   #pragma unroll
           for (int e = 0; e < 4; ++e) pk[e] = pack_h16x2_flag(acc[2 * e] * inv, acc[2 * e + 1] * inv, err_flag);
-          h16_t* o = out + act_off(u.b, (u.g * G + h) * kHeadDim + d0, Mpad);
+          h16_t* o = out + hand.place(u.b, (u.g * G + h) * kHeadDim + d0);
           st8(o, make_uint2(pk[0], pk[1]));
           st8(o + 4, make_uint2(pk[2], pk[3]));
           if (n_chunks > 1 && d0 == 0)

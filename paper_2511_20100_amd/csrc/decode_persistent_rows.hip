@@ -222,7 +222,7 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
     if (!unit.active) {
       if (!enter_attention()) return;
     } else {
-      if (!attend<true>(unit, sh.at, sh.table, l, wave, 16 * BT, enter_attention)) return;
+      if (!attend<true>(unit, sh.at, sh.table, l, wave, counted_unit(16 * BT, enter_attention))) return;
     }
     leave();
     // ---- O projection: at most one unit per workgroup

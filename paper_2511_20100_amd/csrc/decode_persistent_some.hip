@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_decode_layers_some(PersistArgs 
     for (int place = id; place < kPersistGrid; place += n) {
       const AttnHeld unit(a, place, wave, lane, sh.table, 16 * BT);
       __syncthreads();
-      if (unit.active) attend<false>(unit, sh.at, sh.table, l, wave, 16 * BT, [] { return true; });
+      if (unit.active) attend<false>(unit, sh.at, sh.table, l, wave, counted_unit(16 * BT, [] { return true; }));
       __syncthreads();
     }
     if (!meet()) return;

@@ -351,16 +351,28 @@ bool persistent_fits(const mtmc_weights* w, const Dims& D, int B, int bt, int n_
 }
 // Rows of the largest batch of the call whose steps may run as one launch: its groups of prompts, the last one with the launch
 // shape of the others, and (prompts of different lengths) the slots that live rows are packed into.
-int persistent_rows(const mtmc_weights* w, const Dims& D, const RolloutPlan& p) {
-  int most = 0;
-  if (p.max_new < 2) return most;
-  for (int B : {p.B, ((p.total_prompts - 1) % p.n_prompts + 1) * p.n_samples})
-    if (persistent_fits(w, D, B, tiles16(B), p.n_chunks, p.down_nb, p.ks_down)) most = std::max(most, tiles16(B));
+bf16::PersistHand persist_hand_of(const Dims& D, int B, int n_chunks, int ks_down) {
+  return bf16::persist_hand(B, D.kt_d, D.kt_F, D.nt_qkv, D.kt_nq, D.Hq, n_chunks, ks_down);
+}
+// rows, and the bytes of a piece of what a step of few rows hands on
+struct PersistRoom {
+  int rows;
+  size_t hand;
+};
+PersistRoom persistent_room(const mtmc_weights* w, const Dims& D, const RolloutPlan& p) {
+  PersistRoom room{0, 0};
+  if (p.max_new < 2) return room;
+  auto may_run = [&](int B, int n_chunks, int down_nb, int ks_down) {
+    if (!persistent_fits(w, D, B, tiles16(B), n_chunks, down_nb, ks_down)) return;
+    room.rows = std::max(room.rows, tiles16(B) * 16);
+    if (B <= bf16::kPersistAskRows) room.hand = std::max(room.hand, (size_t)persist_hand_of(D, B, n_chunks, ks_down).bytes);
+  };
+  for (int B : {p.B, ((p.total_prompts - 1) % p.n_prompts + 1) * p.n_samples}) may_run(B, p.n_chunks, p.down_nb, p.ks_down);
   for (int bt = 1; p.ragged && bt < p.bt; ++bt) {
     const DecodeTune t = tune_decode(D, bt * 16, bt, p.max_pages);
-    if (persistent_fits(w, D, bt * 16, bt, t.n_chunks, t.down_nb, t.ks_down)) most = std::max(most, bt);
+    may_run(bt * 16, t.n_chunks, t.down_nb, t.ks_down);
   }
-  return most * 16;
+  return room;
 }
 }  // namespace
 
@@ -389,7 +401,8 @@ void bf16_plan_rollout_extra(const mtmc_weights* w, RolloutPlan& p, Carver& cv) 
   p.ssA = cv.take<float>((size_t)D.nt_d * Mpad);
   p.ssB = cv.take<float>((size_t)D.nt_d * Mpad);
   p.rs_buf = cv.take<float>(Mpad);
-  p.persist_rows = persistent_rows(w, D, p);
+  const PersistRoom room = persistent_room(w, D, p);
+  p.persist_rows = room.rows;
   if (p.persist_rows > 0) {  // what the persistent step hands from phase to phase, a buffer per block
     const size_t rows = p.persist_rows, L = w->cfg.n_layers;
     p.sync = cv.take<uint32_t>(bf16::kPersistSyncWords);
@@ -397,6 +410,7 @@ void bf16_plan_rollout_extra(const mtmc_weights* w, RolloutPlan& p, Carver& cv) 
     p.xo_l = cv.take<h16_t>(L * rows * D.d);
     p.xr_l = cv.take<h16_t>(L * rows * D.d);
     p.act_l = cv.take<h16_t>(L * rows * D.F);
+    p.hand = cv.take<char>(bf16::kPersistPieces * room.hand);
   }
   if (p.ragged) {
     p.slot_row = cv.take<int>(Mpad);
@@ -519,6 +533,10 @@ bf16::PersistArgs persistent_args(const mtmc_weights* w, const Dims& D, const Ro
   a.xo = (h16_t*)p.xo_l; a.xr = (h16_t*)p.xr_l; a.act = (h16_t*)p.act_l;
   a.x_stride = rows * D.d; a.act_stride = rows * D.F;
   a.at = at;
+  if (p.B <= bf16::kPersistAskRows) {
+    a.hand = (char*)p.hand;
+    a.at_hand = persist_hand_of(D, p.B, p.n_chunks, p.ks_down);
+  }
   a.sync = p.sync; a.roll_ticks = 100LL * (w->opt_persistent_wait_us - 1); a.told = w->opt_persistent_told;
   a.gave_up = w->gave_up; a.err_flag = w->err_flag;
   return a;

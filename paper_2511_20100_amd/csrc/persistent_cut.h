@@ -1,6 +1,8 @@
 // Which decode steps run as one launch, and how that one is cut.  Host code only.
 #pragma once
 
+#include <stddef.h>
+
 namespace mtmc {
 namespace bf16 {
 
@@ -37,6 +39,48 @@ inline bool decode_persistent_fits(const PersistShape& s) {
   // sequences, which keeps the splits that were chosen for 128 rows
   const bool down = dn == 5 ? s.ks_down == 8 && s.nt_d <= 96 : s.ks_down * ((s.nt_d + tiles - 1) / tiles) <= kPersistGrid;
   return down && (s.m_tiles == 1 || persist_rows_fit(s.m_tiles, gu, dn));
+}
+
+// Steps of so few rows hand their data to readers that ask for them (decode_persistent.hip).
+constexpr int kPersistAskRows = 4;
+// What the phases of such a step hand on: a piece of memory per block (block l: l % kPersistPieces), in which every buffer has the
+// rows of the batch and no others (bytes from the piece's start).  What all workgroups ask for is there kPersistCopies times, a copy
+// for the workgroups of a die.
+//
+// Readers ask until a word is no longer the one that says that nobody has written it.  The first two pieces are filled with that word
+// before the step.  Later, who writes a place in one block (always the same wavefront) first puts the word into the place of the
+// block behind it and waits for that store.  So
+//   - whoever asks for a place has seen what was written to it in the block before, and with that the word was there;
+//   - what the word goes over is of three blocks before, and its readers are done.  Every writer has asked for something in the
+//     same phase one block earlier (a unit of the attention without a part of the context, too), and each phase's data come, one
+//     phase after the other, of all that was read in the phases of a whole block before.  x, ss0 and the ss1 of the block before are
+//     read one block later than the others: x and ss0 are marked at the end of a block, behind an O projection that came of them
+//     all, ss1 behind the sum of the splits.
+constexpr int kPersistCopies = 8, kPersistPieces = 3;
+struct PersistHand {
+  int x, xo, act, qkv, o, ml, part, ss0, ss1;  // x, ss0: of the block before it; o, ml: chunk by chunk, o_chunk bytes apart
+  int x_copy, ss_copy, o_chunk, bytes;
+};
+inline PersistHand persist_hand(int B, int kt_d, int kt_F, int nt_qkv, int kt_nq, int heads, int n_chunks, int ks_down) {
+  PersistHand h{};
+  auto take = [&](int n) {
+    const int at = h.bytes;
+    h.bytes += (n + 127) / 128 * 128;
+    return at;
+  };
+  h.x_copy = (B * kt_d * 64 + 4095) / 4096 * 4096;
+  h.ss_copy = B * kPersistGrid * 4;
+  h.x = take(kPersistCopies * h.x_copy);
+  h.xo = take(kPersistCopies * h.x_copy);
+  h.act = take(B * kt_F * 64);
+  h.qkv = take(B * nt_qkv * 64);
+  h.o_chunk = B * kt_nq * 64;
+  h.o = take(n_chunks * h.o_chunk);
+  h.ml = take(B * heads * n_chunks * 8);
+  h.part = take(B * kt_d * 128 * ks_down);
+  h.ss0 = take(kPersistCopies * h.ss_copy);
+  h.ss1 = take(kPersistCopies * h.ss_copy);
+  return h;
 }
 
 }  // namespace bf16

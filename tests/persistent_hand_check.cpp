@@ -1,0 +1,36 @@
+// What the one-launch step of few rows hands from phase to phase: every buffer in its place, none over another, all on 128 bytes.
+// Compiled and run by test_few_rows.py; exits non-zero at the first shape that does not hold.
+#include <cstdio>
+#include <cstdlib>
+#include <initializer_list>
+
+#include "persistent_cut.h"
+
+using namespace mtmc::bf16;
+
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s (B %d kt_d %d)\n", __LINE__, #x, B, kt_d); std::exit(1); } } while (0)
+
+int main() {
+  for (int B = 1; B <= kPersistAskRows; ++B)
+    for (int kt_d : {48, 50, 112, 128})
+      for (int kt_F : {1, 16, 35, 280, 640})
+        for (int kv : {1, 4, 32})
+          for (int chunks = 1; chunks <= 8; ++chunks)
+            for (int ks : {1, 4, 8, 40}) {
+              const int heads = 32, kt_nq = heads * 4, nt_qkv = (heads + 2 * kv) * 8;
+              const PersistHand h = persist_hand(B, kt_d, kt_F, nt_qkv, kt_nq, heads, chunks, ks);
+              const long need[][2] = {{h.x, (long)kPersistCopies * h.x_copy}, {h.xo, (long)kPersistCopies * h.x_copy}, {h.act, B * kt_F * 64L},
+                                      {h.qkv, B * nt_qkv * 64L}, {h.o, (long)chunks * h.o_chunk}, {h.ml, B * heads * chunks * 8L},
+                                      {h.part, (long)ks * B * kt_d * 32 * 4}, {h.ss0, (long)kPersistCopies * h.ss_copy},
+                                      {h.ss1, (long)kPersistCopies * h.ss_copy}};
+              CHECK(h.x_copy >= B * kt_d * 64 && h.o_chunk == B * kt_nq * 64 && h.ss_copy >= B * kPersistGrid * 4);
+              long end = 0;
+              for (auto& n : need) {
+                CHECK(n[0] % 128 == 0 && n[0] >= end);
+                end = n[0] + n[1];
+              }
+              CHECK(kPersistPieces == 3 && end <= h.bytes && h.bytes % 128 == 0 && h.x_copy % 128 == 0 && h.o_chunk % 16 == 0 && h.ss_copy % 4 == 0);
+            }
+  std::printf("ok\n");
+  return 0;
+}
