@@ -90,7 +90,7 @@ extern "C" int mtmc_weights_create(const mtmc_config* cfg, const void* blob, siz
   w->aux = nullptr;
   w->opt_hip_graph = 1;
   w->opt_lds_min_blocks = 32;
-  w->opt_stop_poll = 32;
+  w->opt_stop_poll = -1;
   w->opt_admit = 1;
   w->opt_persistent_wait_us = 2000;
   w->opt_persistent_told = false;

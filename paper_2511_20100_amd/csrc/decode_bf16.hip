@@ -1153,7 +1153,7 @@ __global__ void k_count_live(const int* done, int B, int* live) {
   float n = 0.f;
   for (int b = threadIdx.x; b < B; b += blockDim.x) n += done[b] ? 0.f : 1.f;
   const float tot = block_sum(n, red);
-  if (threadIdx.x == 0) live[0] = (int)tot;
+  if (threadIdx.x == 0) __hip_atomic_store(live, (int)tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // the host's memory
 }
 void count_live(const int* done, int B, int* live, hipStream_t st) { k_count_live<<<1, 256, 0, st>>>(done, B, live); }
 
@@ -1252,7 +1252,7 @@ __global__ __launch_bounds__(256) void k_slot_live(const int* done, const int* s
   const int s = threadIdx.x;
   if (s >= n_slots) return;
   const int row = slot_row[s];
-  live[s] = (row >= 0 && !done[row]) ? 1 : 0;
+  __hip_atomic_store(live + s, (row >= 0 && !done[row]) ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 void slot_live(const int* done, const int* slot_row, int n_slots, int* live, hipStream_t st) {
   k_slot_live<<<1, 256, 0, st>>>(done, slot_row, n_slots, live);

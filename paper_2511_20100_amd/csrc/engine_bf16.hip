@@ -62,9 +62,12 @@ struct GraphCache {
   size_t events_used = 0;
   std::vector<hipEvent_t> empty_events;  // pairs recorded back to back (what a pair costs by itself)
   size_t empty_used = 0;
-  // rollouts with a stop token: where the host reads the number of live rows (pinned, two slots used in turn)
+  // rollouts with a stop token: where the host reads the number of live rows (pinned, two places used in turn; the next call has two
+  // others, for a call returns before its last look has been written)
   std::mutex poll_mu;                    // one such rollout at a time per weights handle
   int* host_live = nullptr;
+  unsigned poll_calls = 0;
+  static constexpr unsigned kPollPlaces = 64;
   hipEvent_t poll_events[2] = {nullptr, nullptr};
   int* host_slots = nullptr;            // pinned: which slots hold a sequence that still runs (a batch that takes in prompts)
 };
@@ -708,6 +711,14 @@ int admission_plan(const int* live, const int* slot_region, int n_slots, int n_r
 
 namespace {
 
+// Decode steps between two looks at the stop flags, where the caller has not set them.  A look is a small kernel and an event, 5 us of
+// the stream; what it finds frees tiles 4 to 8 steps after a sequence's end, where 32 steps freed them after 32 to 64 (48 sequences of
+// about 24 tokens, 24 blocks: 171 -> 143 ms).  With few blocks, steps of 0.2 ms, every fourth step costs 0.6 % where nothing ends, hence 8.
+int stop_poll_steps(const mtmc_weights* w) {
+  if (w->opt_stop_poll >= 0) return w->opt_stop_poll;
+  return w->cfg.n_layers < 6 ? 8 : 4;
+}
+
 // A rollout with a stop token and more sequences than one batch holds, run as ONE batch that takes in the call's
 // prompts as it runs.  Every slot of the batch has pages of its own for a whole sequence; the whole pages of a prompt
 // lie in one of n_regions regions shared by the prompt's sequences.  The first n_prompts prompts start together as
@@ -804,8 +815,9 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   std::vector<int> slot_region(B), regions(p.n_regions);  // slot_region: the region a slot's sequence reads
   for (int s = 0; s < B; ++s) slot_region[s] = s / ns;
   int next_prompt = p.n_prompts, steps = 1;  // steps: value of *d_step once the queued work has run
-  int* d_live = p.live + 16;
-  const int period = std::max(1, std::min(w->opt_stop_poll, 8));
+  // every look waits for the stream, 20 to 30 us, and every step between looks is one that ended sequences keep their slots for: 320
+  // sequences of about 20 tokens, 6 blocks: 61 ms with a look every 8 steps, 56.2 every 4, 55.5 every 2
+  const int period = w->opt_stop_poll < 0 ? 2 : std::max(1, std::min(w->opt_stop_poll, 8));
   // every sequence ends within max_new steps of its start and a prompt is taken in whenever all the sequences of
   // an earlier one have ended, at the latest
   const long long step_limit = ((long long)p.total_prompts + 2) * ((long long)p.max_new + 2LL * period);
@@ -821,8 +833,7 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
       return MTMC_EHIP;
     }
     // the tables by slot of the whole batch stay as they are once no prompt is left: the packed batch is always made from them
-    bf16::slot_live(p.done, p.slot_row, B, d_live, st);
-    MTMC_HIP_CHECK(hipMemcpyAsync(gc.host_slots, d_live, B * sizeof(int), hipMemcpyDeviceToHost, st));
+    bf16::slot_live(p.done, p.slot_row, B, gc.host_slots, st);
     MTMC_HIP_CHECK(hipStreamSynchronize(st));
     int n_live = 0;
     for (int s = 0; s < B; ++s) n_live += live[s];
@@ -906,7 +917,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     return MTMC_EINVAL;
   }
   if (sa.prompt_lens && sa.stop_id >= 0 && sa.reuse_len == 0 && p.total_prompts > p.n_prompts && p.max_new > 1 &&
-      w->opt_admit && w->opt_stop_poll > 0) {
+      w->opt_admit && stop_poll_steps(w) > 0) {
     // not while the caller is capturing the stream: the host must not wait then
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone)
@@ -1024,7 +1035,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     // A stop token: every `poll` steps the number of rows still running goes to the host, which reads it one
     // period later, ends the group when it is zero and packs the live rows into fewer 16-row tiles when it
     // frees a tile.  Not while the caller is capturing the stream (the host must not wait then).
-    int poll = (ragged && sa.stop_id >= 0) ? w->opt_stop_poll : 0;
+    int poll = (ragged && sa.stop_id >= 0) ? stop_poll_steps(w) : 0;
     if (poll > 0) {
       hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
@@ -1036,9 +1047,10 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
       GraphCache& gc = graph_cache(w);
       std::lock_guard<std::mutex> poll_lock(gc.poll_mu);
       if (!gc.host_live) {
-        MTMC_HIP_CHECK(hipHostMalloc((void**)&gc.host_live, 64 * sizeof(int), hipHostMallocDefault));
+        MTMC_HIP_CHECK(hipHostMalloc((void**)&gc.host_live, gc.kPollPlaces * 2 * 16 * sizeof(int), hipHostMallocDefault));
         for (hipEvent_t& e : gc.poll_events) MTMC_HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
       }
+      int* const seen = gc.host_live + 32 * (gc.poll_calls++ % gc.kPollPlaces);
       RolloutPlan cur = gp;
       KvPool cur_pool = pool;
       auto step_cur = [&](hipStream_t s) { decode_step_in(s, nullptr, cur, cur_pool); };
@@ -1054,12 +1066,11 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
         }
         i += n;
         if (i >= p.max_new) break;
-        bf16::count_live(p.done, gp.B, p.live, st);
-        MTMC_HIP_CHECK(hipMemcpyAsync(gc.host_live + 16 * slot, p.live, sizeof(int), hipMemcpyDeviceToHost, st));
+        bf16::count_live(p.done, gp.B, seen + 16 * slot, st);
         MTMC_HIP_CHECK(hipEventRecord(gc.poll_events[slot], st));
         if (have_prev) {
           MTMC_HIP_CHECK(hipEventSynchronize(gc.poll_events[slot ^ 1]));
-          const int n_live = gc.host_live[16 * (slot ^ 1)];  // one period old: rows only ever finish, so an upper bound
+          const int n_live = seen[16 * (slot ^ 1)];  // one period old: rows only ever finish, so an upper bound
           if (n_live <= 0) break;  // every later slot of the outputs already holds stop_id / 0
           const int slots = tiles16(n_live) * 16;
           if (slots < cur.bt * 16) {
