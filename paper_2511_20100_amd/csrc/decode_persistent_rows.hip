@@ -9,9 +9,14 @@
 // 64 rows took 133 ms).  They stream, multiply, sum and store; one of them watches the counters, and asks for its share of
 // the next weights behind that (loads return in order).  Two or three k tiles in flight make no difference at 64 rows.
 //
-// 63 steps of the 1.5 B shape, separate launches -> this: 32 rows 100.2 -> 94.2 ms, 64 rows 120.5 -> 114.8; 31 steps of 48
+// (Since the rows of qkv and the sums of the splits are asked for, kAsks below, it is 51 of which four hand-overs are counted.)
+//
+// 63 steps of the 1.5 B shape, separate launches -> this, all counted: 32 rows 100.2 -> 94.2 ms, 64 rows 120.5 -> 114.8; 31 steps of 48
 // rows 62.2 -> 56.6; cached step of the 7 B shape (4 blocks, 8192 tokens, 32 rows, 47 steps) 46.5 -> 44.0.
+#include <type_traits>
+
 #include "decode_persistent.h"
+#include "kernels.h"
 
 namespace mtmc {
 namespace bf16 {
@@ -86,6 +91,35 @@ struct RowSums {
   }
 };
 
+// Whether the attention asks for the rows of qkv and whoever adds up the splits for their sums, each of which has few readers, until they
+// are there: two of six times that a block does not drain stores and count (23 steps of the 1.5 B shape behind 200 tokens: 64 rows
+// 43.3 -> 41.0 ms, 48 rows 39.6 -> 38.0, 32 rows 35.3 -> 32.9).  Not with 10 gate / up tiles, whose registers are full: the loops
+// cost 10 more in scratch, and four 7 B blocks with 32 rows took 17.76 ms instead of 17.58.
+template <int GU_TILES>
+constexpr bool kAsks = GU_TILES == 6;
+// The rows of qkv in block l, and the sums of the splits (persist_hand_rows()).
+template <bool ASK>
+__device__ __forceinline__ float* qkv_of(const PersistArgs& a, int l) {
+  return ASK ? (float*)(a.hand + (l & 1) * a.at_hand.qkv_copy) : a.qkv;
+}
+template <bool ASK>
+__device__ __forceinline__ float* part_of(const PersistArgs& a) { return ASK ? (float*)(a.hand + a.at_hand.part) : a.part; }
+
+// An attention unit that asks for its rows of qkv; enter() as in CountedUnit.
+template <class Enter>
+struct AskingUnit : CountedUnit<Enter> {
+  int l;
+  int* stop;
+  __device__ __forceinline__ AskingUnit(int Mpad, Enter e, int l_, int* stop_) : CountedUnit<Enter>{Mpad, e}, l(l_), stop(stop_) {}
+  __device__ __forceinline__ const float* qkv(const PersistArgs& a) const { return keep(qkv_of<true>(a, l)); }
+  template <class Load>
+  __device__ __forceinline__ bool operator()(const PersistArgs& a, Load load) const {
+    if (!this->enter()) return false;
+    Asker{a, stop}(load);
+    return true;
+  }
+};
+
 // wait_grid() behind the first phase: the roll call.  The watch's first look comes back behind its keys and values: if that took longer
 // than the limit, callers who have set one are told, also where all are there by then.
 __device__ __forceinline__ bool answer_roll(const Ctx& c) {
@@ -123,6 +157,7 @@ template <int BT, int GU_TILES, int DN_RANGES, int NT>
 __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
   constexpr int MU = kUnit<BT, GU_TILES>, NP = (BT + MU - 1) / MU, QT = kQkvTiles<BT, GU_TILES>, OT = kOTiles<BT, GU_TILES>;
   using Gu = GuCut<BT, GU_TILES>;
+  constexpr bool ASK = kAsks<GU_TILES>;
   const v4f zero = v4f{0.f, 0.f, 0.f, 0.f};
   const bool watches = wave == kWatch;
   uint32_t phase = 0;
@@ -146,6 +181,12 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
     lds_barrier();
     ++phase;
   };
+  // Out of a phase whose readers ask for what it gives.
+  auto leave_asked = [&] {
+    if constexpr (ASK) lds_barrier();
+    else leave();
+  };
+  const v4u none = v4u{kNotThere, kNotThere, kNotThere, kNotThere};
   auto loads_done = [] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
   const int n_layers = fresh(wave).a.n_layers;
   const Ctx first = fresh(wave);
@@ -158,7 +199,7 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
       const int w = c.wave, lane = c.lane, rq = (lane >> 4) * 4;
       const h16_t* const W = a.wqkv + (size_t)l * a.layer_stride / sizeof(h16_t);
       const h16_t* const x = keep(x_of(a, l));
-      const Rsrc out = rsrc_of(keep(a.qkv));
+      const Rsrc out = rsrc_of(keep(qkv_of<ASK>(a, l))), behind = rsrc_of(keep(qkv_of<ASK>(a, l + 1)));
       const int kt_d = keep(a.kt_d), nt_qkv = keep(a.nt_qkv), nt_d = keep(a.nt_d), B = keep(a.B), ranges = keep(a.qkv_ranges);
       const int units = (nt_qkv + QT - 1) / QT * NP, per = (kt_d + ranges - 1) / ranges;
       Stream<QT, MU, 3, 3> s0, s1;
@@ -201,17 +242,23 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
           else add_ranges<16>(sum, sh.red, base + w, QT * MU, lane);
           const int row = min(m, 16 * BT - 1);
           const float sc = l > 0 ? scale_of(sh.total[0][row], sh.total[1][row], true, a.inv_d, a.eps) : 1.f;
-          if (m < B && nt < nt_qkv) st16(out, ((m * nt_qkv + nt) * 16 + rq) * 4, 0, __builtin_bit_cast(v4u, sum * sc));
+          if (m < B && nt < nt_qkv) {
+            const int off = ((m * nt_qkv + nt) * 16 + rq) * 4;
+            st16(out, off, 0, written(sum * sc));
+            if (ASK) st16(behind, off, 0, none);  // the units of the block before have read it
+          }
         }
         u += kPersistGrid;
         ++i;
         if (u >= units) break;
         start();
       }
-      leave();
+      if (l == 0) leave();
+      else leave_asked();
     }
     // ---- attention; the first one is behind the roll call
     auto enter_attention = [&] {
+      if (ASK && l > 0) return true;
       if (watches) {
         const Ctx c = fresh(wave);
         if (!(l == 0 ? answer_roll(c) : wait_grid(c, phase))) sh.stop = 1;
@@ -222,7 +269,11 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
     if (!unit.active) {
       if (!enter_attention()) return;
     } else {
-      if (!attend<true>(unit, sh.at, sh.table, l, wave, counted_unit(16 * BT, enter_attention))) return;
+      if constexpr (ASK) {
+        if (!attend<true>(unit, sh.at, sh.table, l, wave, AskingUnit<decltype(enter_attention)>(16 * BT, enter_attention, l, &sh.stop))) return;
+      } else {
+        if (!attend<true>(unit, sh.at, sh.table, l, wave, counted_unit(16 * BT, enter_attention))) return;
+      }
     }
     leave();
     // ---- O projection: at most one unit per workgroup
@@ -489,7 +540,7 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
       const PersistArgs& a = c.a;
       const int w = c.wave, wg = c.wg, lane = c.lane, rq = (lane >> 4) * 4;
       const h16_t* const W = a.wdown + (size_t)l * a.layer_stride / sizeof(h16_t);
-      const Rsrc out = rsrc_of(keep(a.part));
+      const Rsrc out = rsrc_of(keep(part_of<ASK>(a)));
       const int kt_F = keep(a.kt_F), d = keep(a.d), nt_d = keep(a.nt_d), ks = keep(a.ks_down), B = keep(a.B);
       const int per_split = (kt_F + ks - 1) / ks, split = DN_RANGES == 5 ? wg & 7 : wg % ks;
       const int kbeg = split * per_split, kend = min(kt_F, kbeg + per_split);
@@ -529,9 +580,9 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
         if (tile >= nt_d) continue;
         v4f sum = zero;
         add_ranges<DN_RANGES>(sum, sh.red, t * DN_RANGES, 1, lane);
-        if (m < B) st16(out, ((split * 16 * BT + m) * d + tile * 16 + rq) * 4, 0, __builtin_bit_cast(v4u, sum));
+        if (m < B) st16(out, ((split * 16 * BT + m) * d + tile * 16 + rq) * 4, 0, written(sum));
       }
-      leave();
+      leave_asked();
     }
     // ---- sum of the splits, residual, operand of the next block: row tile wg, a wavefront per tile of 16 rows
     {
@@ -540,7 +591,7 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
       const int w = c.wave, wg = c.wg, lane = c.lane, rq = (lane >> 4) * 4, m = min(w, BT - 1) * 16 + (lane & 15);
       const int nt_d = keep(a.nt_d);
       const TileOut to(a, x_behind(a, l), 0, l + 1 == n_layers);
-      const Rsrc part = rsrc_of(keep(a.part));
+      const Rsrc part = rsrc_of(keep(part_of<ASK>(a)));
       const int ks = keep(a.ks_down), at = (min(m, to.B - 1) * to.d + min(wg, nt_d - 1) * 16 + rq) * 4;
       const float* gp = l + 1 == n_layers ? a.final_norm : (const float*)((const char*)a.attn_norm + (l + 1) * a.layer_stride);
       const bool mine = wg < nt_d && w < BT;
@@ -557,13 +608,29 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
           h_old = ld16f(to.h, at, 0);
         }
       };
-      if (!enter(prepare)) return;
+      if constexpr (ASK) {
+        prepare();
+        lds_barrier();
+        if (__builtin_amdgcn_readfirstlane(sh.stop)) return;
+      } else {
+        if (!enter(prepare)) return;
+      }
       if (mine) {
+        const std::conditional_t<ASK, Asker, Known> asker = [&] {
+          if constexpr (ASK) return Asker{a, &sh.stop};
+          else return Known{};
+        }();
         v4f sum = zero;
         for (int s0 = 0; s0 < ks; s0 += 8) {
           v4f v[8];
+          asker([&] {
+            uint32_t top = 0;
 #pragma unroll
-          for (int k = 0; k < 8; ++k) v[k] = ld16f(part, at, min(s0 + k, ks - 1) * 64 * BT * to.d);
+            for (int k = 0; k < 8; ++k) v[k] = ld16f(part, at, min(s0 + k, ks - 1) * 64 * BT * to.d);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) top = max(top, largest(__builtin_bit_cast(v4u, v[k])));
+            return top;
+          });
 #pragma unroll
           for (int k = 0; k < 8; ++k)
             if (s0 + k < ks) sum = sum + v[k];
@@ -572,6 +639,8 @@ __device__ __forceinline__ void step(Shared<BT, GU_TILES, NT>& sh, int wave) {
         residual_tile<BT>(to, wg, w, lane, sum, h_old, gain, scale_of(sh.total[0][m], 0.f, false, a.inv_d, a.eps));
       }
       leave();
+      if (ASK && mine && m < to.B)
+        for (int s = 0; s < ks; ++s) st16(part, at, s * 64 * BT * to.d, none);
     }
   }
 }
@@ -589,6 +658,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_decode_layers_rows(PersistArgs)
 }  // namespace
 
 void launch_rows(const PersistArgs& a, int bt, int gu_tiles, hipStream_t st) {
+  if (gu_tiles == 6) launch_fill_u32(reinterpret_cast<uint32_t*>(a.hand), kNotThere, (size_t)a.at_hand.bytes / 4, st);
   if (bt == 2 && gu_tiles == 6) k_decode_layers_rows<2, 6, 5><<<kPersistGrid, kThreads, 0, st>>>(a);
   else if (bt == 2) k_decode_layers_rows<2, 10, 4><<<kPersistGrid, kThreads, 0, st>>>(a);
   else if (bt == 3) k_decode_layers_rows<3, 6, 5><<<kPersistGrid, kThreads, 0, st>>>(a);

@@ -96,7 +96,7 @@ struct RolloutPlan {
   uint32_t* sync;        // its counters (kPersistSyncWords; fp32 path: f32::kRolloutSyncWords)
   float* ss_in;          // its sums of squares
   void *xo_l, *xr_l, *act_l;  // its operands, one of each per block
-  void* hand;            // what it hands on with few rows (bf16::persist_hand)
+  void* hand;            // what it hands to readers that ask (bf16::persist_hand, persist_hand_rows)
   bool samples_alone;    // the decode attention takes every sequence in a workgroup of its own
   int ks_qkv, ks_o, ks_down;       // split-K factors of the decode GEMMs
   int down_nb;                     // weight row tiles per workgroup of the down projection (2 or 4)

@@ -59,8 +59,18 @@ constexpr int kPersistAskRows = 4;
 constexpr int kPersistCopies = 8, kPersistPieces = 3;
 struct PersistHand {
   int x, xo, act, qkv, o, ml, part, ss0, ss1;  // x, ss0: of the block before it; o, ml: chunk by chunk, o_chunk bytes apart
-  int x_copy, ss_copy, o_chunk, bytes;
+  int x_copy, ss_copy, qkv_copy, o_chunk, bytes;
 };
+// What a step of more than one tile of rows hands to readers that ask for it: the rows of qkv (block l: buffer l % 2) and the sums of
+// the splits.  Filled with the word before the step.  Whoever writes a row of qkv marks its place in the other buffer a block ahead,
+// whoever adds up the splits marks what it has read; several waits of all workgroups lie between either and the next write.
+inline PersistHand persist_hand_rows(int bt, int kt_d, int nt_qkv, int ks_down) {
+  PersistHand h{};
+  h.qkv_copy = bt * 16 * nt_qkv * 64;
+  h.part = 2 * h.qkv_copy;
+  h.bytes = h.part + bt * 16 * kt_d * 128 * ks_down;
+  return h;
+}
 inline PersistHand persist_hand(int B, int kt_d, int kt_F, int nt_qkv, int kt_nq, int heads, int n_chunks, int ks_down) {
   PersistHand h{};
   auto take = [&](int n) {
