@@ -204,7 +204,7 @@ struct PersistArgs {
   AttnDecArgs at;        // layer is set by the kernel
   int gu_ranges, dn_ranges;  // of the gate / up and of the down projection; decode_persistent() sets them
   char* hand;            // what is handed to readers that ask: up to kPersistAskRows rows kPersistPieces pieces of at_hand.bytes
-                         // (persist_hand), from 17 rows at_hand.bytes (persist_hand_rows), else NULL
+                         // (persist_hand), else at_hand.bytes (persist_hand_rows)
   PersistHand at_hand;
   uint32_t* sync;        // kPersistSyncWords, zero at the first launch; the sampler merge clears the counters after every step
   long long roll_ticks;  // how long a workgroup waits for all of them to be there, of the 100 MHz clock

@@ -7,13 +7,15 @@
 // last one gives: they depend on nothing.  A phase gets its operand in one of two ways:
 //
 //   ASK false  the grid waits on counters in memory: stores drained (0.5 to 1 us), counted (1.5 us from the last arrival), and
-//              then the operand is read (1 us), through the caches where many workgroups read the same.
+//              then the operand is read (1 us), through the caches where many workgroups read the same.  But the rows of qkv and
+//              the sums of the splits, which have few readers each, are asked for as below (two of six waits of a block; 23 steps
+//              of the 1.5 B shape behind 200 tokens, 16 rows: 27.2 -> 25.6 ms, 8 rows 25.0 -> 22.6).
 //   ASK true   (up to kPersistAskRows rows) readers ask for the operand until no word of it says "not written yet", past the
 //              caches: 1.5 to 2 us from the store to the product.  Every round of asking moves the operand of all workgroups,
 //              so this is for few rows, and what all of them ask for is there in eight copies (one: the asking alone took the
 //              first 2 us of the gate / up projection).  23 steps of the 1.5 B shape behind 200 tokens, counters -> asking:
-//              one row 23.8 -> 19.7 ms, 4 rows 25.0 -> 22.5, 8 rows 25.0 -> 24.1; of four 7 B blocks one row 14.6 -> 14.4,
-//              8 rows 15.1 -> 15.8: the line is at 4.
+//              one row 21.4 -> 19.7 ms, 2 rows 21.4 -> 20.4, 4 rows 22.48 -> 22.56; 1.3 B blocks with a kv head per query head, 4
+//              rows, 8.33 -> 8.57; of four 7 B blocks one row 14.62 -> 14.53: the line is at 2.
 //
 // With either, the gate / up weights of which registers hold four k tiles have the others in LDS, asked for ahead of the O
 // projection: by the time its operand is there all of them are (same steps, all in registers -> this: one row 24.5 -> 23.8 ms,
@@ -121,11 +123,11 @@ struct Place {
   }
   __device__ __forceinline__ float* qkv() const {
     if constexpr (ASK) return (float*)(hand(l) + a.at_hand.qkv);
-    else return const_cast<float*>(a.at.qkv);
+    else return (float*)(a.hand + (l & 1) * a.at_hand.qkv_copy);  // persist_hand_rows()
   }
   __device__ __forceinline__ float* part() const {
     if constexpr (ASK) return (float*)(hand(l) + a.at_hand.part);
-    else return a.part;
+    else return (float*)(a.hand + a.at_hand.part);
   }
   __device__ __forceinline__ int o_chunk() const { return ASK ? a.at_hand.o_chunk : (int)(a.at.o_chunk_stride * sizeof(h16_t)); }
   __device__ __forceinline__ h16_t* o(int chunk) const {
@@ -167,7 +169,7 @@ struct OneTileUnit {
   template <class Load>
   __device__ __forceinline__ bool operator()(const PersistArgs& a, Load load) const {
     if (!enter()) return false;
-    Place<ASK>::asker(a, stop)(load);
+    Asker{a, stop}(load);
     return true;
   }
 };
@@ -355,10 +357,12 @@ __device__ __forceinline__ void control(Shared& sh, int wave) {
           const int nt = place + u * kPersistGrid;
           marked();
           const v4f sum = sum_ranges<16>(sh, (u & 1) * 16, lane);
-          if (m < B) st16(out, ((m * nt_qkv + nt) * 16 + rq) * 4, 0, written(sum * sh.scale[m]));
+          const int off = ((m * nt_qkv + nt) * 16 + rq) * 4;
+          if (m < B) st16(out, off, 0, written(sum * sh.scale[m]));
+          if (!ASK && m < B) st16(rsrc_of(Place<ASK>{a, l + 1, wg}.qkv()), off, 0, none);  // the units of the block before have read it
         }
       }
-      if (!done(c)) return;
+      if (!(l == 0 ? done(c) : running())) return;
     }
     // ---- attention
     {
@@ -367,8 +371,7 @@ __device__ __forceinline__ void control(Shared& sh, int wave) {
         if (ASK && c.lane == 0) count_in(c, 0);
         if (!answer_roll(c)) sh.stop = 1;
       }
-      if (ASK && l == 0 && !running()) return;
-      if (!enter(c)) return;
+      if (l == 0 && !running()) return;
       if (attends) {
         if (attn_active) {
           lds_barrier();
@@ -474,7 +477,7 @@ __device__ __forceinline__ void control(Shared& sh, int wave) {
         const v4f sum = sum_ranges<DN_RANGES>(sh, cw * DN_RANGES, lane);
         if (m < B) st16(out, off, 0, written(sum));
       }
-      if (!done(c)) return;
+      if (!running()) return;
     }
     // ---- sum of the splits, residual, operand of the next block: the lead alone
     if (lead) {
@@ -493,10 +496,8 @@ __device__ __forceinline__ void control(Shared& sh, int wave) {
         const Place<ASK> behind{a, l + 1, wg};
         not_there(TileOut(a, behind.x(l + 2, 0), behind.ss0(l + 2, 0), 0, a.B, kPersistCopies, false, lane), wg, lane);
       }
-      if (!ASK && !wait_grid(c, phase)) {
-        sh.stop = 1;
-      } else if (has_tile) {
-        const auto asker = at.asker(a, &sh.stop);
+      if (has_tile) {
+        const Asker asker{a, &sh.stop};
         v4f sum = v4f{0.f, 0.f, 0.f, 0.f};
         for (int s0 = 0; s0 < ks; s0 += 8) {
           v4f v[8];
@@ -518,6 +519,8 @@ __device__ __forceinline__ void control(Shared& sh, int wave) {
       if (!ASK) {
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         if (c.lane == 0) count_in(c, phase);
+        if (has_tile && m < to.B)  // read
+          for (int s = 0; s < ks; ++s) st16(part, from, s * step, none);
       }
     }
     ++phase;
@@ -669,7 +672,7 @@ __device__ __forceinline__ void compute(Shared& sh, int wave) {
     // ---- attention
     {
       const Ctx c = fresh(wave);
-      auto enter_attention = [&] { return !ASK || l == 0 ? running() : true; };  // the first time the roll call
+      auto enter_attention = [&] { return l == 0 ? running() : true; };  // the first time the roll call
       const auto hand = OneTileUnit<ASK, decltype(enter_attention)>{l, &sh.stop, Place<ASK>{c.a, l, c.wg}.rows(), enter_attention};
       const int tid = c.wave * 64 + c.lane;
       if (ASK && unit.there && l + 1 < n_layers) {
@@ -959,7 +962,10 @@ void launch_ask(const PersistArgs& a, int gu_tiles, int dn, hipStream_t st) {
 }  // namespace
 
 void launch_one_tile(const PersistArgs& a, int gu_tiles, int dn_ranges, hipStream_t st) {
-  if (!a.hand) return launch_ask<false>(a, gu_tiles, dn_ranges, st);
+  if (a.B > kPersistAskRows) {
+    launch_fill_u32(reinterpret_cast<uint32_t*>(a.hand), kNotThere, (size_t)a.at_hand.bytes / 4, st);
+    return launch_ask<false>(a, gu_tiles, dn_ranges, st);
+  }
   launch_fill_u32(reinterpret_cast<uint32_t*>(a.hand), kNotThere, (size_t)a.at_hand.bytes / 2, st);  // two pieces
   launch_ask<true>(a, gu_tiles, dn_ranges, st);
 }

@@ -370,7 +370,7 @@ PersistRoom persistent_room(const mtmc_weights* w, const Dims& D, const RolloutP
     room.rows = std::max(room.rows, tiles16(B) * 16);
     if (B <= bf16::kPersistAskRows)
       room.hand = std::max(room.hand, bf16::kPersistPieces * (size_t)persist_hand_of(D, B, n_chunks, ks_down).bytes);
-    else if (B > 16)
+    else
       room.hand = std::max(room.hand, (size_t)bf16::persist_hand_rows(tiles16(B), D.kt_d, D.nt_qkv, ks_down).bytes);
   };
   for (int B : {p.B, ((p.total_prompts - 1) % p.n_prompts + 1) * p.n_samples}) may_run(B, p.n_chunks, p.down_nb, p.ks_down);
@@ -542,7 +542,7 @@ bf16::PersistArgs persistent_args(const mtmc_weights* w, const Dims& D, const Ro
   if (p.B <= bf16::kPersistAskRows) {
     a.hand = (char*)p.hand;
     a.at_hand = persist_hand_of(D, p.B, p.n_chunks, p.ks_down);
-  } else if (p.bt > 1) {
+  } else {
     a.hand = (char*)p.hand;
     a.at_hand = bf16::persist_hand_rows(p.bt, D.kt_d, D.nt_qkv, p.ks_down);
   }

@@ -42,7 +42,7 @@ inline bool decode_persistent_fits(const PersistShape& s) {
 }
 
 // Steps of so few rows hand their data to readers that ask for them (decode_persistent.hip).
-constexpr int kPersistAskRows = 4;
+constexpr int kPersistAskRows = 2;
 // What the phases of such a step hand on: a piece of memory per block (block l: l % kPersistPieces), in which every buffer has the
 // rows of the batch and no others (bytes from the piece's start).  What all workgroups ask for is there kPersistCopies times, a copy
 // for the workgroups of a die.
@@ -61,7 +61,7 @@ struct PersistHand {
   int x, xo, act, qkv, o, ml, part, ss0, ss1;  // x, ss0: of the block before it; o, ml: chunk by chunk, o_chunk bytes apart
   int x_copy, ss_copy, qkv_copy, o_chunk, bytes;
 };
-// What a step of more than one tile of rows hands to readers that ask for it: the rows of qkv (block l: buffer l % 2) and the sums of
+// What a step of more rows hands to readers that ask for it: the rows of qkv (block l: buffer l % 2) and the sums of
 // the splits.  Filled with the word before the step.  Whoever writes a row of qkv marks its place in the other buffer a block ahead,
 // whoever adds up the splits marks what it has read; several waits of all workgroups lie between either and the next write.
 inline PersistHand persist_hand_rows(int bt, int kt_d, int nt_qkv, int ks_down) {

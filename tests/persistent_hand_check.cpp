@@ -31,6 +31,14 @@ int main() {
               }
               CHECK(kPersistPieces == 3 && end <= h.bytes && h.bytes % 128 == 0 && h.x_copy % 128 == 0 && h.o_chunk % 16 == 0 && h.ss_copy % 4 == 0);
             }
+  for (int bt = 1; bt <= 4; ++bt)
+    for (int kt_d : {48, 50, 112, 128})
+      for (int ks : {1, 4, 8, 40}) {
+        const int B = bt * 16, nt_qkv = 2 * kt_d + 32;
+        const PersistHand h = persist_hand_rows(bt, kt_d, nt_qkv, ks);
+        CHECK(h.qkv == 0 && h.qkv_copy >= B * nt_qkv * 16 * 4 && h.part >= 2 * h.qkv_copy && h.part % 128 == 0 && h.qkv_copy % 128 == 0);
+        CHECK(h.bytes >= h.part + ks * B * kt_d * 32 * 4);
+      }
   std::printf("ok\n");
   return 0;
 }

@@ -29,7 +29,7 @@ def test_rows_on_both_sides_of_the_line(shape):
     cfg = SHAPES[shape]
     handle = lib.mtmc_weights_create(lib.make_config(cfg, 2400), inputs.make_weights(cfg, seed=0, std=0.04, gain_std=0.1).blob())
     try:
-        for n_prompts, plen, n_samples, max_new in ((1, 3, 3, 40), (3, 250, 1, 20), (1, 1500, 4, 9), (2, 2000, 2, 6), (5, 40, 1, 9), (1, 5, 2, 200)):
+        for n_prompts, plen, n_samples, max_new in ((1, 3, 3, 40), (3, 250, 1, 20), (1, 1500, 4, 9), (2, 2000, 2, 6), (5, 40, 1, 9), (1, 5, 2, 200), (3, 200, 4, 9)):
             prompts = torch.from_numpy(inputs.make_prompts(n_prompts, plen, cfg.vocab, seed=plen)).cuda()
             lens = torch.from_numpy(np.random.default_rng(plen).integers(1, plen + 1, n_prompts).astype(np.int32)).cuda()
             got, stop = [], -1
