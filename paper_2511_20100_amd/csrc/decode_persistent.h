@@ -310,6 +310,7 @@ struct Asker {
   __device__ __forceinline__ void operator()(Load load) const {
     long long t0 = 0;
     for (int i = 0; missing(load()); ++i) {
+      asm volatile("" ::: "memory");  // the loads are made again
       if (i == 0) t0 = wall_clock64();
       if (i % 64 != 63) continue;
       const Word ended = word_of(a, kPersistEnded);

@@ -93,42 +93,61 @@ void embed(float* h, const int* ids, int T, const bf16_t* E, int d, int vocab, i
 }
 
 // ---------------------------------------------------------------- residual add + RMSNorm
-// One workgroup per row; a thread owns 8 consecutive features (one 16-byte chunk of the tiled
-// operand).  Pass 1 folds the split-K partial sums into the fp32 residual and accumulates the
-// sum of squares; pass 2 writes bf16(h * rsqrt(mean + eps) * gain).
+// One workgroup per row; a thread owns 8 consecutive features (one 16-byte chunk of the tiled operand), two such chunks at
+// most, which stay in registers between the passes.  Pass 1 folds the split-K partial sums into the fp32 residual and accumulates
+// the sum of squares; pass 2 writes fp16(h * rsqrt(mean + eps) * gain).  A row is one chain of trips to memory, so all that a chunk
+// needs is asked for at once (511 rows x 1536, slice after slice and h read again -> this: 7.9 -> 7.3 us; 200 rows 6.2 -> 5.2).
 __global__ __launch_bounds__(256) void k_add_norm(float* h, const float* P, int n_split, int ldp, int Mpad_p,
                                                   const float* gain, float eps, h16_t* x, int Mpad, int d,
                                                   int* err_flag, const int* d_rows) {
   __shared__ float red[16];
+  constexpr int kChunks = 2, kStep = 256 * 8;  // d up to 4096
   const int m = blockIdx.x;
   if (d_rows && m >= ((*d_rows + 255) & ~255)) return;  // rows packed on the device: no token in this 256-row block
   float* hr = h + (size_t)m * d;
+  v4f a[kChunks], b[kChunks], ga[kChunks], gb[kChunks];
   float ss = 0.f;
-  for (int k = threadIdx.x * 8; k < d; k += blockDim.x * 8) {
-    v4f a = *reinterpret_cast<const v4f*>(hr + k), b = *reinterpret_cast<const v4f*>(hr + k + 4);
-#pragma unroll 8
-    for (int s = 0; s < n_split; ++s) {
-      const float* pr = P + ((size_t)s * Mpad_p + m) * ldp + k;
-      a = a + *reinterpret_cast<const v4f*>(pr);
-      b = b + *reinterpret_cast<const v4f*>(pr + 4);
-    }
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) {
+    const int k = threadIdx.x * 8 + c * kStep;
+    if (k >= d) continue;
+    a[c] = *reinterpret_cast<const v4f*>(hr + k);
+    b[c] = *reinterpret_cast<const v4f*>(hr + k + 4);
+    ga[c] = *reinterpret_cast<const v4f*>(gain + k);
+    gb[c] = *reinterpret_cast<const v4f*>(gain + k + 4);
+    over_slices(n_split, [&](auto number, int first) {
+      constexpr int N = decltype(number)::value;
+      const float* pr = P + ((size_t)first * Mpad_p + m) * ldp + k;
+      v4f pa[N], pb[N];
+#pragma unroll
+      for (int s = 0; s < N; ++s) {
+        pa[s] = *reinterpret_cast<const v4f*>(pr + (size_t)s * Mpad_p * ldp);
+        pb[s] = *reinterpret_cast<const v4f*>(pr + (size_t)s * Mpad_p * ldp + 4);
+      }
+#pragma unroll
+      for (int s = 0; s < N; ++s) {
+        a[c] = a[c] + pa[s];
+        b[c] = b[c] + pb[s];
+      }
+    });
     if (n_split > 0) {
-      *reinterpret_cast<v4f*>(hr + k) = a;
-      *reinterpret_cast<v4f*>(hr + k + 4) = b;
+      *reinterpret_cast<v4f*>(hr + k) = a[c];
+      *reinterpret_cast<v4f*>(hr + k + 4) = b[c];
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) ss += a[e] * a[e] + b[e] * b[e];
+    for (int e = 0; e < 4; ++e) ss += a[c][e] * a[c][e] + b[c][e] * b[c][e];
   }
   ss = block_sum(ss, red);
   const float r = 1.0f / sqrtf(ss / (float)d + eps);
-  for (int k = threadIdx.x * 8; k < d; k += blockDim.x * 8) {
-    const v4f a = *reinterpret_cast<const v4f*>(hr + k), b = *reinterpret_cast<const v4f*>(hr + k + 4);
-    const v4f ga = *reinterpret_cast<const v4f*>(gain + k), gb = *reinterpret_cast<const v4f*>(gain + k + 4);
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) {
+    const int k = threadIdx.x * 8 + c * kStep;
+    if (k >= d) continue;
     v4u pk;
-    pk[0] = pack_h16x2_flag(a[0] * r * ga[0], a[1] * r * ga[1], err_flag);
-    pk[1] = pack_h16x2_flag(a[2] * r * ga[2], a[3] * r * ga[3], err_flag);
-    pk[2] = pack_h16x2_flag(b[0] * r * gb[0], b[1] * r * gb[1], err_flag);
-    pk[3] = pack_h16x2_flag(b[2] * r * gb[2], b[3] * r * gb[3], err_flag);
+    pk[0] = pack_h16x2_flag(a[c][0] * r * ga[c][0], a[c][1] * r * ga[c][1], err_flag);
+    pk[1] = pack_h16x2_flag(a[c][2] * r * ga[c][2], a[c][3] * r * ga[c][3], err_flag);
+    pk[2] = pack_h16x2_flag(b[c][0] * r * gb[c][0], b[c][1] * r * gb[c][1], err_flag);
+    pk[3] = pack_h16x2_flag(b[c][2] * r * gb[c][2], b[c][3] * r * gb[c][3], err_flag);
     *reinterpret_cast<v4u*>(x + act_off(m, k, Mpad)) = pk;
   }
 }
@@ -244,10 +263,19 @@ __global__ __launch_bounds__(256) void k_rope_kv_page(h16_t* q, const float* qkv
   h16_t* kv = (h16_t*)pool.base;
   const size_t page_elems = (size_t)kPageTokens * HD;
   const int tid = threadIdx.x;
-  // four values of the projection: the sum of its split-K slices, if it comes in slices
+  // four values of the projection: the sum of its split-K slices, if it comes in slices (511 rows, 14 heads, one after the other ->
+  // all at once: 10.2 -> 7.5 us)
   auto load4 = [&](const float* p) {
     v4f v = *reinterpret_cast<const v4f*>(p);
-    for (int s = 1; s < n_split; ++s) v = v + *reinterpret_cast<const v4f*>(p + s * split_stride);
+    over_slices(n_split - 1, [&](auto number, int first) {
+      constexpr int N = decltype(number)::value;
+      const float* q = p + (size_t)(first + 1) * split_stride;
+      v4f w[N];
+#pragma unroll
+      for (int s = 0; s < N; ++s) w[s] = *reinterpret_cast<const v4f*>(q + s * split_stride);
+#pragma unroll
+      for (int s = 0; s < N; ++s) v = v + w[s];
+    });
     return v;
   };
   // ---- rotation of the q and k heads: unit = (slot, quad).  gridDim.z workgroups share out the heads of a page.

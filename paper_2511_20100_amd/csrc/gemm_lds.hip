@@ -434,7 +434,15 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(float* out, int ld_out, c
   if (d_rows && m >= *d_rows) return;
   float* o = out + (size_t)m * ld_out + n;
   v4f acc = accumulate ? *reinterpret_cast<const v4f*>(o) : v4f{0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < S; ++s) acc = acc + *reinterpret_cast<const v4f*>(part + ((size_t)s * M + m) * N + n);
+  over_slices(S, [&](auto number, int first) {
+    constexpr int K = decltype(number)::value;
+    const float* p = part + ((size_t)first * M + m) * N + n;
+    v4f v[K];
+#pragma unroll
+    for (int s = 0; s < K; ++s) v[s] = *reinterpret_cast<const v4f*>(p + (size_t)s * M * N);
+#pragma unroll
+    for (int s = 0; s < K; ++s) acc = acc + v[s];
+  });
   *reinterpret_cast<v4f*>(o) = acc;
 }
 
