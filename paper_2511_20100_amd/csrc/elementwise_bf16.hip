@@ -239,7 +239,9 @@ void add_norm(float* h, const float* P, int n_split, int ldp, int Mpad_p, const 
 // Thread (token, quad) rotates 4 + 4 values of a head at a time.  The K and V values of a kv head are collected
 // token-major in LDS and leave as the page's 16-byte pieces (one per thread, 4 KiB contiguous at HD = 128); a
 // page that the launch fills only partly is written value by value for its live slots instead.
-template <int HD>
+// SPLIT: the projection comes in n_split slices (an instance of its own: the slices on their way take registers that the others
+// would be slower for, 256 candidate rows behind 8 states 27.5 -> 27.7 ms).
+template <int HD, bool SPLIT>
 __global__ __launch_bounds__(256) void k_rope_kv_page(h16_t* q, const float* qkv, int ld, int S, int Hq, int Hkv,
                                                       const float* cos, const float* sin, int row_stride, int pos_base,
                                                       KvPool pool, int layer, int* err_flag, const int* seq_start,
@@ -267,6 +269,7 @@ __global__ __launch_bounds__(256) void k_rope_kv_page(h16_t* q, const float* qkv
   // all at once: 10.2 -> 7.5 us)
   auto load4 = [&](const float* p) {
     v4f v = *reinterpret_cast<const v4f*>(p);
+    if constexpr (!SPLIT) return v;
     over_slices(n_split - 1, [&](auto number, int first) {
       constexpr int N = decltype(number)::value;
       const float* q = p + (size_t)(first + 1) * split_stride;
@@ -353,12 +356,12 @@ void rope_kv_write(h16_t* q, const float* qkv, int ld, int T, int S, int Hq, int
   // few pages: the heads of a page are shared out until about 2048 workgroups are there (32 pages x 14 heads of 128 dims:
   // 12.6 us with one workgroup per page)
   const dim3 grid(n_pg, seq_start ? n_seqs : T / S, std::max(1, std::min(Hq + Hkv, 2048 / pages)));
-  if (pool.head_dim == 64)
-    k_rope_kv_page<64><<<grid, 256, 0, st>>>(q, qkv, ld, S, Hq, Hkv, cos, sin, map.row_stride, map.pos_base, pool, layer,
-                                             err_flag, seq_start, n_split, split_stride);
-  else
-    k_rope_kv_page<128><<<grid, 256, 0, st>>>(q, qkv, ld, S, Hq, Hkv, cos, sin, map.row_stride, map.pos_base, pool,
-                                              layer, err_flag, seq_start, n_split, split_stride);
+  auto launch = [&](auto* kernel) {
+    kernel<<<grid, 256, 0, st>>>(q, qkv, ld, S, Hq, Hkv, cos, sin, map.row_stride, map.pos_base, pool, layer, err_flag, seq_start,
+                                 n_split, split_stride);
+  };
+  if (pool.head_dim == 64) launch(n_split > 1 ? k_rope_kv_page<64, true> : k_rope_kv_page<64, false>);
+  else launch(n_split > 1 ? k_rope_kv_page<128, true> : k_rope_kv_page<128, false>);
 }
 
 }  // namespace bf16
