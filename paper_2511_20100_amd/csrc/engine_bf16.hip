@@ -422,7 +422,6 @@ void bf16_plan_rollout_extra(const mtmc_weights* w, RolloutPlan& p, Carver& cv) 
     p.slot_row = cv.take<int>(Mpad);
     p.page_table_c = cv.take<int>(Mpad * p.max_pages);
     p.row_pos_c = cv.take<int>(Mpad);
-    p.live = cv.take<int>(16 + 256);
     p.row_step0 = cv.take<int>(Mpad);
     p.prefill_table = cv.take<int>(Mpad * p.max_pages);
     p.slot_row_c = cv.take<int>(Mpad);
