@@ -683,10 +683,11 @@ __device__ __forceinline__ void compute(Shared& sh, int wave) {
         if (!attend<false>(unit, sh.at, sh.table, l, wave, hand)) return;
       } else {
         if (!enter_attention()) return;
-        if (ASK && unit.there) {
-          // a chunk beyond the context contributes nothing, which its consumer learns from a zero sum; it waits for the rows of qkv as
-          // the others do, or a workgroup with nothing else to do would be blocks ahead (persist_hand())
-          const float* const row = hand.qkv(c.a) + (size_t)unit.b * c.a.nt_qkv * 16 + unit.g * (c.a.at.Hq / c.a.at.Hkv) * kHeadDim;
+        const int G = c.a.at.Hq / c.a.at.Hkv;
+        if (ASK && unit.there && persist_empty_unit_asks(c.wave, G)) {
+          // a chunk beyond the context contributes nothing, which its consumer learns from a zero sum; who stores that waits for the rows
+          // of qkv as the others do, or a workgroup with nothing else to do would be blocks ahead (persist_hand())
+          const float* const row = hand.qkv(c.a) + (size_t)unit.b * c.a.nt_qkv * 16 + unit.g * G * kHeadDim;
           Asker{c.a, &sh.stop}([&] { return __float_as_uint(ld4(row + c.lane)); });
           hand.before_stores();
           hand.write(c.a, unit, tid, make_uint2(0u, 0u), make_uint2(0xff800000u, 0u));

@@ -56,7 +56,12 @@ constexpr int kPersistAskRows = 2;
 //     phase after the other, of all that was read in the phases of a whole block before.  x, ss0 and the ss1 of the block before are
 //     read one block later than the others: x and ss0 are marked at the end of a block, behind an O projection that came of them
 //     all, ss1 behind the sum of the splits.
+// The second point needs a store of the workgroup behind everything that one of its wavefronts has asked for, in the same phase: of its
+// own, or behind a barrier that it takes part in.
 constexpr int kPersistCopies = 8, kPersistPieces = 3;
+// A unit of the attention whose chunk holds no part of the context stores zeros, 16 threads per query head, without such a barrier: only
+// wavefronts that store ask for the rows of qkv.
+constexpr bool persist_empty_unit_asks(int wave, int heads) { return wave * 64 < heads * 16; }
 struct PersistHand {
   int x, xo, act, qkv, o, ml, part, ss0, ss1;  // x, ss0: of the block before it; o, ml: chunk by chunk, o_chunk bytes apart
   int x_copy, ss_copy, qkv_copy, o_chunk, bytes;

@@ -21,6 +21,10 @@ def test_the_buffers_of_a_block_lie_apart(tmp_path):
     _run(tmp_path, "persistent_hand_check")
 
 
+def test_nobody_finds_an_earlier_or_a_later_block_in_a_place(tmp_path):
+    _run(tmp_path, "persistent_order_check")
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", SHAPES)
 def test_rows_on_both_sides_of_the_line(shape):
