@@ -81,6 +81,7 @@ def test_the_bits_of_separate_launches(lib, policy, n_prompts, plen, n_samples, 
 # more than one tile of rows: which shapes that form takes, and where its units are more than one round
 MANY_ROWS = {
     "1p5b": SHAPES["1p5b"],
+    "7 blocks": inputs.POLICY_1P5B.with_(n_layers=7, vocab=V),                      # more than the buffers that rows of qkv take in turn
     "7b": SHAPES["7b"],                                                             # up to 32 rows
     "qkv-2-rounds": inputs.ModelConfig(2, 1536, 24, 4, 128, 8960, V, dtype="bf16"),  # 512 units of 16 ranges
     "qkv-3-rounds": inputs.ModelConfig(2, 1536, 28, 4, 128, 8960, V, dtype="bf16"),  # 576 units of 8 ranges
@@ -91,6 +92,7 @@ MANY_ROWS = {
     ("1p5b", [(3, 1, 6, 18), (17, 1100, 1, 5), (2, 2300, 9, 4), (4, 300, 8, 20),   # 18, 17, 18, 32 rows: 1, 3, 3, 2 chunks
               (11, 127, 3, 4), (5, 700, 8, 18), (6, 20, 8, 12),                     # 33, 40, 48 rows
               (7, 90, 7, 20), (8, 300, 8, 20), (4, 1500, 16, 3)]),                  # 49, 64, 64 rows
+    ("7 blocks", [(17, 40, 1, 9), (4, 300, 8, 6), (6, 700, 8, 6), (8, 20, 8, 9)]),  # 17, 32, 48, 64 rows
     ("7b", [(17, 300, 1, 6), (4, 100, 8, 12), (3, 1500, 8, 4)]),
     ("qkv-2-rounds", [(3, 40, 8, 6), (5, 140, 8, 6), (8, 40, 8, 6)]),
     ("qkv-3-rounds", [(3, 40, 8, 6), (5, 140, 8, 6), (8, 40, 8, 6)]),
