@@ -11,6 +11,7 @@
 #include "lease_cache.h"
 #include "outside_captures.h"
 #include "persistent_turn.h"
+#include "stop_looks.h"
 
 namespace mtmc {
 
@@ -62,13 +63,10 @@ struct GraphCache {
   size_t events_used = 0;
   std::vector<hipEvent_t> empty_events;  // pairs recorded back to back (what a pair costs by itself)
   size_t empty_used = 0;
-  // rollouts with a stop token: where the host reads the number of live rows (pinned, two places used in turn; the next call has two
-  // others, for a call returns before its last look has been written)
+  // rollouts with a stop token: where the host reads the number of live rows (pinned), and when (run_with_looks)
   std::mutex poll_mu;                    // one such rollout at a time per weights handle
   int* host_live = nullptr;
-  unsigned poll_calls = 0;
-  static constexpr unsigned kPollPlaces = 64;
-  hipEvent_t poll_events[2] = {nullptr, nullptr};
+  hipEvent_t poll_event = nullptr;
   int* host_slots = nullptr;            // pinned: which slots hold a sequence that still runs (a batch that takes in prompts)
 };
 
@@ -113,8 +111,7 @@ void destroy_graph_cache(mtmc_weights* w) {
   if (w->graphs->capture_stream) (void)hipStreamDestroy(w->graphs->capture_stream);
   for (hipEvent_t e : w->graphs->events) (void)hipEventDestroy(e);
   for (hipEvent_t e : w->graphs->empty_events) (void)hipEventDestroy(e);
-  for (hipEvent_t e : w->graphs->poll_events)
-    if (e) (void)hipEventDestroy(e);
+  if (w->graphs->poll_event) (void)hipEventDestroy(w->graphs->poll_event);
   if (w->graphs->host_live) (void)hipHostFree(w->graphs->host_live);
   if (w->graphs->host_slots) (void)hipHostFree(w->graphs->host_slots);
   delete w->graphs;
@@ -1051,51 +1048,48 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     if (p.max_new > 1 && poll > 0) {
       GraphCache& gc = graph_cache(w);
       std::lock_guard<std::mutex> poll_lock(gc.poll_mu);
-      if (!gc.host_live) {
-        MTMC_HIP_CHECK(hipHostMalloc((void**)&gc.host_live, gc.kPollPlaces * 2 * 16 * sizeof(int), hipHostMallocDefault));
-        for (hipEvent_t& e : gc.poll_events) MTMC_HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-      }
-      int* const seen = gc.host_live + 32 * (gc.poll_calls++ % gc.kPollPlaces);
+      if (!gc.poll_event) MTMC_HIP_CHECK(hipEventCreateWithFlags(&gc.poll_event, hipEventDisableTiming));
+      if (!gc.host_live) MTMC_HIP_CHECK(hipHostMalloc((void**)&gc.host_live, 16 * sizeof(int), hipHostMallocDefault));
       RolloutPlan cur = gp;
       KvPool cur_pool = pool;
       auto step_cur = [&](hipStream_t s) { decode_step_in(s, nullptr, cur, cur_pool); };
       StepGraph graph;
       if (int rc = decode_graph(w, cur, st, step_cur, &graph)) return rc;
-      int i = 1, slot = 0;
-      bool have_prev = false;
-      while (i < p.max_new) {
-        const int n = std::min(poll, p.max_new - i);
+      auto steps = [&](int n) -> int {
         for (int j = 0; j < n; ++j) {
           if (graph) MTMC_HIP_CHECK(graph.launch(st));
           else step_cur(st);
         }
-        i += n;
-        if (i >= p.max_new) break;
-        bf16::count_live(p.done, gp.B, seen + 16 * slot, st);
-        MTMC_HIP_CHECK(hipEventRecord(gc.poll_events[slot], st));
-        if (have_prev) {
-          MTMC_HIP_CHECK(hipEventSynchronize(gc.poll_events[slot ^ 1]));
-          const int n_live = seen[16 * (slot ^ 1)];  // one period old: rows only ever finish, so an upper bound
-          if (n_live <= 0) break;  // every later slot of the outputs already holds stop_id / 0
-          const int slots = tiles16(n_live) * 16;
-          if (slots < cur.bt * 16) {
-            bf16::compact_rows(p.done, gp.B, slots, p.slot_row, p.page_table, p.row_pos, p.max_pages, p.page_table_c,
-                               p.row_pos_c, st);
-            cur = gp;
-            cur.B = slots; cur.bt = slots / 16; cur.n_samples = 1; cur.ragged = 2;
-            cur.row_pos = p.row_pos_c;
-            apply_tune(cur, tune_decode(D, cur.B, cur.bt, p.max_pages));
-            cur.persistent = may_persist && persistent_shape(w, D, cur) && turn.take(w->device, st);
-            cur_pool.page_table = p.page_table_c;
-            ctl.slot_row = p.slot_row;
-            bf16::set_sample_ctl((bf16::SampleCtl*)p.ctl, ctl, st);
-            bf16::embed_slots(p.slot_row, p.cur_ids, slots, embed_args(cur), st);
-            if (int rc = decode_graph(w, cur, st, step_cur, &graph)) return rc;
-          }
-        }
-        have_prev = true;
-        slot ^= 1;
-      }
+        return MTMC_OK;
+      };
+      auto look = [&]() -> int {
+        bf16::count_live(p.done, gp.B, gc.host_live, st);
+        MTMC_HIP_CHECK(hipEventRecord(gc.poll_event, st));
+        return MTMC_OK;
+      };
+      auto read = [&](int* live) -> int {
+        MTMC_HIP_CHECK(hipEventSynchronize(gc.poll_event));
+        *live = *gc.host_live;  // none: every later slot of the outputs already holds stop_id / 0
+        return MTMC_OK;
+      };
+      auto pack = [&](int live) -> int {
+        const int slots = tiles16(live) * 16;
+        if (slots >= cur.bt * 16) return MTMC_OK;
+        bf16::compact_rows(p.done, gp.B, slots, p.slot_row, p.page_table, p.row_pos, p.max_pages, p.page_table_c,
+                           p.row_pos_c, st);
+        cur = gp;
+        cur.B = slots; cur.bt = slots / 16; cur.n_samples = 1; cur.ragged = 2;
+        cur.row_pos = p.row_pos_c;
+        apply_tune(cur, tune_decode(D, cur.B, cur.bt, p.max_pages));
+        cur.persistent = may_persist && persistent_shape(w, D, cur) && turn.take(w->device, st);
+        cur_pool.page_table = p.page_table_c;
+        ctl.slot_row = p.slot_row;
+        bf16::set_sample_ctl((bf16::SampleCtl*)p.ctl, ctl, st);
+        bf16::embed_slots(p.slot_row, p.cur_ids, slots, embed_args(cur), st);
+        return decode_graph(w, cur, st, step_cur, &graph);
+      };
+      auto settle = [&] { (void)hipStreamSynchronize(st); };
+      if (int rc = run_with_looks(p.max_new, poll, steps, look, read, pack, settle)) return rc;
     } else if (p.max_new > 1) {
       StepGraph graph;
       if (int rc = decode_graph(w, gp, st, decode_step, &graph)) return rc;

@@ -1,5 +1,5 @@
-"""Looks at the stop flags where the caller has not said how often: the results of looks every that many steps, and looks of a call
-that has ended do not reach the next one."""
+"""Looks at the stop flags where the caller has not said how often: the results of looks every that many steps, and of calls that
+follow each other without a wait."""
 import numpy as np
 import pytest
 
@@ -31,8 +31,8 @@ def test_steps_that_the_library_chooses(layers, steps):
     assert ends[17] < 40 and ends[-1] > 4 * steps  # tiles were freed while rows still ran
 
 
-def test_calls_one_after_the_other_on_two_streams():
-    """The first call's last look (nobody runs any more) is written after the call has returned."""
+def test_calls_in_turn_on_two_streams():
+    """Nobody waits for a call but the looks of the next one, which are on the other stream, at the same place of the host's memory."""
     import torch
     from paper_2511_20100_amd import mtmc as lib
     cfg = inputs.ModelConfig(6, 256, 4, 2, 128, 688, V, dtype="bf16")
@@ -40,16 +40,25 @@ def test_calls_one_after_the_other_on_two_streams():
     try:
         lens = torch.full((4,), 20, dtype=torch.int32, device="cuda")
         prompts = torch.from_numpy(inputs.make_prompts(4, 20, V, seed=2)).cuda()
-        run = lambda ws, st, **kw: lib.mtmc_rollout_ragged(handle, prompts, lens, 4, 100, 1.0, 1, stop_id=3, workspace=ws, **kw)
         size = lib.mtmc_rollout_ragged_workspace_bytes(handle, 4, 20, 4, 100)
         spaces = [torch.empty(size, dtype=torch.uint8, device="cuda") for _ in range(2)]
         streams = [torch.cuda.Stream() for _ in range(2)]
-        want = [t.cpu() for t in run(spaces[0], None)]
+
+        def run(i, seed):
+            with torch.cuda.stream(streams[i]):
+                return lib.mtmc_rollout_ragged(handle, prompts, lens, 4, 100, 1.0, seed, stop_id=3, workspace=spaces[i],
+                                               stream=streams[i])
+
         torch.cuda.synchronize()
-        for i in range(8):
-            with torch.cuda.stream(streams[i % 2]):
-                got = run(spaces[i % 2], None, stream=streams[i % 2])
-            streams[i % 2].synchronize()
-            assert all(torch.equal(a, b.cpu()) for a, b in zip(want, got)), i
+        want = []
+        for seed in range(3):
+            outs = run(0, seed)
+            torch.cuda.synchronize()
+            want.append([t.cpu() for t in outs])
+        got = [(i % 3, run(i % 2, i % 3)) for i in range(70)]
+        torch.cuda.synchronize()
+        lib.mtmc_poll_errors(handle)
+        for i, (seed, outs) in enumerate(got):
+            assert all(torch.equal(a, b.cpu()) for a, b in zip(want[seed], outs)), i
     finally:
         lib.mtmc_weights_destroy(handle)
