@@ -713,11 +713,18 @@ int admission_plan(const int* live, const int* slot_region, int n_slots, int n_r
 
 namespace {
 
-// Decode steps between two looks at the stop flags, where the caller has not set them.  A look is a small kernel and an event, 5 us of
-// the stream; what it finds frees tiles 4 to 8 steps after a sequence's end, where 32 steps freed them after 32 to 64 (48 sequences of
-// about 24 tokens, 24 blocks: 171 -> 143 ms).  With few blocks, steps of 0.2 ms, every fourth step costs 0.6 % where nothing ends, hence 8.
-int stop_poll_steps(const mtmc_weights* w) {
+// Decode steps between two looks at the stop flags of a call of max_new tokens, 0 for none.  Where the caller has not set them:
+//   - a call of up to kQueuedTokens is queued as a whole and returns: a look is waited for, and callers that have other work for the
+//     host or for another stream count on short calls to leave them the thread;
+//   - else 4, with few blocks 8.  A look is a small kernel and an event, 5 us of the stream; what it finds frees tiles 4 to 8 steps after a
+//     sequence's end, where 32 steps freed them after 32 to 64 (48 sequences of about 24 tokens, 24 blocks: 171 -> 143 ms).
+//     128 tokens, a look every 4 / 8 / 32 steps: 48 sequences of about 24 tokens, 1.5 B shape with 2 blocks 22.8 / 22.9 / 24.3 ms,
+//     with 8 blocks 49.7 / 50.1 / 54.7, four 7 B blocks 85.5 / 86.1 / 93.6; 4 sequences of which none ends 20.65 / 20.54 / 20.47,
+//     40.44 / 40.31 / 40.27, 76.54 / 76.42 / 76.35: what 4 gain on 8 and what they cost are both under 1 %.
+constexpr int kQueuedTokens = 65;
+int stop_poll_steps(const mtmc_weights* w, int max_new) {
   if (w->opt_stop_poll >= 0) return w->opt_stop_poll;
+  if (max_new <= kQueuedTokens) return 0;
   return w->cfg.n_layers < 6 ? 8 : 4;
 }
 
@@ -919,7 +926,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     return MTMC_EINVAL;
   }
   if (sa.prompt_lens && sa.stop_id >= 0 && sa.reuse_len == 0 && p.total_prompts > p.n_prompts && p.max_new > 1 &&
-      w->opt_admit && stop_poll_steps(w) > 0) {
+      w->opt_admit && w->opt_stop_poll != 0) {
     // not while the caller is capturing the stream: the host must not wait then
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone)
@@ -1037,7 +1044,7 @@ int bf16_rollout(const mtmc_weights* w, const RolloutPlan& p, const int* prompts
     // A stop token: every `poll` steps the number of rows still running goes to the host, which reads it one
     // period later, ends the group when it is zero and packs the live rows into fewer 16-row tiles when it
     // frees a tile.  Not while the caller is capturing the stream (the host must not wait then).
-    int poll = (ragged && sa.stop_id >= 0) ? stop_poll_steps(w) : 0;
+    int poll = (ragged && sa.stop_id >= 0) ? stop_poll_steps(w, p.max_new) : 0;
     if (poll > 0) {
       hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {

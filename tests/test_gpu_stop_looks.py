@@ -62,3 +62,32 @@ def test_calls_in_turn_on_two_streams():
             assert all(torch.equal(a, b.cpu()) for a, b in zip(want[seed], outs)), i
     finally:
         lib.mtmc_weights_destroy(handle)
+
+
+def test_a_short_call_only_enqueues():
+    """Up to 65 tokens, a stop token among them: the call returns while the stream still has other work ahead of it."""
+    import torch
+    from paper_2511_20100_amd import mtmc as lib
+    cfg = inputs.ModelConfig(6, 256, 4, 2, 128, 688, V, dtype="bf16")
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 256), inputs.make_weights(cfg, seed=0, std=0.05, gain_std=0.1).blob())
+    try:
+        lens = torch.full((4,), 20, dtype=torch.int32, device="cuda")
+        prompts = torch.from_numpy(inputs.make_prompts(4, 20, V, seed=2)).cuda()
+        for new in (40, 64, 65):
+            ws = torch.empty(lib.mtmc_rollout_ragged_workspace_bytes(handle, 4, 20, 4, new), dtype=torch.uint8, device="cuda")
+            want = [t.cpu() for t in lib.mtmc_rollout_ragged(handle, prompts, lens, 4, new, 1.0, 1, stop_id=3, workspace=ws)]
+            a = torch.randn(16384, 16384, dtype=torch.float16, device="cuda")
+            c = torch.empty_like(a)
+            torch.matmul(a, a, out=c)
+            torch.cuda.synchronize()
+            done = torch.cuda.Event()
+            for _ in range(40):  # about 0.3 s; the call is a few milliseconds of host work
+                torch.matmul(a, a, out=c)
+            done.record()
+            got = lib.mtmc_rollout_ragged(handle, prompts, lens, 4, new, 1.0, 1, stop_id=3, workspace=ws)
+            assert not done.query(), new
+            torch.cuda.synchronize()
+            lib.mtmc_poll_errors(handle)
+            assert all(torch.equal(x, y.cpu()) for x, y in zip(want, got)), new
+    finally:
+        lib.mtmc_weights_destroy(handle)
