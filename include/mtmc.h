@@ -322,8 +322,8 @@ const char* mtmc_data_error_string(int bits);
  *   their own block size, 128 x 64 to 256 x 256, by the call's sizes), smaller ones in the direct
  *   128 x 128 kernel.  Both sum over K in the same order; results agree to
  *   the fp32 rounding inside the matrix instruction.
- *   MTMC_OPT_STOP_POLL_STEPS (0 = off; until it is set the library chooses: 0 for calls of up to 65 new tokens, 4 or 8 for longer
- *   ones): MTMC_BF16 rollouts with a stop token look at the rows' stop flags every this many decode steps.  The look itself is
+ *   MTMC_OPT_STOP_POLL_STEPS (0 = off; until it is set, and with MTMC_STOP_POLL_CHOOSE, the library chooses: 0 for calls of up to 65
+ *   new tokens, 4 or 8 for longer ones): MTMC_BF16 rollouts with a stop token look at the rows' stop flags every this many decode steps.  The look itself is
  *   queued on the stream; the host reads it one period later (so the GPU never waits for the host), ends the call once every row has stopped and packs
  *   the rows still running into fewer 16-row tiles when that frees a tile, so that a batch costs less as
  *   its rows finish.  With it the call blocks the calling thread on the stream (it returns when at most
@@ -358,6 +358,7 @@ const char* mtmc_data_error_string(int bits);
 #define MTMC_OPT_HIP_GRAPH 1
 #define MTMC_OPT_GEMM_LDS_MIN_BLOCKS 2
 #define MTMC_OPT_STOP_POLL_STEPS 3
+#define MTMC_STOP_POLL_CHOOSE (-1)  /* value of MTMC_OPT_STOP_POLL_STEPS: as before it was set */
 #define MTMC_OPT_ADMIT_PROMPTS 4
 #define MTMC_OPT_PERSISTENT_DECODE 5
 int mtmc_set_option(mtmc_weights* w, int option, int value);

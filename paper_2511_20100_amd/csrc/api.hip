@@ -90,7 +90,7 @@ extern "C" int mtmc_weights_create(const mtmc_config* cfg, const void* blob, siz
   w->aux = nullptr;
   w->opt_hip_graph = 1;
   w->opt_lds_min_blocks = 32;
-  w->opt_stop_poll = -1;
+  w->opt_stop_poll = MTMC_STOP_POLL_CHOOSE;
   w->opt_admit = 1;
   w->opt_persistent_wait_us = 2000;
   w->opt_persistent_told = false;
@@ -151,7 +151,8 @@ extern "C" int mtmc_set_option(mtmc_weights* w, int option, int value) {
   if (option == MTMC_OPT_HIP_GRAPH) {
     w->opt_hip_graph = value ? 1 : 0;
   } else if (option == MTMC_OPT_STOP_POLL_STEPS) {
-    MTMC_REQUIRE(value >= 0 && value <= (1 << 20), "MTMC_OPT_STOP_POLL_STEPS needs a value in [0, 2^20]");
+    MTMC_REQUIRE((value >= 0 && value <= (1 << 20)) || value == MTMC_STOP_POLL_CHOOSE,
+                 "MTMC_OPT_STOP_POLL_STEPS needs a value in [0, 2^20], or MTMC_STOP_POLL_CHOOSE");
     w->opt_stop_poll = value;
   } else if (option == MTMC_OPT_ADMIT_PROMPTS) {
     w->opt_admit = value ? 1 : 0;

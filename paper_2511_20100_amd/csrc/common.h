@@ -94,7 +94,7 @@ struct mtmc_weights {
   int d_ffn_pad;        // F rounded up to the K-tile of the bf16 kernels (== F for fp32)
   int opt_hip_graph;    // replay decode steps as a captured HIP graph (default 1)
   int opt_lds_min_blocks;  // output blocks (256 x 256) from which large GEMMs use the LDS-staged kernel
-  int opt_stop_poll;       // decode steps between two looks at the stop flags of a rollout with a stop token (0: never, negative: not set)
+  int opt_stop_poll;       // decode steps between two looks at the stop flags of a rollout with a stop token (0: never, MTMC_STOP_POLL_CHOOSE: not set)
   int opt_admit;           // a rollout with a stop token and more sequences than one batch holds runs as one batch
                            // that takes in the next prompts as sequences finish and leave slots (0: batch after batch)
   int opt_persistent_wait_us;  // how long a persistent launch waits for its workgroups (0: steps run as separate launches)

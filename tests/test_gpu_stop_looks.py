@@ -10,6 +10,31 @@ from paper_2511_20100_amd import inputs
 V = 64
 
 
+def test_the_choice_can_be_given_back():
+    """A call of 65 tokens: not packed unless a period is set, which changes bits; the library's choice, set again, is the one it
+    began with, and so are the bits.  Other values below zero are refused as ever."""
+    import torch
+    from paper_2511_20100_amd import mtmc as lib
+    cfg = inputs.ModelConfig(2, 256, 4, 2, 128, 688, V, dtype="bf16")
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 256), inputs.make_weights(cfg, seed=0, std=0.05, gain_std=0.1).blob())
+    try:
+        lens = torch.from_numpy((3 + np.arange(10) * 11 % 50).astype(np.int32)).cuda()
+        prompts = torch.from_numpy(inputs.make_prompts(10, 53, V, seed=2)).cuda()
+        got = []
+        for value in (None, 2, lib.MTMC_STOP_POLL_CHOOSE):
+            if value is not None:
+                lib.mtmc_set_option(handle, lib.MTMC_OPT_STOP_POLL_STEPS, value)
+            got.append([t.cpu() for t in lib.mtmc_rollout_ragged(handle, prompts, lens, 5, 65, 1.0, 1, stop_id=3)])
+            lib.mtmc_poll_errors(handle)
+        assert all(torch.equal(a, b) for a, b in zip(got[0], got[2]))
+        assert not torch.equal(got[0][1], got[1][1])
+        for value in (-2, -(1 << 31), (1 << 20) + 1):
+            with pytest.raises(lib.MtmcError, match="STOP_POLL"):
+                lib.mtmc_set_option(handle, lib.MTMC_OPT_STOP_POLL_STEPS, value)
+    finally:
+        lib.mtmc_weights_destroy(handle)
+
+
 @pytest.mark.parametrize("layers,steps", [(2, 8), (6, 4)])
 def test_steps_that_the_library_chooses(layers, steps):
     import torch
