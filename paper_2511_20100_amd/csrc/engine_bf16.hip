@@ -715,7 +715,9 @@ namespace {
 
 // Decode steps between two looks at the stop flags of a call of max_new tokens, 0 for none.  Where the caller has not set them:
 //   - a call of up to kQueuedTokens is queued as a whole and returns: a look is waited for, and callers that have other work for the
-//     host or for another stream count on short calls to leave them the thread;
+//     host or for another stream count on short calls to leave them the thread.  That is not for speed: a caller that waits for
+//     the call anyway sets a period (48 sequences of about 24 tokens, up to 40, a look every 4 steps against none: 24 blocks with a kv
+//     head per query head 55.1 / 69.5 ms, 28 blocks of the 1.5 B shape 55.6 / 63.0; up to 16: 31.3 / 31.7, 29.8 / 30.1);
 //   - else 4, with few blocks 8.  A look is a small kernel and an event, 5 us of the stream; what it finds frees tiles 4 to 8 steps after a
 //     sequence's end, where 32 steps freed them after 32 to 64 (48 sequences of about 24 tokens, 24 blocks: 171 -> 143 ms).
 //     128 tokens, a look every 4 / 8 / 32 steps: 48 sequences of about 24 tokens, 1.5 B shape with 2 blocks 22.8 / 22.9 / 24.3 ms,
@@ -824,8 +826,11 @@ int bf16_rollout_admit(const mtmc_weights* w, const RolloutPlan& p, const int* p
   std::vector<int> slot_region(B), regions(p.n_regions);  // slot_region: the region a slot's sequence reads
   for (int s = 0; s < B; ++s) slot_region[s] = s / ns;
   int next_prompt = p.n_prompts, steps = 1;  // steps: value of *d_step once the queued work has run
-  // every look waits for the stream, 20 to 30 us, and every step between looks is one that ended sequences keep their slots for: 320
-  // sequences of about 20 tokens, 6 blocks: 61 ms with a look every 8 steps, 56.2 every 4, 55.5 every 2
+  // Every look waits for the stream, 20 to 30 us, and every step between looks is one that ended sequences keep their slots for.  A
+  // look every 2 / 4 / 8 steps, 1.5 B shape, 320 sequences: of about 20 tokens with 6 blocks 55.7 / 55.4 / 57.1 ms, with 28 blocks
+  // 210.9 / 211.3 / 218.6; of about 10 with 2 blocks 21.3 / 22.1 / 22.5, with 4 blocks 32.3 / 33.4 / 34.1.  What 2 steps cost
+  // where none of 64 tokens' sequences ends: with 2 blocks (steps of 0.2 ms) 52.7 / 52.2 / 52.1, 1024 of them 154.8 / 153.1 / 152.0, with 4
+  // blocks 80.9 / 80.5 / 80.5, with 28 nothing.
   const int period = w->opt_stop_poll < 0 ? 2 : std::max(1, std::min(w->opt_stop_poll, 8));
   // every sequence ends within max_new steps of its start and a prompt is taken in whenever all the sequences of
   // an earlier one have ended, at the latest
