@@ -4,6 +4,7 @@
 #include "common.h"
 #include "frag.h"
 #include "persistent_cut.h"
+#include "slices.h"
 
 namespace mtmc {
 namespace bf16 {
@@ -331,7 +332,7 @@ void compact_slots(const int* done, int B, int slots, const int* slot_row, const
                    int* row_step0_c, hipStream_t st);
 void embed(float* h, const int* ids, int T, const bf16_t* E, int d, int vocab, int* err_flag,
            hipStream_t st, const int* d_rows = nullptr);
-// h[m, :] += sum_s P[s][m][:] (n_split may be 0); x = bf16(RMSNorm(h; gain)) in tiled layout.  From kNormTileRows rows on
+// h[m, :] += sum_s P[s][m][:] (n_split 0 .. kMaxSlices); x = bf16(RMSNorm(h; gain)) in tiled layout.  From kNormTileRows rows on
 // (and without partial sums) the form that works on tiles of 16 rows.
 constexpr int kNormTileRows = 1024;
 void add_norm(float* h, const float* P, int n_split, int ldp, int Mpad_p, const float* gain, float eps,
@@ -341,7 +342,7 @@ void add_norm(float* h, const float* P, int n_split, int ldp, int Mpad_p, const 
 // seq_start (device, may be NULL): sequences of different lengths packed back to back: sequence s holds the
 // tokens seq_start[s] .. seq_start[s + 1] - 1 at positions map.pos_base + 0, 1, ...; S is then the longest
 // length a sequence can have and n_seqs the number of sequences (T is ignored).
-// n_split > 1: qkv is the sum, in order, of n_split arrays that lie split_stride floats apart.
+// n_split > 1 (up to kMaxSlices): qkv is the sum, in order, of n_split arrays that lie split_stride floats apart.
 void rope_kv_write(h16_t* q, const float* qkv, int ld, int T, int S, int Hq, int Hkv, const float* cos,
                    const float* sin, TokMap map, KvPool pool, int layer, int* err_flag, hipStream_t st,
                    const int* seq_start = nullptr, int n_seqs = 0, int n_split = 1, size_t split_stride = 0);

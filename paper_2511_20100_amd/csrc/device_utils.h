@@ -4,8 +4,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <type_traits>
-
 #include "common.h"
 
 namespace mtmc {
@@ -155,25 +153,6 @@ __device__ __forceinline__ Top2 top2_merge(Top2 a, Top2 b) {
 __device__ __forceinline__ int tok_seq(const TokMap& m, int t) { return t / m.S; }
 __device__ __forceinline__ int tok_pos(const TokMap& m, int t) {
   return (m.row_pos ? m.row_pos[t / m.S] : m.pos_base) + (m.d_step ? *m.d_step : 0) + t % m.S;
-}
-
-// f(number, first): the slices first .. first + number - 1 of n, at most eight at a time, `number` a constant.  A loop over a count that
-// only the launch knows asks for one slice after the other, a trip to memory each (gemm_lds_split leaves 2 to 8).
-template <class F>
-__device__ __forceinline__ void over_slices(int n, F f) {
-  int first = 0;
-  for (; n - first > 8; first += 8) f(std::integral_constant<int, 8>{}, first);
-  switch (n - first) {
-    case 1: f(std::integral_constant<int, 1>{}, first); break;
-    case 2: f(std::integral_constant<int, 2>{}, first); break;
-    case 3: f(std::integral_constant<int, 3>{}, first); break;
-    case 4: f(std::integral_constant<int, 4>{}, first); break;
-    case 5: f(std::integral_constant<int, 5>{}, first); break;
-    case 6: f(std::integral_constant<int, 6>{}, first); break;
-    case 7: f(std::integral_constant<int, 7>{}, first); break;
-    case 8: f(std::integral_constant<int, 8>{}, first); break;
-    default: break;
-  }
 }
 
 }  // namespace mtmc

@@ -433,17 +433,9 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(float* out, int ld_out, c
   const int m = (int)(i / n4), n = (int)(i - (size_t)m * n4) * 4;
   if (d_rows && m >= *d_rows) return;
   float* o = out + (size_t)m * ld_out + n;
-  v4f acc = accumulate ? *reinterpret_cast<const v4f*>(o) : v4f{0.f, 0.f, 0.f, 0.f};
-  over_slices(S, [&](auto number, int first) {
-    constexpr int K = decltype(number)::value;
-    const float* p = part + ((size_t)first * M + m) * N + n;
-    v4f v[K];
-#pragma unroll
-    for (int s = 0; s < K; ++s) v[s] = *reinterpret_cast<const v4f*>(p + (size_t)s * M * N);
-#pragma unroll
-    for (int s = 0; s < K; ++s) acc = acc + v[s];
-  });
-  *reinterpret_cast<v4f*>(o) = acc;
+  const v4f acc = accumulate ? *reinterpret_cast<const v4f*>(o) : v4f{0.f, 0.f, 0.f, 0.f};
+  const float* p = part + (size_t)m * N + n;
+  *reinterpret_cast<v4f*>(o) = add_slices(acc, S, [&](int s) { return *reinterpret_cast<const v4f*>(p + (size_t)s * M * N); });
 }
 
 // Scoring LM head on the same engine: a work item is one block of rows and one slice of the vocabulary (`bps` blocks of
@@ -813,12 +805,12 @@ void lmhead_score_lds(const ScoreHeadArgs& a, hipStream_t st) {
   else a.want_top ? launch_lmhead<Tile<8, 8, 4, 1>, true>(a, st) : launch_lmhead<Tile<8, 8, 4, 1>, false>(a, st);
 }
 
-// The most splits, up to 8 and to one round of blocks of 256 x 256, that leave every range even and at least 8 k-steps
+// The most splits, up to kMaxSlices and to one round of blocks of 256 x 256, that leave every range even and at least 8 k-steps
 // long.  Not by the tile that the launch chooses: the order of the sums then follows from the sizes alone.
 int gemm_lds_splits(const LargeArgs& a, size_t part_floats) {
   const int blocks = (a.n_tiles + 15) / 16 * ((a.m_tiles + 15) / 16);  // of 256 x 256
   if (blocks > kCus / 2 || a.N % 4 != 0) return 0;
-  for (int s = std::min(8, kCus / blocks); s >= 2; --s)
+  for (int s = std::min(kMaxSlices, kCus / blocks); s >= 2; --s)
     if (a.k_tiles % s == 0 && (a.k_tiles / s) % 2 == 0 && a.k_tiles / s >= 8 && (size_t)s * a.M * a.N <= part_floats) return s;
   return 0;
 }

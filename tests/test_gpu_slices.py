@@ -1,5 +1,6 @@
 """Sums of split-K slices by the kernels that read them: one prompt of sizes that leave 2 to 8 slices, widths of one and two chunks per
-thread of the norm, against the whole reduction in one block."""
+thread of the norm, against the whole reduction in one block.  That a slice is left out, read twice or misplaced would show here; the order
+of the sums, on which their bits hang, is checked by test_slices.py."""
 import numpy as np
 import pytest
 
