@@ -96,7 +96,7 @@ struct RowSums {
 // 43.3 -> 41.0 ms, 48 rows 39.6 -> 38.0, 32 rows 35.3 -> 32.9).  Not with 10 gate / up tiles, whose registers are full: the loops
 // cost 10 more in scratch, and four 7 B blocks with 32 rows took 17.76 ms instead of 17.58.
 template <int GU_TILES>
-constexpr bool kAsks = GU_TILES == 6;
+constexpr bool kAsks = persist_some_ask(2, GU_TILES);
 // The rows of qkv in block l, and the sums of the splits (persist_hand_rows()).
 template <bool ASK>
 __device__ __forceinline__ float* qkv_of(const PersistArgs& a, int l) {
@@ -658,7 +658,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_decode_layers_rows(PersistArgs)
 }  // namespace
 
 void launch_rows(const PersistArgs& a, int bt, int gu_tiles, hipStream_t st) {
-  if (gu_tiles == 6) launch_fill_u32(reinterpret_cast<uint32_t*>(a.hand), kNotThere, (size_t)a.at_hand.bytes / 4, st);
+  if (persist_some_ask(bt, gu_tiles)) launch_fill_u32(reinterpret_cast<uint32_t*>(a.hand), kNotThere, (size_t)a.at_hand.bytes / 4, st);
   if (bt == 2 && gu_tiles == 6) k_decode_layers_rows<2, 6, 5><<<kPersistGrid, kThreads, 0, st>>>(a);
   else if (bt == 2) k_decode_layers_rows<2, 10, 4><<<kPersistGrid, kThreads, 0, st>>>(a);
   else if (bt == 3) k_decode_layers_rows<3, 6, 5><<<kPersistGrid, kThreads, 0, st>>>(a);

@@ -349,12 +349,15 @@ bool persistent_fits(const mtmc_weights* w, const Dims& D, int B, int bt, int n_
   return bf16::decode_persistent_fits(
       bf16::PersistShape{bt, w->cfg.head_dim, D.kt_d, D.nt_d, D.nt_qkv, D.nt_gu, n_chunks, B * D.Hkv, down_nb, ks_down});
 }
-// Rows of the largest batch of the call whose steps may run as one launch: its groups of prompts, the last one with the launch
-// shape of the others, and (prompts of different lengths) the slots that live rows are packed into.
+// What a step of B rows hands to readers that ask; all of it (bytes) is there kPersistPieces times up to kPersistAskRows rows.
 bf16::PersistHand persist_hand_of(const Dims& D, int B, int n_chunks, int ks_down) {
-  return bf16::persist_hand(B, D.kt_d, D.kt_F, D.nt_qkv, D.kt_nq, D.Hq, n_chunks, ks_down);
+  if (B <= bf16::kPersistAskRows) return bf16::persist_hand(B, D.kt_d, D.kt_F, D.nt_qkv, D.kt_nq, D.Hq, n_chunks, ks_down);
+  if (!bf16::persist_some_ask(tiles16(B), bf16::persist_gu_tiles(D.nt_gu))) return {};
+  return bf16::persist_hand_rows(tiles16(B), D.kt_d, D.nt_qkv, ks_down);
 }
-// rows, and the bytes of what is handed to readers that ask
+// Rows of the largest batch of the call whose steps may run as one launch: its groups of prompts, the last one with the launch
+// shape of the others, and (prompts of different lengths) the slots that live rows are packed into.  With it the bytes of what such
+// batches hand to readers that ask.
 struct PersistRoom {
   int rows;
   size_t hand;
@@ -365,10 +368,8 @@ PersistRoom persistent_room(const mtmc_weights* w, const Dims& D, const RolloutP
   auto may_run = [&](int B, int n_chunks, int down_nb, int ks_down) {
     if (!persistent_fits(w, D, B, tiles16(B), n_chunks, down_nb, ks_down)) return;
     room.rows = std::max(room.rows, tiles16(B) * 16);
-    if (B <= bf16::kPersistAskRows)
-      room.hand = std::max(room.hand, bf16::kPersistPieces * (size_t)persist_hand_of(D, B, n_chunks, ks_down).bytes);
-    else
-      room.hand = std::max(room.hand, (size_t)bf16::persist_hand_rows(tiles16(B), D.kt_d, D.nt_qkv, ks_down).bytes);
+    const size_t bytes = persist_hand_of(D, B, n_chunks, ks_down).bytes;
+    room.hand = std::max(room.hand, B <= bf16::kPersistAskRows ? bf16::kPersistPieces * bytes : bytes);
   };
   for (int B : {p.B, ((p.total_prompts - 1) % p.n_prompts + 1) * p.n_samples}) may_run(B, p.n_chunks, p.down_nb, p.ks_down);
   for (int bt = 1; p.ragged && bt < p.bt; ++bt) {
@@ -413,7 +414,7 @@ void bf16_plan_rollout_extra(const mtmc_weights* w, RolloutPlan& p, Carver& cv) 
     p.xo_l = cv.take<h16_t>(L * rows * D.d);
     p.xr_l = cv.take<h16_t>(L * rows * D.d);
     p.act_l = cv.take<h16_t>(L * rows * D.F);
-    p.hand = cv.take<char>(room.hand);
+    if (room.hand) p.hand = cv.take<char>(room.hand);
   }
   if (p.ragged) {
     p.slot_row = cv.take<int>(Mpad);
@@ -535,13 +536,8 @@ bf16::PersistArgs persistent_args(const mtmc_weights* w, const Dims& D, const Ro
   a.xo = (h16_t*)p.xo_l; a.xr = (h16_t*)p.xr_l; a.act = (h16_t*)p.act_l;
   a.x_stride = rows * D.d; a.act_stride = rows * D.F;
   a.at = at;
-  if (p.B <= bf16::kPersistAskRows) {
-    a.hand = (char*)p.hand;
-    a.at_hand = persist_hand_of(D, p.B, p.n_chunks, p.ks_down);
-  } else {
-    a.hand = (char*)p.hand;
-    a.at_hand = bf16::persist_hand_rows(p.bt, D.kt_d, D.nt_qkv, p.ks_down);
-  }
+  a.hand = (char*)p.hand;
+  a.at_hand = persist_hand_of(D, p.B, p.n_chunks, p.ks_down);
   a.sync = p.sync; a.roll_ticks = 100LL * (w->opt_persistent_wait_us - 1); a.told = w->opt_persistent_told;
   a.gave_up = w->gave_up; a.err_flag = w->err_flag;
   return a;

@@ -43,6 +43,9 @@ inline bool decode_persistent_fits(const PersistShape& s) {
 
 // Steps of so few rows hand their data to readers that ask for them (decode_persistent.hip).
 constexpr int kPersistAskRows = 2;
+// Steps of more rows in which readers ask for some of it (persist_hand_rows()): not with 10 gate / up tiles and several tiles of rows
+// (decode_persistent_rows.hip, kAsks), which need no memory for that.
+constexpr bool persist_some_ask(int bt, int gu_tiles) { return bt == 1 || gu_tiles == 6; }
 // What the phases of such a step hand on: a piece of memory per block (block l: l % kPersistPieces), in which every buffer has the
 // rows of the batch and no others (bytes from the piece's start).  What all workgroups ask for is there kPersistCopies times, a copy
 // for the workgroups of a die.

@@ -39,6 +39,12 @@ int main() {
         CHECK(h.qkv == 0 && h.qkv_copy >= B * nt_qkv * 16 * 4 && h.part >= 2 * h.qkv_copy && h.part % 128 == 0 && h.qkv_copy % 128 == 0);
         CHECK(h.bytes >= h.part + ks * B * kt_d * 32 * 4);
       }
+  // one tile of rows always has memory for readers that ask, several with the cuts whose readers do
+  for (int bt = 1; bt <= 4; ++bt)
+    for (int gu : {4, 6, 10}) {
+      const int B = 0, kt_d = gu;
+      CHECK(persist_some_ask(bt, gu) == (bt == 1 || gu == 6));
+    }
   std::printf("ok\n");
   return 0;
 }

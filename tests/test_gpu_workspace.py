@@ -52,3 +52,20 @@ def test_bytes_per_block(cfg, call, rows):
                                                          per_group * n_samples * pages) * cfg.n_kv_heads * 16 * cfg.head_dim * 2
         most = min(64, -(-per_group * n_samples // 16) * 16)
         assert abs(grown - 4 * 2 * most * (2 * cfg.d_model + cfg.d_ffn)) <= 4 * 256
+
+
+WIDE = inputs.ModelConfig(1, 3584, 28, 4, 128, 18944, 272, dtype="bf16")  # 10 gate / up tiles: from 17 rows all hand-overs are counted
+
+
+@pytest.mark.parametrize("cfg,n_prompts,handed_in_8_splits", [(D128, 4, 1), (D128, 6, 1), (D128, 8, 1), (WIDE, 4, 0)])
+def test_no_room_for_hand_overs_that_nobody_asks_for(cfg, n_prompts, handed_in_8_splits):
+    from paper_2511_20100_amd import mtmc as lib
+    handle = lib.mtmc_weights_create(lib.make_config(cfg, 1024), inputs.make_weights(cfg, seed=0).blob())
+    try:
+        # the first call decodes nothing: the difference is what the one-launch step takes
+        one, two = (lib.mtmc_rollout_workspace_bytes(handle, n_prompts, 40, 8, max_new) for max_new in (1, 2))
+    finally:
+        lib.mtmc_weights_destroy(handle)
+    rows, d, n_qkv = n_prompts * 8, cfg.d_model, (cfg.n_q_heads + 2 * cfg.n_kv_heads) * 128
+    taken = 2 * rows * (2 * d + cfg.d_ffn) + 2 * 64 * 256 * 4 + handed_in_8_splits * 4 * rows * (2 * n_qkv + 8 * d)
+    assert abs(two - one - taken) <= 16 << 10  # the counters, and the alignment of each buffer
