@@ -242,7 +242,7 @@ def inference_legs(torch, mtmc, dev, handle, weights, cfg, prompts, n_samples, m
         del ws
         # eight batches of 128 sequences in one call: the slots of finished sequences go to the next prompt of the
         # call, against batch after batch (each ending with its last row, rows giving up their places as above)
-        mtmc.mtmc_set_option(h2, mtmc.MTMC_OPT_STOP_POLL_STEPS, 32)
+        mtmc.mtmc_set_option(h2, mtmc.MTMC_OPT_STOP_POLL_STEPS, mtmc.MTMC_STOP_POLL_CHOOSE)
         many = 8 * (128 // n_samples)
         m_prompts = torch.from_numpy(inputs.make_prompts(many, prompt_len, cfg.vocab, seed=8)).to(dev)
         m_lens = torch.full((many,), prompt_len, dtype=torch.int32, device=dev)

@@ -322,20 +322,22 @@ const char* mtmc_data_error_string(int bits);
  *   their own block size, 128 x 64 to 256 x 256, by the call's sizes), smaller ones in the direct
  *   128 x 128 kernel.  Both sum over K in the same order; results agree to
  *   the fp32 rounding inside the matrix instruction.
- *   MTMC_OPT_STOP_POLL_STEPS (0 = off; until it is set, and with MTMC_STOP_POLL_CHOOSE, the library chooses: 0 for calls of up to 65
- *   new tokens, 4 or 8 for longer ones): MTMC_BF16 rollouts with a stop token look at the rows' stop flags every this many decode steps.  The look itself is
- *   queued on the stream; the host reads it one period later (so the GPU never waits for the host), ends the call once every row has stopped and packs
+ *   MTMC_OPT_STOP_POLL_STEPS (0 = off; until it is set, and with MTMC_STOP_POLL_CHOOSE, the library chooses: off for
+ *   calls of up to 65 new tokens, 4 or 8 for longer ones): MTMC_BF16 rollouts with a stop token look at the rows' stop
+ *   flags every this many decode steps.  The look itself is queued on the stream; the host reads it one
+ *   period later (so the GPU never waits for the host), ends the call once every row has stopped and packs
  *   the rows still running into fewer 16-row tiles when that frees a tile, so that a batch costs less as
  *   its rows finish.  With it the call blocks the calling thread on the stream (it returns when at most
- *   two periods of work are still queued) and calls with a stop token on one weights handle take turns;
- *   with 0, or when `stream` is being captured, the call only enqueues, as mtmc_rollout does, every row keeps
- *   its place, and the call costs what it costs without a stop token.  Packing changes the tiling, hence
+ *   two periods of work are still queued) and such calls on one weights handle take turns; off, or when `stream` is
+ *   being captured, the call only enqueues, as mtmc_rollout does, every row keeps its place, and the call costs what it
+ *   costs without a stop token (a caller that waits for short calls anyway is served better with a period set).
+ *   Packing changes the tiling, hence
  *   the order of the fp32 sums, of the steps after it: log-probabilities then agree with the unpacked call's
  *   to about 1e-3 (an id can differ where two candidates are that close), and with the definition as
  *   closely as before.
- *   MTMC_OPT_ADMIT_PROMPTS (default 1): a MTMC_BF16 mtmc_rollout_ragged call with a stop token, more than 128
- *   sequences and MTMC_OPT_STOP_POLL_STEPS > 0 or not set (whatever its length) runs as one batch of 128 slots; every min(8, poll steps) steps (2 if not set) the
- *   calling thread waits for the stream, and prompts of the call that find n_samples free slots (left by
+ *   MTMC_OPT_ADMIT_PROMPTS (default 1): a MTMC_BF16 mtmc_rollout_ragged call with a stop token and more than 128
+ *   sequences, whatever its length, runs as one batch of 128 slots unless MTMC_OPT_STOP_POLL_STEPS is 0; every min(8, poll
+ *   steps) steps (2 where the library chooses) the calling thread waits for the stream, and prompts of the call that find n_samples free slots (left by
  *   sequences that have ended) are prefilled and join the batch, each sequence at its own step; when no prompt is
  *   left the sequences still running are packed as described above.  A sequence's random numbers go by its row and
  *   its own step, so results are those of the call that runs batch after batch (value 0) up to the rounding order

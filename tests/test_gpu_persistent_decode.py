@@ -126,7 +126,7 @@ def test_lengths_stop_tokens_and_empty_slots(lib, policy):
             lib.mtmc_set_option(handle, lib.MTMC_OPT_PERSISTENT_DECODE, value)
             outs.append([t.cpu() for t in lib.mtmc_rollout_ragged(handle, prompts, lens, n_samples, max_new, 1.0, 4, stop_id=stop)])
             lib.mtmc_poll_errors(handle)
-        lib.mtmc_set_option(handle, lib.MTMC_OPT_STOP_POLL_STEPS, 32)
+        lib.mtmc_set_option(handle, lib.MTMC_OPT_STOP_POLL_STEPS, lib.MTMC_STOP_POLL_CHOOSE)
         assert all(torch.equal(a, b) for a, b in zip(*outs))
 
 
